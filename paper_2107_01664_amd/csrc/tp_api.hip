@@ -403,10 +403,10 @@ struct tp_problem {
     bool have_pcg = false;
     PcgSetup pcg;
     DevBuf<int32_t> pcg_perm, pcg_pcol, pcg_bstart, pcg_whole, pcg_blk, pcg_astart, pcg_aob, pcg_acomp,
-        pcg_abl_off, pcg_abl;
+        pcg_abl_off, pcg_abl, pcg_lcol, pcg_hoff, pcg_hrow;
     DevBuf<int8_t> pcg_rslot, pcg_eslot;
     DevBuf<float> pcg_Binv;
-    DevBuf<double> pcg_pval, pcg_phi, pcg_rw, pcg_esum, pcg_C0inv, pcg_Vb, pcg_rho, pcg_red, pcg_bp, pcg_xp;
+    DevBuf<double> pcg_pval, pcg_phi, pcg_rw, pcg_esum, pcg_C0inv, pcg_U, pcg_G, pcg_X, pcg_bp, pcg_xp;
     // more blocks than one co-resident workgroup each: the multi-launch solve and its work
     bool pcg_ml = false;
     DevBuf<double> ml_r, ml_p, ml_s, ml_m, ml_an, ml_v, ml_shares, ml_g, ml_part;
@@ -491,9 +491,10 @@ struct tp_problem {
              ell_val.bytes();
         b += pcg_perm.bytes() + pcg_pcol.bytes() + pcg_bstart.bytes() + pcg_whole.bytes() + pcg_blk.bytes() +
              pcg_astart.bytes() + pcg_aob.bytes() + pcg_acomp.bytes() + pcg_abl_off.bytes() + pcg_abl.bytes() +
+             pcg_lcol.bytes() + pcg_hoff.bytes() + pcg_hrow.bytes() +
              pcg_rslot.bytes() + pcg_eslot.bytes() + pcg_phi.bytes() + pcg_rw.bytes() + pcg_esum.bytes() +
-             pcg_Binv.bytes() + pcg_pval.bytes() + pcg_C0inv.bytes() + pcg_Vb.bytes() +
-             pcg_rho.bytes() + pcg_red.bytes() + pcg_bp.bytes() + pcg_xp.bytes();
+             pcg_Binv.bytes() + pcg_pval.bytes() + pcg_C0inv.bytes() + pcg_U.bytes() +
+             pcg_G.bytes() + pcg_X.bytes() + pcg_bp.bytes() + pcg_xp.bytes();
         b += gm_V.bytes() + gm_Z.bytes() + gm_w.bytes() + gm_b.bytes() + gm_r.bytes() + gm_x.bytes() +
              gm_small.bytes() + gm_red.bytes() + gm_Q.bytes() + gm_Qn.bytes() + gm_AQ.bytes() + gm_one.bytes() +
              gm_lab0.bytes() + gm_dinv.bytes() + gm_sv.bytes() + gm_sw.bytes() + gm_smw.bytes() + obs_x.bytes() + obs_tree.bytes() +
@@ -792,6 +793,38 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
             eslot[(size_t)e * n + i] = (int8_t)q;
         }
     }
+    // per block the rows of other blocks its rows have entries in, and the columns as slots of
+    // the block's rows and of that list (rows beyond the list's capacity are read one by one)
+    std::vector<int32_t> lcol, halo_off(1, 0), hrow;
+    int max_halo = 0;
+    if (!P->pcg_ml) {
+        lcol.resize((size_t)w * n);
+        std::vector<int32_t> lst, slot(n, -1);   // slot: of a row in the current block's list
+        for (int b = 0; b < nb; ++b) {
+            const int32_t i0 = bstart[b], i1 = bstart[b + 1];
+            lst.clear();
+            for (int e = 0; e < w; ++e)
+                for (int32_t i = i0; i < i1; ++i) {
+                    const int32_t j = pcol[(size_t)e * n + i];
+                    if ((j < i0 || j >= i1) && slot[j] < 0) {
+                        slot[j] = 0;
+                        lst.push_back(j);
+                    }
+                }
+            std::sort(lst.begin(), lst.end());
+            const int nh = std::min((int)lst.size(), kPcgMaxHalo);
+            for (int q = 0; q < (int)lst.size(); ++q) slot[lst[q]] = q < nh ? BS + q : ~lst[q];
+            for (int e = 0; e < w; ++e)
+                for (int32_t i = i0; i < i1; ++i) {
+                    const int32_t j = pcol[(size_t)e * n + i];
+                    lcol[(size_t)e * n + i] = j >= i0 && j < i1 ? j - i0 : slot[j];
+                }
+            for (int32_t j : lst) slot[j] = -1;
+            hrow.insert(hrow.end(), lst.begin(), lst.begin() + nh);
+            halo_off.push_back((int32_t)hrow.size());
+            max_halo = std::max(max_halo, nh);
+        }
+    }
     auto up = [&](auto& buf, const auto& host) -> tp_status {
         TP_TRY(buf.ensure(std::max<size_t>(host.size(), 1), s));
         TP_HIP(hipMemcpyAsync(buf.p, host.data(), sizeof(host[0]) * host.size(), hipMemcpyHostToDevice, s));
@@ -809,6 +842,9 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
     TP_TRY(up(P->pcg_abl, abl));
     TP_TRY(up(P->pcg_rslot, rslot));
     TP_TRY(up(P->pcg_eslot, eslot));
+    TP_TRY(up(P->pcg_lcol, lcol));
+    TP_TRY(up(P->pcg_hoff, halo_off));
+    TP_TRY(up(P->pcg_hrow, hrow));
     const int nc = 4 * na;
     TP_TRY(P->pcg_pval.ensure((size_t)w * n, s));
     TP_TRY(P->pcg_phi.ensure((size_t)4 * n, s));
@@ -823,6 +859,7 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
     ps.bstart = P->pcg_bstart.p; ps.whole = P->pcg_whole.p; ps.blk = P->pcg_blk.p;
     ps.astart = P->pcg_astart.p; ps.agg_of_block = P->pcg_aob.p; ps.acomp = P->pcg_acomp.p;
     ps.abl_off = P->pcg_abl_off.p; ps.abl = P->pcg_abl.p; ps.rslot = P->pcg_rslot.p; ps.eslot = P->pcg_eslot.p;
+    ps.lcol = P->pcg_lcol.p; ps.hoff = P->pcg_hoff.p; ps.hrow = P->pcg_hrow.p; ps.max_halo = max_halo;
     ps.phi = P->pcg_phi.p; ps.rw = P->pcg_rw.p; ps.esum = P->pcg_esum.p;
     ps.Binv = P->pcg_Binv.p; ps.C0inv = P->pcg_C0inv.p;
     P->have_pcg = true;
@@ -1574,9 +1611,9 @@ tp_status ensure_cg(tp_problem* P, int k)
         TP_TRY(P->pcg_bp.ensure(n * kc, s));
         TP_TRY(P->pcg_xp.ensure(n * kc, s));
         if (!P->pcg_ml) {
-            TP_TRY(P->pcg_Vb.ensure(2 * n * kc, s));
-            TP_TRY(P->pcg_rho.ensure((size_t)2 * P->pcg.nb * 4 * kc, s));
-            TP_TRY(P->pcg_red.ensure((size_t)2 * P->pcg.nb * 3 * kc, s));
+            TP_TRY(P->pcg_U.ensure(2 * n * kc, s));
+            TP_TRY(P->pcg_G.ensure((size_t)2 * P->pcg.nb * pcg_share_stride((int)kc), s));
+            TP_TRY(P->pcg_X.ensure((size_t)3 * P->pcg.nb * pcg_sum_stride((int)kc), s));
         } else {
             for (DevBuf<double>* v : {&P->ml_r, &P->ml_p, &P->ml_s, &P->ml_m, &P->ml_an, &P->ml_v})
                 TP_TRY(v->ensure(n * kc, s));
@@ -1671,8 +1708,8 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
                 it.warm = warm && P->warm_now ? 1 : 0;
                 if (it.warm)
                     TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, x[pc[q]], P->pcg_xp.p, true, s));
-                it.w.Vb = P->pcg_Vb.p; it.w.rho = P->pcg_rho.p; it.w.red = P->pcg_red.p;
-                it.w.bar = P->cg_bar.p; it.w.flags = P->flags.p;
+                it.w.U = P->pcg_U.p; it.w.G = P->pcg_G.p; it.w.X = P->pcg_X.p;
+                it.w.flags = P->flags.p;
                 it.w.iters = P->cg_iters.p + c0;
                 it.w.relres = P->cg_relres.p + c0;
                 it.rtol = P->prm.cg_rtol;
@@ -2920,9 +2957,12 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
             b += 4 * n + 13 * n * w + 4 * 2 * (nb + 1) + 4 * nb * (4 + pcg_max_block_aggregates()) + 4 * n +
                  (4 + 32 + 8 * 4 * kPcgRowSlots) * n + 8 * ncmax + 4 * nb * bs * bs + 8 * ncmax * ncmax;
             if (nb <= pcg_max_blocks()) {
-                // solve work: two copies of the block solves, block shares of the coarse
-                // right-hand side and partial sums, permuted b and x
-                b += 8.0 * n * kMaxGroupCols * 4 + 8 * 2 * nb * 4 * kMaxGroupCols + 8 * 6 * nb * kMaxGroupCols;
+                // solve work: two copies of the block solves and of the block shares of the
+                // coarse right-hand side, three of the partial sums, permuted b and x
+                // and the columns as slots with the halo lists
+                b += 4.0 * n * w + 4.0 * (nb + 1) + 4.0 * std::min(n * w, nb * (double)kPcgMaxHalo);
+                b += 8.0 * n * kMaxGroupCols * 4 + 8 * 2 * nb * pcg_share_stride(kMaxGroupCols) +
+                     8 * 3 * nb * pcg_sum_stride(kMaxGroupCols);
             } else {
                 // multi-launch work: six [n][k] vectors, permuted b and x, block shares, coarse
                 // right-hand side, per-workgroup partial sums, state

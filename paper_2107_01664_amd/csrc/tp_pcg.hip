@@ -15,11 +15,9 @@
 // The solver is the Chronopoulos-Gear form of preconditioned CG: with u = M^{-1} r and
 // w = C u, the sums gamma = (r,u) and delta = (w,u) give beta = gamma / gamma_old and
 // alpha = gamma / (delta - beta gamma / alpha_old), and p = u + beta p, s = w + beta s (= C p),
-// x += alpha p, r -= alpha s.  One workgroup of 2 kBS threads owns one block (kBS row
-// owners and kBS helpers for the block product) and keeps C_BB^{-1} for the whole solve: in
-// LDS, or with four or more columns in registers, half a column per thread.  An iteration
-// has two grid exchanges through per-workgroup flag lines, the
-// exchanged values written and read as agent-scope atomics.  In the first, every block
+// x += alpha p, r -= alpha s.  One workgroup of kPcgThreads threads owns one block and keeps
+// C_BB^{-1} in registers for the whole solve.  An iteration has two exchanges between the
+// workgroups, of values that carry their own arrival (publish / peek).  In the first, every block
 // publishes its block solve v = C_BB^{-1} r_B and its shares Phi_B^T r of the coarse
 // right-hand side; after it, every workgroup forms the coarse values of the aggregates its
 // rows touch, u = v + Phi c and C u from the neighbours' v.  In the second, the block
@@ -43,10 +41,9 @@
 namespace tp {
 
 constexpr int kBS = 128;            // vertices per block = row-owning threads of a solver workgroup
-constexpr int kThreads = 2 * kBS;   // threads per solver workgroup: row owners + helpers
+constexpr int kThreads = 2 * kBS;   // threads per workgroup of the multi-launch block kernel
 constexpr int kMaxAggNbn = 16;      // aggregates touching a block (its own included)
 constexpr int kMaxNbPcg = 256;      // blocks (one co-resident workgroup per block)
-static_assert(kMaxNbPcg <= kMaxBarrierW, "one barrier flag per block");
 constexpr int kMaxAggBlocks = 7;    // blocks per aggregate: ceil(4 kMaxNbPcg / kCoarseMax)
 constexpr int kMaxNbMulti = 16384;  // blocks of the multi-launch solve (2,097,152 vertices)
 
@@ -520,70 +517,6 @@ __global__ void k_permute_rows(int64_t n, int k, const int32_t* __restrict__ per
     else dst[(int64_t)perm[i] * ld + c0 + c] = src[i * k + c];
 }
 
-// ---------------------------------------------------------------- solver
-
-struct PcgArgs {
-    int64_t n;
-    int nb;
-    int nc;                   // coarse functions (4 per aggregate)
-    int ell_w;
-    const int32_t* pcol;      // [ell_w][n]
-    const double* pval;       // [ell_w][n]
-    const int32_t* bstart;    // [nb + 1]
-    const int32_t* astart;    // [na + 1] first block of each aggregate
-    const int32_t* agg_of_block;
-    const int32_t* abl_off;   // [nb + 1] aggregates touching each block (sorted, own included)
-    const int32_t* abl;
-    const int8_t* rslot;      // [kPcgRowSlots][n], filled in order, -1 after the last
-    const double* phi;        // [n][4]
-    const double* rw;         // [kPcgRowSlots][4][n]
-    const float* Binv;        // [nb][kBS][kBS], FP32
-    const double* C0inv;      // [nc][nc]
-    const double* b;          // [n][k] (block order)
-    double* x;                // [n][k]
-    double* Vb;               // [2][n][k] block solves, copy = barrier count % 2
-    double* rho;              // [2][nb][4][k] block sums of phi times the preconditioned vector
-    double* red;              // [2][nb][3k] block partial sums
-    unsigned* bar;
-    int* iters;
-    double* relres;
-    int* flags;
-    double rtol;
-    int maxiter;
-    int k;
-    int block0;               // first workgroup of this problem in its launch
-    int stage;                // the block shares fit the LDS staging area after PcgShared
-    int warm;                 // 1: x holds an initial guess (the previous solution)
-};
-
-constexpr int kCrowMax = 7680;      // cached coarse-inverse entries (FP32: 30 KB)
-
-// With four or more columns a thread keeps its half column of the block inverse in
-// registers; with fewer the inverse stays in LDS (the same product, bit for bit: measured on
-// the 40,000-face torus, registers took 5 % off a 9-column solve, 3 % off a 6-column one,
-// and were no faster with 3).
-template <int KG>
-constexpr bool kRegInv = KG >= 4;
-
-template <int KG>
-struct PcgShared {
-    alignas(16) float Binv[kRegInv<KG> ? 4 : kBS * kBS];
-    alignas(16) float crow[kCrowMax];   // rows of C0inv of the coarse functions of the touching
-                                        // aggregates, rounded to FP32 (as the block inverses are)
-    alignas(16) float r[kBS * KG];      // the vector of the block product, rounded to FP32
-                                        // (16-byte aligned: read four values at a time)
-    double rho[kCoarseMax * KG];    // coarse right-hand side [nc][KG] (and the block product's halves)
-    double c[kMaxAggNbn * 4 * KG];  // coarse values [slot][4][KG]
-    double wave[(kThreads / 64) * 4 * KG];
-    double sums[4 * KG];
-    double coef[2 * KG];            // alpha, beta of every column
-    int live[KG];                   // column not yet converged
-    double part[kThreads];
-    int32_t nbl[kMaxAggNbn];
-    int32_t ast[kCoarseMax / 4 + 1];  // first block of each aggregate
-};
-static_assert(kCoarseMax >= kBS, "the block product's halves go through PcgShared::rho");
-
 // Sum of n values p[0], p[stride], ... in a fixed order: four interleaved partial sums, so
 // four loads are in flight at a time, added as (s0 + s1) + (s2 + s3).
 __device__ __forceinline__ double sum_fixed(const double* __restrict__ p, int n, int64_t stride)
@@ -602,44 +535,25 @@ __device__ __forceinline__ double sum_fixed(const double* __restrict__ p, int n,
     return (a0 + a1) + (a2 + a3);
 }
 
-// Sum in a fixed order of n values published by other workgroups (loaded with xload):
-// the loads of 8 values at a time are all in flight before they are added, value i to
-// partial sum i % 4, and the partial sums are added as (s0 + s1) + (s2 + s3).
-__device__ __forceinline__ double sum_fixed_x(const double* __restrict__ p, int n, int64_t stride)
-{
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int i = 0; i < n; i += 8) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = i + u < n ? xload(p + (int64_t)(i + u) * stride) : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a[u & 3] += v[u];
-    }
-    return (a[0] + a[1]) + (a[2] + a[3]);
-}
-
 // Dot product sum_i a[i] b[i * bstride] in a fixed order: the loads of 8 terms at a time
 // are issued before they are added, term i to partial sum i % 4, and the partial sums are
 // added as (s0 + s1) + (s2 + s3).
-template <class TA, bool ROUND32 = false>
-__device__ __forceinline__ double dot_fixed(const TA* __restrict__ a, const double* __restrict__ b, int n,
+__device__ __forceinline__ double dot_fixed(const double* __restrict__ a, const double* __restrict__ b, int n,
                                             int bstride)
 {
-    // the terms a[i] b[i], with a[i] rounded to FP32 first when ROUND32
-    auto av = [&](int i) -> double { return ROUND32 ? (double)(float)a[i] : (double)a[i]; };
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     int i = 0;
     for (; i + 8 <= n; i += 8) {
         double x[8], y[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            x[u] = av(i + u);
+            x[u] = a[i + u];
             y[u] = b[(i + u) * bstride];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc[u & 3] += x[u] * y[u];
     }
-    for (; i < n; ++i) acc[i & 3] += av(i) * b[i * bstride];
+    for (; i < n; ++i) acc[i & 3] += a[i] * b[i * bstride];
     return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
@@ -664,536 +578,806 @@ __device__ __forceinline__ void wg_reduce(const double (&v)[M], double* wave_sh,
     __syncthreads();
 }
 
-// One launch solves the systems of ntab independent problems: problem m owns workgroups
-// [tab[m].block0, tab[m + 1].block0) and synchronises only among them (its own barrier
-// words), so its iterates are those of a launch of its own.
-template <int KG>
-__global__ __launch_bounds__(kThreads) void k_pcg(const PcgArgs* __restrict__ tab, int ntab)
+// ---------------------------------------------------------------- solver
+
+struct PcgArgs {
+    int64_t n;
+    int nb;
+    int nc;                   // coarse functions (4 per aggregate)
+    int ell_w;
+    const int32_t* lcol;      // [ell_w][n] columns: a row of the block, then kBS + its halo slot, or ~row
+                              // (padding entries: the row itself, value 0)
+    const int32_t* hoff;      // [nb + 1] halo of each block: rows of other blocks that its rows
+    const int32_t* hrow;      //          have entries in (sorted, at most kPcgMaxHalo)
+    const double* pval;       // [ell_w][n]
+    const int32_t* bstart;    // [nb + 1]
+    const int32_t* astart;    // [na + 1] first block of each aggregate
+    const int32_t* agg_of_block;
+    const int32_t* abl_off;   // [nb + 1] aggregates touching each block (sorted, own included)
+    const int32_t* abl;
+    const int8_t* rslot;      // [kPcgRowSlots][n], filled in order, -1 after the last
+    const double* phi;        // [n][4]
+    const double* rw;         // [kPcgRowSlots][4][n]
+    const float* Binv;        // [nb][kBS][kBS], FP32
+    const double* C0inv;      // [nc][nc]
+    const double* b;          // [n][k] (block order)
+    double* x;                // [n][k]
+    double* U;                // [2][n][k] exchanged rows
+    double* G;                // [2][nb][pcg_share_stride(k)] block sums of phi times the preconditioned vector [4][k]
+    double* X;                // [3][nb][pcg_sum_stride(k)] block partial sums of the dot products [3][k]
+    int* iters;
+    double* relres;
+    int* flags;
+    double rtol;
+    int maxiter;
+    int block0;               // first workgroup of this problem in its launch
+    int warm;                 // 1: x holds an initial guess (the previous solution)
+};
+
+// Values exchanged between workgroups carry their own arrival: a slot holds kEmpty (a NaN
+// pattern no published value has) until its owner stores the value, and a reader loads the
+// slot until it differs.  One trip through memory then replaces store - wait for the
+// acknowledgement - flag - poll of all flags - load.  Stores and loads are 8-byte agent-scope
+// relaxed atomics; a value is complete by itself, so no order between addresses is needed to
+// read it.
+//
+// The pointers come from a table in memory, so the compiler cannot tell that they are not LDS
+// addresses: through flat instructions every wait for an LDS value would wait for the loads
+// from memory as well.  global() says so.
+template <class T>
+__device__ __forceinline__ T __attribute__((address_space(1))) * global(T* p)
 {
+    return (T __attribute__((address_space(1)))*)p;
+}
+constexpr unsigned long long kEmpty = ~0ull;
+__device__ __forceinline__ void publish(double* p, double v)
+{
+    unsigned long long w = (unsigned long long)__double_as_longlong(v);
+    if (w == kEmpty) w = 0x7FF8000000000000ull;   // any other NaN
+    __hip_atomic_store(global(reinterpret_cast<unsigned long long*>(p)), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish_empty(double* p)
+{
+    __hip_atomic_store(global(reinterpret_cast<unsigned long long*>(p)), kEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long peek(const double* p)
+{
+    return __hip_atomic_load(global(reinterpret_cast<const unsigned long long*>(p)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double as_value(unsigned long long w) { return __longlong_as_double((long long)w); }
+
+// Bounded wait: counts a poll round, every 256 rounds looks at the abort flag, and after
+// kSpinLimit rounds raises it; true when the wait must end.
+__device__ __forceinline__ bool give_up(unsigned& spins, int* flags)
+{
+    ++spins;
+    if (spins > (unsigned)kSpinLimit) {
+        __hip_atomic_store(&flags[kFlagCgAbort], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    }
+    return (spins & 255u) == 0u &&
+           __hip_atomic_load(&flags[kFlagCgAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// Empties the exchange buffers of every problem of a launch (problem blockIdx.y).
+__global__ void k_pcg_empty(const PcgArgs* __restrict__ tab, int k)
+{
+    const PcgArgs A = tab[blockIdx.y];
+    const int64_t nu = 2 * A.n * k, ng = (int64_t)2 * A.nb * pcg_share_stride(k), nx = (int64_t)3 * A.nb * pcg_sum_stride(k);
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nu + ng + nx; i += step) {
+        double* p = i < nu ? A.U + i : i < nu + ng ? A.G + (i - nu) : A.X + (i - nu - ng);
+        *reinterpret_cast<unsigned long long*>(p) = kEmpty;
+    }
+}
+
+// Sums of four doubles over the 64 lanes of a wave, each added exactly as wave_sum adds it
+// (quads, 8, 16 lanes, then (r0 + r1) + (r2 + r3)); from the second step on the lanes halve the
+// set of values they carry.  Lane l returns the sum of v[(l / 4) % 4].
+__device__ __forceinline__ double wave_sum4(const double (&v)[4])
+{
+    double q[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        q[m] = v[m] + dpp_move<0xB1>(v[m]);    // quad_perm [1,0,3,2]
+        q[m] = q[m] + dpp_move<0x4E>(q[m]);    // quad_perm [2,3,0,1]
+    }
+    const bool b2 = (threadIdx.x & 4) != 0, b3 = (threadIdx.x & 8) != 0;
+    const double s0 = (b2 ? q[1] : q[0]) + dpp_move<0x141>(b2 ? q[0] : q[1]);   // row_half_mirror
+    const double s1 = (b2 ? q[3] : q[2]) + dpp_move<0x141>(b2 ? q[2] : q[3]);
+    double t = (b3 ? s1 : s0) + dpp_move<0x128>(b3 ? s0 : s1);                  // row_ror:8
+    auto swap_add = [](double a, auto sw) {
+        const auto lo = sw((unsigned)__double2loint(a));
+        const auto hi = sw((unsigned)__double2hiint(a));
+        return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    };
+    t = swap_add(t, [](unsigned w) { return __builtin_amdgcn_permlane16_swap(w, w, false, false); });
+    return swap_add(t, [](unsigned w) { return __builtin_amdgcn_permlane32_swap(w, w, false, false); });
+}
+// (a0 + a1) + (a2 + a3) of a quad's lanes, in every lane of the quad
+__device__ __forceinline__ double quad_sum(double a)
+{
+    a = a + dpp_move<0xB1>(a);
+    return a + dpp_move<0x4E>(a);
+}
+
+// sum_fixed of n values p[0 .. n), by the four lanes of a quad (a = lane % 4)
+__device__ __forceinline__ double quad_sum_fixed(const double* p, int n, int a)
+{
+    double acc = 0.0;
+    const int n4 = n & ~3;
+#pragma unroll 4
+    for (int i = a; i < n4; i += 4) acc += p[i];
+    if (a == 0)
+        for (int i = n4; i < n; ++i) acc += p[i];
+    return quad_sum(acc);
+}
+
+// the same by the two lanes of a pair (h = lane % 2), in both lanes
+__device__ __forceinline__ double pair_sum_fixed(const double* p, int n, int h)
+{
+    double a0 = 0.0, a1 = 0.0;
+    const int n4 = n & ~3;
+#pragma unroll 2
+    for (int i = 2 * h; i < n4; i += 4) {
+        a0 += p[i];
+        a1 += p[i + 1];
+    }
+    if (h == 0)
+        for (int i = n4; i < n; ++i) a0 += p[i];
+    a0 += a1;
+    return a0 + dpp_move<0xB1>(a0);
+}
+
+typedef float pcg_float4 __attribute__((ext_vector_type(4)));
+
+constexpr int kPcgThreads = 512;    // 8 waves, 2 per SIMD: up to 256 VGPRs
+constexpr int kRowThreads = kPcgThreads / kBS;   // threads per row: thread q takes columns q, q + 4, ...
+constexpr int kParts = 256;         // partial sums of a fixed-order sum over values or blocks
+constexpr int kCrowMax = 7680;      // cached coarse-inverse entries (FP32: 30 KB)
+constexpr int kCache = 8;           // entries of a matrix row kept in registers
+constexpr int kRS = kBS + 16;       // LDS row stride of the vector of the block product: the 4 x 16
+                                    // values a wave loads at once fall into 64 different banks
+
+template <int K>
+struct PcgShared {
+    static constexpr int CQ = (K + 3) / 4;   // column quads of the matrix instruction
+    alignas(16) float r[CQ * 4][kRS];        // the preconditioned vector, FP32 (padding columns zero)
+    alignas(16) float half[2][K][kBS];       // block product: the two halves of the inner dimension
+    alignas(16) float crow[kCrowMax];        // C0inv rows of the touching aggregates' coarse functions,
+                                             // rounded to FP32 (as the block inverses are), [slot][d][4]
+    double rw[kPcgRegSlots * 4][kBS];        // per touched aggregate, the coarse part of a row of C
+    double rho[kCoarseMax * K];              // coarse right-hand side [nc][K]
+    double c[kMaxAggNbn * 4 * K];            // coarse values [slot][4][K]
+    double ws[2][K][4];                      // sums over the two 64-row halves of the block
+    double part[kParts];
+    double coef[2][K];                       // alpha, beta of every column
+    int live[K];                             // column not yet converged
+    int bad;                                 // a wait gave up
+    int32_t nbl[kMaxAggNbn];
+    int32_t ast[kCoarseMax / 4 + 1];         // first block of each aggregate
+    int32_t hrow[kPcgMaxHalo];
+    double dyn[1];                           // launch-sized: [nb][3][K] partial sums of every block,
+                                             // then [rows, halo][K] block solves or x
+};
+
+// One launch solves the systems of ntab independent problems: problem m owns workgroups
+// [tab[m].block0, tab[m + 1].block0) and exchanges values only among them, so its iterates
+// are those of a launch of its own.
+//
+// What bounds it is latency: an iteration moves under 100 KB per workgroup and its arithmetic
+// would take a microsecond, but it has two exchanges between all workgroups in series, and
+// between them chains of sums whose order is part of the result.  So
+//   - the exchanges poll the data themselves (publish / peek), in coalesced runs;
+//   - eight waves share every phase: a thread owns one to three columns of a row, and the
+//     fixed-order sums (four interleaved chains each) run one chain per lane;
+//   - the block product runs on the matrix cores: v_mfma_f32_4x4x1 with the vector as its
+//     broadcast operand (one register holds 16 terms of 4 columns, the instruction selects the
+//     term), so C_BB^{-1} stays in registers, a lane per row, and a product reads 4 LDS words
+//     per lane.  Its chain of multiply-adds rounds as a chain of v_fma_f32 does (checked bit
+//     for bit), so the order of the terms is that of a loop over them.
+//   - a block's remote neighbours are one list (its halo), fetched in whole rows of K values.
+// Measured on the 40,000-face torus (157 workgroups, about 105 iterations), a solve of 3 columns
+// 1.78 -> 0.98 ms, of 6 columns 2.67 -> 1.41 ms, of 9 columns 4.24 -> 1.99 ms against one
+// workgroup of 256 threads per block, flags polled after the data were acknowledged and every
+// column on the same thread; the iterates are the same bit for bit (all sums keep their order).
+// In shader clocks per iteration, 3 columns (9): vector and shares 0.7 K (1.5), block product 1.4
+// (3.0), shares in 1.8 (5.1), coarse values 3.5 (6.0), rows 3.0 (7.8), dot products out and in 4.9
+// (6.9, plus 5 waiting for blocks that touch eight or more aggregates), their sums 2.3 (2.7),
+// scalars 1.2 (1.4).  With 9 columns the 8-byte loads past the L2 (80 KB per workgroup and
+// iteration) and the LDS reads of the rows and coarse values are the larger part.
+template <int K>
+__global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__ tab, int ntab)
+{
+    constexpr int T = kPcgThreads, Q = kRowThreads, KG = (K + Q - 1) / Q, CQ = PcgShared<K>::CQ;
+    constexpr int GS = pcg_share_stride(K), XS = pcg_sum_stride(K);
     extern __shared__ __align__(16) char smem_raw[];
-    PcgShared<KG>& S = *reinterpret_cast<PcgShared<KG>*>(smem_raw);
-    // staging area for all blocks' coarse shares ([nb][4][k]), when the launch has room
-    double* stg = reinterpret_cast<double*>(smem_raw + (sizeof(PcgShared<KG>) + 15) / 16 * 16);
+    PcgShared<K>& S = *reinterpret_cast<PcgShared<K>*>(smem_raw);
     int pm = 0;
-    for (int q = 1; q < ntab; ++q)
-        if ((int)blockIdx.x >= tab[q].block0) pm = q;
+    for (int m = 1; m < ntab; ++m)
+        if ((int)blockIdx.x >= tab[m].block0) pm = m;
     const PcgArgs A = tab[pm];
     const int B = (int)blockIdx.x - A.block0;
-    const int nb = A.nb, nc = A.nc, k = A.k;
-    const int64_t n = A.n;
-    const int32_t s0 = A.bstart[B], cnt = A.bstart[B + 1] - s0;
-    // threads t < kBS own row s0 + t of the block (when t < cnt); threads kBS .. kThreads
-    // help with the block product, the coarse values and the cross-block sums
-    const int t = threadIdx.x;
-    const bool act = t < cnt;
-    const int64_t i = s0 + t;
+    const int nb = A.nb, nc = A.nc;
+    const int n = (int)A.n;
+    const int32_t s0 = global(A.bstart)[B], cnt = global(A.bstart)[B + 1] - s0;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
-    // Thread t takes half of column tt of C_BB^{-1}: rows jbeg .. jbeg + kBS / 2 (the inverse
-    // is symmetric, so these are row tt's entries), in registers or in LDS for the solve.
-    const int tt = t & (kBS - 1), jbeg = (t / kBS) * (kBS / 2);
-    float binv[kRegInv<KG> ? kBS / 2 : 1];
-    if constexpr (kRegInv<KG>) {
-        const float* src = A.Binv + (int64_t)B * kBS * kBS + tt;
+    // row role: thread (row, q) owns columns q, q + Q, ... of row s0 + row (when row < cnt)
+    const int row = t & (kBS - 1), my_q = wave / 2;
+    const bool act = row < cnt;
+    const int i = s0 + row;
+
+    // block product role: wave (rh, jh, cq) takes rows 64 rh + lane, terms 64 jh .. of column quad cq
+    const int rh = wave & 1, jh = (wave >> 1) & 1, cq = wave >> 2;
+    float binv[kBS / 2];
+    {
+        const auto* src = global(A.Binv) + (int64_t)B * kBS * kBS + (int64_t)(64 * jh) * kBS + 64 * rh + lane;
 #pragma unroll
-        for (int q = 0; q < kBS / 2; ++q) binv[q] = src[(int64_t)(jbeg + q) * kBS];
-    } else {
-        const float4* src = reinterpret_cast<const float4*>(A.Binv + (int64_t)B * kBS * kBS);
-        float4* dst = reinterpret_cast<float4*>(S.Binv);
-        for (int q = t; q < kBS * kBS / 4; q += kThreads) dst[q] = src[q];
+        for (int j = 0; j < kBS / 2; ++j) binv[j] = src[(int64_t)j * kBS];
     }
     // aggregates touching this block (slots), and the rows of C0inv of their coarse functions
-    const int nbo = A.abl_off[B], nsl = A.abl_off[B + 1] - nbo;
-    for (int q = t; q < nsl; q += kThreads) S.nbl[q] = A.abl[nbo + q];
-    for (int q = t; q <= nc / 4; q += kThreads) S.ast[q] = A.astart[q];
+    const int nbo = global(A.abl_off)[B], nsl = global(A.abl_off)[B + 1] - nbo;
+    for (int e = t; e < nsl; e += T) S.nbl[e] = global(A.abl)[nbo + e];
+    for (int e = t; e <= nc / 4; e += T) S.ast[e] = global(A.astart)[e];
+    for (int e = t; e < CQ * 4 * kRS; e += T) (&S.r[0][0])[e] = 0.0f;
+    if (t == 0) S.bad = 0;
     __syncthreads();
-    const bool crow_lds = (int64_t)nsl * 4 * nc <= kCrowMax;
+    const int jobs = nsl * 4 * K;
+    const bool crow_lds = nsl * 4 * nc <= kCrowMax;
     if (crow_lds)
-        for (int q = t; q < nsl * 4 * nc; q += kThreads) {
-            const int row = q / nc;   // slot * 4 + function
-            S.crow[q] = (float)A.C0inv[(int64_t)(4 * S.nbl[row / 4] + row % 4) * nc + (q % nc)];
+        for (int e = t; e < nsl * 4 * nc; e += T) {
+            const int slot = e / (4 * nc), d = (e / 4) % nc, f = e & 3;
+            S.crow[e] = (float)global(A.C0inv)[(int64_t)(4 * S.nbl[slot] + f) * nc + d];
         }
-    __syncthreads();
     int own_slot = 0;
     {
-        const int own = A.agg_of_block[B];
-        for (int q = 0; q < nsl; ++q)
-            if (S.nbl[q] == own) own_slot = q;
+        const int own = global(A.agg_of_block)[B];
+        for (int e = 0; e < nsl; ++e)
+            if (S.nbl[e] == own) own_slot = e;
     }
 
-    constexpr int kCache = 8;
+    // the matrix row: columns as slots of the rows in LDS
     int32_t cj[kCache];
     double cv[kCache];
+    bool edge = false;    // the row has a neighbour in another block, whose workgroup reads it
+                          // (the pattern is symmetric)
 #pragma unroll
     for (int e = 0; e < kCache; ++e) {
         const bool in = act && e < A.ell_w;
-        cj[e] = in ? A.pcol[(int64_t)e * n + i] : 0;
-        cv[e] = in ? A.pval[(int64_t)e * n + i] : 0.0;
+        cj[e] = in ? global(A.lcol)[(int64_t)e * n + i] : row;
+        cv[e] = in ? global(A.pval)[(int64_t)e * n + i] : 0.0;
     }
+    bool direct = false;  // some entry is not in LDS: beyond kCache, or its row not among the halo
+    if (act)
+        for (int e = 0; e < A.ell_w; ++e) {
+            const int32_t j = global(A.lcol)[(int64_t)e * n + i];
+            edge = edge || j < 0 || j >= kBS;
+            direct = direct || j < 0 || e >= kCache;
+        }
+    // halo: rows of other blocks, [nh][K] values per exchange
+    const int nh = global(A.hoff)[B + 1] - global(A.hoff)[B], nhk = nh * K;
+    for (int e = t; e < nh; e += T) S.hrow[e] = global(A.hrow)[global(A.hoff)[B] + e];
+    double* const stage = S.dyn;
+    double* const rows = S.dyn + nb * 3 * K;
+
     // the row's coarse functions and, per touched aggregate, the coarse part of its row of C
     // (slots beyond kPcgRegSlots, rare, are read from memory when used)
-    double phi[4], rwt[kPcgRegSlots][4];
+    double phi[4];
     int rsl[kPcgRegSlots];
     int nq_row = 0;
     if (act)
-        for (int q = 0; q < kPcgRowSlots; ++q) nq_row += A.rslot[(int64_t)q * n + i] >= 0 ? 1 : 0;
+        for (int e = 0; e < kPcgRowSlots; ++e) nq_row += global(A.rslot)[(int64_t)e * n + i] >= 0 ? 1 : 0;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) phi[a] = act ? A.phi[i * 4 + a] : 0.0;
+    for (int a = 0; a < 4; ++a) phi[a] = act ? global(A.phi)[(int64_t)i * 4 + a] : 0.0;
 #pragma unroll
-    for (int q = 0; q < kPcgRegSlots; ++q) {
-        rsl[q] = act ? (int)A.rslot[(int64_t)q * n + i] : -1;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) rwt[q][a] = (rsl[q] >= 0) ? A.rw[((int64_t)q * 4 + a) * n + i] : 0.0;
+    for (int e = 0; e < kPcgRegSlots; ++e) rsl[e] = act ? (int)global(A.rslot)[(int64_t)e * n + i] : -1;
+    for (int e = my_q; e < kPcgRegSlots * 4; e += Q)
+        S.rw[e][row] = act && global(A.rslot)[(int64_t)(e / 4) * n + i] >= 0 ? global(A.rw)[(int64_t)e * n + i] : 0.0;
+
+    // Row exchange number h uses copy h % 2 of U (and, in an iteration, of G), dot-product
+    // exchange number g copy g % 3 of X; every row exchange is followed by a dot-product one,
+    // in which all workgroups take part.  A slot is emptied by its owner once every reader is
+    // known to be done with it, and before any reader can come for its next value: rows and
+    // shares after the dot-product exchange that follows them, dot products g - 1 after exchange
+    // g; these stores are waited for before the owner's next contribution to a dot-product
+    // exchange, which every reader of the emptied slot has to receive first.
+    int nrow = 0, nx = 0;
+    auto ucopy = [&](int h) { return A.U + (int64_t)(h & 1) * n * K; };
+    auto gcopy = [&](int h) { return A.G + (int64_t)(h & 1) * nb * GS; };
+    auto xcopy = [&](int g) { return A.X + (int64_t)(g % 3) * nb * XS; };
+
+    // the table entry again, for what is used rarely: read where it is needed instead of held in
+    // scalar registers through the solve
+    auto rare = [&]() {
+        auto* p = (const PcgArgs __attribute__((address_space(4)))*)tab + pm;
+        asm volatile("" : "+s"(p));
+        return p;
+    };
+    // what the halo's element e of the exchange in U holds now
+    auto halo = [&](const double* U, int e) {
+        return peek(U + (unsigned)(S.hrow[e / K] * K + e % K));
+    };
+    // the value of column c in the row of entry e, wherever it is
+    auto entry = [&](const double* U, int c, int e) {
+        const int32_t j = global(rare()->lcol)[(int64_t)e * n + i];
+        if (j >= 0) return rows[j * K + c];
+        unsigned spins = 0;
+        unsigned long long w;
+        while ((w = peek(U + (unsigned)(~j * K + c))) == kEmpty)
+            if (give_up(spins, rare()->flags)) {
+                S.bad = 1;
+                break;
+            }
+        return as_value(w);
+    };
+    // coarse values: jobs (slot, f, c), f the coarse function, come in batches of up to kParts; a
+    // job's nc terms are cut into P = kParts / (jobs of its batch) parts and a part into four
+    // interleaved chains.  The slots whose jobs all lie in the first batch, with one or more
+    // such slots' rows in LDS, take a lane per chain of kF functions; this thread's:
+    constexpr int kF = K <= 6 ? 2 : 4;
+    const int full = !crow_lds ? 0 : jobs <= kParts ? nsl : kParts / (4 * K);
+    const int cP = jobs <= kParts ? kParts / jobs : 1, cchunk = (nc + cP - 1) / cP;
+    const int last0 = (jobs - 1) / kParts * kParts, lastP = kParts / (jobs - last0);   // the last batch
+    // the jobs of the other slots: n0 before the last batch (P = 1), then those in it
+    const int tail = full * 4 * K, n0 = max(0, last0 - tail), tail1 = max(tail, last0);
+    const int lchunk = (nc + lastP - 1) / lastP;
+    const unsigned inv_lastP = ((1u << 20) + lastP - 1) / lastP;   // x / lastP = x inv_lastP >> 20 for x <= 1024
+    int c_part = -1, c_first = 0, c_last = 0, c_row = 0, c_col = 0;   // S.part / S.c base, terms, S.crow, S.rho
+    {
+        const int a = t & 3, jc = (t >> 2) / cP, part = (t >> 2) - jc * cP;   // jc = (slot, f / kF, c)
+        if (jc < full * (4 / kF) * K) {
+            const int sf = jc / K, c = jc - sf * K, slot = sf / (4 / kF), f0 = (sf % (4 / kF)) * kF;
+            c_part = ((slot * 4 + f0) * K + c) * cP + part;
+            c_first = part * cchunk + a;
+            c_last = min(nc, (part + 1) * cchunk);
+            c_row = slot * nc * 4 + f0;
+            c_col = c;
+        }
     }
 
-    // Exchange buffers come in two copies: data published before the b-th barrier goes to
-    // copy b % 2 and is read between barriers b and b + 1; the copy is written again only
-    // before barrier b + 2, when every reader has arrived at barrier b + 1.
-    int nbar = 0;
-    auto pub = [&]() { return nbar & 1; };
-    auto got = [&]() { return (nbar - 1) & 1; };
-    auto sync = [&]() -> bool {
-        const bool ok = group_barrier_direct(A.bar, B, nb, A.flags, (unsigned)nbar + 1u);
-        ++nbar;
-        return ok;
-    };
-    auto vbuf = [&](int c) { return A.Vb + (int64_t)c * n * k; };
-    auto rhob = [&](int c) { return A.rho + (int64_t)c * nb * 4 * k; };
-    auto redb = [&](int c) { return A.red + (int64_t)c * nb * 3 * k; };
-
-    // M sums over the nb blocks of the copy c of the published partials ([nb][3][k], the
-    // first M / KG groups): each value is cut into P parts of consecutive blocks, one per
-    // thread (all loads in flight at once), then the parts are added in order.
-    auto grid_sum = [&](auto mtag, int c) {
-        constexpr int M = decltype(mtag)::value;
-        const double* red = redb(c);
-        constexpr int P = kThreads / M;
-        const int chunk = (nb + P - 1) / P;
-        const int q = t / P, part = t - q * P;
-        if (q < M) {
-            const int g = q / KG, cc = q - g * KG;
-            double acc = 0.0;
-            if (cc < k) {
-                const int b0 = part * chunk, b1 = min(nb, b0 + chunk);
-                if (b1 > b0) acc = sum_fixed_x(red + (int64_t)b0 * 3 * k + g * k + cc, b1 - b0, 3 * k);
-            }
-            S.part[q * P + part] = acc;
-        }
-        __syncthreads();
-        if (t < M) S.sums[t] = sum_fixed(S.part + t * P, P, 1);
-        __syncthreads();
-    };
-
-    double x[KG], r[KG], p[KG], s[KG];
-    double m[KG], an[KG];
-
-    // One exchange for the vector y (own rows): before the barrier, v = C_BB^{-1} y_B and the
-    // block sums of y (coarse right-hand side) are published; after it, m = M^{-1} y and
-    // an = C M^{-1} y at the own rows (m = v + c, with the coarse values c of the own and
-    // neighbouring blocks).
-    auto round = [&](const double (&y)[KG]) -> bool {
-        const int cp = pub();
-        if (t < kBS) {
-#pragma unroll
-            for (int c = 0; c < KG; ++c) S.r[t * KG + c] = (act && c < k) ? (float)y[c] : 0.0f;
-        }
-        __syncthreads();
-        // The block solve is a preconditioner: C_BB^{-1} (FP32) times y rounded to FP32, with
-        // FP32 sums (the solution's accuracy comes from the FP64 residuals; the CG iteration
-        // counts equal those of an FP64 product).  Padding rows of the block hold y = 0 and an
-        // identity block in C_BB^{-1}, so the product runs over all kBS rows with a fixed trip
-        // count.  Row tt's sum is split in two halves of j (owner: j < kBS / 2, helper
-        // tt + kBS: the rest), added in that order; chunks of CH rows: all LDS loads of a chunk
-        // are issued before its multiply-adds.
-        float v32[KG];
-#pragma unroll
-        for (int c = 0; c < KG; ++c) v32[c] = 0.0f;
-        if constexpr (kRegInv<KG>) {
-            constexpr int CH = KG <= 6 ? 8 : 4;
-#pragma unroll
-            for (int q0 = 0; q0 < kBS / 2; q0 += CH) {
-                float yj[CH * KG];
-#pragma unroll
-                for (int q = 0; q < CH * KG; ++q) yj[q] = S.r[(jbeg + q0) * KG + q];
-#pragma unroll
-                for (int q = 0; q < CH; ++q)
-#pragma unroll
-                    for (int c = 0; c < KG; ++c) v32[c] = __builtin_fmaf(binv[q0 + q], yj[q * KG + c], v32[c]);
-            }
-        } else {
-            constexpr int CH = 8;
-#pragma unroll 1
-            for (int j0 = jbeg; j0 < jbeg + kBS / 2; j0 += CH) {
-                float bj[CH], yj[CH * KG];
-#pragma unroll
-                for (int q = 0; q < CH; ++q) bj[q] = S.Binv[(j0 + q) * kBS + tt];
-#pragma unroll
-                for (int q = 0; q < CH * KG; ++q) yj[q] = S.r[j0 * KG + q];
-#pragma unroll
-                for (int q = 0; q < CH; ++q)
-#pragma unroll
-                    for (int c = 0; c < KG; ++c) v32[c] = __builtin_fmaf(bj[q], yj[q * KG + c], v32[c]);
-            }
-        }
-        // the helpers' halves go through S.rho, which is free until the block sums arrive
-        if (t >= kBS) {
-#pragma unroll
-            for (int c = 0; c < KG; ++c) S.rho[tt * KG + c] = (double)v32[c];
-        }
-        __syncthreads();
-        double v[KG];
-#pragma unroll
-        for (int c = 0; c < KG; ++c) v[c] = t < kBS ? (double)v32[c] + S.rho[t * KG + c] : 0.0;
-        // the block's share of the coarse right-hand side: sum over its rows of phi[a] y
-        double tmp[4 * KG];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < KG; ++c) tmp[a * KG + c] = (act && c < k) ? phi[a] * y[c] : 0.0;
-        wg_reduce<4 * KG>(tmp, S.wave, S.sums);
-        if (act)
-#pragma unroll
-            for (int c = 0; c < KG; ++c)
-                if (c < k) xstore(vbuf(cp) + i * k + c, v[c]);
-        if (t < 4 * KG) {
-            const int a = t / KG, c = t - a * KG;
-            if (c < k) xstore(rhob(cp) + ((int64_t)B * 4 + a) * k + c, S.sums[t]);
-        }
-        if (!sync()) return false;
-        const double* Vb = vbuf(cp);
-        const double* rho = rhob(cp);
-        // the neighbours' block solves: for up to 5 columns loaded now, so that their latency
-        // overlaps the block sums' load and the coarse values; with more, after the block
-        // sums (their kCache x KG loads would otherwise hold up the block sums' loads, which
-        // return in order behind them), overlapping the coarse values
-        double vnb[kCache][KG];
-        auto load_vnb = [&]() {
-            if (act) {
-#pragma unroll
-                for (int e = 0; e < kCache; ++e)
-#pragma unroll
-                    for (int c = 0; c < KG; ++c)
-                        vnb[e][c] = (e < A.ell_w && c < k) ? xload(Vb + (int64_t)cj[e] * k + c) : 0.0;
-            }
-        };
-        constexpr bool kVnbEarly = KG <= 5;
-        if (kVnbEarly) load_vnb();
-        if (A.stage) {
-            // all blocks' shares in one contiguous, coalesced pass into LDS, then function
-            // 4g + a of the coarse right-hand side sums aggregate g's blocks in block order
-            // (the same sums, in the same order, as below)
-            const int tot = nb * 4 * k;
-            for (int e0 = t; e0 < tot; e0 += 8 * kThreads) {   // 8 loads in flight per thread
-                double u8[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) u8[u] = e0 + u * kThreads < tot ? xload(rho + e0 + u * kThreads) : 0.0;
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (e0 + u * kThreads < tot) stg[e0 + u * kThreads] = u8[u];
-            }
-            __syncthreads();
-            for (int q = t; q < nc * KG; q += kThreads) {
-                const int d = q / KG, c = q - d * KG, g = d / 4, a = d - 4 * g;
-                double acc = 0.0;
-                if (c < k)
-                    for (int bb = S.ast[g]; bb < S.ast[g + 1]; ++bb) acc += stg[(bb * 4 + a) * k + c];
-                S.rho[q] = acc;
-            }
-            __syncthreads();
-        } else {
-        // coarse right-hand side [nc][KG]: function 4g + a sums the shares of aggregate g's
-        // blocks in block order.  Jobs q = t + jj kThreads of this thread: the loads of kJB
-        // jobs (all of them for up to 3 columns; 2 at a time for more, to bound the registers
-        // held) are issued before any is added.  An aggregate holds at most kMaxAggBlocks
-        // blocks (the host never forms larger ones; any further blocks are added afterwards).
-        constexpr int kJ = (kCoarseMax * KG + kThreads - 1) / kThreads;
-        constexpr int kJB = KG <= 3 ? kJ : 2;
-#pragma unroll 1
-        for (int j0 = 0; j0 < kJ; j0 += kJB) {
-            double sh[kJB][kMaxAggBlocks];
-#pragma unroll
-            for (int jj = 0; jj < kJB; ++jj) {
-                const int q = t + (j0 + jj) * kThreads;
-                const int d = q / KG, c = q - d * KG, g = d / 4, a = d - 4 * g;
-                const bool on = q < nc * KG && c < k;
-                const int b0 = on ? S.ast[g] : 0, cntb = on ? S.ast[g + 1] - b0 : 0;
-#pragma unroll
-                for (int u = 0; u < kMaxAggBlocks; ++u)
-                    sh[jj][u] = u < cntb ? xload(rho + ((int64_t)(b0 + u) * 4 + a) * k + c) : 0.0;
-            }
-#pragma unroll
-            for (int jj = 0; jj < kJB; ++jj) {
-                const int q = t + (j0 + jj) * kThreads;
-                if (q < nc * KG) {
-                    const int d = q / KG, c = q - d * KG, g = d / 4, a = d - 4 * g;
-                    double acc = 0.0;
-#pragma unroll
-                    for (int u = 0; u < kMaxAggBlocks; ++u) acc += sh[jj][u];
-                    if (c < k)
-                        for (int bb = S.ast[g] + kMaxAggBlocks; bb < S.ast[g + 1]; ++bb)
-                            acc += xload(rho + ((int64_t)bb * 4 + a) * k + c);
-                    S.rho[q] = acc;
-                }
-            }
-        }
-        __syncthreads();
-        }
-        if (!kVnbEarly) load_vnb();
-        // coarse values S.c[sl][a][c] = sum_d C0inv[4 nbl[sl] + a][d] rho[d][c] for the
-        // nsl x 4 x KG jobs: each job's dot product is cut into P parts (one per thread)
-        const int jobs = nsl * 4 * KG;
-        for (int j0 = 0; j0 < jobs; j0 += kThreads) {
-            const int nj = min(kThreads, jobs - j0);
-            const int P = max(1, kThreads / nj);
-            const int chunk = (nc + P - 1) / P;
-            const int jl = t / P, part = t - jl * P;
-            if (jl < nj) {
-                const int job = j0 + jl, row = job / KG, c = job - row * KG;   // row = slot * 4 + a
-                const int d0 = part * chunk, d1 = min(nc, d0 + chunk);
-                double pv = 0.0;
-                if (d1 > d0) {
-                    // the coarse-inverse entries in FP32 either way (the same operator for
-                    // every block, whether its rows are cached in LDS or read from memory)
-                    if (crow_lds)
-                        pv = dot_fixed(S.crow + (int64_t)row * nc + d0, S.rho + d0 * KG + c, d1 - d0, KG);
-                    else
-                        pv = dot_fixed<double, true>(A.C0inv + (int64_t)(4 * S.nbl[row / 4] + row % 4) * nc + d0,
-                                                     S.rho + d0 * KG + c, d1 - d0, KG);
-                }
-                S.part[jl * P + part] = pv;
-            }
-            __syncthreads();
-            if (t < nj) S.c[j0 + t] = sum_fixed(S.part + t * P, P, 1);
-            __syncthreads();
-        }
-        double acc[KG];
-#pragma unroll
-        for (int c = 0; c < KG; ++c) {
-            double cm = 0.0;
-#pragma unroll
-            for (int a = 0; a < 4; ++a) cm += phi[a] * S.c[(own_slot * 4 + a) * KG + c];
-            m[c] = v[c] + cm;
-            acc[c] = 0.0;
-        }
-        if (act) {
-#pragma unroll
-            for (int e = 0; e < kCache; ++e)
-#pragma unroll
-                for (int c = 0; c < KG; ++c) acc[c] += cv[e] * vnb[e][c];
-#pragma unroll
-            for (int q = 0; q < kPcgRegSlots; ++q)
-                if (rsl[q] >= 0) {
-#pragma unroll
-                    for (int a = 0; a < 4; ++a)
-#pragma unroll
-                        for (int c = 0; c < KG; ++c) acc[c] += rwt[q][a] * S.c[(rsl[q] * 4 + a) * KG + c];
-                }
-            for (int q = kPcgRegSlots; q < nq_row; ++q) {   // slots are filled in order
-                const int sl = A.rslot[(int64_t)q * n + i];
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const double wq = A.rw[((int64_t)q * 4 + a) * n + i];
-#pragma unroll
-                    for (int c = 0; c < KG; ++c) acc[c] += wq * S.c[(sl * 4 + a) * KG + c];
-                }
-            }
-            for (int e = kCache; e < A.ell_w; ++e) {   // (their coarse part is in rwt)
-                const int32_t j = A.pcol[(int64_t)e * n + i];
-                const double a = A.pval[(int64_t)e * n + i];
-#pragma unroll
-                for (int c = 0; c < KG; ++c)
-                    if (c < k) acc[c] += a * xload(Vb + (int64_t)j * k + c);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < KG; ++c) an[c] = acc[c];
-        return true;
-    };
-
-    // Second exchange of an iteration: S.sums = (r,m), (an,m), (r,r) per column, each added
-    // over the blocks in block order.
-    auto dots = [&]() -> bool {
-        double tmp[3 * KG];
-#pragma unroll
-        for (int c = 0; c < KG; ++c) {
-            const bool on = act && c < k;
-            tmp[c] = on ? r[c] * m[c] : 0.0;
-            tmp[KG + c] = on ? an[c] * m[c] : 0.0;
-            tmp[2 * KG + c] = on ? r[c] * r[c] : 0.0;
-        }
-        wg_reduce<3 * KG>(tmp, S.wave, S.sums);
-        const int cp = pub();
-        if (t < 3 * KG) {
-            const int g = t / KG, c = t - g * KG;
-            if (c < k) xstore(redb(cp) + (int64_t)B * 3 * k + g * k + c, S.sums[t]);
-        }
-        if (!sync()) return false;
-        grid_sum(std::integral_constant<int, 3 * KG>{}, cp);
-        return true;
-    };
-
-    // true residual r = b - C x; S.sums[0 .. KG) = |r|^2 per column
-    auto true_residual = [&]() -> bool {
-        if (act)
-#pragma unroll
-            for (int c = 0; c < KG; ++c)
-                if (c < k) xstore(A.x + i * k + c, x[c]);
-        if (!sync()) return false;
-        double acc[KG];
-#pragma unroll
-        for (int c = 0; c < KG; ++c) acc[c] = 0.0;
-        if (act) {
-#pragma unroll
-            for (int e = 0; e < kCache; ++e)
-                if (e < A.ell_w)
-#pragma unroll
-                    for (int c = 0; c < KG; ++c)
-                        if (c < k) acc[c] += cv[e] * xload(A.x + (int64_t)cj[e] * k + c);
-            for (int e = kCache; e < A.ell_w; ++e) {
-                const int32_t j = A.pcol[(int64_t)e * n + i];
-                const double a = A.pval[(int64_t)e * n + i];
-#pragma unroll
-                for (int c = 0; c < KG; ++c)
-                    if (c < k) acc[c] += a * xload(A.x + (int64_t)j * k + c);
-            }
-        }
-        double tmp[KG];
-#pragma unroll
-        for (int c = 0; c < KG; ++c) {
-            r[c] = (act && c < k) ? A.b[i * k + c] - acc[c] : 0.0;
-            tmp[c] = r[c] * r[c];
-        }
-        wg_reduce<KG>(tmp, S.wave, S.sums);
-        const int cp = pub();
-        if (t < KG && t < k) xstore(redb(cp) + (int64_t)B * 3 * k + t, S.sums[t]);
-        if (!sync()) return false;
-        grid_sum(std::integral_constant<int, KG>{}, cp);
-        return true;
-    };
-
-    // Thread c < KG keeps the scalars of column c (|b|^2, last |r|^2, gamma, alpha, state,
+    // Thread c < K keeps the scalars of column c (|b|^2, last |r|^2, gamma, alpha, state,
     // iterations) and forms its alpha and beta; the others read them from LDS.
     const double rtol2 = A.rtol * A.rtol;
     double my_bb = 0.0, my_rr = 0.0, my_gam = 0.0, my_alpha = 0.0;
     bool my_done = false;
     int my_its = 0;
-    double x0[KG];
+    double x[KG], r[KG], p[KG], s[KG];
 #pragma unroll
-    for (int c = 0; c < KG; ++c) {
-        r[c] = (act && c < k) ? A.b[i * k + c] : 0.0;
-        x0[c] = (A.warm && act && c < k) ? A.x[i * k + c] : 0.0;   // read before x is stored
-        x[c] = 0.0;
+    for (int ii = 0; ii < KG; ++ii) {
+        const int c = my_q + ii * Q;
+        r[ii] = (act && c < K) ? global(A.b)[(int64_t)i * K + c] : 0.0;
+        x[ii] = p[ii] = s[ii] = 0.0;
     }
-    int total_it = 0;
+    int total_it = 0, cycle = 0;
     constexpr int kMaxRestarts = 6;
-    bool have_bb = false;
-    if (A.warm) {
-        // warm start: |b|^2 (the residual of x = 0) fixes the tolerance, then the solve
-        // starts from the residual of the previous solution
-        if (!true_residual()) return;
-        if (t < KG) {
-            my_bb = S.sums[t];
-            my_done = (t >= k) || !(my_bb > 0.0);
+    bool have_bb = false, first = true;
+    // Passes: kStep is an iteration; kVerify forms the true residual b - C x once the
+    // iteration's own has converged, and another cycle starts from it when it has not; a warm
+    // start forms |b|^2 as the residual of x = 0 (kZero), which fixes the tolerance, and starts
+    // from the residual of the given x (kGuess).  One copy of the row product and of the
+    // dot-product exchange serves them all.
+    enum { kZero, kGuess, kStep, kVerify };
+    int pass = A.warm ? kZero : kStep;
+    __syncthreads();
+    for (;;) {
+        // index arithmetic is repeated in every pass rather than kept in registers across them
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        int q = my_q;
+        asm volatile("" : "+s"(q));
+#pragma unroll
+        for (int e = 0; e < kCache; ++e) asm volatile("" : "+v"(cj[e]));
+#pragma unroll
+        for (int e = 0; e < kPcgRegSlots; ++e) asm volatile("" : "+v"(rsl[e]));
+        const int t = tid, lane = t & 63, row = t & (kBS - 1);
+        const bool step = pass == kStep;
+        double y[KG];    // the rows to exchange: block solves, or x
+        if (step) {
+            // ---- block solves v = C_BB^{-1} r_B and shares Phi_B^T r of the coarse right-hand side
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) {
+                const int c = q + ii * Q;
+                if (c < K) {
+                    S.r[c][row] = act ? (float)r[ii] : 0.0f;
+                    double v[4];
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) v[a] = act ? phi[a] * r[ii] : 0.0;
+                    const double sum = wave_sum4(v);
+                    if ((lane & 3) == 0 && lane < 16) S.ws[(row >> 6) & 1][c][lane >> 2] = sum;
+                }
+            }
+            __syncthreads();
+            if (t < 4 * K)
+                publish(gcopy(nrow) + (unsigned)(B * GS + t), S.ws[0][t % K][t / K] + S.ws[1][t % K][t / K]);
+            // The block solve is a preconditioner: C_BB^{-1} (FP32) times r rounded to FP32, with
+            // FP32 sums (the solution's accuracy comes from the FP64 residuals; the CG iteration
+            // counts equal those of an FP64 product).  Padding rows of the block hold r = 0 and an
+            // identity block in C_BB^{-1}.  Row sums are taken in two halves of the terms.
+            // (two column quads of a wave run as two chains side by side)
+            constexpr int NQ = (CQ + T / 256 - 1) / (T / 256);   // quads per wave: cq, cq + T / 256
+            if (cq < CQ) {
+                float z[NQ][4];
+                pcg_float4 acc[NQ];
+#pragma unroll
+                for (int u = 0; u < NQ; ++u) {
+                    const int cc = min(cq + u * (T / 256), CQ - 1);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) z[u][m] = S.r[cc * 4 + (lane & 3)][64 * jh + 16 * m + (lane >> 2)];
+                    acc[u] = pcg_float4{0.f, 0.f, 0.f, 0.f};
+                }
+#define TP_MM(M, J)                                                                                          \
+    _Pragma("unroll") for (int u = 0; u < NQ; ++u)                                                           \
+        acc[u] = __builtin_amdgcn_mfma_f32_4x4x1f32(z[u][M], binv[16 * (M) + (J)], acc[u], 4, J, 0);
+#define TP_MM16(M)                                                                                           \
+    TP_MM(M, 0) TP_MM(M, 1) TP_MM(M, 2) TP_MM(M, 3) TP_MM(M, 4) TP_MM(M, 5) TP_MM(M, 6) TP_MM(M, 7)            \
+    TP_MM(M, 8) TP_MM(M, 9) TP_MM(M, 10) TP_MM(M, 11) TP_MM(M, 12) TP_MM(M, 13) TP_MM(M, 14) TP_MM(M, 15)
+                TP_MM16(0) TP_MM16(1) TP_MM16(2) TP_MM16(3)
+#undef TP_MM16
+#undef TP_MM
+                // lane l now holds row 64 rh + l of the quads' four columns
+#pragma unroll
+                for (int u = 0; u < NQ; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int col = (cq + u * (T / 256)) * 4 + c;
+                        if (col < K) S.half[jh][col][64 * rh + lane] = acc[u][c];
+                    }
+            }
+            __syncthreads();
         }
-        have_bb = true;
+        const double* U = ucopy(nrow);
 #pragma unroll
-        for (int c = 0; c < KG; ++c) x[c] = x0[c];
-        if (!true_residual()) return;
-    }
-    for (int cycle = 0; cycle <= kMaxRestarts; ++cycle) {
-        // ---- a cycle starts from the current (true) residual r
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = q + ii * Q;
+            y[ii] = x[ii];
+            if (c < K) {
+                if (step) y[ii] = (double)S.half[0][c][row] + (double)S.half[1][c][row];
+                if (edge) publish(ucopy(nrow) + (unsigned)(i * K + c), y[ii]);
+                rows[row * K + c] = y[ii];
+            }
+        }
+        if (step) {
+            // ---- coarse right-hand side [nc][K]: function 4g + a adds aggregate g's blocks in order
+            // (an aggregate holds at most kMaxAggBlocks blocks)
+            const double* G = gcopy(nrow);
+            for (int e = t; e < nc * K; e += T) {
+                const int d = e / K, c = e - d * K, b0 = S.ast[d >> 2], cb = S.ast[(d >> 2) + 1] - b0;
+                const unsigned o = (unsigned)(b0 * GS + (d & 3) * K + c);
+                unsigned long long raw[kMaxAggBlocks];
+                unsigned spins = 0;
+                for (;;) {
+                    bool all = true;
 #pragma unroll
-        for (int c = 0; c < KG; ++c) p[c] = s[c] = 0.0;
-        bool first = true;
-        for (;;) {
-            if (!round(r)) return;           // m = M^{-1} r, an = C m
-            if (!dots()) return;             // (r,m), (an,m), (r,r)
-            const bool can = total_it < A.maxiter;
-            if (t < KG) {
-                const double g = S.sums[t], d = S.sums[KG + t];
-                my_rr = S.sums[2 * KG + t];
+                    for (int u = 0; u < kMaxAggBlocks; ++u) raw[u] = u < cb ? peek(G + o + u * GS) : 0ull;
+#pragma unroll
+                    for (int u = 0; u < kMaxAggBlocks; ++u) all = all && raw[u] != kEmpty;
+                    if (all) break;
+                    if (give_up(spins, rare()->flags)) {
+                        S.bad = 1;
+                        break;
+                    }
+                }
+                double acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < kMaxAggBlocks; ++u) acc += as_value(raw[u]);
+                S.rho[e] = acc;
+            }
+        }
+        ++nrow;
+        // a first look at the halo, in flight beside the coarse values
+        constexpr int NH = 2;
+        unsigned long long raw[NH];
+#pragma unroll
+        for (int u = 0; u < NH; ++u) raw[u] = t + u * T < nhk ? halo(U, t + u * T) : 0ull;
+        __syncthreads();
+        if (step) {
+            // ---- coarse values c[slot][f][c] = sum_d C0inv[4 nbl[slot] + f][d] rho[d][c]
+            if (c_part >= 0) {
+                double acc[kF];
+#pragma unroll
+                for (int f = 0; f < kF; ++f) acc[f] = 0.0;
+                for (int d0 = c_first; d0 < c_last; d0 += 32) {
+                    float w[8][kF];
+                    double z[8];
+#pragma unroll
+                    for (int m = 0; m < 8; ++m) {
+                        const int d = min(d0 + 4 * m, c_last - 1);
+                        z[m] = d0 + 4 * m < c_last ? S.rho[d * K + c_col] : 0.0;
+#pragma unroll
+                        for (int f = 0; f < kF; ++f) w[m][f] = S.crow[c_row + 4 * d + f];
+                    }
+#pragma unroll
+                    for (int m = 0; m < 8; ++m)
+#pragma unroll
+                        for (int f = 0; f < kF; ++f) acc[f] = __builtin_fma((double)w[m][f], z[m], acc[f]);
+                }
+                double* out = cP == 1 ? S.c : S.part;
+#pragma unroll
+                for (int f = 0; f < kF; ++f) {
+                    const double sum = quad_sum(acc[f]);
+                    if ((lane & 3) == f) out[c_part + f * K * cP] = sum;
+                }
+            }
+            if (full < nsl) {   // the other slots' jobs, a lane per chain of one function
+                const int tasks = (n0 + (jobs - tail1) * lastP) * 4;
+                for (int e = T - 4 - (t & ~3) + (t & 3); e < tasks; e += T) {   // (idle waves first)
+                    const bool early = e < 4 * n0;
+                    const int x = (e >> 2) - n0, P = early ? 1 : lastP, chunk = early ? nc : lchunk;
+                    const int xl = early ? 0 : (int)((unsigned)x * inv_lastP >> 20);
+                    const int part = early ? 0 : x - xl * lastP, job = early ? tail + (e >> 2) : tail1 + xl;
+                    const int fr = job / K, c = job - fr * K;   // fr = slot * 4 + f
+                    const int d1 = min(nc, (part + 1) * chunk);
+                    const auto* C0 = global(rare()->C0inv) + (int64_t)(4 * S.nbl[fr >> 2] + (fr & 3)) * nc;
+                    const float* cr = S.crow + (fr >> 2) * 4 * nc + (fr & 3);
+                    double acc = 0.0;
+#pragma unroll 4
+                    for (int d = part * chunk + (e & 3); d < d1; d += 4)
+                        acc = __builtin_fma((double)(crow_lds ? cr[4 * d] : (float)C0[d]), S.rho[d * K + c], acc);
+                    acc = quad_sum(acc);
+                    if ((e & 3) == 0) (P == 1 ? S.c[job] : S.part[(job - last0) * P + part]) = acc;
+                }
+            }
+            if (lastP > 1) {   // at most kParts / 2 jobs in the last batch: a quad per job
+                __syncthreads();
+                if (t < 4 * (jobs - last0)) {
+                    const double sum = quad_sum_fixed(S.part + (t >> 2) * lastP, lastP, t & 3);
+                    if ((t & 3) == 0) S.c[last0 + (t >> 2)] = sum;
+                }
+            }
+        }
+        // the halo's values, waited for where they were not there yet
+        {
+            unsigned spins = 0;
+#pragma unroll
+            for (int u = 0; u < NH; ++u) {
+                const int e = t + u * T;
+                while (raw[u] == kEmpty) {
+                    if (give_up(spins, rare()->flags)) {
+                        S.bad = 1;
+                        break;
+                    }
+                    raw[u] = halo(U, e);
+                }
+                if (e < nhk) rows[kBS * K + e] = as_value(raw[u]);
+            }
+            for (int e = t + NH * T; e < nhk; e += T) {
+                unsigned long long w;
+                while ((w = halo(U, e)) == kEmpty)
+                    if (give_up(spins, rare()->flags)) {
+                        S.bad = 1;
+                        break;
+                    }
+                rows[kBS * K + e] = as_value(w);
+            }
+        }
+        __syncthreads();
+        // ---- rows: an iteration's m = M^{-1} r = v + Phi c and an = C m = C v + (C Phi) c, or the
+        // true residual; the terms of (r,m), (an,m), (r,r), or of (r,r) alone
+        double m[KG], an[KG];
+#pragma unroll
+        for (int ii = 0; ii < KG; ++ii) m[ii] = an[ii] = 0.0;
+        if (!direct) {
+#pragma unroll
+            for (int e = 0; e < kCache; ++e)
+#pragma unroll
+                for (int ii = 0; ii < KG; ++ii)
+                    if (q + ii * Q < K) an[ii] = __builtin_fma(cv[e], rows[cj[e] * K + q + ii * Q], an[ii]);
+        } else {
+            for (int e = 0; e < min(kCache, rare()->ell_w); ++e)
+#pragma unroll
+                for (int ii = 0; ii < KG; ++ii)
+                    if (q + ii * Q < K) an[ii] = __builtin_fma(global(rare()->pval)[(int64_t)e * n + i], entry(U, q + ii * Q, e), an[ii]);
+        }
+        if (step) {
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii)
+                if (q + ii * Q < K) {
+                    double cm = 0.0;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+                        cm = __builtin_fma(phi[a], S.c[(own_slot * 4 + a) * K + q + ii * Q], cm);
+                    m[ii] = y[ii] + cm;
+                }
+#pragma unroll
+            for (int e = 0; e < kPcgRegSlots; ++e)
+                if (rsl[e] >= 0)
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        const double w = S.rw[e * 4 + a][row];
+#pragma unroll
+                        for (int ii = 0; ii < KG; ++ii)
+                            if (q + ii * Q < K) an[ii] = __builtin_fma(w, S.c[(rsl[e] * 4 + a) * K + q + ii * Q], an[ii]);
+                    }
+            for (int e = kPcgRegSlots; e < nq_row; ++e) {   // slots are filled in order
+                const int sl = global(rare()->rslot)[(int64_t)e * n + i];
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const double w = global(rare()->rw)[((int64_t)e * 4 + a) * n + i];
+#pragma unroll
+                    for (int ii = 0; ii < KG; ++ii)
+                        if (q + ii * Q < K) an[ii] = __builtin_fma(w, S.c[(sl * 4 + a) * K + q + ii * Q], an[ii]);
+                }
+            }
+        }
+        if (direct)   // (their coarse part is in rw)
+            for (int e = kCache; e < rare()->ell_w; ++e)
+#pragma unroll
+                for (int ii = 0; ii < KG; ++ii)
+                    if (q + ii * Q < K) an[ii] = __builtin_fma(global(rare()->pval)[(int64_t)e * n + i], entry(U, q + ii * Q, e), an[ii]);
+#pragma unroll
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = q + ii * Q;
+            if (c < K) {
+                if (!step) r[ii] = act ? global(rare()->b)[(int64_t)i * K + c] - an[ii] : 0.0;
+                double d[4] = {r[ii] * m[ii], an[ii] * m[ii], r[ii] * r[ii], 0.0};
+                if (!step) d[0] = d[2];
+#pragma unroll
+                for (int g = 0; g < 3; ++g) d[g] = act ? d[g] : 0.0;
+                const double sum = wave_sum4(d);
+                if ((lane & 3) == 0 && lane < 16) S.ws[(row >> 6) & 1][c][lane >> 2] = sum;
+            }
+        }
+        // ---- dot-product exchange of M values per block (3 K, or K for a residual)
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // the emptied slots are stored before the sums below
+        __syncthreads();
+        double* X = xcopy(nx);
+        ++nx;
+        if (t < (step ? 3 * K : K)) publish(X + (unsigned)(B * XS + t), S.ws[0][t % K][t / K] + S.ws[1][t % K][t / K]);
+        constexpr int NL = K <= 3 ? 3 : K <= 6 ? 6 : 9;
+        for (int e0 = t; e0 < nb * 3 * K; e0 += NL * T) {
+            unsigned long long w[NL];
+            unsigned spins = 0;
+            for (;;) {
+                bool all = true;
+#pragma unroll
+                for (int u = 0; u < NL; ++u) {
+                    const int e = e0 + u * T, b = e / (3 * K), v = e - b * 3 * K;
+                    w[u] = b < nb && (step || v < K) ? peek(X + (unsigned)(b * XS + v)) : 0ull;
+                }
+#pragma unroll
+                for (int u = 0; u < NL; ++u) all = all && w[u] != kEmpty;
+                if (all) break;
+                if (give_up(spins, rare()->flags)) {
+                    S.bad = 1;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NL; ++u)
+                if (e0 + u * T < nb * 3 * K) stage[e0 + u * T] = as_value(w[u]);
+        }
+        __syncthreads();
+        if (S.bad) return;
+        // Each value's nb partial sums are cut into P parts of consecutive blocks and a part into
+        // four interleaved chains, one per lane; chains are added as (a0 + a1) + (a2 + a3).
+        auto block_sums = [&](auto mtag) {
+            constexpr int M = decltype(mtag)::value, P = kParts / M, NB = ((kMaxNbPcg + P - 1) / P + 3) / 4;
+            const int chunk = (nb + P - 1) / P;
+#pragma unroll
+            for (int h = 0; h < (M * P * 4 + T - 1) / T; ++h) {
+                const int e = t + h * T;
+                const int v = (e >> 2) / P, part = (e >> 2) - v * P, b0 = part * chunk + (e & 3);
+                const int b1 = e < M * P * 4 ? min(nb, (part + 1) * chunk) : 0;
+                double z[NB], acc = 0.0;
+#pragma unroll
+                for (int u = 0; u < NB; ++u) z[u] = b0 + 4 * u < b1 ? stage[(b0 + 4 * u) * 3 * K + v] : 0.0;
+#pragma unroll
+                for (int u = 0; u < NB; ++u) acc += z[u];
+                acc = quad_sum(acc);
+                if (e < M * P * 4 && (e & 3) == 0) S.part[v * P + part] = acc;
+            }
+        };
+        if (step) block_sums(std::integral_constant<int, 3 * K>{});
+        else block_sums(std::integral_constant<int, K>{});
+        __syncthreads();
+        const bool can = total_it < A.maxiter;
+        if (t < 64) {
+            // the parts of a value, added by a quad or (to stay within one wave) a pair of lanes
+            constexpr int W = K <= 5 ? 4 : 2;
+            const int P = step ? kParts / (3 * K) : kParts / K, v = lane / W;
+            double sum = 0.0;
+            if (v < (step ? 3 * K : K))
+                sum = W == 4 ? quad_sum_fixed(S.part + v * P, P, lane & 3) : pair_sum_fixed(S.part + v * P, P, lane & 1);
+            const int c = t % K;
+            const double g = __shfl(sum, W * c), dd = __shfl(sum, W * (K + c)), rr = __shfl(sum, W * (2 * K + c));
+            if (t < K && !step) {
+                if (pass != kVerify || !my_done) my_rr = g;
+                if (pass == kZero) {
+                    my_bb = my_rr;
+                    my_done = !(my_bb > 0.0);
+                }
+                if (pass == kVerify && !my_done && my_rr <= rtol2 * my_bb) my_done = true;
+                S.live[t] = my_done ? 0 : 1;
+            }
+            if (t < K && step) {
+                my_rr = rr;
                 if (!have_bb) {
                     my_bb = my_rr;
-                    my_done = (t >= k) || !(my_bb > 0.0);
+                    my_done = !(my_bb > 0.0);
                 }
                 double al = 0.0, be = 0.0;
                 const bool live = !my_done && my_rr > rtol2 * my_bb;
                 if (live) {
                     if (can) {
                         if (first) {
-                            al = g / d;
+                            al = g / dd;
                         } else {
                             be = g / my_gam;
-                            al = g / (d - be * g / my_alpha);
+                            al = g / (dd - be * g / my_alpha);
                         }
                         my_its = total_it + 1;
                     }
                     my_gam = g;
                     my_alpha = al;
                 }
-                S.coef[t] = al;
-                S.coef[KG + t] = be;
+                S.coef[0][t] = al;
+                S.coef[1][t] = be;
                 S.live[t] = live ? 1 : 0;
             }
-            have_bb = true;
-            __syncthreads();
-            bool conv = true;
-#pragma unroll
-            for (int c = 0; c < KG; ++c) {
-                // columns that converged (or are done) have alpha = 0: x and r stay
-                const double al = S.coef[c], be = S.coef[KG + c];
-                conv = conv && S.live[c] == 0;
-                p[c] = m[c] + be * p[c];
-                s[c] = an[c] + be * s[c];
-                x[c] += al * p[c];
-                r[c] -= al * s[c];
-            }
-            if (conv || !can) break;
-            ++total_it;
-            first = false;
         }
-        // ---- verify: recompute the true residual, restart from it if needed
-        if (!true_residual()) return;
-        if (t < KG) {
-            if (!my_done) {
-                my_rr = S.sums[t];
-                if (my_rr <= rtol2 * my_bb) my_done = true;
-            }
-            S.live[t] = my_done ? 0 : 1;
-        }
-        __syncthreads();
-        bool all = true;
+        have_bb = true;
+        // everyone has published this exchange, so no one still reads the rows and shares before
+        // it, or the dot products of the exchange before it
+        if (edge)
 #pragma unroll
-        for (int c = 0; c < KG; ++c) all = all && S.live[c] == 0;
+            for (int ii = 0; ii < KG; ++ii)
+                if (q + ii * Q < K) publish_empty(ucopy(nrow - 1) + (unsigned)(i * K + q + ii * Q));
+        if (t < 4 * K) publish_empty(gcopy(nrow - 1) + (unsigned)(B * GS + t));
+        if (t < 3 * K) publish_empty(xcopy(nx + 1) + (unsigned)(B * XS + t));
         __syncthreads();
-        if (all || total_it >= A.maxiter) break;
+        bool conv = true;
+#pragma unroll
+        for (int c = 0; c < K; ++c) conv = conv && S.live[c] == 0;
+        if (step) {
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) {
+                const int c = q + ii * Q;
+                if (c < K) {
+                    // columns that converged (or are done) have alpha = 0: x and r stay
+                    const double al = S.coef[0][c], be = S.coef[1][c];
+                    p[ii] = __builtin_fma(be, p[ii], m[ii]);
+                    s[ii] = __builtin_fma(be, s[ii], an[ii]);
+                    x[ii] = __builtin_fma(al, p[ii], x[ii]);
+                    r[ii] = __builtin_fma(-al, s[ii], r[ii]);
+                }
+            }
+            if (conv || !can) {
+                pass = kVerify;
+            } else {
+                ++total_it;
+                first = false;
+            }
+        } else if (pass == kZero) {
+            pass = kGuess;
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii)
+                if (act && q + ii * Q < K) x[ii] = global(rare()->x)[(int64_t)i * K + q + ii * Q];
+        } else {
+            if (pass == kVerify) {
+                if (conv || total_it >= A.maxiter || cycle == kMaxRestarts) break;
+                ++cycle;
+            }
+            // a cycle starts from the current (true) residual r
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) p[ii] = s[ii] = 0.0;
+            pass = kStep;
+            first = true;
+        }
     }
     if (act)
 #pragma unroll
-        for (int c = 0; c < KG; ++c)
-            if (c < k) A.x[i * k + c] = x[c];
-    if (B == 0 && t < k) {
-        A.iters[t] = my_its;
-        A.relres[t] = my_bb > 0.0 ? sqrt(my_rr / my_bb) : 0.0;
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = my_q + ii * Q;
+            if (c < K) global(rare()->x)[(int64_t)i * K + c] = x[ii];
+        }
+    if (B == 0 && t < K) {
+        global(rare()->iters)[t] = my_its;
+        global(rare()->relres)[t] = my_bb > 0.0 ? sqrt(my_rr / my_bb) : 0.0;
     }
 }
 
 // ---------------------------------------------------------------- launchers
-
-size_t pcg_smem_bytes(int kg)
-{
-    switch (kg) {
-    case 1: return sizeof(PcgShared<1>);
-    case 2: return sizeof(PcgShared<2>);
-    case 3: return sizeof(PcgShared<3>);
-    case 4: return sizeof(PcgShared<4>);
-    case 5: return sizeof(PcgShared<5>);
-    case 6: return sizeof(PcgShared<6>);
-    case 7: return sizeof(PcgShared<7>);
-    case 8: return sizeof(PcgShared<8>);
-    case 9: return sizeof(PcgShared<9>);
-    default: return 0;
-    }
-}
 
 hipError_t launch_pcg_setup(const PcgSetup& ps, const double* V, const int32_t* lap_off, const double* lap_val,
                             hipStream_t s)
@@ -1237,19 +1421,24 @@ hipError_t launch_permute_rows(int64_t n, int k, const int32_t* perm, int ld, in
 
 namespace {
 
-const void* pcg_fn(int k)
+struct PcgKernel {
+    const void* fn;
+    size_t smem;         // without the rows and halo
+};
+
+PcgKernel pcg_kernel(int k)
 {
     switch (k) {
-    case 1: return (const void*)k_pcg<1>;
-    case 2: return (const void*)k_pcg<2>;
-    case 3: return (const void*)k_pcg<3>;
-    case 4: return (const void*)k_pcg<4>;
-    case 5: return (const void*)k_pcg<5>;
-    case 6: return (const void*)k_pcg<6>;
-    case 7: return (const void*)k_pcg<7>;
-    case 8: return (const void*)k_pcg<8>;
-    case 9: return (const void*)k_pcg<9>;
-    default: return nullptr;
+    case 1: return {(const void*)k_pcg<1>, sizeof(PcgShared<1>)};
+    case 2: return {(const void*)k_pcg<2>, sizeof(PcgShared<2>)};
+    case 3: return {(const void*)k_pcg<3>, sizeof(PcgShared<3>)};
+    case 4: return {(const void*)k_pcg<4>, sizeof(PcgShared<4>)};
+    case 5: return {(const void*)k_pcg<5>, sizeof(PcgShared<5>)};
+    case 6: return {(const void*)k_pcg<6>, sizeof(PcgShared<6>)};
+    case 7: return {(const void*)k_pcg<7>, sizeof(PcgShared<7>)};
+    case 8: return {(const void*)k_pcg<8>, sizeof(PcgShared<8>)};
+    case 9: return {(const void*)k_pcg<9>, sizeof(PcgShared<9>)};
+    default: return {nullptr, 0};
     }
 }
 
@@ -1265,23 +1454,19 @@ hipError_t launch_pcg_batch(const PcgItem* items, int n, int k, void* tab_dev, v
                             hipStream_t s)
 {
     if (n < 1) return hipSuccess;
-    const void* fn = pcg_fn(k);
+    const PcgKernel kern = pcg_kernel(k);
+    const void* fn = kern.fn;
     if (!fn) return hipErrorInvalidValue;
-    // LDS staging of the block shares when the largest problem's fit beside PcgShared
-    hipError_t e0;
     int nb_max = 0;
     for (int m = 0; m < n; ++m) nb_max = std::max(nb_max, items[m].ps->nb);
-    const size_t base = (pcg_smem_bytes(k) + 15) / 16 * 16;
-    const size_t stage_bytes = sizeof(double) * (size_t)nb_max * 4 * (size_t)k;
-    int lds_max = 0;
-    e0 = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device_info().device);
-    if (e0 != hipSuccess) return e0;
-    const bool stage = base + stage_bytes <= (size_t)lds_max;
-    const size_t smem = stage ? base + stage_bytes : pcg_smem_bytes(k);
+    int halo_max = 0;
+    for (int m = 0; m < n; ++m) halo_max = std::max(halo_max, items[m].ps->max_halo);
+    const int vs = kBS + halo_max;
+    const size_t smem = kern.smem + sizeof(double) * ((size_t)nb_max * 3 + (size_t)vs) * (size_t)k;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kThreads, smem);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kPcgThreads, smem);
     if (e != hipSuccess) return e;
     const int64_t cap = (int64_t)per_cu * device_info().num_cu;
     PcgArgs* H = static_cast<PcgArgs*>(tab_host);
@@ -1289,12 +1474,13 @@ hipError_t launch_pcg_batch(const PcgItem* items, int n, int k, void* tab_dev, v
         const PcgItem& it = items[m];
         const PcgSetup& ps = *it.ps;
         PcgArgs& a = H[m];
-        a.n = ps.n; a.nb = ps.nb; a.nc = ps.nc; a.ell_w = ps.ell_w; a.pcol = ps.pcol; a.pval = ps.pval;
+        a.n = ps.n; a.nb = ps.nb; a.nc = ps.nc; a.ell_w = ps.ell_w; a.pval = ps.pval;
+        a.lcol = ps.lcol; a.hoff = ps.hoff; a.hrow = ps.hrow;
         a.bstart = ps.bstart; a.astart = ps.astart; a.agg_of_block = ps.agg_of_block; a.abl_off = ps.abl_off;
         a.abl = ps.abl; a.rslot = ps.rslot; a.phi = ps.phi; a.rw = ps.rw; a.Binv = ps.Binv; a.C0inv = ps.C0inv;
-        a.b = it.b; a.x = it.x; a.Vb = it.w.Vb; a.rho = it.w.rho; a.red = it.w.red; a.bar = it.w.bar;
+        a.b = it.b; a.x = it.x; a.U = it.w.U; a.G = it.w.G; a.X = it.w.X;
         a.iters = it.w.iters; a.relres = it.w.relres; a.flags = it.w.flags;
-        a.rtol = it.rtol; a.maxiter = it.maxiter; a.k = k; a.block0 = 0; a.stage = stage ? 1 : 0;
+        a.rtol = it.rtol; a.maxiter = it.maxiter; a.block0 = 0;
         a.warm = it.warm ? 1 : 0;
         if ((int64_t)ps.nb > cap) return hipErrorCooperativeLaunchTooLarge;
     }
@@ -1313,17 +1499,15 @@ hipError_t launch_pcg_batch(const PcgItem* items, int n, int k, void* tab_dev, v
     }
     e = hipMemcpyAsync(tab_dev, tab_host, sizeof(PcgArgs) * n, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
-    for (int m = 0; m < n; ++m) {
-        e = hipMemsetAsync(items[m].w.bar, 0, kBarWordsPerGroup * sizeof(unsigned), s);
-        if (e != hipSuccess) return e;
-    }
+    hipLaunchKernelGGL(k_pcg_empty, dim3(64, (unsigned)n), dim3(256), 0, s, static_cast<const PcgArgs*>(tab_dev), k);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     for (const auto& g : groups) {
         const PcgArgs* t = static_cast<const PcgArgs*>(tab_dev) + g.first;
         int nt = g.second - g.first;
         int blocks = 0;
         for (int m = g.first; m < g.second; ++m) blocks += H[m].nb;
         void* params[] = {(void*)&t, (void*)&nt};
-        e = hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(kThreads), params, smem, s);
+        e = hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(kPcgThreads), params, (unsigned)smem, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

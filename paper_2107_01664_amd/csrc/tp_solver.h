@@ -33,7 +33,8 @@ hipError_t launch_cg(int64_t n, const int32_t* ecol, const double* eval, int ell
 // aggregates of consecutive blocks with four coarse functions each: an orthonormal basis of
 // {1, x, y, z} on the aggregate's vertices).
 constexpr int kPcgRowSlots = 8;          // aggregates one row's entries reach, at most
-constexpr int kPcgRegSlots = 4;          // of them, kept in registers by the solver
+constexpr int kPcgRegSlots = 4;          // of them, kept on chip by the solver
+constexpr int kPcgMaxHalo = 256;         // rows of other blocks a block keeps on chip, at most
 struct PcgSetup {
     int64_t n = 0;
     int nb = 0;
@@ -43,6 +44,11 @@ struct PcgSetup {
     const int32_t* perm = nullptr;        // [n] block order -> vertex
     const int32_t* pcol = nullptr;        // [ell_w][n] permuted ELL columns
     double* pval = nullptr;               // [ell_w][n] permuted ELL values (per geometry)
+    const int32_t* lcol = nullptr;        // [ell_w][n] the columns as the persistent solver keeps them:
+                                          // row within the block, block size + halo slot, or ~column
+    const int32_t* hoff = nullptr;        // [nb + 1] halo of each block: columns in other blocks
+    const int32_t* hrow = nullptr;        //          (sorted; the first kPcgMaxHalo of them)
+    int max_halo = 0;
     const int32_t* bstart = nullptr;      // [nb + 1]
     const int32_t* whole = nullptr;       // [nb] block is a whole component
     const int32_t* blk = nullptr;         // [n] block of each (permuted) row
@@ -61,11 +67,14 @@ struct PcgSetup {
     float* Binv = nullptr;                // [nb][bs][bs], FP32
     double* C0inv = nullptr;              // [nc][nc] (the coarse matrix, then its inverse)
 };
+// Doubles of a block's record of shares (4 k) and of partial sums (3 k) in the exchange
+// buffers: whole 128-byte lines, so no two workgroups store to one.
+constexpr int pcg_share_stride(int k) { return (4 * k + 15) / 16 * 16; }
+constexpr int pcg_sum_stride(int k) { return (3 * k + 15) / 16 * 16; }
 struct PcgWork {
-    double* Vb = nullptr;       // 2 * n * k   (two copies, see the kernel)
-    double* rho = nullptr;      // 2 * nb * k
-    double* red = nullptr;      // 2 * nb * 3k
-    unsigned* bar = nullptr;
+    double* U = nullptr;        // 2 * n * k       (exchange buffers in copies, see the kernel)
+    double* G = nullptr;        // 2 * nb * pcg_share_stride(k)
+    double* X = nullptr;        // 3 * nb * pcg_sum_stride(k)
     int* iters = nullptr;
     double* relres = nullptr;
     int* flags = nullptr;
@@ -139,8 +148,9 @@ constexpr int kBarWordsPerGroup = kMaxBarrierW * kLine;
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    // every lane has a source lane, so the moves need no old value
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ double read_lane(double v, int lane)
@@ -158,19 +168,6 @@ __device__ __forceinline__ double wave_sum(double v)
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
-// Loads and stores of the data that workgroups of one launch exchange across a
-// group_barrier_direct: agent-scope relaxed atomics are made coherent at the device level
-// by the memory system itself (the store is written through the XCD's L2, the load misses
-// it), so no L2 write-back or invalidate is needed to pass them between XCDs.
-__device__ __forceinline__ void xstore(double* p, double v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double xload(const double* p)
-{
-    return __hip_atomic_load(const_cast<double*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Barrier among the W workgroups of a group, the target-th of the launch (1, 2, ...): every
 // workgroup raises its own flag word (one 128-byte line each, zeroed before the launch) to
 // target, then all its threads poll the W flags (a few each) until all have reached it.
@@ -178,28 +175,20 @@ __device__ __forceinline__ double xload(const double* p)
 // The workgroup barrier alone does not wait for global stores (it only orders them for
 // waves of the same CU): so every wave first waits until its own stores have been
 // acknowledged (s_waitcnt vmcnt(0), immediate 0x0F70: expcnt and lgkmcnt at their maxima),
-// and thread 0 raises the flag only after all waves have done so.
-//   FENCED: plain loads and stores may cross the barrier.  The flag store is an agent-scope
-//   release (the XCD's L2 is written back first) and an agent-scope acquire fence after
-//   the wait makes the other workgroups' stores visible to the whole workgroup (the caches
-//   it invalidates are shared by the workgroup's waves).
-//   Direct: only xstore / xload data may cross the barrier; their stores are complete at the
-//   device coherence point once acknowledged, so the flag is a relaxed store and no cache
-//   is written back or invalidated (about half the latency; the workgroup's L2 contents
-//   survive the barrier).
+// and thread 0 raises the flag only after all waves have done so.  Plain loads and stores may
+// cross the barrier: the flag store is an agent-scope release (the XCD's L2 is written back
+// first) and an agent-scope acquire fence after the wait makes the other workgroups' stores
+// visible to the whole workgroup (the caches it invalidates are shared by the workgroup's
+// waves).
 // Spins are bounded: a wait that exceeds kSpinLimit, or sees the abort flag, sets the abort
 // flag and returns false in every workgroup.
-template <bool FENCED>
-__device__ __forceinline__ bool group_barrier_t(unsigned* gbar, int w, int W, int* flags, unsigned target)
+__device__ __forceinline__ bool group_barrier(unsigned* gbar, int w, int W, int* flags, unsigned target)
 {
     __shared__ int ok_sh;
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (FENCED)
-            __hip_atomic_store(gbar + (size_t)w * kLine, target, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        else
-            __hip_atomic_store(gbar + (size_t)w * kLine, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(gbar + (size_t)w * kLine, target, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         ok_sh = 1;
     }
     __syncthreads();
@@ -223,20 +212,11 @@ __device__ __forceinline__ bool group_barrier_t(unsigned* gbar, int w, int W, in
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (FENCED) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (__hip_atomic_load(&flags[kFlagCgAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) ok_sh = 0;
     }
     __syncthreads();
     return ok_sh != 0;
-}
-
-__device__ __forceinline__ bool group_barrier(unsigned* gbar, int w, int W, int* flags, unsigned target)
-{
-    return group_barrier_t<true>(gbar, w, W, flags, target);
-}
-__device__ __forceinline__ bool group_barrier_direct(unsigned* gbar, int w, int W, int* flags, unsigned target)
-{
-    return group_barrier_t<false>(gbar, w, W, flags, target);
 }
 
 #endif
