@@ -466,13 +466,11 @@ struct tp_problem {
     double rho2 = 0.0;               // FP64 near-field radius^2: (2 x mean edge of the first mesh)^2
 
     // FP64 near-field grid (TP_PREC_FP32_NEAR64), rebuilt per geometry
-    DevBuf<uint32_t> ng_kin, ng_kout;
-    DevBuf<int32_t> ng_vin, ng_vout;
+    DevBuf<int32_t> ng_key, ng_rank, ng_tmp, ng_ord;
     DevBuf<float4> ng_sfx, ng_sfl;
     DevBuf<int2> ng_cell;
-    DevBuf<char> ng_tmp;
     DevBuf<NearGridParams> ng_prm;
-    NearGrid ng;
+    NearGridJob ng;
     uint64_t ng_ver = ~0ull;         // geometry version the grid was built for
 
     // pinned host mirrors of device scalars, flags and CG results; multi-problem CG tables
@@ -514,8 +512,8 @@ struct tp_problem {
              bct_far_col.bytes() + bct_near_off.bytes() + bct_near_col.bytes() + bct_yt.bytes() +
              bct_fr0.bytes() + bct_fr1.bytes() + bct_fkeys.bytes() + bct_nkeys.bytes() + bct_sorted.bytes() +
              bct_grow.bytes() + bct_tmp.bytes() + bct_cnt.bytes() + bct_rec.bytes();
-        b += ng_kin.bytes() + ng_kout.bytes() + ng_vin.bytes() + ng_vout.bytes() + ng_sfx.bytes() + ng_sfl.bytes() +
-             ng_cell.bytes() + ng_tmp.bytes() + ng_prm.bytes();
+        b += ng_key.bytes() + ng_rank.bytes() + ng_tmp.bytes() + ng_ord.bytes() + ng_sfx.bytes() + ng_sfl.bytes() +
+             ng_cell.bytes() + ng_prm.bytes();
         return b;
     }
 };
@@ -1242,36 +1240,41 @@ size_t near_grid_bytes(int64_t nF)
 {
     const int64_t gm = near_grid_gmax(nF);
     return (size_t)nF * (4 + 4 + 4 + 4 + 16 + 16) + (size_t)(gm * gm * gm) * sizeof(int2) +
-           near_grid_sort_temp_bytes(nF) + sizeof(NearGridParams);
+           sizeof(NearGridParams);
 }
 
-// The near-field grid of the current face data (built once per geometry).
-tp_status ensure_near_grid(tp_problem* P)
+// The near-field grids of the current face data of the problems that have none yet, in shared
+// launches (built once per geometry).
+tp_status ensure_near_grids(const Batch& B)
 {
-    hipStream_t s = P->stream;
-    const size_t n = (size_t)P->nF;
-    NearGrid& g = P->ng;
-    if (!g.prm) {
-        g.gmax = near_grid_gmax(P->nF);
-        const size_t gm = (size_t)g.gmax;
-        TP_TRY(P->ng_kin.ensure(n, s));
-        TP_TRY(P->ng_kout.ensure(n, s));
-        TP_TRY(P->ng_vin.ensure(n, s));
-        TP_TRY(P->ng_vout.ensure(n, s));
-        TP_TRY(P->ng_sfx.ensure(n, s));
-        TP_TRY(P->ng_sfl.ensure(n, s));
-        TP_TRY(P->ng_cell.ensure(gm * gm * gm, s));
-        g.sort_bytes = near_grid_sort_temp_bytes(P->nF);
-        TP_TRY(P->ng_tmp.ensure(g.sort_bytes, s));
-        TP_TRY(P->ng_prm.ensure(1, s));
-        g.kin = P->ng_kin.p; g.kout = P->ng_kout.p; g.vin = P->ng_vin.p; g.vout = P->ng_vout.p;
-        g.sfx = P->ng_sfx.p; g.sfl = P->ng_sfl.p; g.cell = P->ng_cell.p; g.sort_tmp = P->ng_tmp.p;
-        g.prm = P->ng_prm.p;
-    }
-    if (P->ng_ver != P->geom_ver) {
-        TP_HIP(launch_near_grid_build(g, P->fd, P->nF, (float)P->rho2, s));
+    std::vector<NearGridJob> jobs;
+    for (tp_problem* P : B) {
+        if (!near_field(P) || P->ng_ver == P->geom_ver) continue;
+        hipStream_t s = P->stream;
+        const size_t n = (size_t)P->nF;
+        NearGridJob& g = P->ng;
+        if (!g.prm) {
+            g.gmax = near_grid_gmax(P->nF);
+            const size_t gm = (size_t)g.gmax;
+            TP_TRY(P->ng_key.ensure(n, s));
+            TP_TRY(P->ng_rank.ensure(n, s));
+            TP_TRY(P->ng_tmp.ensure(n, s));
+            TP_TRY(P->ng_ord.ensure(n, s));
+            TP_TRY(P->ng_sfx.ensure(n, s));
+            TP_TRY(P->ng_sfl.ensure(n, s));
+            TP_TRY(P->ng_cell.ensure(gm * gm * gm, s));
+            TP_TRY(P->ng_prm.ensure(1, s));
+            g.key = P->ng_key.p; g.rank = P->ng_rank.p; g.tmp = P->ng_tmp.p; g.ord = P->ng_ord.p;
+            g.sfx = P->ng_sfx.p; g.sfl = P->ng_sfl.p; g.cell = P->ng_cell.p; g.prm = P->ng_prm.p;
+        }
+        g.fx = P->fd.fx; g.fl = P->fd.fl; g.tbox = P->fd.tbox;
+        g.ntiles = (int)(P->fd.cap / kTileJ);
+        g.nF = (int)P->nF;
+        g.rho2 = (float)P->rho2;
         P->ng_ver = P->geom_ver;
+        jobs.push_back(g);
     }
+    if (!jobs.empty()) TP_HIP(launch_near_grid_build(jobs.data(), (int)jobs.size(), B[0]->stream));
     return TP_OK;
 }
 
@@ -1280,16 +1283,16 @@ tp_status ensure_near_grid(tp_problem* P)
 tp_status enqueue_near(const Batch& B, const std::vector<PairPlan>& plans, int nacc, bool grad)
 {
     std::vector<PairJob> jobs;
+    TP_TRY(ensure_near_grids(B));
     for (size_t m = 0; m < B.size(); ++m) {
         tp_problem* P = B[m];
         if (!near_field(P)) continue;
         const PairPlan& pl = plans[m];
-        TP_TRY(ensure_near_grid(P));
         PairJob J = make_pair_job(P->fd, pl, P->part.p + (size_t)pl.n_split * nacc * pl.irows);
         J.n_itiles = (int)((P->nF + near_block_faces() - 1) / near_block_faces());
         J.tiles_per_split = J.ntiles_j;
         J.rho2 = (float)P->rho2;
-        J.nord = P->ng.vout;
+        J.nord = P->ng.ord;
         J.nfx = P->ng.sfx;
         J.nfl = P->ng.sfl;
         J.ncell = P->ng.cell;

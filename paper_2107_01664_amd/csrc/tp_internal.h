@@ -100,6 +100,7 @@ struct NearGridParams {
     float inv_cs;     // cells per unit length
     int g;            // cells per axis
     int n;            // faces in the grid (the real faces of the problem)
+    int used;         // places of the cell order given to cells so far (during the build)
 };
 
 // One problem's share of an all-pairs launch.  A launch covers up to kMaxPairJobs
@@ -119,7 +120,7 @@ struct PairJob {
     float rho2 = 0.f;               // TP_PREC_FP32_NEAR64: pairs with r2 < rho2 are left out
     const float4* tbox = nullptr;   // tile boxes (FaceData::tbox)
     // near-field grid (NearGrid): faces in cell order, their FP32 hi / lo barycenters in
-    // that order, [begin, end) of every cell, parameters
+    // that order, (begin, count) of every cell, parameters
     const int32_t* nord = nullptr;
     const float4* nfx = nullptr;
     const float4* nfl = nullptr;
@@ -311,24 +312,27 @@ hipError_t launch_bh_frac(const BhBuffers& b, int64_t nF, int leaf, double theta
                           const FaceData& fd, const void* ub, int kp, int k, double* nm, double* z, int64_t zstride,
                           hipStream_t s);
 
-// Buffers of the near-field grid of one problem (device memory owned by the problem).
-struct NearGrid {
-    uint32_t* kin = nullptr;      // [nF] cell index of each face
-    uint32_t* kout = nullptr;     // [nF] sorted
-    int32_t* vin = nullptr;       // [nF] face numbers
-    int32_t* vout = nullptr;      // [nF] faces in cell order (ties in face order)
-    float4* sfx = nullptr;        // [nF] fx in cell order
-    float4* sfl = nullptr;        // [nF] fl in cell order
-    int2* cell = nullptr;         // [gmax^3] (begin, end) in cell order; empty cells (0, 0)
-    void* sort_tmp = nullptr;
-    size_t sort_bytes = 0;
-    int gmax = 1;
+// Near-field grid of one problem (device memory owned by the problem): what its build reads and
+// writes.
+struct NearGridJob {
+    const float4* fx = nullptr;
+    const float4* fl = nullptr;
+    const float4* tbox = nullptr;
+    int ntiles = 0;
+    int nF = 0;
+    int gmax = 1;                 // cells per axis at most
+    float rho2 = 0.f;             // squared near radius
+    int32_t* key = nullptr;       // [nF] cell of each face
+    int32_t* rank = nullptr;      // [nF] its place among the faces of its cell, as counted
+    int32_t* tmp = nullptr;       // [nF] faces by cell, each cell's as counted
+    int32_t* ord = nullptr;       // [nF] faces by cell, each cell's in face order
+    float4* sfx = nullptr;        // [nF] fx in that order
+    float4* sfl = nullptr;        // [nF] fl in that order
+    int2* cell = nullptr;         // [gmax^3] (begin, count); empty cells (0, 0)
     NearGridParams* prm = nullptr;
 };
 int near_grid_gmax(int64_t nF);                 // cells per axis at most: cbrt(8 nF), 1..128
-size_t near_grid_sort_temp_bytes(int64_t nF);
-// Grid of the first nF faces of fd for the squared near radius rho2.
-hipError_t launch_near_grid_build(const NearGrid& g, const FaceData& fd, int64_t nF, float rho2, hipStream_t s);
+hipError_t launch_near_grid_build(const NearGridJob* jobs, int njobs, hipStream_t s);
 
 // FP64 near field (TP_PREC_FP32_NEAR64), as one launch over the problems of a batch: for
 // every face S, the pairs (S, T), T != S, whose FP32 hi+lo squared barycenter distance is

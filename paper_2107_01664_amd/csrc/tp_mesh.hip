@@ -36,11 +36,42 @@ __device__ __forceinline__ void write_pad(const FaceData& fd, int64_t s)
     fd.dn[s] = make_double4(0.0, 0.0, 0.0, 0.0);
 }
 
-__global__ void k_face_geom(const double* __restrict__ V, int64_t nV, const int32_t* __restrict__ F,
-                            int64_t nF, FaceData fd, int* __restrict__ flags)
+// Box of the FP32 barycenters (hi parts) of the real faces of the tile of kTileJ faces that this
+// thread's face s lies in (a workgroup holds whole tiles; x: the hi parts, ignored for s >= nF);
+// a tile of padding faces gets an empty box (lo = +inf, hi = -inf).
+__device__ __forceinline__ void write_tile_box(const FaceData& fd, int64_t s, const float4& x)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= fd.cap) return;
+    static_assert(kTileJ == 128, "a tile is two waves");
+    float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (s < fd.nF) {
+        v[0] = v[3] = x.x;
+        v[1] = v[4] = x.y;
+        v[2] = v[5] = x.z;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            v[m] = fminf(v[m], __shfl_xor(v[m], o));
+            v[3 + m] = fmaxf(v[3 + m], __shfl_xor(v[3 + m], o));
+        }
+    __shared__ float sh[8][6];
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0)
+        for (int m = 0; m < 6; ++m) sh[wave][m] = v[m];
+    __syncthreads();
+    if (threadIdx.x % kTileJ == 0 && s < fd.cap) {
+        const float* a = sh[wave];
+        const float* b = sh[wave + 1];
+        fd.tbox[2 * (s / kTileJ)] = make_float4(fminf(a[0], b[0]), fminf(a[1], b[1]), fminf(a[2], b[2]), 0.f);
+        fd.tbox[2 * (s / kTileJ) + 1] = make_float4(fmaxf(a[3], b[3]), fmaxf(a[4], b[4]), fmaxf(a[5], b[5]), 0.f);
+    }
+}
+
+// Face data of face s from V and F (a padding face where it cannot be formed).
+__device__ __forceinline__ void face_geom(const double* __restrict__ V, int64_t nV, const int32_t* __restrict__ F,
+                                          int64_t nF, const FaceData& fd, int* __restrict__ flags, int64_t s)
+{
     if (s >= nF) {
         write_pad(fd, s);
         return;
@@ -80,60 +111,28 @@ __global__ void k_face_geom(const double* __restrict__ V, int64_t nV, const int3
     write_face(fd, s, X[0], X[1], X[2], c0 / cn, c1 / cn, c2 / cn, 0.5 * cn);
 }
 
-// Boxes of the FP32 barycenters (hi parts) of the real faces of every tile of kTileJ
-// faces; a tile of padding faces gets an empty box (lo = +inf, hi = -inf).
-__global__ __launch_bounds__(kTileJ) void k_tile_boxes(FaceData fd)
+// One face per thread; fd.cap is a multiple of the tile.  The tile boxes ride along: their own
+// launch took as long as this one (3.3 us each at 5,000 faces, bound by the launch).
+__global__ __launch_bounds__(256) void k_face_geom(const double* __restrict__ V, int64_t nV,
+                                                   const int32_t* __restrict__ F, int64_t nF, FaceData fd,
+                                                   int* __restrict__ flags)
 {
-    __shared__ float sh[6][kTileJ];
-    const int64_t s = (int64_t)blockIdx.x * kTileJ + threadIdx.x;
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    if (s < fd.nF) {
-        const float4 x = fd.fx[s];
-        lo[0] = hi[0] = x.x;
-        lo[1] = hi[1] = x.y;
-        lo[2] = hi[2] = x.z;
-    }
-    for (int m = 0; m < 3; ++m) {
-        sh[m][threadIdx.x] = lo[m];
-        sh[3 + m][threadIdx.x] = hi[m];
-    }
-    __syncthreads();
-    for (int w = kTileJ / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int m = 0; m < 3; ++m) {
-                sh[m][threadIdx.x] = fminf(sh[m][threadIdx.x], sh[m][threadIdx.x + w]);
-                sh[3 + m][threadIdx.x] = fmaxf(sh[3 + m][threadIdx.x], sh[3 + m][threadIdx.x + w]);
-            }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        fd.tbox[2 * blockIdx.x] = make_float4(sh[0][0], sh[1][0], sh[2][0], 0.f);
-        fd.tbox[2 * blockIdx.x + 1] = make_float4(sh[3][0], sh[4][0], sh[5][0], 0.f);
-    }
-}
-
-static hipError_t launch_tile_boxes(const FaceData& fd, hipStream_t s)
-{
-    if (!fd.tbox) return hipSuccess;
-    hipLaunchKernelGGL(k_tile_boxes, dim3((unsigned)(fd.cap / kTileJ)), dim3(kTileJ), 0, s, fd);
-    return hipGetLastError();
+    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < fd.cap) face_geom(V, nV, F, nF, fd, flags, s);
+    if (fd.tbox) write_tile_box(fd, s, s < fd.cap ? fd.fx[s] : make_float4(0.f, 0.f, 0.f, 0.f));
 }
 
 hipError_t launch_face_geom(const double* V, int64_t nV, const int32_t* F, int64_t nF,
                             const FaceData& fd, int* flags, hipStream_t s)
 {
     hipLaunchKernelGGL(k_face_geom, dim3(nblocks(fd.cap)), dim3(256), 0, s, V, nV, F, nF, fd, flags);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_tile_boxes(fd, s);
+    return hipGetLastError();
 }
 
-__global__ void k_face_from_quantities(const double* __restrict__ X, const double* __restrict__ N,
-                                       const double* __restrict__ a, int64_t nF, FaceData fd,
-                                       int* __restrict__ flags)
+__device__ __forceinline__ void face_from_quantities(const double* __restrict__ X, const double* __restrict__ N,
+                                                     const double* __restrict__ a, int64_t nF, const FaceData& fd,
+                                                     int* __restrict__ flags, int64_t s)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= fd.cap) return;
     if (s >= nF) {
         write_pad(fd, s);
         return;
@@ -149,13 +148,21 @@ __global__ void k_face_from_quantities(const double* __restrict__ X, const doubl
     write_face(fd, s, x0, x1, x2, n0, n1, n2, as);
 }
 
+__global__ __launch_bounds__(256) void k_face_from_quantities(const double* __restrict__ X,
+                                                              const double* __restrict__ N,
+                                                              const double* __restrict__ a, int64_t nF, FaceData fd,
+                                                              int* __restrict__ flags)
+{
+    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < fd.cap) face_from_quantities(X, N, a, nF, fd, flags, s);
+    if (fd.tbox) write_tile_box(fd, s, s < fd.cap ? fd.fx[s] : make_float4(0.f, 0.f, 0.f, 0.f));
+}
+
 hipError_t launch_face_from_quantities(const double* X, const double* N, const double* a,
                                        int64_t nF, const FaceData& fd, int* flags, hipStream_t s)
 {
     hipLaunchKernelGGL(k_face_from_quantities, dim3(nblocks(fd.cap)), dim3(256), 0, s, X, N, a, nF, fd, flags);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_tile_boxes(fd, s);
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ vertex-face incidence
