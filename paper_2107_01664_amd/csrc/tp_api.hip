@@ -370,7 +370,7 @@ struct tp_problem {
     FaceData fd;
     DevBuf<float4> fx, fl, fn, tbox;
     DevBuf<double4> dx, dn;
-    DevBuf<int> flags;
+    struct { int* p = nullptr; } flags;          // in scal's buffer
     bool geom_valid = false;     // fd describes V
     bool cotan_valid = false;    // lap_val describes V (or will, once aux_join is reached)
 
@@ -423,6 +423,7 @@ struct tp_problem {
 
     // work
     DevBuf<double> part, gface, zbuf, scal, red, vol6, edge;
+    struct { double* p = nullptr; } dot_red;     // chunk sums and counters of launch_dots, in scal's buffer
     // GMRES on A = B + B0: Krylov blocks V, Z, work vectors, small device arrays
     DevBuf<double> gm_V, gm_Z, gm_w, gm_b, gm_r, gm_x, gm_small, gm_red, gm_Q, gm_Qn, gm_AQ, gm_one, gm_dinv,
         gm_sv, gm_sw, gm_smw;
@@ -481,8 +482,7 @@ struct tp_problem {
     // device memory held by the problem
     size_t device_bytes() const
     {
-        size_t b = V.bytes() + F.bytes() + fx.bytes() + fl.bytes() + fn.bytes() + dx.bytes() + dn.bytes() +
-                   flags.bytes();
+        size_t b = V.bytes() + F.bytes() + fx.bytes() + fl.bytes() + fn.bytes() + dx.bytes() + dn.bytes();
         b += vf_off.bytes() + vf_idx.bytes() + tmp_i.bytes() + tmp_j.bytes() + lap_off.bytes() +
              lap_col.bytes() + comp.bytes() + lap_val.bytes() + inv_count.bytes() + pin_mask.bytes() +
              lap_pin.bytes() + inv_count_pin.bytes() + ell_col.bytes() +
@@ -576,22 +576,17 @@ tp_status validate_params(const tp_params* in, tp_params& out, double& sigma)
 
 tp_status check_flags(tp_problem* P)
 {
-    int h[kNumFlags] = {0, 0, 0, 0};
-    TP_HIP(hipMemcpyAsync(h, P->flags.p, sizeof(h), hipMemcpyDeviceToHost, P->stream));
+    FetchJob J;
+    J.flags = P->flags.p;
+    J.hflags = P->hflags.p;
+    TP_HIP(launch_fetch(&J, 1, P->stream));
     TP_HIP(hipStreamSynchronize(P->stream));
-    if (h[0] | h[1] | h[2] | h[3]) TP_HIP(hipMemsetAsync(P->flags.p, 0, sizeof(h), P->stream));
+    const int* h = P->hflags.p;
+    if (h[0] | h[1] | h[2] | h[3]) TP_HIP(hipMemsetAsync(P->flags.p, 0, sizeof(int) * kNumFlags, P->stream));
     if (h[kFlagBadIndex]) return fail(TP_E_BAD_INDEX, "a face refers to a vertex index outside [0, nV)");
     if (h[kFlagNonFinite]) return fail(TP_E_NONFINITE, "non-finite vertex coordinates or face quantities");
     if (h[kFlagDegenerate]) return fail(TP_E_DEGENERATE_FACE, "a face has zero area (its normal is undefined)");
     if (h[kFlagCgAbort]) return fail(TP_E_DEVICE, "CG workgroup barrier timed out");
-    return TP_OK;
-}
-
-// Read one device double (synchronous).
-tp_status read_scalars(tp_problem* P, const double* dev, double* host, int n)
-{
-    TP_HIP(hipMemcpyAsync(host, dev, sizeof(double) * n, hipMemcpyDeviceToHost, P->stream));
-    TP_HIP(hipStreamSynchronize(P->stream));
     return TP_OK;
 }
 
@@ -612,9 +607,13 @@ tp_status alloc_faces(tp_problem* P)
     P->fd.dx = P->dx.p;
     P->fd.dn = P->dn.p;
     P->fd.tbox = P->tbox.p;
-    TP_TRY(P->flags.ensure(kNumFlags, P->stream));
-    TP_HIP(hipMemsetAsync(P->flags.p, 0, sizeof(int) * kNumFlags, P->stream));
-    TP_TRY(P->scal.ensure(256, P->stream));
+    // scalars, then the sums' scratch, then the flags: one buffer, cleared once
+    constexpr size_t kScal = 256;
+    const size_t nsmall = kScal + dot_scratch_doubles() + kNumFlags;
+    TP_TRY(P->scal.ensure(nsmall, P->stream));
+    P->dot_red.p = P->scal.p + kScal;
+    P->flags.p = reinterpret_cast<int*>(P->dot_red.p + dot_scratch_doubles());
+    TP_HIP(hipMemsetAsync(P->scal.p, 0, sizeof(double) * nsmall, P->stream));
     TP_TRY(P->red.ensure(reduce_scratch_doubles(16), P->stream));
     TP_TRY(P->hs.ensure(256));
     TP_TRY(P->hflags.ensure(kNumFlags));
@@ -1015,26 +1014,6 @@ tp_status ensure_cotan(tp_problem* P)
     return TP_OK;
 }
 
-// Sum of n doubles with stride ld (device), to the host.
-tp_status device_sum(tp_problem* P, const double* x, int ld, int64_t n, double* out)
-{
-    TP_HIP(launch_dot_cols(x, ld, nullptr, 0, n, 1, P->red.p, P->scal.p, P->stream));
-    return read_scalars(P, P->scal.p, out, 1);
-}
-
-// Total area (from the current face data, which must describe Vsrc) and signed volume.
-tp_status total_area_volume(tp_problem* P, const double* Vsrc, double* area, double* vol)
-{
-    // areas are the .w lane of the FP64 barycenter array
-    TP_TRY(device_sum(P, &P->dx.p[0].w, 4, P->nF, area));
-    TP_TRY(P->vol6.ensure(P->nF, P->stream));
-    TP_HIP(launch_face_volume(Vsrc, P->F.p, P->nF, P->vol6.p, P->stream));
-    double v6 = 0;
-    TP_TRY(device_sum(P, P->vol6.p, 1, P->nF, &v6));
-    *vol = v6 / 6.0;
-    return TP_OK;
-}
-
 // ------------------------------------------------------------------ batches
 //
 // A batch is a list of problems that share a device and a stream.  The all-pairs work of
@@ -1048,13 +1027,57 @@ using Batch = std::vector<tp_problem*>;
 
 bool finite(double x) { return std::isfinite(x); }
 
-// Copy the device scalars and flags of every problem to its pinned host mirrors.
+// Copy the device scalars, flags and last solver results of every problem to its pinned host
+// mirrors (one launch: a copy each took a launch of its own).
 tp_status enqueue_fetch(const Batch& B)
 {
+    if (B.empty()) return TP_OK;
+    std::vector<FetchJob> jobs;
     for (tp_problem* P : B) {
-        TP_HIP(hipMemcpyAsync(P->hs.p, P->scal.p, sizeof(double) * kNumSlots, hipMemcpyDeviceToHost, P->stream));
-        TP_HIP(hipMemcpyAsync(P->hflags.p, P->flags.p, sizeof(int) * kNumFlags, hipMemcpyDeviceToHost, P->stream));
+        FetchJob J;
+        J.scal = P->scal.p; J.hscal = P->hs.p; J.nscal = kNumSlots;
+        J.flags = P->flags.p; J.hflags = P->hflags.p;
+        J.iters = P->cg_iters.p; J.hiters = P->hiters.p; J.relres = P->cg_relres.p; J.hrelres = P->hrelres.p;
+        J.ncg = 2 * kMaxCols;
+        jobs.push_back(J);
     }
+    TP_HIP(launch_fetch(jobs.data(), (int)jobs.size(), B[0]->stream));
+    return TP_OK;
+}
+
+// A sum of problem P into scalar slot `slot` (and its host mirror) for launch_dots, using the
+// q-th part of the problem's scratch.
+DotJob dot_job(tp_problem* P, int q, int slot, const double* x, int ldx, const double* y, int ldy, int64_t n, int ncols)
+{
+    DotJob J;
+    double* part = P->dot_red.p + (size_t)q * (dot_scratch_doubles() / kDotSlots);
+    J.x = x; J.ldx = ldx; J.y = y; J.ldy = ldy; J.n = n; J.ncols = ncols;
+    J.part = part + 8;
+    J.arrived = reinterpret_cast<unsigned*>(part);
+    J.out = P->scal.p + slot;
+    J.host = P->hs.p + slot;
+    return J;
+}
+
+// Area and six times the signed volume at Vsrc (the face data must describe Vsrc): their sums as
+// jobs of a launch_dots, from the q-th part of the problem's scratch on.
+tp_status area_volume_jobs(tp_problem* P, const double* Vsrc, int q, std::vector<DotJob>& dots)
+{
+    hipStream_t s = P->stream;
+    TP_TRY(P->vol6.ensure(P->nF, s));
+    TP_HIP(launch_face_volume(Vsrc, P->F.p, P->nF, P->vol6.p, s));
+    dots.push_back(dot_job(P, q, kSlotArea, &P->dx.p[0].w, 4, nullptr, 0, P->nF, 1));
+    dots.push_back(dot_job(P, q + 1, kSlotVol6, P->vol6.p, 1, nullptr, 0, P->nF, 1));
+    return TP_OK;
+}
+
+// Sum of n doubles (device), to the host.
+tp_status device_sum(tp_problem* P, const double* x, int64_t n, double* out)
+{
+    const DotJob J = dot_job(P, 0, kNumSlots, x, 1, nullptr, 0, n, 1);
+    TP_HIP(launch_dots(&J, 1, P->stream));
+    TP_HIP(hipStreamSynchronize(P->stream));
+    *out = P->hs.p[kNumSlots];
     return TP_OK;
 }
 
@@ -1367,13 +1390,14 @@ bool sym_grad_eligible(const tp_params& prm, int64_t nF)
     return (p == TP_PREC_FP32_HILO || p == TP_PREC_FP32 || p == TP_PREC_FP32_NEAR64) && sym_size_ok(prm, nF, kGradOutputs);
 }
 
-// E of every problem (face data must describe the point of evaluation) -> scal[slot].
-tp_status enqueue_energy(const Batch& B, int slot)
+// E of every problem (face data must describe the point of evaluation) -> scal[slot] and its host
+// mirror; with deliver the flags too (else enqueue_fetch brings them).
+tp_status enqueue_energy(const Batch& B, int slot, bool deliver = false)
 {
     if (B.empty()) return TP_OK;
     if (B[0]->prm.theta > 0.0) {
         for (tp_problem* P : B) TP_TRY(enqueue_bh(P, nullptr, slot));
-        return TP_OK;
+        return deliver ? enqueue_fetch(B) : TP_OK;
     }
     hipStream_t s = B[0]->stream;
     const int prec = B[0]->prm.precision;
@@ -1385,17 +1409,16 @@ tp_status enqueue_energy(const Batch& B, int slot)
         tp_problem* P = B[m];
         PairPlan pl = plan_for(kKindEnergy, prec, 1, P->nF, P->cap);
         if (sym_grad_eligible(P->prm, P->nF)) {
-            // symmetric kernel: part = [near field slice (irows)][pair-of-blocks partials]
-            // [a_i near_i (nF)]; the near field goes to slice 0
+            // symmetric kernel: part = [near field slice (irows)][pair-of-blocks partials]; the
+            // near field goes to slice 0
             sym[m] = 1;
             pl.n_split = 0;
-            TP_TRY(P->part.ensure((size_t)pl.irows + (size_t)sym_units(P->nF) + (size_t)P->nF, s));
+            TP_TRY(P->part.ensure((size_t)pl.irows + (size_t)sym_units(P->nF), s));
             plans.push_back(pl);
             continue;
         }
         const int slices = pl.n_split + (near_field(P) ? 1 : 0);
         TP_TRY(P->part.ensure((size_t)slices * pl.irows, s));
-        TP_TRY(P->gface.ensure((size_t)pl.irows, s));
         jobs.push_back(make_pair_job(P->fd, pl, P->part.p));
         jobs.back().rho2 = (float)P->rho2;
         plans.push_back(pl);
@@ -1415,40 +1438,54 @@ tp_status enqueue_energy(const Batch& B, int slot)
         t.stop();
     }
     TP_TRY(enqueue_near(B, plans, 1, false));
+    std::vector<DotJob> dots;
     for (size_t m = 0; m < B.size(); ++m) {
         tp_problem* P = B[m];
         const PairPlan& pl = plans[m];
+        DotJob J;
         if (sym[m]) {
             // E = the partials of the pairs of blocks, then sum_i a_i near_i, in that order
             const int64_t units = sym_units(P->nF);
-            int64_t n = units;
+            J = dot_job(P, 0, slot, P->part.p + pl.irows, 1, nullptr, 0, units, 1);
             if (near_field(P)) {
-                TP_HIP(launch_area_times(P->fd, P->part.p, P->nF, P->part.p + pl.irows + units, s));
-                n += P->nF;
+                J.kind = kDotTail;
+                J.nhead = units;
+                J.n = units + P->nF;
+                J.y = &P->dx.p[0].w;
+                J.ldy = 4;
+                J.z = P->part.p;
             }
-            TP_HIP(launch_dot_cols(P->part.p + pl.irows, 1, nullptr, 0, n, 1, P->red.p, P->scal.p + slot, s));
-            continue;
+        } else {
+            // E = sum_S a_S sum_T a_T K(S,T), the inner sum over the splits in order
+            J = dot_job(P, 0, slot, &P->dx.p[0].w, 4, P->part.p, 1, P->nF, 1);
+            J.kind = kDotSplits;
+            J.nsplit = pl.n_split + (near_field(P) ? 1 : 0);
+            J.stride = pl.irows;
         }
-        const int slices = pl.n_split + (near_field(P) ? 1 : 0);
-        TP_HIP(launch_reduce_splits(P->part.p, slices, 1, pl.irows, P->nF, P->gface.p, pl.irows, s));
-        // E = sum_S a_S sum_T a_T K(S,T)
-        TP_HIP(launch_dot_cols(&P->dx.p[0].w, 4, P->gface.p, 1, P->nF, 1, P->red.p, P->scal.p + slot, s));
+        if (deliver) {
+            J.flags = P->flags.p;
+            J.hflags = P->hflags.p;
+        }
+        dots.push_back(J);
     }
+    TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
     return TP_OK;
 }
 
-// dE of every problem into dE[m] (nV x 3) and 2E -> scal[slot].
-tp_status enqueue_gradient(const Batch& B, double* const* dE, int slot)
+// dE of every problem into dE[m] (nV x 3) and 2E -> scal[slot] and its host mirror; with deliver
+// the flags too.
+tp_status enqueue_gradient(const Batch& B, double* const* dE, int slot, bool deliver = false)
 {
     if (B.empty()) return TP_OK;
     if (B[0]->prm.theta > 0.0) {
         for (size_t m = 0; m < B.size(); ++m) TP_TRY(enqueue_bh(B[m], dE[m], slot));
-        return TP_OK;
+        return deliver ? enqueue_fetch(B) : TP_OK;
     }
     hipStream_t s = B[0]->stream;
     const int prec = B[0]->prm.precision;
     std::vector<PairJob> jobs;
     std::vector<PairPlan> plans;
+    std::vector<DotJob> dots;
     std::vector<char> sym(B.size(), 0);
     double pairs = 0;
     for (size_t m = 0; m < B.size(); ++m) {
@@ -1503,9 +1540,13 @@ tp_status enqueue_gradient(const Batch& B, double* const* dE, int slot)
         TP_HIP(launch_grad_gather(P->V.p, P->F.p, P->nV, P->nF, P->vf_off.p, P->vf_idx.p, P->gface.p,
                                   pl.irows, dE[m], s));
         // 2E = sum_S a_S dE/da_S, since dE/da_S = sum_T a_T (K(S,T) + K(T,S))
-        TP_HIP(launch_dot_cols(&P->dx.p[0].w, 4, P->gface.p + 6 * pl.irows, 1, P->nF, 1, P->red.p,
-                               P->scal.p + slot, s));
+        dots.push_back(dot_job(P, 0, slot, &P->dx.p[0].w, 4, P->gface.p + 6 * pl.irows, 1, P->nF, 1));
+        if (deliver) {
+            dots.back().flags = P->flags.p;
+            dots.back().hflags = P->hflags.p;
+        }
     }
+    TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
     return TP_OK;
 }
 
@@ -1605,8 +1646,8 @@ tp_status ensure_cg(tp_problem* P, int k)
     TP_TRY(P->cg_p.ensure((size_t)P->nV * k, s));
     TP_TRY(P->cg_red.ensure(cg_red_doubles(k), s));
     TP_TRY(P->cg_bar.ensure(cg_bar_words(k), s));
-    TP_TRY(P->cg_iters.ensure(kMaxCols, s));
-    TP_TRY(P->cg_relres.ensure(kMaxCols, s));
+    TP_TRY(P->cg_iters.ensure(2 * kMaxCols, s));
+    TP_TRY(P->cg_relres.ensure(2 * kMaxCols, s));
     TP_TRY(P->red.ensure(std::max(reduce_scratch_doubles(16), project_scratch_doubles(k, P->ncomp)), s));
     if (P->have_pcg) {
         const size_t n = (size_t)P->nV;
@@ -1661,6 +1702,7 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
 {
     if (B.empty()) return TP_OK;
     hipStream_t s = B[0]->stream;
+    const size_t res0 = (size_t)which * kMaxCols;   // this solve's iteration counts and residuals
     std::vector<size_t> pc, ml, plain;
     for (size_t m = 0; m < B.size(); ++m) {
         tp_problem* P = B[m];
@@ -1683,7 +1725,7 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
             const int kc = std::min(kMaxGroupCols, k - c0);
             TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, b[m], P->pcg_bp.p, true, s));
             TP_HIP(launch_pcg_ml(P->pcg, P->pcg_bp.p, P->pcg_xp.p, kc, P->prm.cg_rtol, P->prm.cg_maxiter, w,
-                                 P->cg_iters.p + c0, P->cg_relres.p + c0, s));
+                                 P->cg_iters.p + res0 + c0, P->cg_relres.p + res0 + c0, s));
             TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, P->pcg_xp.p, x[m], false, s));
         }
     }
@@ -1713,8 +1755,8 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
                     TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, x[pc[q]], P->pcg_xp.p, true, s));
                 it.w.U = P->pcg_U.p; it.w.G = P->pcg_G.p; it.w.X = P->pcg_X.p;
                 it.w.flags = P->flags.p;
-                it.w.iters = P->cg_iters.p + c0;
-                it.w.relres = P->cg_relres.p + c0;
+                it.w.iters = P->cg_iters.p + res0 + c0;
+                it.w.relres = P->cg_relres.p + res0 + c0;
                 it.rtol = P->prm.cg_rtol;
                 it.maxiter = P->prm.cg_maxiter;
             }
@@ -1734,7 +1776,7 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
         tp_problem* P = B[m];
         CgWork w;
         w.Z = P->cg_Z.p; w.p = P->cg_p.p; w.red = P->cg_red.p; w.bar = P->cg_bar.p;
-        w.iters = P->cg_iters.p; w.relres = P->cg_relres.p; w.flags = P->flags.p;
+        w.iters = P->cg_iters.p + res0; w.relres = P->cg_relres.p + res0; w.flags = P->flags.p;
         TP_HIP(launch_cg(P->nV, P->ell_col.p, P->ell_val.p, P->ell_w, b[m], x[m], k, P->prm.cg_rtol,
                          P->prm.cg_maxiter, w, s));
     }
@@ -1745,10 +1787,6 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
         // the pinned rows are exactly zero (the coarse correction of the preconditioner
         // leaves rounding-level values there)
         if (P->npins) TP_HIP(launch_zero_pinned(x[m], k, k, P->nV, P->pin_mask.p, s));
-        TP_HIP(hipMemcpyAsync(P->hiters.p + which * kMaxCols, P->cg_iters.p, sizeof(int) * k,
-                              hipMemcpyDeviceToHost, s));
-        TP_HIP(hipMemcpyAsync(P->hrelres.p + which * kMaxCols, P->cg_relres.p, sizeof(double) * k,
-                              hipMemcpyDeviceToHost, s));
     }
     return TP_OK;
 }
@@ -1831,8 +1869,7 @@ tp_status enqueue_precond(const Batch& B, const double* const* R, int k, double*
 tp_status run_energy(tp_problem* P, double* E)
 {
     const Batch B{P};
-    TP_TRY(enqueue_energy(B, kSlotE));
-    TP_TRY(enqueue_fetch(B));
+    TP_TRY(enqueue_energy(B, kSlotE, true));
     TP_TRY(sync_batch(B));
     TP_TRY(flag_status(P));
     *E = P->hs.p[kSlotE];
@@ -1843,8 +1880,7 @@ tp_status run_energy(tp_problem* P, double* E)
 tp_status run_gradient(tp_problem* P, double* E, double* dE)
 {
     const Batch B{P};
-    TP_TRY(enqueue_gradient(B, &dE, kSlotE));
-    TP_TRY(enqueue_fetch(B));
+    TP_TRY(enqueue_gradient(B, &dE, kSlotE, true));
     TP_TRY(sync_batch(B));
     TP_TRY(flag_status(P));
     *E = gradient_energy(P, P->hs.p[kSlotE]);
@@ -2345,7 +2381,7 @@ tp_status create_problem(const double* V, int64_t nV, const int32_t* F, int64_t 
                            nF, P->edge.p);
         double es = 0;
         if (hipGetLastError() != hipSuccess) return bail(fail(TP_E_DEVICE, "edge length launch failed"));
-        if ((st = device_sum(P, P->edge.p, 1, nF, &es)) != TP_OK) return bail(st);
+        if ((st = device_sum(P, P->edge.p, nF, &es)) != TP_OK) return bail(st);
         const double h = es / (3.0 * (double)nF);
         P->rho2 = 4.0 * h * h;
     }
@@ -2358,13 +2394,18 @@ tp_status ensure_initial_measures(tp_problem* P)
 {
     if (P->mean_edge > 0) return TP_OK;
     TP_TRY(ensure_geometry(P));
-    TP_TRY(total_area_volume(P, P->V.p, &P->area0, &P->vol0));
+    std::vector<DotJob> dots;
+    TP_TRY(area_volume_jobs(P, P->V.p, 0, dots));   // the face data describes V
     TP_TRY(P->edge.ensure(P->nF, P->stream));
     hipLaunchKernelGGL(k_face_edges, dim3((unsigned)((P->nF + 255) / 256)), dim3(256), 0, P->stream,
                        P->V.p, P->F.p, P->nF, P->edge.p);
     TP_HIP(hipGetLastError());
-    double es = 0;
-    TP_TRY(device_sum(P, P->edge.p, 1, P->nF, &es));
+    dots.push_back(dot_job(P, 2, kNumSlots, P->edge.p, 1, nullptr, 0, P->nF, 1));
+    TP_HIP(launch_dots(dots.data(), (int)dots.size(), P->stream));
+    TP_HIP(hipStreamSynchronize(P->stream));
+    P->area0 = P->hs.p[kSlotArea];
+    P->vol0 = P->hs.p[kSlotVol6] / 6.0;
+    const double es = P->hs.p[kNumSlots];
     P->mean_edge = es / (3.0 * (double)P->nF);
     return TP_OK;
 }
@@ -2453,14 +2494,11 @@ struct StepState {
     double pen0 = 0.0;   // the penalty at the start of the step
 };
 
-// Area and six times the signed volume at Vsrc (the face data must describe Vsrc).
 tp_status enqueue_area_volume(tp_problem* P, const double* Vsrc)
 {
-    hipStream_t s = P->stream;
-    TP_HIP(launch_dot_cols(&P->dx.p[0].w, 4, nullptr, 0, P->nF, 1, P->red.p, P->scal.p + kSlotArea, s));
-    TP_TRY(P->vol6.ensure(P->nF, s));
-    TP_HIP(launch_face_volume(Vsrc, P->F.p, P->nF, P->vol6.p, s));
-    TP_HIP(launch_dot_cols(P->vol6.p, 1, nullptr, 0, P->nF, 1, P->red.p, P->scal.p + kSlotVol6, s));
+    std::vector<DotJob> dots;
+    TP_TRY(area_volume_jobs(P, Vsrc, 0, dots));
+    TP_HIP(launch_dots(dots.data(), (int)dots.size(), P->stream));
     return TP_OK;
 }
 
@@ -2598,17 +2636,20 @@ tp_status step_group(std::vector<StepState*>& G)
         }
     }
     // 4. Schur system S = J Y and J y_g (device dot products of 3 columns each)
+    std::vector<DotJob> dots;
     for (StepState* S : G) {
         tp_problem* P = S->P;
         const int64_t n = P->nV;
+        int q = 0;
         for (int a = 0; a < S->kc; ++a) {
             for (int b2 = 0; b2 < S->kc; ++b2)
-                TP_HIP(launch_dot_cols(P->R.p + 3 * (1 + a), ncol, P->Y.p + 3 * (1 + b2), ncol, n, 3, P->red.p,
-                                       P->scal.p + kSlotS + 3 * (2 * a + b2), s));
-            TP_HIP(launch_dot_cols(P->R.p + 3 * (1 + a), ncol, P->Y.p, ncol, n, 3, P->red.p,
-                                   P->scal.p + kSlotR + 3 * a, s));
+                dots.push_back(dot_job(P, q++, kSlotS + 3 * (2 * a + b2), P->R.p + 3 * (1 + a), ncol,
+                                       P->Y.p + 3 * (1 + b2), ncol, n, 3));
+            dots.push_back(dot_job(P, q++, kSlotR + 3 * a, P->R.p + 3 * (1 + a), ncol, P->Y.p, ncol, n, 3));
         }
     }
+    TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
+    dots.clear();
     TP_TRY(enqueue_fetch(B));
     TP_TRY(sync_batch(B));
     std::vector<StepState*> L;
@@ -2682,18 +2723,16 @@ tp_status step_group(std::vector<StepState*>& G)
             TP_HIP(launch_add_translation(P->dir.p, P->comp.p, P->bm_t.p, n, s));
             TP_HIP(hipStreamSynchronize(s));
         }
-        TP_HIP(launch_dot_cols(P->gbuf.p, 3, P->gbuf.p, 3, n, 3, P->red.p, P->scal.p + kSlotGG, s));
-        TP_HIP(launch_dot_cols(P->gbuf.p, 3, P->dir.p, 3, n, 3, P->red.p, P->scal.p + kSlotGX, s));
-        TP_HIP(launch_max_rownorm3(P->dir.p, n, P->red.p, P->scal.p + kSlotMax, s));
-        TP_TRY(enqueue_area_volume(P, P->V.p));    // face data describes V
+        dots.push_back(dot_job(P, 0, kSlotGG, P->gbuf.p, 3, P->gbuf.p, 3, n, 3));
+        dots.push_back(dot_job(P, 1, kSlotGX, P->gbuf.p, 3, P->dir.p, 3, n, 3));
+        dots.push_back(dot_job(P, 2, kSlotMax, P->dir.p, 3, nullptr, 0, n, 1));
+        dots.back().kind = kDotMaxRow;
+        TP_TRY(area_volume_jobs(P, P->V.p, 3, dots));    // face data describes V
     }
-    {
-        Batch BL;
-        for (StepState* S : L) BL.push_back(S->P);
-        if (!BL.empty()) {
-            TP_TRY(enqueue_fetch(BL));
-            TP_TRY(sync_batch(BL));
-        }
+    if (!L.empty()) {
+        TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
+        dots.clear();
+        TP_TRY(sync_batch(B));
     }
     std::vector<StepState*> search;
     for (StepState* S : L) {
@@ -2736,8 +2775,12 @@ tp_status step_group(std::vector<StepState*>& G)
             if (S->implicit()) TP_TRY(enqueue_implicit(P));
             BS.push_back(P);
         }
-        TP_TRY(enqueue_energy(BS, kSlotE));
-        TP_TRY(enqueue_fetch(BS));
+        TP_TRY(enqueue_energy(BS, kSlotE, true));   // (the other potentials' scalars lie in scal)
+        for (StepState* S : search)
+            if (S->obstacle() || S->implicit()) {
+                TP_TRY(enqueue_fetch(BS));
+                break;
+            }
         TP_TRY(sync_batch(BS));
         std::vector<StepState*> next;
         for (StepState* S : search) {
@@ -2774,11 +2817,12 @@ tp_status step_group(std::vector<StepState*>& G)
     for (StepState* S : accepted) {
         S->R.tau = S->tau;
         S->R.backtracks = S->bt;
-        TP_TRY(enqueue_area_volume(S->P, S->P->Vt.p));
+        TP_TRY(area_volume_jobs(S->P, S->P->Vt.p, 0, dots));
         BA.push_back(S->P);
     }
     if (!BA.empty()) {
-        TP_TRY(enqueue_fetch(BA));
+        TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
+        dots.clear();
         TP_TRY(sync_batch(BA));
     }
     Batch BF;
@@ -2802,12 +2846,13 @@ tp_status step_group(std::vector<StepState*>& G)
         TP_HIP(launch_face_geom(P->V.p, P->nV, P->F.p, P->nF, P->fd, P->flags.p, s));
         P->fd_V = P->V.p;
         ++P->geom_ver;
-        TP_TRY(enqueue_area_volume(P, P->V.p));
+        TP_TRY(area_volume_jobs(P, P->V.p, 0, dots));
         if (S->obstacle()) TP_TRY(enqueue_obstacle(P));
         if (S->implicit()) TP_TRY(enqueue_implicit(P));
         BF.push_back(P);
         fin.push_back(S);
     }
+    if (!BF.empty()) TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
     TP_TRY(enqueue_energy(BF, kSlotE));
     tm.mark(7);
     if (!BF.empty()) {
@@ -2976,8 +3021,9 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
     }
     // CG state and reductions
     b += 8.0 * (double)cg_state_doubles(nV, ncol) + 8 * n * ncol + 8.0 * (double)cg_red_doubles(ncol) +
-         4.0 * (double)cg_bar_words(ncol) + 12 * kMaxCols;
-    b += 8.0 * (double)std::max(reduce_scratch_doubles(16), project_scratch_doubles(ncol, ncomp)) + 8 * 256;
+         4.0 * (double)cg_bar_words(ncol) + 24 * kMaxCols;
+    b += 8.0 * (double)std::max(reduce_scratch_doubles(16), project_scratch_doubles(ncol, ncomp)) + 8 * 256 +
+         8.0 * (double)dot_scratch_doubles();
     // all-pairs partial sums (shared by the kinds), reduced sums, face averages
     const PairPlan pe = plan_for(kKindEnergy, prec, 1, nF, cap);
     const PairPlan pg = plan_for(kKindGrad, prec, 1, nF, cap);
@@ -2985,7 +3031,7 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
     const PairPlan pf = plan_for(kKindFrac, prec, kf, nF, cap);
     double part = std::max({(double)(pe.n_split + 1) * pe.irows, 7.0 * (pg.n_split + 1) * pg.irows,
                             (double)kf * pf.n_split * pf.irows});
-    if (sym_grad_eligible(prm, nF)) part = std::max(part, (double)pe.irows + (double)sym_units(nF) + (double)nF);
+    if (sym_grad_eligible(prm, nF)) part = std::max(part, (double)pe.irows + (double)sym_units(nF));
     const double gface = std::max((double)pe.irows, 7.0 * pg.irows);
     const double esz = prec == TP_PREC_FP64 ? 8 : 4;
     b += 8 * part + 8 * gface + 8.0 * kf * pf.irows + (double)cap * ((kf + 3) / 4 * 4) * esz;

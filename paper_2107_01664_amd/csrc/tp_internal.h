@@ -188,7 +188,6 @@ hipError_t launch_grad_sym(const FaceData& fd, float* part, int K, int a0, int a
 int64_t sym_units(int64_t nF);
 hipError_t launch_energy_sym(const FaceData& fd, double* upart, int precision, double alpha, double beta, float rho2,
                              hipStream_t s);
-hipError_t launch_area_times(const FaceData& fd, const double* near, int64_t n, double* out, hipStream_t s);
 
 // Sum the n_split partials of every accumulator in split order: out[acc][i].
 hipError_t launch_reduce_splits(const double* part, int n_split, int nacc, int64_t irows,
@@ -232,9 +231,43 @@ size_t reduce_scratch_doubles(int ncols);
 // out[c] = sum_i x[i*ldx + c] * (y ? y[i*ldy + c] : 1) for c < ncols, written to device out.
 hipError_t launch_dot_cols(const double* x, int ldx, const double* y, int ldy, int64_t n,
                            int ncols, double* scratch, double* out, hipStream_t s);
-// out = max_i |x_i| over n rows of 3 (Euclidean row norms), device scalar.
-hipError_t launch_max_rownorm3(const double* x, int64_t n, double* scratch, double* out,
-                               hipStream_t s);
+// A list of such sums in one launch (any number; at most kDotSlots of one problem, which share its
+// scratch), the results also to pinned host memory:
+//   kDotPlain   out[c] = sum_i x[i ldx + c] (y ? y[i ldy + c] : 1)
+//   kDotSplits  out = sum_i x[i ldx] sum_sp y[sp stride + i], the inner sum in order
+//   kDotTail    out = sum_{i < nhead} x[i] + sum_j y[j ldy] z[j], as one sum over n terms
+//   kDotMaxRow  out = max_i |x_i| over n rows of 3 (Euclidean row norms)
+enum DotKind { kDotPlain, kDotSplits, kDotTail, kDotMaxRow };
+struct DotJob {
+    const double* x = nullptr;
+    const double* y = nullptr;
+    const double* z = nullptr;
+    int64_t n = 0, nhead = 0, stride = 0;
+    double* part = nullptr;           // chunk sums
+    unsigned* arrived = nullptr;      // workgroups done; zero between launches
+    double* out = nullptr;
+    double* host = nullptr;           // the result's mirror, or NULL
+    const int* flags = nullptr;       // copied to hflags with the result, or NULL
+    int* hflags = nullptr;
+    int ldx = 1, ldy = 1, nsplit = 0, ncols = 1, kind = kDotPlain;
+};
+constexpr int kMaxDotJobs = 24;       // jobs per launch
+constexpr int kDotSlots = 8;          // jobs of one problem per launch
+size_t dot_scratch_doubles();         // per problem: kDotSlots x (chunk sums of 3 columns, counter)
+hipError_t launch_dots(const DotJob* jobs, int njobs, hipStream_t s);
+// Device scalars, flags and solver results to pinned host memory, for a list of problems.
+struct FetchJob {
+    const double* scal = nullptr;
+    double* hscal = nullptr;
+    const int* flags = nullptr;
+    int* hflags = nullptr;
+    const int* iters = nullptr;       // or NULL
+    int* hiters = nullptr;
+    const double* relres = nullptr;
+    double* hrelres = nullptr;
+    int nscal = 0, ncg = 0;
+};
+hipError_t launch_fetch(const FetchJob* jobs, int njobs, hipStream_t s);
 // Per-component means of k columns, then x -= mean[comp].
 hipError_t launch_project_mean(double* x, int ldx, int k, int64_t n, const int32_t* comp,
                                const double* inv_count, int ncomp, double* scratch,

@@ -660,46 +660,132 @@ hipError_t launch_dot_cols(const double* x, int ldx, const double* y, int ldy, i
     return hipGetLastError();
 }
 
-__device__ __forceinline__ double block_max(double v, double* sh)
+// The same sums for a list of jobs in one launch.  A wave takes one of the kRedBlocks chunks of a
+// job: lane l holds the terms of threads l, l + 64, l + 128 and l + 192 of k_dot_partial's
+// workgroup, so the first two steps of its tree are additions in the lane and the rest shuffles,
+// in the same order.  The last of a job's workgroups to arrive adds the chunks, likewise, and
+// writes the result to the device and to pinned host memory (with the flags, when asked).
+// Partial sums and arrivals go past the L2 caches (agent-scope atomics).  What bounds it is the
+// launch: two launches and a copy to the host per sum took 12 us, of which the sums 1 us.  With one
+// launch per phase for all problems: the energy of 10,240 faces 156 -> 133 us, a step of eight
+// problems of 5,120 faces (300 launches of sums and 170 copies before) 11.05 -> 9.57 ms.
+struct DotBatch {
+    DotJob j[kMaxDotJobs];
+};
+
+__device__ __forceinline__ double chunk_tree(double v0, double v1, double v2, double v3, bool mx)
 {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + w]);
-        __syncthreads();
+    double a = mx ? fmax(v0, v2) : v0 + v2, b = mx ? fmax(v1, v3) : v1 + v3;
+    a = mx ? fmax(a, b) : a + b;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        b = __shfl_down(a, o);
+        a = mx ? fmax(a, b) : a + b;
     }
-    double r = sh[0];
+    return a;   // of lane 0
+}
+
+__global__ __launch_bounds__(256) void k_dots(DotBatch jb)
+{
+#pragma clang fp contract(off)
+    const DotJob& J = jb.j[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int q = blockIdx.x * 4 + wave;   // chunk
+    const int64_t chunk = (J.n + kRedBlocks - 1) / kRedBlocks;
+    const int64_t b = (int64_t)q * chunk, e = min(J.n, b + chunk);
+    const bool mx = J.kind == kDotMaxRow;
+    for (int c = 0; c < J.ncols; ++c) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int64_t i0 = b + lane; i0 < e; i0 += 256)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t i = i0 + 64 * u;
+                if (i >= e) continue;
+                if (mx) {
+                    const double x0 = J.x[3 * i], x1 = J.x[3 * i + 1], x2 = J.x[3 * i + 2];
+                    v[u] = fmax(v[u], sqrt(__builtin_fma(x2, x2, __builtin_fma(x1, x1, x0 * x0))));
+                } else if (J.kind == kDotSplits) {
+                    double y = 0.0;
+#pragma unroll 8
+                    for (int sp = 0; sp < J.nsplit; ++sp) y += J.y[sp * J.stride + i];
+                    v[u] = __builtin_fma(J.x[i * J.ldx], y, v[u]);
+                } else if (J.kind == kDotTail && i >= J.nhead) {
+                    const double y = J.y[(i - J.nhead) * J.ldy] * J.z[i - J.nhead];
+                    v[u] = v[u] + y;
+                } else {
+                    v[u] = __builtin_fma(J.x[i * J.ldx + c], J.y && J.kind == kDotPlain ? J.y[i * J.ldy + c] : 1.0, v[u]);
+                }
+            }
+        const double s = chunk_tree(v[0], v[1], v[2], v[3], mx);
+        if (lane == 0)
+            __hip_atomic_store(J.part + (int64_t)q * J.ncols + c, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // the partial sums have arrived
     __syncthreads();
-    return r;
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        last = __hip_atomic_fetch_add(J.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (last) __hip_atomic_store(J.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last) return;
+    for (int c = wave; c < J.ncols; c += 4) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = __hip_atomic_load(J.part + (int64_t)(lane + 64 * u) * J.ncols + c, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+        const double s = chunk_tree(v[0], v[1], v[2], v[3], mx);
+        if (lane == 0) {
+            J.out[c] = s;
+            if (J.host) J.host[c] = s;
+        }
+    }
+    if (J.flags && threadIdx.x < kNumFlags) J.hflags[threadIdx.x] = J.flags[threadIdx.x];
 }
 
-__global__ __launch_bounds__(256) void k_max_rownorm3(const double* __restrict__ x, int64_t n,
-                                                      double* __restrict__ partial)
+hipError_t launch_dots(const DotJob* jobs, int njobs, hipStream_t s)
 {
-    __shared__ double sh[256];
-    const int64_t chunk = (n + kRedBlocks - 1) / kRedBlocks;
-    const int64_t b = (int64_t)blockIdx.x * chunk, e = min(n, b + chunk);
-    double m = 0.0;
-    for (int64_t i = b + threadIdx.x; i < e; i += 256)
-        m = fmax(m, sqrt(x[3 * i] * x[3 * i] + x[3 * i + 1] * x[3 * i + 1] + x[3 * i + 2] * x[3 * i + 2]));
-    const double r = block_max(m, sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = r;
+    static_assert(kRedBlocks == 256, "a wave adds 256 chunks");
+    for (int m0 = 0; m0 < njobs; m0 += kMaxDotJobs) {
+        DotBatch jb;
+        const int n = std::min(kMaxDotJobs, njobs - m0);
+        for (int m = 0; m < n; ++m) jb.j[m] = jobs[m0 + m];
+        hipLaunchKernelGGL(k_dots, dim3(kRedBlocks / 4, n), dim3(256), 0, s, jb);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
+size_t dot_scratch_doubles() { return (size_t)kDotSlots * (kRedBlocks * 3 + 8); }
 
-__global__ __launch_bounds__(256) void k_max_final(const double* __restrict__ partial,
-                                                   double* __restrict__ out)
+// Scalars, flags and solver results of a list of problems to their pinned host mirrors.
+struct FetchBatch {
+    FetchJob j[kMaxPairJobs];
+};
+__global__ void k_fetch(FetchBatch jb)
 {
-    __shared__ double sh[256];
-    const double r = block_max(partial[threadIdx.x], sh);
-    if (threadIdx.x == 0) out[0] = r;
+    const FetchJob& J = jb.j[blockIdx.x];
+    const int t = threadIdx.x;
+    for (int i = t; i < J.nscal; i += blockDim.x) J.hscal[i] = J.scal[i];
+    if (t < kNumFlags) J.hflags[t] = J.flags[t];
+    if (J.iters)
+        for (int i = t; i < J.ncg; i += blockDim.x) {
+            J.hiters[i] = J.iters[i];
+            J.hrelres[i] = J.relres[i];
+        }
 }
-
-hipError_t launch_max_rownorm3(const double* x, int64_t n, double* scratch, double* out,
-                               hipStream_t s)
+hipError_t launch_fetch(const FetchJob* jobs, int njobs, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_max_rownorm3, dim3(kRedBlocks), dim3(256), 0, s, x, n, scratch);
-    hipLaunchKernelGGL(k_max_final, dim3(1), dim3(256), 0, s, scratch, out);
-    return hipGetLastError();
+    for (int m0 = 0; m0 < njobs; m0 += kMaxPairJobs) {
+        FetchBatch jb;
+        const int n = std::min(kMaxPairJobs, njobs - m0);
+        for (int m = 0; m < n; ++m) jb.j[m] = jobs[m0 + m];
+        hipLaunchKernelGGL(k_fetch, dim3(n), dim3(128), 0, s, jb);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Per-component means: partial[b][comp][col] over the fixed chunk of block b, then

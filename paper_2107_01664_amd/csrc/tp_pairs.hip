@@ -1063,14 +1063,6 @@ __global__ __launch_bounds__(kBlock) void k_energy32_sym(ESymArgs A, Pow pw)
     if (lane == 0) A.upart[unit] = e;
 }
 
-// out[i] = a_i near[i] (the near field's share of the energy per face), i < n.
-__global__ void k_area_times(const double4* __restrict__ dx, const double* __restrict__ near, int64_t n,
-                             double* __restrict__ out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = dx[i].w * near[i];
-}
-
 // The band [a0, a1) of rows, for faces i >= a0 kSymFaces (the others get nothing from it):
 // out[c][i] (0 before the first band) plus, in FP64 and in slice order, row T's slices
 // a in [a0, min(a1, block of i)), then, for faces of the band, row S's slices b >= block of
@@ -2034,13 +2026,6 @@ hipError_t launch_energy_sym(const FaceData& fd, double* upart, int precision, d
         else if (hilo) hipLaunchKernelGGL((k_energy32_sym<true, false, PowGen>), grid, block, 0, s, A, pw);
         else hipLaunchKernelGGL((k_energy32_sym<false, false, PowGen>), grid, block, 0, s, A, pw);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_area_times(const FaceData& fd, const double* near, int64_t n, double* out, hipStream_t s)
-{
-    if (n < 1) return hipSuccess;
-    hipLaunchKernelGGL(k_area_times, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, fd.dx, near, n, out);
     return hipGetLastError();
 }
 
