@@ -309,7 +309,8 @@ struct TabRing {
 
 // Barnes-Hut tree over a static obstacle's faces (built once, when the obstacle is set).
 struct ObsTree {
-    DevBuf<double> flo, fhi, fr2, box, na, nsx, nX, nlo, nhi, nr2;
+    DevBuf<double> flo, fhi, fr2, box, na, nsx, nX, nlo, nhi, nr2, rec;
+    DevBuf<double4> nxa, srt;
     DevBuf<uint64_t> kin, kout;
     DevBuf<char> tmp;
     DevBuf<int32_t> order, pos;
@@ -320,7 +321,7 @@ struct ObsTree {
     {
         return flo.bytes() + fhi.bytes() + fr2.bytes() + box.bytes() + na.bytes() + nsx.bytes() + nX.bytes() +
                nlo.bytes() + nhi.bytes() + nr2.bytes() + kin.bytes() + kout.bytes() + tmp.bytes() + order.bytes() +
-               pos.bytes() + counts.bytes();
+               pos.bytes() + counts.bytes() + rec.bytes() + nxa.bytes() + srt.bytes();
     }
     tp_status ensure(int64_t nFo, int leaf, hipStream_t s)
     {
@@ -328,7 +329,7 @@ struct ObsTree {
         TP_TRY(flo.ensure(3 * nFo, s));
         TP_TRY(fhi.ensure(3 * nFo, s));
         TP_TRY(fr2.ensure(nFo, s));
-        TP_TRY(box.ensure(6, s));
+        TP_TRY(box.ensure(kBhBoxDoubles, s));
         TP_TRY(kin.ensure(nFo, s));
         TP_TRY(kout.ensure(nFo, s));
         const size_t tb = bh_sort_temp_bytes(nFo);
@@ -341,12 +342,15 @@ struct ObsTree {
         TP_TRY(nlo.ensure(3 * M, s));
         TP_TRY(nhi.ensure(3 * M, s));
         TP_TRY(nr2.ensure(M, s));
+        TP_TRY(rec.ensure(8 * M, s));
+        TP_TRY(nxa.ensure(M, s));
+        TP_TRY(srt.ensure(nFo, s));
         TP_TRY(counts.ensure(2, s));
         BhBuffers& b = view;
         b = BhBuffers();
         b.flo = flo.p; b.fhi = fhi.p; b.fr2 = fr2.p; b.box = box.p; b.keys_in = kin.p; b.keys_out = kout.p;
         b.sort_tmp = tmp.p; b.sort_bytes = tb; b.order = order.p; b.pos = pos.p; b.na = na.p; b.nsx = nsx.p;
-        b.nX = nX.p; b.nlo = nlo.p; b.nhi = nhi.p; b.nr2 = nr2.p; b.counts = counts.p;
+        b.nX = nX.p; b.nlo = nlo.p; b.nhi = nhi.p; b.nr2 = nr2.p; b.rec = rec.p; b.nxa = nxa.p; b.srt = srt.p; b.counts = counts.p;
         return TP_OK;
     }
 };
@@ -448,14 +452,13 @@ struct tp_problem {
     // geometry version they describe and their block counts
     DevBuf<int32_t> bct_far_off, bct_far_col, bct_near_off, bct_near_col;
     DevBuf<uint64_t> bct_fr0, bct_fr1, bct_fkeys, bct_nkeys, bct_sorted, bct_grow;
-    DevBuf<double> bct_rec;
     DevBuf<char> bct_tmp;
     DevBuf<unsigned long long> bct_cnt;
     HostBuf<unsigned long long> bct_hcnt;
     DevBuf<double> bct_yt;
     int64_t bct_ver = -1, bct_nadm = 0, bct_ninad = 0;
-    DevBuf<double> bh_flo, bh_fhi, bh_fr2, bh_box, bh_na, bh_nsx, bh_nX, bh_nlo, bh_nhi, bh_nr2, bh_gS, bh_eS,
-        bh_accF, bh_accN;
+    DevBuf<double> bh_flo, bh_fhi, bh_fr2, bh_box, bh_na, bh_nsx, bh_nX, bh_nlo, bh_nhi, bh_nr2, bh_rec, bh_gS, bh_eS;
+    DevBuf<double4> bh_nxa, bh_srt;
     DevBuf<uint64_t> bh_kin, bh_kout;
     DevBuf<char> bh_tmp;
     DevBuf<int32_t> bh_order, bh_pos;
@@ -507,11 +510,11 @@ struct tp_problem {
              Vsave.bytes() + tab.dev.bytes();
         b += bh_flo.bytes() + bh_fhi.bytes() + bh_fr2.bytes() + bh_box.bytes() + bh_na.bytes() + bh_nsx.bytes() +
              bh_nX.bytes() + bh_nlo.bytes() + bh_nhi.bytes() + bh_nr2.bytes() + bh_gS.bytes() + bh_eS.bytes() +
-             bh_accF.bytes() + bh_accN.bytes() + bh_kin.bytes() + bh_kout.bytes() + bh_tmp.bytes() +
+             bh_rec.bytes() + bh_nxa.bytes() + bh_srt.bytes() + bh_kin.bytes() + bh_kout.bytes() + bh_tmp.bytes() +
              bh_order.bytes() + bh_pos.bytes() + bh_counts.bytes() + bh_nm.bytes() + bct_far_off.bytes() +
              bct_far_col.bytes() + bct_near_off.bytes() + bct_near_col.bytes() + bct_yt.bytes() +
              bct_fr0.bytes() + bct_fr1.bytes() + bct_fkeys.bytes() + bct_nkeys.bytes() + bct_sorted.bytes() +
-             bct_grow.bytes() + bct_tmp.bytes() + bct_cnt.bytes() + bct_rec.bytes();
+             bct_grow.bytes() + bct_tmp.bytes() + bct_cnt.bytes();
         b += ng_key.bytes() + ng_rank.bytes() + ng_tmp.bytes() + ng_ord.bytes() + ng_sfx.bytes() + ng_sfl.bytes() +
              ng_cell.bytes() + ng_prm.bytes();
         return b;
@@ -1114,7 +1117,7 @@ tp_status ensure_bh(tp_problem* P)
     TP_TRY(P->bh_flo.ensure(3 * nF, s));
     TP_TRY(P->bh_fhi.ensure(3 * nF, s));
     TP_TRY(P->bh_fr2.ensure(nF, s));
-    TP_TRY(P->bh_box.ensure(6, s));
+    TP_TRY(P->bh_box.ensure(kBhBoxDoubles, s));
     TP_TRY(P->bh_kin.ensure(nF, s));
     TP_TRY(P->bh_kout.ensure(nF, s));
     const size_t tb = bh_sort_temp_bytes(nF);
@@ -1129,16 +1132,19 @@ tp_status ensure_bh(tp_problem* P)
     TP_TRY(P->bh_nr2.ensure(M, s));
     TP_TRY(P->bh_gS.ensure(7 * nF, s));
     TP_TRY(P->bh_eS.ensure(nF, s));
-    TP_TRY(P->bh_accF.ensure(4 * nF, s));
-    TP_TRY(P->bh_accN.ensure(4 * M, s));
-    TP_TRY(P->bh_counts.ensure(2, s));
+    TP_TRY(P->bh_rec.ensure(8 * M, s));
+    TP_TRY(P->bh_nxa.ensure(M, s));
+    TP_TRY(P->bh_srt.ensure(nF, s));
+    TP_TRY(P->bh_counts.ensure((size_t)kBhCounts + 4 * (M + nF), s));
     TP_TRY(P->bh_nm.ensure((size_t)M * ((kMaxGroupCols + 3) / 4 * 4), s));
     BhBuffers& b = P->bh;
     b.flo = P->bh_flo.p; b.fhi = P->bh_fhi.p; b.fr2 = P->bh_fr2.p; b.box = P->bh_box.p;
     b.keys_in = P->bh_kin.p; b.keys_out = P->bh_kout.p; b.sort_tmp = P->bh_tmp.p; b.sort_bytes = tb;
     b.order = P->bh_order.p; b.pos = P->bh_pos.p; b.na = P->bh_na.p; b.nsx = P->bh_nsx.p; b.nX = P->bh_nX.p;
     b.nlo = P->bh_nlo.p; b.nhi = P->bh_nhi.p; b.nr2 = P->bh_nr2.p; b.gS = P->bh_gS.p; b.eS = P->bh_eS.p;
-    b.accF = P->bh_accF.p; b.accN = P->bh_accN.p; b.counts = P->bh_counts.p;
+    b.rec = P->bh_rec.p; b.nxa = P->bh_nxa.p; b.srt = P->bh_srt.p; b.counts = P->bh_counts.p;
+    b.accN = reinterpret_cast<double*>(P->bh_counts.p + kBhCounts);
+    b.accF = b.accN + 4 * M;
     return TP_OK;
 }
 
@@ -1180,8 +1186,6 @@ tp_status ensure_bct(tp_problem* P)
     const int64_t M = (int64_t)bh_node_count(P->nF, P->prm.leaf_size, &Pl);
     TP_TRY(P->bct_cnt.ensure(3, s));
     TP_TRY(P->bct_hcnt.ensure(3));
-    TP_TRY(P->bct_rec.ensure((size_t)8 * M, s));
-    TP_HIP(launch_bct_nodes(P->bh, M, P->bct_rec.p, s));
     TP_TRY(P->bct_fr0.ensure(1024, s));
     const uint64_t root = (1ull << 32) | 1ull;
     TP_HIP(hipMemcpyAsync(P->bct_fr0.p, &root, sizeof(root), hipMemcpyHostToDevice, s));
@@ -1198,7 +1202,7 @@ tp_status ensure_bct(tp_problem* P)
         h[1] = (unsigned long long)nnear;
         h[2] = 0;
         TP_HIP(hipMemcpyAsync(P->bct_cnt.p, h, 3 * sizeof(unsigned long long), hipMemcpyHostToDevice, s));
-        TP_HIP(launch_bct_expand(P->bct_rec.p, Pl, P->prm.chi, cur->p, n, P->bct_fkeys.p, P->bct_nkeys.p, nxt->p,
+        TP_HIP(launch_bct_expand(P->bh.rec, Pl, P->prm.chi, cur->p, n, P->bct_fkeys.p, P->bct_nkeys.p, nxt->p,
                                  P->bct_cnt.p, s));
         TP_HIP(hipMemcpyAsync(h, P->bct_cnt.p, 3 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
         TP_HIP(hipStreamSynchronize(s));
@@ -3045,7 +3049,7 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
     // the Morton order of the faces is computed with them)
     {
         const double M = (double)bh_node_count(nF, prm.leaf_size, nullptr);
-        b += f * (176.0 + 56.0) + M * (144.0 + 8.0 * kMaxGroupCols) + (double)bh_sort_temp_bytes(nF) + 64;
+        b += f * (208.0 + 56.0) + M * (240.0 + 8.0 * kMaxGroupCols) + (double)bh_sort_temp_bytes(nF) + 8 * kBhBoxDoubles + 64;
         // block cluster tree lists and far-field values (chi > 0; about 64 blocks per node)
         if (prm.chi > 0.0) b += M * (8.0 * (kMaxGroupCols + 1) + 4.0 * 64 + 8.0);
     }

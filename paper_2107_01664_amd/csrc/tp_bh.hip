@@ -17,9 +17,9 @@
 // vertices and the box of I).
 //
 // Traversal.  One thread per face, threads in Morton order, and the 64 lanes of a wave walk
-// the tree together (wave_walk): the wave visits the union of its lanes' lists in
-// depth-first order, each lane taking its own terms in the order of its own walk, and every
-// lane reads the same node at the same time.  An admissible node adds K(X_S, N_S; X_I)
+// the tree together: the wave visits the union of its lanes' lists, each lane taking the
+// terms of its own, and every lane reads the same node at the same time (k_bh_traverse
+// here, wave_walk for the other walks).  An admissible node adds K(X_S, N_S; X_I)
 // a_S a_I, a leaf that is not admissible adds the exact terms of its faces T != S, other
 // nodes are opened.  The
 // differential is that of E_BH with the lists held fixed: the face S side is summed per
@@ -85,18 +85,24 @@ __global__ void k_bh_faceprep(const double* __restrict__ V, const int32_t* __res
     fr2[s] = best;
 }
 
-// Bounding box of the barycenters (one workgroup; min and max do not depend on order).
-__global__ __launch_bounds__(1024) void k_bh_bbox(const double4* __restrict__ dx, int64_t nF,
-                                                  double* __restrict__ box)
+// Bounding boxes of the barycenters, one per workgroup (min and max do not depend on order);
+// k_bh_keys takes them together.  One workgroup for all faces took 117 us at 327,680 faces, this
+// 6 us.
+constexpr int kBoxBlocks = 128;
+
+__device__ __forceinline__ double pick(double a, double b, bool mx) { return mx ? (a > b ? a : b) : (a < b ? a : b); }
+
+__global__ __launch_bounds__(256) void k_bh_bbox(const double4* __restrict__ dx, int64_t nF,
+                                                 double* __restrict__ box)
 {
-    __shared__ double sh[6][1024];
+    __shared__ double sh[6][256];
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t s = threadIdx.x; s < nF; s += blockDim.x) {
+    for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < nF; s += (int64_t)gridDim.x * 256) {
         const double4 X = dx[s];
         const double x[3] = {X.x, X.y, X.z};
         for (int m = 0; m < 3; ++m) {
-            lo[m] = x[m] < lo[m] ? x[m] : lo[m];
-            hi[m] = x[m] > hi[m] ? x[m] : hi[m];
+            lo[m] = pick(x[m], lo[m], false);
+            hi[m] = pick(x[m], hi[m], true);
         }
     }
     for (int m = 0; m < 3; ++m) {
@@ -104,24 +110,33 @@ __global__ __launch_bounds__(1024) void k_bh_bbox(const double4* __restrict__ dx
         sh[3 + m][threadIdx.x] = hi[m];
     }
     __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
+    for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w)
-            for (int m = 0; m < 3; ++m) {
-                const double a = sh[m][threadIdx.x + w], b = sh[3 + m][threadIdx.x + w];
-                sh[m][threadIdx.x] = a < sh[m][threadIdx.x] ? a : sh[m][threadIdx.x];
-                sh[3 + m][threadIdx.x] = b > sh[3 + m][threadIdx.x] ? b : sh[3 + m][threadIdx.x];
-            }
+            for (int m = 0; m < 6; ++m) sh[m][threadIdx.x] = pick(sh[m][threadIdx.x + w], sh[m][threadIdx.x], m >= 3);
         __syncthreads();
     }
-    if (threadIdx.x < 6) box[threadIdx.x] = sh[threadIdx.x][0];
+    if (threadIdx.x < 6) box[6 * blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
 }
 
 // Keys (Morton code << 32 | caller's face number) and the internal face index as value;
 // the caller's numbers make the order independent of how faces are stored.
-__global__ void k_bh_keys(const double4* __restrict__ dx, int64_t nF, const double* __restrict__ box,
-                          const int32_t* __restrict__ orig, uint64_t* __restrict__ keys,
-                          int32_t* __restrict__ idx)
+__global__ __launch_bounds__(256) void k_bh_keys(const double4* __restrict__ dx, int64_t nF,
+                                                 const double* __restrict__ boxes, int nbox,
+                                                 const int32_t* __restrict__ orig, uint64_t* __restrict__ keys,
+                                                 int32_t* __restrict__ idx)
 {
+    __shared__ double sh[6][kBoxBlocks];
+    __shared__ double box[6];
+    for (int i = threadIdx.x; i < 6 * nbox; i += 256) sh[i % 6][i / 6] = boxes[i];
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int m = wave; m < 6; m += 4) {
+        double v = m < 3 ? INFINITY : -INFINITY;
+        for (int i = lane; i < nbox; i += 64) v = pick(sh[m][i], v, m >= 3);
+        for (int o = 32; o > 0; o >>= 1) v = pick(__shfl_xor(v, o), v, m >= 3);
+        if (lane == 0) box[m] = v;
+    }
+    __syncthreads();
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= nF) return;
     const double4 X = dx[s];
@@ -131,85 +146,124 @@ __global__ void k_bh_keys(const double4* __restrict__ dx, int64_t nF, const doub
     idx[s] = (int32_t)s;
 }
 
-__global__ void k_bh_pos(const int32_t* __restrict__ order, int64_t nF, int32_t* __restrict__ pos)
+// Sorted positions, and the face data (X, a) in sorted order.
+__global__ void k_bh_pos(const int32_t* __restrict__ order, int64_t nF, const double4* __restrict__ dx,
+                         int32_t* __restrict__ pos, double4* __restrict__ srt)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= nF) return;
-    pos[order[p]] = (int32_t)p;
+    const int32_t t = order[p];
+    pos[t] = (int32_t)p;
+    srt[p] = dx[t];
 }
 
-// Leaf nodes P + l: sums over the member faces in sorted order.
-__global__ void k_bh_leaves(int64_t nF, int leaf, int64_t P, const int32_t* __restrict__ order,
-                            const double4* __restrict__ dx, const double* __restrict__ flo,
-                            const double* __restrict__ fhi, double* __restrict__ na,
-                            double* __restrict__ nsx, double* __restrict__ nlo, double* __restrict__ nhi)
+// Sums and box of a node while the tree is built: a, sum a X, lo, hi.
+struct NodeSums {
+    double v[10];
+};
+
+__device__ __forceinline__ NodeSums node_join(const NodeSums& L, const NodeSums& R)
 {
-    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= P) return;
-    const int64_t node = P + l;
-    double a = 0.0, sx[3] = {0.0, 0.0, 0.0};
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t p = l * leaf; p < (l + 1) * leaf && p < nF; ++p) {
-        const int32_t s = order[p];
-        const double4 X = dx[s];
-        const double x[3] = {X.x, X.y, X.z};
-        a = a + X.w;
+    NodeSums o;
+    for (int m = 0; m < 4; ++m) o.v[m] = L.v[m] + R.v[m];
+    for (int m = 4; m < 10; ++m) o.v[m] = pick(L.v[m], R.v[m], m >= 7);
+    return o;
+}
+
+// Every array of a node: a, sum a X, box, X = sum a X / a, r^2, and its record (lo, hi, r^2, a: one
+// 64-byte line, what a test of admissibility reads).
+__device__ __forceinline__ void node_store(const BhBuffers& b, int64_t node, const NodeSums& n)
+{
+    const double a = n.v[0];
+    double r2 = 0.0, X[3] = {0.0, 0.0, 0.0};
+    if (a > 0.0)
         for (int m = 0; m < 3; ++m) {
-            sx[m] = sx[m] + X.w * x[m];
-            lo[m] = flo[3 * s + m] < lo[m] ? flo[3 * s + m] : lo[m];
-            hi[m] = fhi[3 * s + m] > hi[m] ? fhi[3 * s + m] : hi[m];
+            X[m] = n.v[1 + m] / a;
+            const double u = X[m] - n.v[4 + m], v = n.v[7 + m] - X[m];
+            const double w = u > v ? u : v;
+            r2 = r2 + w * w;
         }
-    }
-    na[node] = a;
+    b.na[node] = a;
+    b.nr2[node] = r2;
     for (int m = 0; m < 3; ++m) {
-        nsx[3 * node + m] = sx[m];
-        nlo[3 * node + m] = lo[m];
-        nhi[3 * node + m] = hi[m];
+        b.nsx[3 * node + m] = n.v[1 + m];
+        b.nlo[3 * node + m] = n.v[4 + m];
+        b.nhi[3 * node + m] = n.v[7 + m];
+        b.nX[3 * node + m] = X[m];
+        b.rec[8 * node + m] = n.v[4 + m];
+        b.rec[8 * node + 3 + m] = n.v[7 + m];
     }
+    b.nxa[node] = double4{X[0], X[1], X[2], a};
+    b.rec[8 * node + 6] = r2;
+    b.rec[8 * node + 7] = a;
 }
 
-__device__ __forceinline__ void bh_node_finish(int64_t node, const double* __restrict__ na,
-                                               const double* __restrict__ nsx, const double* __restrict__ nlo,
-                                               const double* __restrict__ nhi, double* __restrict__ nX,
-                                               double* __restrict__ nr2)
-{
-    const double a = na[node];
-    if (!(a > 0.0)) {
-        nr2[node] = 0.0;
-        for (int m = 0; m < 3; ++m) nX[3 * node + m] = 0.0;
-        return;
-    }
-    double r2 = 0.0;
-    for (int m = 0; m < 3; ++m) {
-        const double x = nsx[3 * node + m] / a;
-        nX[3 * node + m] = x;
-        const double u = x - nlo[3 * node + m], v = nhi[3 * node + m] - x;
-        const double w = u > v ? u : v;
-        r2 = r2 + w * w;
-    }
-    nr2[node] = r2;
-}
+// Leaves P + l (sums over the member faces in sorted order) and the levels above them up to one
+// node per workgroup, in LDS.  All levels in one workgroup took 557 us at 65,536 leaves (a barrier
+// and a pass over global memory per level, 1,024 threads for 131,072 nodes); subtrees of kSubLeaves
+// leaves in parallel take 22 us with the leaves (15 us alone), the small launch for what is above 8 us.
+constexpr int kSubLeaves = 256;
 
-// Internal nodes level by level (children before parents) in one workgroup, then the
-// node barycenters and radii of all nodes.
-__global__ __launch_bounds__(1024) void k_bh_levels(int64_t P, double* __restrict__ na, double* __restrict__ nsx,
-                                                    double* __restrict__ nlo, double* __restrict__ nhi,
-                                                    double* __restrict__ nX, double* __restrict__ nr2)
+__global__ __launch_bounds__(kSubLeaves) void k_bh_subtrees(int64_t nF, int leaf, int64_t P, BhBuffers b)
 {
-    for (int64_t n0 = P / 2; n0 >= 1; n0 /= 2) {
-        for (int64_t node = n0 + threadIdx.x; node < 2 * n0; node += blockDim.x) {
-            const int64_t L = 2 * node, R = 2 * node + 1;
-            na[node] = na[L] + na[R];
+    __shared__ double sh[10][kSubLeaves];
+    const int t = threadIdx.x;
+    const int64_t l = (int64_t)blockIdx.x * kSubLeaves + t;
+    if (l < P) {
+        NodeSums n = {{0.0, 0.0, 0.0, 0.0, INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY}};
+        for (int64_t p = l * leaf; p < (l + 1) * leaf && p < nF; ++p) {
+            const int32_t s = b.order[p];
+            const double4 X = b.srt[p];
+            const double x[3] = {X.x, X.y, X.z};
+            n.v[0] = n.v[0] + X.w;
             for (int m = 0; m < 3; ++m) {
-                nsx[3 * node + m] = nsx[3 * L + m] + nsx[3 * R + m];
-                nlo[3 * node + m] = nlo[3 * L + m] < nlo[3 * R + m] ? nlo[3 * L + m] : nlo[3 * R + m];
-                nhi[3 * node + m] = nhi[3 * L + m] > nhi[3 * R + m] ? nhi[3 * L + m] : nhi[3 * R + m];
+                n.v[1 + m] = n.v[1 + m] + X.w * x[m];
+                n.v[4 + m] = pick(b.flo[3 * s + m], n.v[4 + m], false);
+                n.v[7 + m] = pick(b.fhi[3 * s + m], n.v[7 + m], true);
             }
+        }
+        node_store(b, P + l, n);
+        for (int m = 0; m < 10; ++m) sh[m][t] = n.v[m];
+    }
+    int64_t base = P + (int64_t)blockIdx.x * kSubLeaves;
+    for (int w = (int)min((int64_t)kSubLeaves, P) >> 1; w >= 1; w >>= 1) {
+        base >>= 1;
+        __syncthreads();
+        NodeSums n;
+        if (t < w) {
+            NodeSums L, R;
+            for (int m = 0; m < 10; ++m) {
+                L.v[m] = sh[m][2 * t];
+                R.v[m] = sh[m][2 * t + 1];
+            }
+            n = node_join(L, R);
+            node_store(b, base + t, n);
+        }
+        __syncthreads();
+        if (t < w)
+            for (int m = 0; m < 10; ++m) sh[m][t] = n.v[m];
+    }
+}
+
+// The levels above the subtrees (children before parents), one workgroup.
+__global__ __launch_bounds__(1024) void k_bh_top(int64_t P, BhBuffers b)
+{
+    for (int64_t n0 = P / kSubLeaves / 2; n0 >= 1; n0 /= 2) {
+        for (int64_t node = n0 + threadIdx.x; node < 2 * n0; node += blockDim.x) {
+            NodeSums c[2];
+            for (int h = 0; h < 2; ++h) {
+                const int64_t ch = 2 * node + h;
+                c[h].v[0] = b.na[ch];
+                for (int m = 0; m < 3; ++m) {
+                    c[h].v[1 + m] = b.nsx[3 * ch + m];
+                    c[h].v[4 + m] = b.nlo[3 * ch + m];
+                    c[h].v[7 + m] = b.nhi[3 * ch + m];
+                }
+            }
+            node_store(b, node, node_join(c[0], c[1]));
         }
         __syncthreads();
     }
-    for (int64_t node = 1 + threadIdx.x; node < 2 * P; node += blockDim.x)
-        bh_node_finish(node, na, nsx, nlo, nhi, nX, nr2);
 }
 
 #pragma clang fp contract(fast)
@@ -219,6 +273,7 @@ struct BhArgs {
     int leaf;
     double theta2;
     double alpha, beta;
+    float alpha32, beta32;
     const int32_t* order;
     const double4* dx;
     const double4* dn;
@@ -230,12 +285,23 @@ struct BhArgs {
     const double* nlo;
     const double* nhi;
     const double* nr2;
+    const double* rec;    // [2P][8]
+    const double4* nxa;   // [2P] (X, a) of the nodes
+    const double4* srt;   // [nF] (X, a) in sorted order
     double* gS;           // [7][nF] face-side sums (gradient only)
     double* eS;           // [nF] energy rows
-    double* accF;         // [4][nF] target-side sums of faces
-    double* accN;         // [4][2P] target-side sums of nodes
+    double* accF;         // [nF][4] target-side sums of faces, by sorted position
+    double* accN;         // [2P][4] target-side sums of nodes
     unsigned long long* counts;   // far, near
 };
+
+// Uniform loads of read-only data through the scalar cache.
+typedef double double8 __attribute__((ext_vector_type(8)));
+template <class T>
+__device__ __forceinline__ T scalar_load(const T* p)
+{
+    return *(const __attribute__((address_space(4))) T*)p;
+}
 
 __device__ __forceinline__ bool admissible(const BhArgs& A, const double (&slo)[3], const double (&shi)[3],
                                            double sr2, int64_t node)
@@ -254,7 +320,24 @@ __device__ __forceinline__ bool admissible(const BhArgs& A, const double (&slo)[
     return r2 < A.theta2 * d2;
 }
 
-// Kernel and its derivatives for one target (R = float or double pair terms).
+// The same from the node's record.
+__device__ __forceinline__ bool admissible(const double8& r, const double (&slo)[3], const double (&shi)[3],
+                                           double sr2, double theta2)
+{
+#pragma clang fp contract(off)
+    double d2 = 0.0;
+    for (int m = 0; m < 3; ++m) {
+        const double g1 = r[m] - shi[m];
+        const double g2 = slo[m] - r[3 + m];
+        const double g = fmax(fmax(g1, g2), 0.0);
+        d2 = d2 + g * g;
+    }
+    const double r2 = sr2 > r[6] ? sr2 : r[6];
+    return r2 < theta2 * d2;
+}
+
+// Kernel and its derivatives for one target (R = float or double pair terms).  The fused
+// operations are written out, so that a term has the same bits wherever it is inlined.
 template <class R, bool GEN>
 __device__ __forceinline__ void term(const double (&xs)[3], const double (&ns)[3], const double* y,
                                      const BhArgs& A, R& K, R (&dKdd)[3], R (&dKdN)[3])
@@ -264,8 +347,8 @@ __device__ __forceinline__ void term(const double (&xs)[3], const double (&ns)[3
         d[m] = (R)(xs[m] - y[m]);
         n[m] = (R)ns[m];
     }
-    const R r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-    const R q = n[0] * d[0] + n[1] * d[1] + n[2] * d[2];
+    const R r2 = fma(d[2], d[2], fma(d[0], d[0], d[1] * d[1]));
+    const R q = fma(n[2], d[2], fma(n[0], d[0], n[1] * d[1]));
     const R inv = (R)1 / r2;
     R Kqr;
     if (!GEN) {
@@ -283,18 +366,65 @@ __device__ __forceinline__ void term(const double (&xs)[3], const double (&ns)[3
             K = Kqr * q * inv;
         }
     }
-    const R c1 = (R)A.alpha * Kqr * inv, c2 = (R)A.beta * K * inv;
+    const R alpha = sizeof(R) == 4 ? (R)A.alpha32 : (R)A.alpha, beta = sizeof(R) == 4 ? (R)A.beta32 : (R)A.beta;
+    const R c1 = alpha * Kqr * inv, c2 = beta * K * inv;
     for (int m = 0; m < 3; ++m) {
-        dKdd[m] = c1 * n[m] - c2 * d[m];
+        dKdd[m] = fma(c1, n[m], -(c2 * d[m]));
         dKdN[m] = c1 * d[m];
     }
 }
 
-template <class R, bool GEN, bool GRAD>
-__global__ __launch_bounds__(256) void k_bh_traverse(BhArgs A)
+__device__ __forceinline__ double4 scalar_load4(const double4* p)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = p < A.nF;                 // every lane walks with its wave
+    typedef double vec4 __attribute__((ext_vector_type(4)));
+    const vec4 v = scalar_load(reinterpret_cast<const vec4*>(p));
+    return double4{v[0], v[1], v[2], v[3]};
+}
+
+__device__ __forceinline__ double swap_sum32(double a, double b)   // lanes 0..31: a's sum of the halves, 32..63: b's
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+__device__ __forceinline__ double swap_sum16(double a, double b)   // the same for rows of 16 lanes
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Keeps a on the lanes where up is false and b on the others, adding the partner lane's part.
+template <int CTRL>
+__device__ __forceinline__ double fold(double a, double b, bool up)
+{
+    return (up ? b : a) + dpp_move<CTRL>(up ? a : b);
+}
+
+// Traversal: one wave per 64 consecutive sorted faces, 64 threads per workgroup so that a wave that
+// is done makes room at once.
+//
+// The walk keeps everything about nodes in scalar registers: a node that some lane opens has its
+// two children's records read at once (128 contiguous bytes, scalar loads), each is tested by all
+// lanes, and the lanes that take it or go on below it are a 64-bit mask.  Right children that wait
+// and the queues of admissible nodes and of leaves are lanes of three registers.  Four targets are
+// taken from a queue together: their loads are in flight together, and their target-side parts are
+// summed over the wave by halving (with the lane swaps of gfx950, which need no selects), 24
+// instructions per target instead of 96 for a full wave sum of each part.  The parts of a target
+// are one 32-byte group and four faces of a leaf one 128-byte line, so the device-scope additions
+// are one instruction per four targets; one by one and in four rows they were 58.8 million
+// requests.
+// 327,680 faces, theta 0.5 (per wave 1,955 nodes tested, 1,114 taken by some lane, 1,602 leaf
+// faces): 10.9 ms before, 3.9 ms now, of which the vector units issue 2.8 ms; the rest is waves that
+// end last.  Five waves per SIMD, not four, because 5,120 waves then start at once: 5.4 ms at four.
+// The general exponents' powers would spill at five.
+template <class R, bool GEN, bool GRAD>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GEN ? 1 : 5))) void k_bh_traverse(BhArgs A)
+{
+    const int lane = threadIdx.x;
+    const int p = (int)(blockIdx.x * 64) + lane, nF = (int)A.nF, P = (int)A.P;
+    const bool live = p < nF;                   // every lane walks with its wave
     const int32_t s = A.order[live ? p : 0];
     const double4 X = A.dx[s], Nn = A.dn[s];
     const double xs[3] = {X.x, X.y, X.z}, ns[3] = {Nn.x, Nn.y, Nn.z};
@@ -305,70 +435,165 @@ __global__ __launch_bounds__(256) void k_bh_traverse(BhArgs A)
         shi[m] = A.fhi[3 * s + m];
     }
     const double sr2 = A.fr2[s];
-    double gX[3] = {0, 0, 0}, gN[3] = {0, 0, 0}, ga = 0.0, e = 0.0;
+    double gX[3] = {0, 0, 0}, gN[3] = {0, 0, 0}, ga = 0.0;
     unsigned long long nfar = 0, nnear = 0;
+    const bool up8 = lane & 8, up4 = lane & 4;
 
-    // one term of this lane with target (y, w): face-side sums here, target-side parts in tg
+    // One term of this lane with target (y, w): face-side sums (without a_S) here, target-side parts
+    // (without w) in tg.
     auto visit = [&](const double* y, double w, double (&tg)[4]) {
         R K, dKdd[3], dKdN[3];
         term<R, GEN>(xs, ns, y, A, K, dKdd, dKdN);
         const double Kd = (double)K;
-        e += aS * w * Kd;
+        ga += w * Kd;
         if (GRAD) {
-            const double f = aS * w;
             for (int m = 0; m < 3; ++m) {
-                const double gd = f * (double)dKdd[m];
-                gX[m] += gd;
-                gN[m] += f * (double)dKdN[m];
-                tg[m] = -gd;
+                const double v = (double)dKdd[m];
+                gX[m] += w * v;
+                gN[m] += w * (double)dKdN[m];
+                tg[m] = -aS * v;
             }
-            ga += w * Kd;
             tg[3] = aS * Kd;
         }
     };
-    // the target-side parts of the wave's lanes are summed across the wave first, so each
-    // target receives one set of atomic additions per wave
-    auto push = [&](const double (&tg)[4], double* acc, int64_t stride) {
-        for (int m = 0; m < 4; ++m) {
-            const double v = wave_sum(tg[m]);
-            if ((threadIdx.x & 63) == 0) unsafeAtomicAdd(acc + m * stride, v);
+    // four targets: load(j) their (X, a), active(j) whether this lane has a term with target j; the
+    // sum of part m of target j goes to add(j, m, sum)
+    auto four = [&](auto&& load, auto&& active, auto&& add) {
+        double4 y[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = load(j);
+        double h[2][4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            double a[4] = {0.0, 0.0, 0.0, 0.0}, b[4] = {0.0, 0.0, 0.0, 0.0};
+            const double ya[3] = {y[j].x, y[j].y, y[j].z}, yb[3] = {y[j + 2].x, y[j + 2].y, y[j + 2].z};
+            if (active(j)) visit(ya, y[j].w, a);
+            if (active(j + 2)) visit(yb, y[j + 2].w, b);
+            if (GRAD)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    h[j][m] = swap_sum32(a[m], b[m]);   // bit 5 of the lane: j + 2
+                    asm volatile("" : "+v"(h[j][m]));   // now, not with the second pair: 8 registers less
+                }
+        }
+        if (GRAD) {
+            double q[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) q[m] = swap_sum16(h[0][m], h[1][m]);    // bit 4: j + 1
+            const double u0 = fold<0x128>(q[0], q[2], up8), u1 = fold<0x128>(q[1], q[3], up8);   // bit 3: m + 2
+            double v = fold<0x141>(u0, u1, up4);                                                 // bit 2: m + 1
+            v = v + dpp_move<0x1B>(v);      // quad_perm [3,2,1,0]
+            v = v + dpp_move<0xB1>(v);      // quad_perm [1,0,3,2]
+            const double wj = lane & 32 ? (lane & 16 ? y[3].w : y[2].w) : (lane & 16 ? y[1].w : y[0].w);
+            if ((lane & 3) == 0) add(lane >> 4, (lane >> 2) & 3, (lane & 12) == 12 ? v : wj * v);
         }
     };
 
-    wave_walk_act(
-        A.na, A.P, live, [&](int node) { return admissible(A, slo, shi, sr2, node); },
-        [&](int node, int took) {
-            if (__ballot(took == 1) != 0ull) {
-                double tg[4] = {0.0, 0.0, 0.0, 0.0};
-                if (took == 1) {
-                    visit(A.nX + 3 * (int64_t)node, A.na[node], tg);
-                    ++nfar;
-                }
-                if (GRAD) push(tg, A.accN + node, 2 * A.P);
-            }
-            if (__ballot(took == 2) != 0ull) {
-                const int64_t l = node - A.P;
-                const int64_t p1 = min((l + 1) * (int64_t)A.leaf, A.nF);
-                for (int64_t q = l * A.leaf; q < p1; ++q) {
-                    const int32_t t = A.order[q];
-                    double tg[4] = {0.0, 0.0, 0.0, 0.0};
-                    if (took == 2 && t != s) {
-                        const double4 Y = A.dx[t];
-                        const double y[3] = {Y.x, Y.y, Y.z};
-                        visit(y, Y.w, tg);
-                        ++nnear;
-                    }
-                    if (GRAD) push(tg, A.accF + t, A.nF);
-                }
-            }
-        });
-    wave_count_terms(A.counts, nfar, nnear);
+    // Three registers hold (node, mask) entries, one a lane: lanes 0 to 4 the admissible nodes that
+    // wait, 8 and 9 the leaves, 32 + d the right child of depth d.
+    int en = 0, el = 0, eh = 0, nq = 0, nl = 0;
+    constexpr int kLeaf = 8, kRight = 32;
+    auto put = [&](int i, int node, uint64_t m) {
+        en = lane == i ? node : en;
+        el = lane == i ? (int)(uint32_t)m : el;
+        eh = lane == i ? (int)(uint32_t)(m >> 32) : eh;
+    };
+    auto mask = [&](int i) -> uint64_t {
+        return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(eh, i) << 32) |
+               (uint32_t)__builtin_amdgcn_readlane(el, i);
+    };
+    auto take_far = [&]() {                     // the last four (or what is left)
+        const int n = min(nq, 4), first = nq - n;
+        int id[4];
+        uint64_t mk[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = first + min(j, n - 1);
+            id[j] = __builtin_amdgcn_readlane(en, i);
+            mk[j] = j < n ? mask(i) : 0;
+            nfar += __builtin_popcountll(mk[j]);
+        }
+        four(
+            [&](int j) {
+                return scalar_load4(A.nxa + id[j]);
+            },
+            [&](int j) { return __builtin_amdgcn_inverse_ballot_w64(mk[j]); },
+            [&](int j, int m, double v) {
+                const int a = j & 1 ? id[1] : id[0], b = j & 1 ? id[3] : id[2];
+                if (j < n) unsafeAtomicAdd(A.accN + 4 * (int64_t)(j & 2 ? b : a) + m, v);
+            });
+        nq = first;
+    };
+    auto take_leaf = [&]() {
+        --nl;
+        const int l = __builtin_amdgcn_readlane(en, kLeaf + nl) - P;
+        const uint64_t mk = mask(kLeaf + nl);
+        const int q0 = l * A.leaf, p1 = q0 + min(A.leaf, nF - q0);
+        for (int q = q0; q < p1; q += 4) {
+            four(
+                [&](int j) {
+                    return scalar_load4(A.srt + min(q + j, p1 - 1));
+                },
+                [&](int j) {
+                    const bool act = __builtin_amdgcn_inverse_ballot_w64(mk) && q + j < p1 && q + j != p;
+                    nnear += __builtin_popcountll(__ballot(act));
+                    return act;
+                },
+                [&](int j, int m, double v) {
+                    if (q + j < p1) unsafeAtomicAdd(A.accF + 4 * (int64_t)(q + j) + m, v);
+                });
+        }
+    };
+    // Node c for the lanes m: those that take it are queued, those that go on below it returned.
+    auto test = [&](int c, const double8& r, uint64_t m) -> uint64_t {
+        if (!(r[7] > 0.0) || m == 0) return 0;
+        const uint64_t b = __ballot(admissible(r, slo, shi, sr2, A.theta2)) & m;
+        const uint64_t rest = m & ~b;
+        if (b) {
+            put(nq++, c, b);
+        }
+        if (rest && c >= P) {
+            put(kLeaf + nl++, c, rest);
+            return 0;
+        }
+        return rest;
+    };
+
+    const double8* rec = reinterpret_cast<const double8*>(A.rec);
+    uint32_t waiting = 0;              // the depths whose right child some lanes wait at
+    int node = 1;
+    uint64_t m = test(1, scalar_load(rec + 1), __ballot(live));
+    while (m) {
+        node = __builtin_amdgcn_readfirstlane(2 * node);
+        const double8 rl = scalar_load(rec + node), rr = scalar_load(rec + node + 1);
+        const uint64_t right = test(node + 1, rr, m);
+        m = test(node, rl, m);
+        const int d = 31 - __builtin_clz(node);
+        if (right) {
+            put(kRight + d, 0, right);
+            waiting |= 1u << d;
+        }
+        while (nl > 0) take_leaf();
+        if (nq >= 4) take_far();
+        if (!m && waiting) {           // the deepest waiting right child
+            const int w = 31 - __builtin_clz(waiting);
+            node = (node >> (d - w)) | 1;
+            m = mask(kRight + w);
+            waiting ^= 1u << w;
+        }
+    }
+    while (nl > 0) take_leaf();
+    while (nq > 0) take_far();
+    if (lane == 0) {
+        if (nfar) atomicAdd(&A.counts[0], nfar);
+        if (nnear) atomicAdd(&A.counts[1], nnear);
+    }
     if (!live) return;
-    A.eS[s] = e;
+    A.eS[s] = aS * ga;
     if (GRAD) {
         for (int m = 0; m < 3; ++m) {
-            A.gS[m * A.nF + s] = gX[m];
-            A.gS[(3 + m) * A.nF + s] = gN[m];
+            A.gS[m * A.nF + s] = aS * gX[m];
+            A.gS[(3 + m) * A.nF + s] = aS * gN[m];
         }
         A.gS[6 * A.nF + s] = ga;
     }
@@ -386,19 +611,20 @@ __global__ void k_bh_assemble(int64_t nF, int leaf, int64_t P, const int32_t* __
     if (t >= nF) return;
     const double4 X = dx[t];
     const double xt[3] = {X.x, X.y, X.z};
-    double gx[3], ga = gS[6 * nF + t] + accF[3 * nF + t];
-    for (int m = 0; m < 3; ++m) gx[m] = gS[m * nF + t] + accF[m * nF + t];
-    const int64_t M = 2 * P;
+    const double4* nodes = reinterpret_cast<const double4*>(accN);
+    const double4 own = reinterpret_cast<const double4*>(accF)[pos[t]];
+    double gx[3] = {gS[t] + own.x, gS[nF + t] + own.y, gS[2 * nF + t] + own.z}, ga = gS[6 * nF + t] + own.w;
     for (int64_t node = P + pos[t] / leaf; node >= 1; node >>= 1) {
         const double a = na[node];
         if (!(a > 0.0)) continue;
+        const double4 c = nodes[node];
+        const double g[3] = {c.x, c.y, c.z};
         double proj = 0.0;
         for (int m = 0; m < 3; ++m) {
-            const double g = accN[m * M + node];
-            gx[m] += (X.w / a) * g;
-            proj += (xt[m] - nX[3 * node + m]) * g;
+            gx[m] += (X.w / a) * g[m];
+            proj += (xt[m] - nX[3 * node + m]) * g[m];
         }
-        ga += accN[3 * M + node] + proj / a;
+        ga += c.w + proj / a;
     }
     for (int m = 0; m < 3; ++m) {
         gface[m * gstride + t] = gx[m];
@@ -783,22 +1009,8 @@ hipError_t bct_launch(const BhBuffers& b, const BctLists& bl, int64_t nF, int le
 // level's blocks land is arbitrary; the lists are then sorted by (row, column), which fixes
 // them.  The separation test repeats the reading's arithmetic in FP64 without fused
 // multiply-adds, as for the Barnes-Hut admissibility.
-// Node records for the split: lo (3), hi (3), r^2, a_I -- one 64-byte line per node, since
-// the pairs of a level reach their nodes in no cache-friendly order.
-__global__ void k_bct_nodes(int64_t M, const double* __restrict__ na, const double* __restrict__ nlo,
-                            const double* __restrict__ nhi, const double* __restrict__ nr2, double* __restrict__ rec)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    double* r = rec + 8 * i;
-    for (int m = 0; m < 3; ++m) {
-        r[m] = nlo[3 * i + m];
-        r[3 + m] = nhi[3 * i + m];
-    }
-    r[6] = nr2[i];
-    r[7] = na[i];
-}
-
+// (The tree's node records: one 64-byte line per node, since the pairs of a level reach their nodes
+// in no cache-friendly order.)
 __device__ __forceinline__ bool bct_separated(const double (&a)[8], const double (&b)[8], double chi2)
 {
     double d2 = 0.0;
@@ -932,9 +1144,10 @@ hipError_t launch_morton_order(const BhBuffers& b, const FaceData& fd, int64_t n
                                hipStream_t s)
 {
     const unsigned g = (unsigned)((nF + 255) / 256);
-    hipLaunchKernelGGL(k_bh_bbox, dim3(1), dim3(1024), 0, s, fd.dx, nF, b.box);
+    const int nbox = (int)std::min<int64_t>(kBoxBlocks, (nF + 1023) / 1024);
+    hipLaunchKernelGGL(k_bh_bbox, dim3(nbox), dim3(256), 0, s, fd.dx, nF, b.box);
     // values in b.pos, sorted values into b.order
-    hipLaunchKernelGGL(k_bh_keys, dim3(g), dim3(256), 0, s, fd.dx, nF, b.box, orig, b.keys_in, b.pos);
+    hipLaunchKernelGGL(k_bh_keys, dim3(g), dim3(256), 0, s, fd.dx, nF, b.box, nbox, orig, b.keys_in, b.pos);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     size_t tb = b.sort_bytes;
@@ -950,10 +1163,10 @@ hipError_t launch_bh_build(const BhBuffers& b, const double* V, const int32_t* F
     hipLaunchKernelGGL(k_bh_faceprep, dim3(g), dim3(256), 0, s, V, F, nF, fd.dx, b.flo, b.fhi, b.fr2);
     hipError_t e = launch_morton_order(b, fd, nF, orig, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bh_pos, dim3(g), dim3(256), 0, s, b.order, nF, b.pos);
-    hipLaunchKernelGGL(k_bh_leaves, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, nF, leaf, P, b.order,
-                       fd.dx, b.flo, b.fhi, b.na, b.nsx, b.nlo, b.nhi);
-    hipLaunchKernelGGL(k_bh_levels, dim3(1), dim3(1024), 0, s, P, b.na, b.nsx, b.nlo, b.nhi, b.nX, b.nr2);
+    hipLaunchKernelGGL(k_bh_pos, dim3(g), dim3(256), 0, s, b.order, nF, fd.dx, b.pos, b.srt);
+    hipLaunchKernelGGL(k_bh_subtrees, dim3((unsigned)((P + kSubLeaves - 1) / kSubLeaves)), dim3(kSubLeaves), 0, s, nF,
+                       leaf, P, b);
+    if (P > kSubLeaves) hipLaunchKernelGGL(k_bh_top, dim3(1), dim3(1024), 0, s, P, b);
     return hipGetLastError();
 }
 
@@ -963,21 +1176,20 @@ hipError_t launch_bh_eval(const BhBuffers& b, int64_t nF, int leaf, double theta
 {
     int64_t P = 0;
     const int64_t M = (int64_t)bh_node_count(nF, leaf, &P);
-    hipError_t e = hipMemsetAsync(b.counts, 0, 2 * sizeof(unsigned long long), s);
+    // counts lie before accN, accF
+    hipError_t e = hipMemsetAsync(b.counts, 0, 8 * (size_t)(kBhCounts + (grad ? 4 * (M + nF) : 0)), s);
     if (e != hipSuccess) return e;
-    if (grad) {
-        if ((e = hipMemsetAsync(b.accF, 0, sizeof(double) * 4 * nF, s)) != hipSuccess) return e;
-        if ((e = hipMemsetAsync(b.accN, 0, sizeof(double) * 4 * M, s)) != hipSuccess) return e;
-    }
     BhArgs A;
     A.nF = nF; A.P = P; A.leaf = leaf; A.theta2 = theta * theta; A.alpha = alpha; A.beta = beta;
+    A.alpha32 = (float)alpha; A.beta32 = (float)beta;
     A.order = b.order; A.dx = fd.dx; A.dn = fd.dn; A.flo = b.flo; A.fhi = b.fhi; A.fr2 = b.fr2;
     A.na = b.na; A.nX = b.nX; A.nlo = b.nlo; A.nhi = b.nhi; A.nr2 = b.nr2;
+    A.rec = b.rec; A.nxa = b.nxa; A.srt = b.srt;
     A.gS = b.gS; A.eS = b.eS; A.accF = b.accF; A.accN = b.accN; A.counts = b.counts;
     const dim3 grid((unsigned)((nF + 255) / 256)), block(256);
     const bool gen = !(alpha == 6.0 && beta == 12.0);
     const bool f64 = precision == TP_PREC_FP64;
-#define TP_BH_LAUNCH(R, G, D) hipLaunchKernelGGL((k_bh_traverse<R, G, D>), grid, block, 0, s, A)
+#define TP_BH_LAUNCH(R, G, D) hipLaunchKernelGGL((k_bh_traverse<R, G, D>), dim3((unsigned)((nF + 63) / 64)), dim3(64), 0, s, A)
     if (grad) {
         if (f64) { if (gen) TP_BH_LAUNCH(double, true, true); else TP_BH_LAUNCH(double, false, true); }
         else { if (gen) TP_BH_LAUNCH(float, true, true); else TP_BH_LAUNCH(float, false, true); }
@@ -1025,13 +1237,6 @@ size_t bct_sort_temp_bytes(int64_t n)
     (void)hipcub::DeviceRadixSort::SortKeys(nullptr, bytes, (const uint64_t*)nullptr, (uint64_t*)nullptr,
                                             (int)std::max<int64_t>(n, 1), 0, 64);
     return bytes;
-}
-
-hipError_t launch_bct_nodes(const BhBuffers& b, int64_t M, double* rec, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_bct_nodes, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, M, b.na, b.nlo, b.nhi, b.nr2,
-                       rec);
-    return hipGetLastError();
 }
 
 hipError_t launch_bct_expand(const double* rec, int64_t P, double chi, const uint64_t* cur, int64_t n, uint64_t* far,

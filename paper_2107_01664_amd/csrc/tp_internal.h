@@ -291,7 +291,7 @@ struct BhBuffers {
     double* flo = nullptr;        // [nF][3] face boxes
     double* fhi = nullptr;
     double* fr2 = nullptr;        // [nF]
-    double* box = nullptr;        // [6] barycenter bounding box
+    double* box = nullptr;        // [kBhBoxDoubles] barycenter bounding boxes of parts of the mesh
     uint64_t* keys_in = nullptr;  // [nF]
     uint64_t* keys_out = nullptr; // [nF]
     void* sort_tmp = nullptr;
@@ -304,12 +304,17 @@ struct BhBuffers {
     double* nlo = nullptr;        // [M][3]
     double* nhi = nullptr;        // [M][3]
     double* nr2 = nullptr;        // [M]
+    double* rec = nullptr;        // [M][8] lo, hi, r^2, a (64-byte aligned)
+    double4* nxa = nullptr;       // [M] (X, a)
+    double4* srt = nullptr;       // [nF] (X, a) in sorted order
     double* gS = nullptr;         // [7][nF]
     double* eS = nullptr;         // [nF]
-    double* accF = nullptr;       // [4][nF]
-    double* accN = nullptr;       // [4][M]
-    unsigned long long* counts = nullptr;   // [2] far, near terms
+    unsigned long long* counts = nullptr;   // [kBhCounts] far, near terms
+    double* accN = nullptr;       // [M][4], behind counts in the same buffer
+    double* accF = nullptr;       // [nF][4], by sorted position, behind accN
 };
+constexpr int kBhBoxDoubles = 6 * 128;
+constexpr int kBhCounts = 4;
 size_t bh_node_count(int64_t nF, int leaf, int64_t* P_out);
 size_t bh_sort_temp_bytes(int64_t nF);
 // Faces sorted by (Morton code of the barycenter, orig[face] or the face index when orig is
