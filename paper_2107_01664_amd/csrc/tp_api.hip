@@ -1718,13 +1718,13 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
         if (P->have_pcg && P->pcg_ml) ml.push_back(m);
         else (P->have_pcg ? pc : plain).push_back(m);
     }
-    // multi-launch solves (one problem at a time; each call returns after its solve)
+    // solves of many blocks, one problem at a time
     for (size_t m : ml) {
         tp_problem* P = B[m];
         PcgMlWork w;
         w.r = P->ml_r.p; w.p = P->ml_p.p; w.s = P->ml_s.p; w.m = P->ml_m.p; w.an = P->ml_an.p; w.v = P->ml_v.p;
         w.shares = P->ml_shares.p; w.g = P->ml_g.p; w.part = P->ml_part.p;
-        w.state = P->ml_state.p; w.state_host = P->ml_state_host.p;
+        w.state = P->ml_state.p; w.state_host = P->ml_state_host.p; w.flags = P->flags.p;
         for (int c0 = 0; c0 < k; c0 += kMaxGroupCols) {
             const int kc = std::min(kMaxGroupCols, k - c0);
             TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, b[m], P->pcg_bp.p, true, s));

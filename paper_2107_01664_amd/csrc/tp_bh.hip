@@ -381,27 +381,6 @@ __device__ __forceinline__ double4 scalar_load4(const double4* p)
     return double4{v[0], v[1], v[2], v[3]};
 }
 
-__device__ __forceinline__ double swap_sum32(double a, double b)   // lanes 0..31: a's sum of the halves, 32..63: b's
-{
-    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-
-__device__ __forceinline__ double swap_sum16(double a, double b)   // the same for rows of 16 lanes
-{
-    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-
-// Keeps a on the lanes where up is false and b on the others, adding the partner lane's part.
-template <int CTRL>
-__device__ __forceinline__ double fold(double a, double b, bool up)
-{
-    return (up ? b : a) + dpp_move<CTRL>(up ? a : b);
-}
-
 // Traversal: one wave per 64 consecutive sorted faces, 64 threads per workgroup so that a wave that
 // is done makes room at once.
 //

@@ -29,8 +29,8 @@
 // unchanged up to 1e-13.)  A solve may start from a given x (warm start; the tolerance
 // stays relative to |b|).  Every solve ends by checking the true residual b - C x and
 // restarts from it when the recursively updated residual has drifted.  Problems with more
-// blocks than can be resident at once run the same iteration as one launch per phase
-// (k_ml_*, further below).
+// blocks than can be resident at once run the same iteration with two or four blocks per
+// workgroup (k_pcg_wide), beyond 1,024 blocks as one launch per phase (k_ml_*).
 #include "tp_solver.h"
 
 #include <algorithm>
@@ -1514,9 +1514,630 @@ hipError_t launch_pcg_batch(const PcgItem* items, int n, int k, void* tab_dev, v
 }
 
 
+// ---------------------------------------------------------------- wide solve
+//
+// Problems of more blocks than workgroups that can be resident at once, but no more than a few
+// per workgroup: a persistent kernel with NBK blocks in each.
+
+namespace {
+
+struct WideArgs {
+    int64_t n;
+    int nb, nc, ell_w;
+    const int32_t* pcol;      // [ell_w][n] (padding entries: the row itself, value 0)
+    const double* pval;       // [ell_w][n]
+    const int32_t* bstart;    // [nb + 1]
+    const int32_t* blk;       // [n] block of each row
+    const int32_t* agg_of_block;
+    const double* phi;        // [n][4]
+    const float* Binv;        // [nb][kBS][kBS], FP32
+    const double* C0inv;      // [nc][nc]
+    const double* b;          // [n][ld] (block order)
+    double* x;                // [n][ld]
+    int ld;
+    double* U0;               // [n][k] row values of the neighbour exchanges, two copies
+    double* U1;
+    double* X;                // [3][entries][k][kWideSum] sums of the all-to-all exchanges
+    int* iters;
+    double* relres;
+    int* flags;
+    double rtol;
+    int maxiter;
+};
+
+typedef float wide_float4 __attribute__((ext_vector_type(4)));
+constexpr int kWideCols = 3;          // columns at most: what the registers of a workgroup hold
+constexpr int kWideThreads = 512;     // per workgroup: 256 registers each, 64 NBK / 2 of them for the inverses
+constexpr int kWideSum = 8;           // doubles of a record of the all-to-all exchange (seven used)
+constexpr int kWideCache = 8;         // entries of a matrix row kept in LDS
+constexpr int kWideEntries = kMaxBarrierW + kCoarseMax / 4;   // records: one per workgroup and one more per aggregate
+
+template <int K, int NBK>
+struct WideDims {
+    static constexpr int T = kWideThreads;
+    static constexpr int R = kBS * NBK;              // rows per workgroup
+    static constexpr int Q = T / R;                  // threads per row: thread q takes columns q, q + Q, ...
+    static constexpr int KG = (K + Q - 1) / Q;       // columns per thread
+    static constexpr int NW = T / 64;                // waves
+    static constexpr int UN = R / 64;                // 64-row units of the block product
+    static constexpr int SEG = NW / UN;              // parts of its inner dimension
+    static constexpr int JS = kBS / SEG;             // terms per part
+    static constexpr int P = NW / K;                 // waves per column in the all-to-all exchange
+    static constexpr int RS = R + 4;                 // LDS row stride (floats): quads of columns miss each other's banks
+    static constexpr int XE = 144 * NBK;             // entries in rows of other workgroups, kept in LDS
+    static constexpr int MB = NBK == 2 ? 8 : 4;   // records per lane with their loads in flight together
+    static_assert(K <= 4 && NW >= K && SEG >= 1, "one quad of columns, a wave per column, a wave per unit");
+};
+
+template <int K, int NBK>
+struct WideShared {
+    using D = WideDims<K, NBK>;
+    union {
+        struct {
+            alignas(16) float r[4][D::RS];            // residual rounded to FP32 (columns from K on are not used)
+            alignas(16) float part[D::SEG][K][D::RS]; // block product by parts of its inner dimension
+        };
+        double ext[K][D::XE];                         // u (or x) of the rows of other workgroups
+    };
+    int32_t xrow[D::XE];                              // which rows
+    int nx;
+    double u[K][D::R];                                // M^{-1} r (or x) of the own rows
+    double x[K][D::R], p[K][D::R], s[K][D::R];
+    double ws[NBK][2][K][8];                          // sums of the two 64-row halves of a block
+    double xp[K][D::P][NBK][8];                       // all-to-all sums by wave (0-2: products, 3-6: coarse)
+    double coef[2][K];                                // alpha, beta of every column
+    double cval[NBK][4][K];                           // coarse values of the own aggregates
+    double crow[NBK][kCoarseMax / 4][16];             // their rows of C0^{-1}, by aggregate
+    int live[K];                                      // column not yet converged
+    int bad;                                          // a wait gave up
+    int wcount[D::NW], e0, ne;                        // records: this workgroup's first, all
+    int la[NBK];                                      // own aggregate of each own block
+    uint8_t eagg[kWideEntries];                       // aggregate of each record
+    double cv[kWideCache][D::R];                      // matrix rows and coarse functions
+    int32_t cj[kWideCache][D::R];
+    double phi[4][D::R];
+};
+
+__global__ void k_wide_empty(WideArgs A, int k)
+{
+    const int64_t nu = A.n * k, nx = (int64_t)3 * kWideEntries * k * kWideSum;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 2 * nu + nx; i += step) {
+        double* p = i < nu ? A.U0 + i : i < 2 * nu ? A.U1 + (i - nu) : A.X + (i - 2 * nu);
+        *reinterpret_cast<unsigned long long*>(p) = kEmpty;
+    }
+}
+
+// What bounds it: two exchanges between workgroups in series per iteration, and the block product
+// and rows of NBK blocks between them.  The five launches per iteration of the multi-launch solve
+// read 51 MB of inverses and 40 MB of vectors again each time (782 blocks); here everything that
+// an iteration reads stays on chip: the inverses in registers (a lane's register is its row of the
+// 4 x 4 x 1 matrix tiles), matrix rows, coarse functions and the own rows of C0^{-1} in LDS, the
+// iteration's vectors in registers.  The coarse solve costs no exchange of its own: the shares
+// Phi^T (C u) ride with the dot products, every workgroup multiplies them by the rows of C0^{-1}
+// of its own aggregates while it adds the dot products, and the coarse values of the new residual
+// follow by the recurrence of the residual itself (c -= alpha C0^{-1} Phi^T s), restarted from the
+// true residual with it; then u = M^{-1} r is known before the first exchange, which passes
+// boundary values to neighbouring blocks only.  A workgroup's blocks in one aggregate are one
+// record of the all-to-all exchange, so what it polls does not grow with NBK.
+// Three columns of 100,002 vertices (782 blocks, 185 iterations): 7.8 ms in five launches per
+// iteration (42 us), 2.8 ms here (15 us); one column 6.9 and 1.5 ms.  1,024 threads with two columns
+// each spill (133 registers).  A record read by one lane in seven loads instead of by eight lanes
+// in one: 3.5 ms, because each load of a lane is a request of its own to the coherence point.
+template <int K, int NBK>
+__global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
+{
+    using D = WideDims<K, NBK>;
+    constexpr int R = D::R, Q = D::Q, KG = D::KG, P = D::P, MB = D::MB;
+    extern __shared__ __align__(16) char smem_raw[];
+    WideShared<K, NBK>& S = *reinterpret_cast<WideShared<K, NBK>*>(smem_raw);
+    const int B0 = (int)blockIdx.x * NBK;                   // first block of the workgroup
+    const int nb = A.nb, nc = A.nc;
+    const int nown = min(NBK, nb - B0);                     // its blocks
+    const int64_t n = A.n;
+    int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+
+    // row role: thread (row, q) owns columns q, q + Q, ... of a row; waves share q and block
+    int row = t & (R - 1);
+    const int q = wave / (R / 64), lb = wave % (R / 64) / 2;
+    const bool has = lb < nown;
+    const int32_t s0 = has ? A.bstart[B0 + lb] : 0;
+    const int32_t cnt = has ? A.bstart[B0 + lb + 1] - s0 : 0;
+    const bool act = (row & (kBS - 1)) < cnt;
+    int i = s0 + (row & (kBS - 1));
+
+    // block product role: wave (unit, seg) takes rows 64 unit + lane and terms seg JS ..
+    const int unit = wave % D::UN, seg = wave / D::UN;
+    float binv[D::JS];
+    {
+        const int ub = unit / 2;
+        const float* src = A.Binv + (int64_t)(B0 + (ub < nown ? ub : 0)) * kBS * kBS + (unit & 1) * 64 + lane;
+#pragma unroll
+        for (int j = 0; j < D::JS; ++j) binv[j] = src[(int64_t)(seg * D::JS + j) * kBS];
+    }
+    // matrix rows: columns of the workgroup's own rows as LDS slots (>= 0), others as ~row
+    auto slot_of = [&](int32_t j) -> int32_t {
+        const int jb = A.blk[j] - B0;
+        return jb >= 0 && jb < nown ? jb * kBS + (j - A.bstart[B0 + jb]) : ~j;
+    };
+    bool edge = false;    // the row is read by another workgroup (the pattern is symmetric)
+    if (t == 0) S.nx = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kWideCache; ++e) {
+        const bool in = act && e < A.ell_w;
+        int32_t sl = in ? slot_of(A.pcol[(int64_t)e * n + i]) : row;
+        const double v = in ? A.pval[(int64_t)e * n + i] : 0.0;
+        edge = edge || sl < 0;
+        if (q == 0) {
+            if (sl < 0) {                                   // R + the value's place in ext, when there is room
+                const int at = atomicAdd(&S.nx, 1);
+                if (at < D::XE) {
+                    S.xrow[at] = ~sl;
+                    sl = R + at;
+                }
+            }
+            S.cj[e][row] = sl;
+            S.cv[e][row] = v;
+        }
+    }
+    if (act)
+        for (int e = kWideCache; e < A.ell_w; ++e) edge = edge || slot_of(A.pcol[(int64_t)e * n + i]) < 0;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const double v = act ? A.phi[i * 4 + a] : 0.0;
+        if (q == 0) S.phi[a][row] = v;
+    }
+    // coarse data: the own blocks' aggregates are consecutive numbers from A0
+    const int A0 = A.agg_of_block[B0];
+    const int nloc = A.agg_of_block[B0 + nown - 1] - A0 + 1;
+    const int my_la = has ? A.agg_of_block[B0 + lb] - A0 : 0;
+    if (t < NBK) S.la[t] = t < nown ? A.agg_of_block[B0 + t] - A0 : -1;
+    for (int e = t; e < nloc * (nc / 4) * 16; e += D::T) {
+        const int la = e / (nc * 4), g = (e / 16) % (nc / 4), a = (e / 4) & 3, a2 = e & 3;
+        S.crow[la][g][a * 4 + a2] = A.C0inv[(int64_t)(4 * (A0 + la) + a) * nc + 4 * g + a2];
+    }
+    // entries of the all-to-all exchange: the blocks of one workgroup in one aggregate, in block order
+    for (int b0 = 0, before = 0; b0 < nb; b0 += D::T) {
+        const int b = b0 + t;
+        const bool starts = b < nb && (b % NBK == 0 || A.agg_of_block[b] != A.agg_of_block[b - 1]);
+        const unsigned long long m = __ballot(starts);
+        if (lane == 0) S.wcount[wave] = __builtin_popcountll(m);
+        __syncthreads();
+        int id = before + __builtin_popcountll(m & ((1ull << lane) - 1ull));
+        for (int v = 0; v < D::NW; ++v) {
+            if (v < wave) id += S.wcount[v];
+            before += S.wcount[v];
+        }
+        if (starts) S.eagg[id] = (uint8_t)A.agg_of_block[b];
+        if (b == B0) S.e0 = id;
+        if (t == 0) S.ne = before;
+        __syncthreads();
+    }
+    if (t == 0) S.bad = 0;
+    __syncthreads();
+    const int e0 = S.e0, ne = S.ne;
+
+    // Neighbour exchange number h uses copy h % 2 of U, all-to-all exchange number g copy g % 3
+    // of X; every neighbour exchange is followed by an all-to-all one.  A slot is emptied by its
+    // owner after every reader is known to be done with it and before any reader can come for
+    // its next value: rows after the all-to-all exchange that follows them (every workgroup
+    // took part in it after reading), sums of exchange g - 2 after exchange g - 1, and both
+    // stores are waited for before the owner's next contribution to an all-to-all exchange.
+    int nhalo = 0, nx = 0;
+    auto ucopy = [&](int h) { return h & 1 ? A.U1 : A.U0; };
+    auto xcopy = [&](int g) { return A.X + (int64_t)(g % 3) * ne * K * kWideSum; };
+    auto empty_rows = [&]() {    // of the neighbour exchange before
+        if (nhalo > 0 && edge) {
+            double* U = ucopy(nhalo - 1);
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii)
+                if (q + ii * Q < K) publish_empty(U + i * K + q + ii * Q);
+        }
+    };
+
+    // w = C u for the vector u of the own rows in registers: shares it, polls the neighbours'
+    auto product = [&](const double (&u)[KG], double (&w)[KG]) {
+        double* U = ucopy(nhalo);
+#pragma unroll
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = q + ii * Q;
+            if (c < K) {
+                if (edge) publish(U + i * K + c, u[ii]);
+                S.u[c][row] = act ? u[ii] : 0.0;
+            }
+        }
+        __syncthreads();
+        ++nhalo;
+        bool fail = false;
+        auto wait_for = [&](int32_t j, int c) -> double {
+            unsigned spins = 0;
+            unsigned long long v = peek(U + (unsigned)(j * K + c));
+            while (v == kEmpty && !fail) {
+                v = peek(U + (unsigned)(j * K + c));
+                fail = give_up(spins, A.flags);
+            }
+            return as_value(v);
+        };
+        const int nx = min(S.nx, D::XE) * K;
+        constexpr int PX = 4;             // values per thread with their loads in flight together
+        for (int f0 = t; f0 < nx && !fail; f0 += PX * D::T) {
+            unsigned long long raw[PX];
+            unsigned spins = 0;
+            for (;;) {
+                bool wait = false;
+#pragma unroll
+                for (int m = 0; m < PX; ++m) {
+                    const int f = f0 + m * D::T;
+                    raw[m] = f < nx ? peek(U + (unsigned)(S.xrow[f / K] * K + f % K)) : 0ull;
+                }
+#pragma unroll
+                for (int m = 0; m < PX; ++m) wait = wait || raw[m] == kEmpty;
+                if (!wait) break;
+                if (give_up(spins, A.flags)) {
+                    fail = true;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < PX; ++m) {
+                const int f = f0 + m * D::T;
+                if (f < nx) S.ext[f % K][f / K] = as_value(raw[m]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = q + ii * Q;
+            double acc = 0.0;
+            if (c < K) {
+#pragma unroll
+                for (int e = 0; e < kWideCache; ++e) {
+                    const int32_t j = S.cj[e][row];
+                    const double v = j < 0 ? wait_for(~j, c) : *(j < R ? &S.u[c][j] : &S.ext[c][j - R]);
+                    acc += S.cv[e][row] * v;
+                }
+                if (act)
+                    for (int e = kWideCache; e < A.ell_w && !fail; ++e) {   // rows of more than kWideCache entries
+                        const int32_t j = slot_of(A.pcol[(int64_t)e * n + i]);
+                        acc += A.pval[(int64_t)e * n + i] * (j >= 0 ? S.u[c][j] : wait_for(~j, c));
+                    }
+            }
+            w[ii] = acc;
+        }
+        if (fail) S.bad = 1;
+    };
+
+    // All-to-all exchange of the sums of r u, w u, r r and phi[a] w over every block's rows:
+    // afterwards S.xp holds, by wave, the sums of the three products and of the rows of
+    // C0^{-1} of the own aggregates times the shares Phi^T w.  False when a wait gave up.
+    auto exchange = [&](const double (&r)[KG], const double (&u)[KG], const double (&w)[KG]) -> bool {
+#pragma unroll
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = q + ii * Q;
+            if (c < K) {
+                double v[8] = {r[ii] * u[ii], w[ii] * u[ii], r[ii] * r[ii], 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int a = 0; a < 4; ++a) v[3 + a] = S.phi[a][row] * w[ii];
+                if (!act)
+#pragma unroll
+                    for (int m = 0; m < 7; ++m) v[m] = 0.0;
+                const double sum = wave_sum8(v);
+                if ((lane & 7) == 0) S.ws[lb][(row >> 6) & 1][c][lane >> 3] = sum;
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // the emptied slots are stored before the sums below
+        __syncthreads();
+        double* X = xcopy(nx);
+        if (t < nloc * K * 7) {
+            const int la = t / (K * 7), c = (t / 7) % K, m = t % 7;
+            double sum = 0.0;
+            for (int l = 0; l < nown; ++l)
+                if (S.la[l] == la) sum += S.ws[l][0][c][m] + S.ws[l][1][c][m];
+            publish(X + ((int64_t)(e0 + la) * K + c) * kWideSum + m, sum);
+        }
+        ++nx;
+        bool fail = false;
+        const int c = wave % K, part = wave / K;
+        if (part < P) {
+            // eight lanes read a record together (one request each; a lane that reads a record alone
+            // makes seven): lane v of them value v
+            const int v = lane & 7;
+            double d = 0.0, cw[NBK][4];
+#pragma unroll
+            for (int l = 0; l < NBK; ++l)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) cw[l][a] = 0.0;
+            for (int b0 = (lane >> 3) + 8 * part; b0 < ne && !fail; b0 += 8 * P * MB) {
+                unsigned long long raw[MB];
+                unsigned spins = 0;
+                for (;;) {
+                    bool wait = false;
+#pragma unroll
+                    for (int m = 0; m < MB; ++m) {
+                        const int b = b0 + 8 * P * m;
+                        raw[m] = b < ne && v < 7 ? peek(X + (unsigned)((b * K + c) * kWideSum + v)) : 0ull;
+                    }
+#pragma unroll
+                    for (int m = 0; m < MB; ++m) wait = wait || raw[m] == kEmpty;
+                    if (!wait) break;
+                    if (give_up(spins, A.flags)) {
+                        fail = true;
+                        break;
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    const int b = b0 + 8 * P * m;
+                    const double val = as_value(raw[m]);
+                    if (v < 3) {
+                        d += val;
+                    } else if (b < ne && v < 7) {
+                        const int g = S.eagg[b];
+#pragma unroll
+                        for (int l = 0; l < NBK; ++l)
+                            if (l < nloc) {
+                                const double* cr = &S.crow[l][g][v - 3];
+#pragma unroll
+                                for (int a = 0; a < 4; ++a) cw[l][a] += cr[a * 4] * val;
+                            }
+                    }
+                }
+            }
+#pragma unroll
+            for (int l = 0; l < NBK; ++l)
+                if (l < nloc) {
+                    double u8[8] = {v == 0 ? d : 0.0, v == 1 ? d : 0.0, v == 2 ? d : 0.0,
+                                    cw[l][0], cw[l][1], cw[l][2], cw[l][3], 0.0};
+                    const double sum = wave_sum8(u8);
+                    if ((lane & 7) == 0) S.xp[c][part][l][lane >> 3] = sum;
+                }
+        }
+        if (fail) S.bad = 1;
+        __syncthreads();
+        if (S.bad) return false;
+        // everyone has the sums of this exchange, so the rows read before it and the sums of
+        // the exchange before it are no longer needed by anyone
+        empty_rows();
+        double* Xe = xcopy(nx + 1);
+        if (t < nloc * K * 7) publish_empty(Xe + ((int64_t)(e0 + t / (K * 7)) * K + (t / 7) % K) * kWideSum + t % 7);
+        return true;
+    };
+    // scalar role: thread t < 4 K nloc keeps column sc_c's scalars (all threads of a column
+    // alike) and the coarse value sc_a of an own aggregate
+    const bool scalar = t < 4 * K * nloc;
+    const int sc_c = t % K, sc_a = t / K;
+    auto total = [&](int v) {
+        double s = S.xp[sc_c][0][sc_a >> 2][v];
+#pragma unroll
+        for (int m = 1; m < P; ++m) s += S.xp[sc_c][m][sc_a >> 2][v];
+        return s;
+    };
+    double my_bb = 0.0, my_rr = 0.0, my_gam = 0.0, my_alpha = 0.0, my_c = 0.0, my_cs = 0.0;
+    bool my_done = false;
+    int my_its = 0;
+    double r[KG];
+#pragma unroll
+    for (int ii = 0; ii < KG; ++ii) {
+        r[ii] = 0.0;
+        if (q + ii * Q < K) S.x[q + ii * Q][row] = S.p[q + ii * Q][row] = S.s[q + ii * Q][row] = 0.0;
+    }
+    const double rtol2 = A.rtol * A.rtol;
+    constexpr int kMaxRestarts = 6;
+    int total_it = 0, cycle = 0;
+    bool first = true;
+    // Passes: kZero forms the residual of x = 0 (which gives |b|^2 and so fixes the tolerance),
+    // kStep is an iteration, kVerify forms the true residual
+    // once the iteration's own has converged, and starts another cycle from it when it has
+    // not.  One copy of the product and of the exchange serves them all.
+    enum { kZero, kStep, kVerify };
+    int pass = kZero;
+    __syncthreads();
+    for (;;) {
+        // addresses are formed anew in each pass: kept across it they would not fit the registers
+        asm volatile("" : "+v"(t), "+v"(lane), "+v"(row), "+v"(i));
+        double u[KG], w[KG];
+        if (pass == kStep) {
+            // u = M^{-1} r.  The block solve is a preconditioner: C_BB^{-1} (FP32) times r
+            // rounded to FP32, with FP32 sums (the solution's accuracy comes from the FP64
+            // residuals).  Padding rows hold r = 0 and an identity block in C_BB^{-1}.
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii)
+                if (q + ii * Q < K) S.r[q + ii * Q][row] = act ? (float)r[ii] : 0.0f;
+            __syncthreads();
+            {
+                const float* y = &S.r[lane & 3][(unit / 2) * kBS + seg * D::JS];
+                wide_float4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < D::JS; j += 4) {
+                    const float4 yj = *reinterpret_cast<const float4*>(y + j);
+                    a0 = __builtin_amdgcn_mfma_f32_4x4x1f32(binv[j], yj.x, a0, 0, 0, 0);
+                    a1 = __builtin_amdgcn_mfma_f32_4x4x1f32(binv[j + 1], yj.y, a1, 0, 0, 0);
+                    a0 = __builtin_amdgcn_mfma_f32_4x4x1f32(binv[j + 2], yj.z, a0, 0, 0, 0);
+                    a1 = __builtin_amdgcn_mfma_f32_4x4x1f32(binv[j + 3], yj.w, a1, 0, 0, 0);
+                }
+                // lane l now holds rows 4 (l / 4) .. + 3 of column l % 4
+                const int c = lane & 3;
+                if (c < K) {
+                    const wide_float4 v = a0 + a1;
+                    *reinterpret_cast<float4*>(&S.part[seg][c][unit * 64 + (lane & ~3)]) =
+                        make_float4(v.x, v.y, v.z, v.w);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) {
+                const int c = q + ii * Q;
+                u[ii] = 0.0;
+                if (c < K) {
+                    float v = S.part[0][c][row];
+#pragma unroll
+                    for (int m = 1; m < D::SEG; ++m) v += S.part[m][c][row];
+                    double cm = 0.0;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) cm += S.phi[a][row] * S.cval[my_la][a][c];
+                    u[ii] = (double)v + cm;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) u[ii] = q + ii * Q < K ? S.x[q + ii * Q][row] : 0.0;
+        }
+        product(u, w);
+        if (pass != kStep)
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) {
+                const int c = q + ii * Q;
+                r[ii] = act && c < K ? A.b[(int64_t)i * A.ld + c] - w[ii] : 0.0;
+                if (c < K) S.p[c][row] = S.s[c][row] = 0.0;
+                u[ii] = 0.0;
+                w[ii] = r[ii];
+            }
+        // sums of r u, w u, r r and the shares of w (of the true residual: u = 0, w = r)
+        if (!exchange(r, u, w)) return;
+        if (pass != kStep) {
+            if (scalar) {
+                my_rr = total(2);
+                my_c = total(3 + (sc_a & 3));
+                my_cs = 0.0;
+                S.cval[sc_a >> 2][sc_a & 3][sc_c] = my_c;
+                if (pass == kZero) {
+                    my_bb = my_rr;
+                    my_done = !(my_bb > 0.0);
+                }
+                if (pass == kVerify && !my_done && my_rr <= rtol2 * my_bb) my_done = true;
+                if (sc_a == 0) S.live[sc_c] = my_done ? 0 : 1;
+            }
+            if (pass == kVerify) {
+                __syncthreads();
+                bool all = true;
+#pragma unroll
+                for (int c = 0; c < K; ++c) all = all && S.live[c] == 0;
+                if (all || total_it >= A.maxiter || cycle == kMaxRestarts) break;
+                ++cycle;
+            }
+            pass = kStep;
+            first = true;
+            continue;
+        }
+        const bool can = total_it < A.maxiter;
+        if (scalar) {
+            const double g = total(0), d = total(1);
+            my_rr = total(2);
+            double al = 0.0, be = 0.0;
+            const bool live = !my_done && my_rr > rtol2 * my_bb;
+            if (live) {
+                if (can) {
+                    if (first) {
+                        al = g / d;
+                    } else {
+                        be = g / my_gam;
+                        al = g / (d - be * g / my_alpha);
+                    }
+                    my_its = total_it + 1;
+                }
+                my_gam = g;
+                my_alpha = al;
+            }
+            my_cs = total(3 + (sc_a & 3)) + be * my_cs;
+            my_c -= al * my_cs;
+            S.cval[sc_a >> 2][sc_a & 3][sc_c] = my_c;
+            if (sc_a == 0) {
+                S.coef[0][sc_c] = al;
+                S.coef[1][sc_c] = be;
+                S.live[sc_c] = live ? 1 : 0;
+            }
+        }
+        __syncthreads();
+        bool conv = true;
+#pragma unroll
+        for (int c = 0; c < K; ++c) conv = conv && S.live[c] == 0;
+#pragma unroll
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = q + ii * Q;
+            if (c < K) {
+                // columns that converged (or are done) have alpha = 0: x and r stay
+                const double al = S.coef[0][c], be = S.coef[1][c];
+                const double pn = u[ii] + be * S.p[c][row], sn = w[ii] + be * S.s[c][row];
+                S.p[c][row] = pn;
+                S.s[c][row] = sn;
+                S.x[c][row] += al * pn;
+                r[ii] -= al * sn;
+            }
+        }
+        if (conv || !can) {
+            pass = kVerify;
+        } else {
+            ++total_it;
+            first = false;
+        }
+    }
+    if (act)
+#pragma unroll
+        for (int ii = 0; ii < KG; ++ii) {
+            const int c = q + ii * Q;
+            if (c < K) A.x[(int64_t)i * A.ld + c] = S.x[c][row];
+        }
+    if (B0 == 0 && t < K) {
+        A.iters[t] = my_its;
+        A.relres[t] = my_bb > 0.0 ? sqrt(my_rr / my_bb) : 0.0;
+    }
+}
+
+// Solves in groups of up to kWideCols columns when every workgroup can be resident; *done says so.
+// Two blocks per workgroup up to 512 blocks, four up to 1,024: at 392 blocks three columns take
+// 1.61 ms with two and 1.97 ms with four (145 iterations).  Nine columns are three groups, one after
+// the other: 8.5 ms at 782 blocks, where the multi-launch solve of all nine takes 13.2 ms.
+hipError_t launch_pcg_wide(const PcgSetup& ps, const double* b, double* x, int k, double rtol, int maxiter,
+                           const PcgMlWork& w, int* iters, double* relres, hipStream_t s, bool* done)
+{
+    *done = false;
+    static_assert(sizeof(WideShared<kWideCols, 4>) <= 160 * 1024, "LDS of a workgroup");
+    if (ps.nb > 4 * kMaxBarrierW || 3 * kWideEntries * kWideSum > ps.n) return hipSuccess;
+    const int nbk = ps.nb <= 2 * kMaxBarrierW ? 2 : 4;
+    const int wgs = (ps.nb + nbk - 1) / nbk;
+    struct Kernel {
+        const void* fn;
+        size_t smem;
+    };
+    static const Kernel kernels[2][kWideCols] = {
+        {{(const void*)k_pcg_wide<1, 2>, sizeof(WideShared<1, 2>)},
+         {(const void*)k_pcg_wide<2, 2>, sizeof(WideShared<2, 2>)},
+         {(const void*)k_pcg_wide<3, 2>, sizeof(WideShared<3, 2>)}},
+        {{(const void*)k_pcg_wide<1, 4>, sizeof(WideShared<1, 4>)},
+         {(const void*)k_pcg_wide<2, 4>, sizeof(WideShared<2, 4>)},
+         {(const void*)k_pcg_wide<3, 4>, sizeof(WideShared<3, 4>)}}};
+    WideArgs A;
+    A.n = ps.n; A.nb = ps.nb; A.nc = ps.nc; A.ell_w = ps.ell_w; A.pcol = ps.pcol; A.pval = ps.pval;
+    A.bstart = ps.bstart; A.blk = ps.blk; A.agg_of_block = ps.agg_of_block; A.phi = ps.phi; A.Binv = ps.Binv;
+    A.C0inv = ps.C0inv; A.ld = k; A.U0 = w.m; A.U1 = w.an; A.X = w.v; A.flags = w.flags; A.rtol = rtol;
+    A.maxiter = maxiter;
+    for (int c0 = 0; c0 < k; c0 += kWideCols) {
+        const int kc = std::min(kWideCols, k - c0);
+        const Kernel& kern = kernels[nbk == 2 ? 0 : 1][kc - 1];
+        hipError_t e = hipFuncSetAttribute(kern.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kern.smem);
+        if (e != hipSuccess) return e;
+        int per_cu = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern.fn, kWideThreads, kern.smem);
+        if (e != hipSuccess) return e;
+        if (c0 == 0 && (int64_t)wgs > (int64_t)per_cu * device_info().num_cu) return hipSuccess;
+        A.b = b + c0; A.x = x + c0; A.iters = iters + c0; A.relres = relres + c0;
+        hipLaunchKernelGGL(k_wide_empty, dim3(256), dim3(256), 0, s, A, kc);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        void* params[] = {(void*)&A};
+        e = hipLaunchCooperativeKernel(kern.fn, dim3(wgs), dim3(kWideThreads), params, (unsigned)kern.smem, s);
+        if (e != hipSuccess) return e;
+    }
+    *done = true;
+    return hipSuccess;
+}
+
+}  // namespace
+
 // ---------------------------------------------------------------- multi-launch solve
 //
-// For problems with more blocks than workgroups that can be resident at once, the same
+// For problems with more than four blocks per workgroup that can be resident at once, the same
 // preconditioned Chronopoulos-Gear iteration runs as one kernel per phase; the kernel
 // boundaries are the grid-wide synchronisation.  Per iteration:
 //   k_ml_block       the previous iteration's update of the block's rows (p = m + beta p,
@@ -2029,6 +2650,9 @@ size_t pcg_ml_part_doubles(int64_t n)
 hipError_t launch_pcg_ml(const PcgSetup& ps, const double* b, double* x, int k, double rtol, int maxiter,
                          const PcgMlWork& w, int* iters, double* relres, hipStream_t s)
 {
+    bool done = false;
+    const hipError_t e = launch_pcg_wide(ps, b, x, k, rtol, maxiter, w, iters, relres, s, &done);
+    if (done || e != hipSuccess) return e;
     switch (k) {
     case 1: return launch_pcg_ml_k<1>(ps, b, x, k, rtol, maxiter, w, iters, relres, s);
     case 2: return launch_pcg_ml_k<2>(ps, b, x, k, rtol, maxiter, w, iters, relres, s);

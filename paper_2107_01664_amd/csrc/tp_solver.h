@@ -107,13 +107,16 @@ size_t pcg_table_bytes(int n);
 hipError_t launch_pcg_batch(const PcgItem* items, int n, int k, void* tab_dev, void* tab_host,
                             hipStream_t s);
 
-// Multi-launch form of the same solve for problems of more than pcg_max_blocks() blocks
-// (up to pcg_max_blocks_multi()): one kernel per phase of an iteration, the host reading
-// a device stop flag every few iterations (so the call returns after the solve has ended).
+// The same solve for problems of more than pcg_max_blocks() blocks (up to
+// pcg_max_blocks_multi()): persistent with several blocks per workgroup, or one kernel per
+// phase of an iteration, the host reading a device stop flag every few iterations (the call then
+// returns after the solve has ended).
 // b, x in block order [n][k], k <= kMaxGroupCols; work arrays [n][k] (r, p, s, m, an, v),
 // shares [nb][4][kMaxGroupCols], g [nc][kMaxGroupCols], part pcg_ml_part_doubles(n),
-// state pcg_ml_state_bytes() on the device and in pinned host memory.
+// state pcg_ml_state_bytes() on the device and in pinned host memory; flags: the problem's
+// device flags.
 struct PcgMlWork {
+    int* flags = nullptr;
     double* r = nullptr;
     double* p = nullptr;
     double* s = nullptr;
@@ -166,6 +169,44 @@ __device__ __forceinline__ double wave_sum(double v)
     v = v + dpp_move<0x141>(v);   // row_half_mirror
     v = v + dpp_move<0x140>(v);   // row_mirror
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+}
+
+// Lane swaps of gfx950: halves of the wave (and rows of 16 lanes) are added with no selects.
+__device__ __forceinline__ double swap_sum32(double a, double b)   // lanes 0..31: a's sum of the halves, 32..63: b's
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+__device__ __forceinline__ double swap_sum16(double a, double b)   // the same for rows of 16 lanes
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Keeps a on the lanes where up is false and b on the others, adding the partner lane's part.
+template <int CTRL>
+__device__ __forceinline__ double fold(double a, double b, bool up)
+{
+    return (up ? b : a) + dpp_move<CTRL>(up ? a : b);
+}
+
+// Sums of eight doubles over the wave in a fixed order: the lanes halve the set of values they
+// carry while they add, so eight sums take 10 additions instead of 56.  Lane l returns the sum of
+// v[l / 8].
+__device__ __forceinline__ double wave_sum8(double (&v)[8])
+{
+#pragma unroll
+    for (int m = 0; m < 4; ++m) v[m] = swap_sum32(v[m], v[m + 4]);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) v[m] = swap_sum16(v[m], v[m + 2]);
+    double s = fold<0x128>(v[0], v[1], (threadIdx.x & 8) != 0);   // row_ror:8
+    s += dpp_move<0x141>(s);        // row_half_mirror
+    s += dpp_move<0x4E>(s);         // quad_perm [2,3,0,1]
+    s += dpp_move<0xB1>(s);         // quad_perm [1,0,3,2]
+    return s;
 }
 
 // Barrier among the W workgroups of a group, the target-th of the launch (1, 2, ...): every
