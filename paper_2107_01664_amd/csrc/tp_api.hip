@@ -456,6 +456,11 @@ struct tp_problem {
     DevBuf<unsigned long long> bct_cnt;
     HostBuf<unsigned long long> bct_hcnt;
     DevBuf<double> bct_yt;
+    DevBuf<char> bct_ubs;
+    DevBuf<int2> bct_seg;
+    DevBuf<int32_t> bct_first;       // then the count of segments
+    DevBuf<double> bct_part;
+    BctSegs bct_segs;
     int64_t bct_ver = -1, bct_nadm = 0, bct_ninad = 0;
     DevBuf<double> bh_flo, bh_fhi, bh_fr2, bh_box, bh_na, bh_nsx, bh_nX, bh_nlo, bh_nhi, bh_nr2, bh_rec, bh_gS, bh_eS;
     DevBuf<double4> bh_nxa, bh_srt;
@@ -512,7 +517,8 @@ struct tp_problem {
              bh_nX.bytes() + bh_nlo.bytes() + bh_nhi.bytes() + bh_nr2.bytes() + bh_gS.bytes() + bh_eS.bytes() +
              bh_rec.bytes() + bh_nxa.bytes() + bh_srt.bytes() + bh_kin.bytes() + bh_kout.bytes() + bh_tmp.bytes() +
              bh_order.bytes() + bh_pos.bytes() + bh_counts.bytes() + bh_nm.bytes() + bct_far_off.bytes() +
-             bct_far_col.bytes() + bct_near_off.bytes() + bct_near_col.bytes() + bct_yt.bytes() +
+             bct_far_col.bytes() + bct_near_off.bytes() + bct_near_col.bytes() + bct_yt.bytes() + bct_ubs.bytes() +
+             bct_seg.bytes() + bct_first.bytes() + bct_part.bytes() +
              bct_fr0.bytes() + bct_fr1.bytes() + bct_fkeys.bytes() + bct_nkeys.bytes() + bct_sorted.bytes() +
              bct_grow.bytes() + bct_tmp.bytes() + bct_cnt.bytes();
         b += ng_key.bytes() + ng_rank.bytes() + ng_tmp.bytes() + ng_ord.bytes() + ng_sfx.bytes() + ng_sfl.bytes() +
@@ -1222,10 +1228,19 @@ tp_status ensure_bct(tp_problem* P)
     TP_TRY(P->bct_near_off.ensure((size_t)Pl + 1, s));
     TP_TRY(P->bct_near_col.ensure((size_t)std::max<int64_t>(nnear, 1), s));
     TP_TRY(P->bct_yt.ensure((size_t)M * ((kMaxGroupCols + 3) / 4 * 4 + 4), s));
-    TP_HIP(launch_bct_sort_csr(P->bct_fkeys.p, P->bct_sorted.p, nfar, P->bct_tmp.p, tb, M, P->bct_far_off.p,
+    TP_HIP(launch_bct_sort_csr(P->bct_fkeys.p, P->bct_sorted.p, nfar, P->bct_tmp.p, tb, Pl, M, P->bct_far_off.p,
                                P->bct_far_col.p, s));
-    TP_HIP(launch_bct_sort_csr(P->bct_nkeys.p, P->bct_sorted.p, nnear, P->bct_tmp.p, tb, Pl, P->bct_near_off.p,
+    TP_HIP(launch_bct_sort_csr(P->bct_nkeys.p, P->bct_sorted.p, nnear, P->bct_tmp.p, tb, Pl, Pl, P->bct_near_off.p,
                                P->bct_near_col.p, s));
+    if (P->prm.leaf_size <= 8) {
+        const int64_t nleaf = (P->nF + P->prm.leaf_size - 1) / P->prm.leaf_size;
+        BctSegs& g = P->bct_segs;
+        g.max = (int)(nnear / kBctSeg);
+        TP_TRY(P->bct_seg.ensure((size_t)std::max(g.max, 1), s));
+        TP_TRY(P->bct_first.ensure((size_t)nleaf + 1, s));
+        g.seg = P->bct_seg.p; g.first = P->bct_first.p; g.count = P->bct_first.p + nleaf;
+        TP_HIP(launch_bct_long(nleaf, P->bct_near_off.p, g, s));
+    }
     P->bct_nadm = nfar;
     P->bct_ninad = nnear;
     P->bct_ver = P->geom_ver;
@@ -1583,11 +1598,15 @@ tp_status enqueue_fractional(const Batch& B, const double* const* u, int ldu, in
                 // block cluster tree: hierarchical product, the row sums straight into zbuf
                 TP_TRY(ensure_bct(P));
                 TP_TRY(P->bh_nm.ensure((size_t)bh_node_count(P->nF, P->prm.leaf_size, nullptr) * kp, s));
+                TP_TRY(P->bct_ubs.ensure((size_t)P->nF * kp * esz, s));
                 BctLists bl;
                 bl.far_off = P->bct_far_off.p; bl.far_col = P->bct_far_col.p;
                 bl.near_off = P->bct_near_off.p; bl.near_col = P->bct_near_col.p;
+                bl.segs = P->bct_segs;
+                TP_TRY(P->bct_part.ensure((size_t)bl.segs.max * 8 * kp + 1, s));
+                bl.segs.part = P->bct_part.p;
                 TP_HIP(launch_bct_frac(P->bh, bl, P->nF, P->prm.leaf_size, prec, P->sigma, P->fd, P->ub.p, kp, kc,
-                                       P->bh_nm.p, P->bct_yt.p, P->zbuf.p, pl.irows, s));
+                                       P->bh_nm.p, P->bct_yt.p, P->bct_ubs.p, P->zbuf.p, pl.irows, s));
                 continue;
             }
             if (P->prm.theta > 0.0) {
@@ -3051,7 +3070,7 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
         const double M = (double)bh_node_count(nF, prm.leaf_size, nullptr);
         b += f * (208.0 + 56.0) + M * (240.0 + 8.0 * kMaxGroupCols) + (double)bh_sort_temp_bytes(nF) + 8 * kBhBoxDoubles + 64;
         // block cluster tree lists and far-field values (chi > 0; about 64 blocks per node)
-        if (prm.chi > 0.0) b += M * (8.0 * (kMaxGroupCols + 1) + 4.0 * 64 + 8.0);
+        if (prm.chi > 0.0) b += M * (8.0 * (2 * kMaxGroupCols + 1) + 4.0 * 64 + 8.0) + f * ((kf + 3) / 4 * 4) * esz;
     }
     // FP64 near-field grid
     if (prm.precision == TP_PREC_FP32_NEAR64) b += (double)near_grid_bytes(nF);

@@ -645,32 +645,54 @@ __device__ __forceinline__ void load_row(const T* __restrict__ row, double (&out
     }
 }
 
-// Node moments [2P][KP], leaves first (member faces in sorted order), then level by level.
+// Node moments [2P][KP]: leaves (member faces in sorted order) and the levels above them up to one
+// node per workgroup, in LDS; also ub in sorted order, when asked (ubs).  All levels in one
+// workgroup took 76 us at 32,768 leaves and four columns, this and the launch for the top 16 us.
 template <class UB, int KP>
-__global__ void k_bh_moment_leaves(int64_t nF, int leaf, int64_t P, const int32_t* __restrict__ order,
-                                   const double4* __restrict__ dx, const UB* __restrict__ ub,
-                                   double* __restrict__ nm)
+__global__ __launch_bounds__(kSubLeaves) void k_bh_moments(int64_t nF, int leaf, int64_t P,
+                                                           const int32_t* __restrict__ order,
+                                                           const double4* __restrict__ srt, const UB* __restrict__ ub,
+                                                           double* __restrict__ nm, UB* __restrict__ ubs)
 {
-    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= P) return;
+    __shared__ double sh[KP][kSubLeaves];
+    const int t = threadIdx.x;
+    const int64_t l = (int64_t)blockIdx.x * kSubLeaves + t;
     double acc[KP];
+    if (l < P) {
 #pragma unroll
-    for (int c = 0; c < KP; ++c) acc[c] = 0.0;
-    for (int64_t p = l * leaf; p < (l + 1) * leaf && p < nF; ++p) {
-        const int32_t t = order[p];
-        const double a = dx[t].w;
-        double u[KP];
-        load_row<KP>(ub + (int64_t)t * KP, u);
+        for (int c = 0; c < KP; ++c) acc[c] = 0.0;
+        for (int64_t p = l * leaf; p < (l + 1) * leaf && p < nF; ++p) {
+            const UB* row = ub + (int64_t)order[p] * KP;
+            const double a = srt[p].w;
+            double u[KP];
+            load_row<KP>(row, u);
 #pragma unroll
-        for (int c = 0; c < KP; ++c) acc[c] = acc[c] + a * u[c];
+            for (int c = 0; c < KP; ++c) acc[c] = acc[c] + a * u[c];
+            if (ubs)
+#pragma unroll
+                for (int c = 0; c < KP; ++c) ubs[p * KP + c] = (UB)u[c];
+        }
+#pragma unroll
+        for (int c = 0; c < KP; ++c) nm[(P + l) * KP + c] = sh[c][t] = acc[c];
     }
+    int64_t base = P + (int64_t)blockIdx.x * kSubLeaves;
+    for (int w = (int)min((int64_t)kSubLeaves, P) >> 1; w >= 1; w >>= 1) {
+        base >>= 1;
+        __syncthreads();
+        if (t < w)
 #pragma unroll
-    for (int c = 0; c < KP; ++c) nm[(P + l) * KP + c] = acc[c];
+            for (int c = 0; c < KP; ++c) acc[c] = sh[c][2 * t] + sh[c][2 * t + 1];
+        __syncthreads();
+        if (t < w)
+#pragma unroll
+            for (int c = 0; c < KP; ++c) nm[(base + t) * KP + c] = sh[c][t] = acc[c];
+    }
 }
 
-__global__ __launch_bounds__(1024) void k_bh_moment_levels(int64_t P, int kp, double* __restrict__ nm)
+// The levels above.
+__global__ __launch_bounds__(1024) void k_bh_moment_top(int64_t P, int kp, double* __restrict__ nm)
 {
-    for (int64_t n0 = P / 2; n0 >= 1; n0 /= 2) {
+    for (int64_t n0 = P / kSubLeaves / 2; n0 >= 1; n0 /= 2) {
         for (int64_t e = threadIdx.x; e < n0 * kp; e += blockDim.x) {
             const int64_t node = n0 + e / kp;
             const int c = (int)(e % kp);
@@ -685,7 +707,7 @@ __device__ __forceinline__ double frac_kernel(const double (&xs)[3], const doubl
 {
     R d[3];
     for (int m = 0; m < 3; ++m) d[m] = (R)(xs[m] - y[m]);
-    const R r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+    const R r2 = fma(d[2], d[2], fma(d[0], d[0], d[1] * d[1]));   // the same bits wherever it is inlined
     if (sizeof(R) == sizeof(float))
         return (double)__builtin_amdgcn_exp2f((float)expo * __builtin_amdgcn_logf((float)r2));
     return pow((double)r2, expo);
@@ -743,12 +765,12 @@ __global__ __launch_bounds__(256) void k_bh_frac(BhArgs A, const UB* __restrict_
 }
 
 template <class UB, int KP>
-void moments_launch(const BhBuffers& b, int64_t nF, int leaf, int64_t P, const FaceData& fd, const UB* ub,
-                    double* nm, hipStream_t s)
+void moments_launch(const BhBuffers& b, int64_t nF, int leaf, int64_t P, const UB* ub,
+                    double* nm, UB* ubs, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_bh_moment_leaves<UB, KP>), dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, nF, leaf,
-                       P, b.order, fd.dx, ub, nm);
-    hipLaunchKernelGGL(k_bh_moment_levels, dim3(1), dim3(1024), 0, s, P, KP, nm);
+    hipLaunchKernelGGL((k_bh_moments<UB, KP>), dim3((unsigned)((P + kSubLeaves - 1) / kSubLeaves)), dim3(kSubLeaves), 0,
+                       s, nF, leaf, P, b.order, b.srt, ub, nm, ubs);
+    if (P > kSubLeaves) hipLaunchKernelGGL(k_bh_moment_top, dim3(1), dim3(1024), 0, s, P, KP, nm);
 }
 
 template <class UB, int KP>
@@ -757,7 +779,7 @@ hipError_t bh_frac_launch(const BhBuffers& b, int64_t nF, int leaf, double theta
 {
     int64_t P = 0;
     (void)bh_node_count(nF, leaf, &P);
-    moments_launch<UB, KP>(b, nF, leaf, P, fd, ub, nm, s);
+    moments_launch<UB, KP>(b, nF, leaf, P, ub, nm, nullptr, s);
     BhArgs A;
     A.nF = nF; A.P = P; A.leaf = leaf; A.theta2 = theta * theta; A.alpha = 0.0; A.beta = 0.0;
     A.order = b.order; A.dx = fd.dx; A.dn = fd.dn; A.flo = b.flo; A.fhi = b.fhi; A.fr2 = b.fr2;
@@ -783,12 +805,13 @@ hipError_t bh_frac_launch(const BhBuffers& b, int64_t nF, int leaf, double theta
 // y~ rows are 4 + KP wide: [sum w a_J, 0, 0, 0, sum w m_J (KP)].
 
 // Admissible blocks: one wave per row node I.  The lanes take the node's list in strides of
-// 64 entries; the sums are then added across the wave in a fixed order (butterfly), so the
-// result does not depend on timing.
+// 64 entries, the loads of U of them in flight together (9.79 million entries of 200,000 faces:
+// 276 us with one at a time, 154 us); the sums are then added across the wave in a fixed order
+// (butterfly), so the result does not depend on timing.
 template <class R, int KP>
 __global__ __launch_bounds__(256) void k_bct_far(int64_t M, const int32_t* __restrict__ off,
-                                                 const int32_t* __restrict__ col, const double* __restrict__ nX,
-                                                 const double* __restrict__ na, const double* __restrict__ nm,
+                                                 const int32_t* __restrict__ col, const double4* __restrict__ nxa,
+                                                 const double* __restrict__ nm,
                                                  double expo, double* __restrict__ yt)
 {
     const int64_t I = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
@@ -797,16 +820,30 @@ __global__ __launch_bounds__(256) void k_bct_far(int64_t M, const int32_t* __res
     double a0 = 0.0, acc[KP];
 #pragma unroll
     for (int c = 0; c < KP; ++c) acc[c] = 0.0;
-    const double xi[3] = {nX[3 * I], nX[3 * I + 1], nX[3 * I + 2]};
+    const double4 XI = nxa[I];
+    const double xi[3] = {XI.x, XI.y, XI.z};
     const int32_t e1 = off[I + 1];
-    for (int32_t e = off[I] + lane; e < e1; e += 64) {
-        const int32_t J = col[e];
-        double m[KP];
-        load_row<KP>(nm + (int64_t)J * KP, m);
-        const double w = frac_kernel<R>(xi, nX + 3 * J, expo);
-        a0 += w * na[J];
+    constexpr int U = KP == 4 ? 4 : 2;        // entries with their loads in flight together
+    for (int32_t e = off[I] + lane; e < e1; e += 64 * U) {
+        int32_t J[U];
+        double4 Y[U];
+        double m[U][KP];
 #pragma unroll
-        for (int c = 0; c < KP; ++c) acc[c] += w * m[c];
+        for (int q = 0; q < U; ++q) J[q] = col[min(e + 64 * q, e1 - 1)];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            Y[q] = nxa[J[q]];
+            load_row<KP>(nm + (int64_t)J[q] * KP, m[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const double y[3] = {Y[q].x, Y[q].y, Y[q].z};
+            const double w = e + 64 * q < e1 ? frac_kernel<R>(xi, y, expo) : 0.0;   // (no branch: it would
+                                                                                    // hold the loads back)
+            a0 += w * Y[q].w;
+#pragma unroll
+            for (int c = 0; c < KP; ++c) acc[c] += w * m[q][c];
+        }
     }
     a0 = wave_sum(a0);
 #pragma unroll
@@ -845,59 +882,87 @@ __device__ __forceinline__ void bct_down(const double* __restrict__ yt, int64_t 
 // Inadmissible (exact) blocks for leaves of at most 8 faces: one wave per row leaf L, lane
 // (i, j) = (lane / 8, lane % 8) takes the pair (face i of L, face j of J) for every leaf J of
 // L's list, all lanes walking the same list (64 list entries are read at once and handed
-// out lane by lane; the gathers of U leaves are issued before any of them is used); the 8
-// lanes of face i are then added in a fixed order and lane (i, 0) adds the far field of L's
-// path to the root.
-template <class R, class UB, int KP>
-__global__ __launch_bounds__(256) void k_bct_leaf8(int64_t nF, int leaf, int64_t P, const int32_t* __restrict__ order,
-                                                   const double4* __restrict__ dx, const UB* __restrict__ ub, int k,
-                                                   const int32_t* __restrict__ noff,
-                                                   const int32_t* __restrict__ ncol, const double* __restrict__ yt,
-                                                   double expo, double* __restrict__ z, int64_t zstride)
+// out as scalars); the 8 lanes of face i are then added in a fixed order and lane (i, 0) adds the
+// far field of L's path to the root.
+//
+// A leaf whose faces lie apart (the Morton order jumps inside it) has a large box and a list of
+// thousands of leaves, where the mean is 211: one such wave took 4.5 ms, the others together
+// 0.6 ms.  So a wave takes kBctSeg entries at most; what a list has beyond them are segments, each a
+// wave of a launch before (k_bct_long counts them when the lists are built), whose sums are added
+// in order.
+// A leaf's faces through order[], then their data from wherever they are stored, were two trips to
+// memory per batch of four leaves; positions and values in sorted order are contiguous and need the
+// list alone, and the loads of U leaves are in flight together.  Consecutive leaves have nearly the
+// same lists: each XCD takes a contiguous range of leaves, so that its L2 serves them.
+// 200,000 faces, three columns, 5.29 million leaf pairs: 6.4 ms before, 0.68 ms now (both
+// launches; 0.77 ms with segments of 512 entries).
+struct BctLeafArgs {
+    int nF, leaf, nleaf;
+    const double4* srt;       // [nF] (X, a) in sorted order
+    const int32_t* noff;      // [nleaf + 1]
+    const int32_t* ncol;
+    BctSegs sg;
+    double expo;
+};
+
+__global__ void k_bct_long(int nleaf, const int32_t* __restrict__ noff, BctSegs sg)
 {
-    constexpr int U = 4;
-    const int64_t L = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    const int64_t nleaf = (nF + leaf - 1) / leaf;
-    if (L >= nleaf) return;                   // the whole wave
-    const int i = lane >> 3, j = lane & 7;
-    const int64_t ps = L * leaf + i;
-    const bool own = i < leaf && ps < nF;
-    const bool lane_on = own && j < leaf;
-    const int32_t s = own ? order[ps] : order[0];
-    const double4 X = dx[s];
+    const int L = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (L >= nleaf) return;
+    const int n = (noff[L + 1] - noff[L] - 1) / kBctSeg;   // segments beyond the first (an empty list: 0)
+    int at = -1;
+    if (n > 0) {
+        at = atomicAdd(sg.count, n);
+        for (int q = 0; q < n; ++q) sg.seg[at + q] = make_int2(L, q + 1);
+    }
+    sg.first[L] = at;
+}
+
+// The sums of leaf L over the list entries [e0, e1): lane (i, j) returns face i's sum.
+template <class R, class UB, int KP>
+__device__ __forceinline__ void bct_leaf_sum(const BctLeafArgs& A, const UB* __restrict__ ubs, int L, int32_t e0,
+                                             int32_t e1, double (&us)[KP], double (&acc)[KP])
+{
+    constexpr int U = sizeof(UB) * KP <= 16 ? 8 : 4;   // as many as the registers hold
+    typedef typename Vec4Of<UB>::type Vec;
+    const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+    const int ps = L * A.leaf + i;
+    const bool own = i < A.leaf && ps < A.nF;
+    const bool lane_on = own && j < A.leaf;
+    const double4 X = A.srt[own ? ps : 0];
     const double xs[3] = {X.x, X.y, X.z};
-    double us[KP], acc[KP];
-    load_row<KP>(ub + (int64_t)s * KP, us);
+    load_row<KP>(ubs + (int64_t)(own ? ps : 0) * KP, us);
 #pragma unroll
     for (int c = 0; c < KP; ++c) acc[c] = 0.0;
-    const int32_t e0 = noff[L], e1 = noff[L + 1];
     for (int32_t eb = e0; eb < e1; eb += 64) {
-        const int32_t mine = eb + lane < e1 ? ncol[eb + lane] : 0;
+        const int32_t mine = eb + lane < e1 ? A.ncol[eb + lane] : 0;
         const int nb = min(64, e1 - eb);
         for (int q0 = 0; q0 < nb; q0 += U) {
-            int32_t t[U];
-#pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const int32_t J = __shfl(mine, q0 + q, 64);
-                const int64_t pt = (int64_t)J * leaf + j;
-                t[q] = (lane_on && q0 + q < nb && pt < nF) ? order[pt] : -1;
-            }
+            bool on[U];
             double4 Y[U];
-            double ut[U][KP];
+            Vec ut[U][KP / 4];
 #pragma unroll
             for (int q = 0; q < U; ++q) {
-                const int32_t tq = t[q] >= 0 ? t[q] : s;
-                Y[q] = dx[tq];
-                load_row<KP>(ub + (int64_t)tq * KP, ut[q]);
+                const int J = __builtin_amdgcn_readlane(mine, min(q0 + q, 63));
+                const int pt = J * A.leaf + j;
+                on[q] = lane_on && q0 + q < nb && pt < A.nF && pt != ps;
+                const int at = min(pt, A.nF - 1);
+                Y[q] = A.srt[at];
+#pragma unroll
+                for (int h = 0; h < KP / 4; ++h) ut[q][h] = reinterpret_cast<const Vec*>(ubs + (int64_t)at * KP)[h];
             }
 #pragma unroll
             for (int q = 0; q < U; ++q) {
-                if (t[q] < 0 || t[q] == s) continue;
+                if (!on[q]) continue;
                 const double y[3] = {Y[q].x, Y[q].y, Y[q].z};
-                const double w = frac_kernel<R>(xs, y, expo) * Y[q].w;
+                const double w = frac_kernel<R>(xs, y, A.expo) * Y[q].w;
 #pragma unroll
-                for (int c = 0; c < KP; ++c) acc[c] += w * (us[c] - ut[q][c]);
+                for (int h = 0; h < KP / 4; ++h) {
+                    acc[4 * h] += w * (us[4 * h] - (double)ut[q][h].x);
+                    acc[4 * h + 1] += w * (us[4 * h + 1] - (double)ut[q][h].y);
+                    acc[4 * h + 2] += w * (us[4 * h + 2] - (double)ut[q][h].z);
+                    acc[4 * h + 3] += w * (us[4 * h + 3] - (double)ut[q][h].w);
+                }
             }
         }
     }
@@ -909,7 +974,42 @@ __global__ __launch_bounds__(256) void k_bct_leaf8(int64_t nF, int leaf, int64_t
         v += __shfl_xor(v, 1, 64);
         acc[c] = v;
     }
-    if (!own || j != 0) return;
+}
+
+// One wave per segment: part[segment][face of the leaf][KP].
+template <class R, class UB, int KP>
+__global__ __launch_bounds__(256) void k_bct_segs(BctLeafArgs A, const UB* __restrict__ ubs)
+{
+    const int u = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (u >= *A.sg.count) return;             // the whole wave
+    const int2 g = A.sg.seg[u];
+    const int L = __builtin_amdgcn_readfirstlane(g.x), q = __builtin_amdgcn_readfirstlane(g.y);
+    const int32_t e0 = A.noff[L] + q * kBctSeg;
+    double us[KP], acc[KP];
+    bct_leaf_sum<R, UB, KP>(A, ubs, L, e0, min(e0 + kBctSeg, A.noff[L + 1]), us, acc);
+    if ((lane & 7) == 0)
+#pragma unroll
+        for (int c = 0; c < KP; ++c) A.sg.part[((int64_t)u * 8 + (lane >> 3)) * KP + c] = acc[c];
+}
+
+template <class R, class UB, int KP>
+__global__ __launch_bounds__(256) void k_bct_leaf8(BctLeafArgs A, const UB* __restrict__ ubs, int64_t P, int k,
+                                                   const int32_t* __restrict__ order, const double* __restrict__ yt,
+                                                   double* __restrict__ z, int64_t zstride)
+{
+    const int wg = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);   // gridDim.x: 8 m
+    const int L = wg * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (L >= A.nleaf) return;                 // the whole wave
+    const int32_t e0 = A.noff[L], e1 = A.noff[L + 1];
+    double us[KP], acc[KP];
+    bct_leaf_sum<R, UB, KP>(A, ubs, L, e0, min(e1, e0 + kBctSeg), us, acc);
+    const int lane = threadIdx.x & 63, i = lane >> 3, ps = L * A.leaf + i;
+    if (i >= A.leaf || ps >= A.nF || (lane & 7) != 0) return;
+    const int f = A.sg.first[L];
+    for (int q = 0; q < (f < 0 ? 0 : (e1 - e0 - 1) / kBctSeg); ++q)
+#pragma unroll
+        for (int c = 0; c < KP; ++c) acc[c] += A.sg.part[((int64_t)(f + q) * 8 + i) * KP + c];
+    const int32_t s = order[ps];
     bct_down<KP>(yt, P, L, us, acc);
 #pragma unroll
     for (int c = 0; c < KP; ++c)
@@ -957,23 +1057,28 @@ __global__ __launch_bounds__(256) void k_bct_faces(int64_t nF, int leaf, int64_t
 
 template <class UB, int KP>
 hipError_t bct_launch(const BhBuffers& b, const BctLists& bl, int64_t nF, int leaf, bool f64, const FaceData& fd,
-                      const UB* ub, int k, double expo, double* nm, double* yt, double* z, int64_t zstride,
+                      const UB* ub, int k, double expo, double* nm, double* yt, void* ubs, double* z, int64_t zstride,
                       hipStream_t s)
 {
     int64_t P = 0;
     const int64_t M = (int64_t)bh_node_count(nF, leaf, &P);
-    moments_launch<UB, KP>(b, nF, leaf, P, fd, ub, nm, s);
+    moments_launch<UB, KP>(b, nF, leaf, P, ub, nm, leaf <= 8 ? static_cast<UB*>(ubs) : nullptr, s);
     // one wave (64 lanes) per node for the admissible blocks, per leaf for the exact ones
     const int64_t nleaf = (nF + leaf - 1) / leaf;
-    const dim3 gm((unsigned)((M * 64 + 255) / 256)), gl((unsigned)((nleaf * 64 + 255) / 256)),
+    const dim3 gm((unsigned)((M * 64 + 255) / 256)), gl((unsigned)((nleaf + 31) / 32 * 8)),
         gf((unsigned)((nF + 255) / 256)), blk(256);
     // pair terms in the precision of the face averages (FP64 for TP_PREC_FP64, else FP32)
     (void)f64;
-    hipLaunchKernelGGL((k_bct_far<UB, KP>), gm, blk, 0, s, M, bl.far_off, bl.far_col, b.nX, b.na, nm, expo, yt);
-    if (leaf <= 8)
-        hipLaunchKernelGGL((k_bct_leaf8<UB, UB, KP>), gl, blk, 0, s, nF, leaf, P, b.order, fd.dx, ub, k, bl.near_off,
-                           bl.near_col, yt, expo, z, zstride);
-    else
+    hipLaunchKernelGGL((k_bct_far<UB, KP>), gm, blk, 0, s, M, bl.far_off, bl.far_col, b.nxa, nm, expo, yt);
+    if (leaf <= 8) {
+        BctLeafArgs A;
+        A.nF = (int)nF; A.leaf = leaf; A.nleaf = (int)nleaf; A.srt = b.srt; A.noff = bl.near_off; A.ncol = bl.near_col;
+        A.sg = bl.segs; A.expo = expo;
+        const UB* us = static_cast<const UB*>(ubs);
+        if (bl.segs.max > 0)
+            hipLaunchKernelGGL((k_bct_segs<UB, UB, KP>), dim3((unsigned)((bl.segs.max + 3) / 4)), blk, 0, s, A, us);
+        hipLaunchKernelGGL((k_bct_leaf8<UB, UB, KP>), gl, blk, 0, s, A, us, P, k, b.order, yt, z, zstride);
+    } else
         hipLaunchKernelGGL((k_bct_faces<UB, UB, KP>), gf, blk, 0, s, nF, leaf, P, b.order, fd.dx, ub, k, bl.near_off,
                            bl.near_col, yt, expo, z, zstride);
     return hipGetLastError();
@@ -1012,8 +1117,8 @@ __device__ __forceinline__ bool bct_separated(const double (&a)[8], const double
 constexpr int kExpThreads = 1024, kExpPer = 4;
 
 __global__ __launch_bounds__(kExpThreads) void k_bct_expand(const uint64_t* __restrict__ cur, int64_t n,
-                                                            const double4* __restrict__ rec, int64_t P, double chi2,
-                                                            uint64_t* __restrict__ far, uint64_t* __restrict__ near,
+                                                            const double4* __restrict__ rec, int64_t P, int bits,
+                                                            double chi2, uint64_t* __restrict__ far, uint64_t* __restrict__ near,
                                                             uint64_t* __restrict__ next,
                                                             unsigned long long* __restrict__ cnt)
 {
@@ -1069,9 +1174,9 @@ __global__ __launch_bounds__(kExpThreads) void k_bct_expand(const uint64_t* __re
     for (int q = 0; q < kExpPer; ++q) {
         const int64_t I = (int64_t)(key[q] >> 32), J = (int64_t)(key[q] & 0xffffffffull);
         if (what[q] == 1) {
-            far[off[0]++] = key[q];
+            far[off[0]++] = (uint64_t)I << bits | (uint64_t)J;
         } else if (what[q] == 2) {
-            near[off[1]++] = ((uint64_t)(I - P) << 32) | (uint64_t)(J - P);
+            near[off[1]++] = (uint64_t)(I - P) << bits | (uint64_t)(J - P);
         } else if (what[q] == 3) {
             for (int a = 0; a < 2; ++a)
                 for (int b = 0; b < 2; ++b)
@@ -1083,12 +1188,12 @@ __global__ __launch_bounds__(kExpThreads) void k_bct_expand(const uint64_t* __re
 
 // CSR of sorted (row << 32 | column) keys: off[r] = first key of row r (r = 0 .. rows),
 // col[e] = column of key e.
-__global__ void k_bct_csr(const uint64_t* __restrict__ keys, int64_t n, int64_t rows, int32_t* __restrict__ off,
+__global__ void k_bct_csr(const uint64_t* __restrict__ keys, int64_t n, int64_t rows, int bits, int32_t* __restrict__ off,
                           int32_t* __restrict__ col)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t <= rows) {
-        const uint64_t target = (uint64_t)t << 32;
+        const uint64_t target = (uint64_t)t << bits;
         int64_t lo = 0, hi = n;
         while (lo < hi) {
             const int64_t mid = (lo + hi) >> 1;
@@ -1097,7 +1202,7 @@ __global__ void k_bct_csr(const uint64_t* __restrict__ keys, int64_t n, int64_t 
         }
         off[t] = (int32_t)lo;
     }
-    if (t < n) col[t] = (int32_t)(keys[t] & 0xffffffffull);
+    if (t < n) col[t] = (int32_t)(keys[t] & ((1ull << bits) - 1ull));
 }
 
 }  // namespace
@@ -1199,15 +1304,24 @@ hipError_t launch_bh_frac(const BhBuffers& b, int64_t nF, int leaf, double theta
 
 hipError_t launch_bct_frac(const BhBuffers& b, const BctLists& bl, int64_t nF, int leaf, int precision,
                            double sigma, const FaceData& fd, const void* ub, int kp, int k, double* nm, double* yt,
-                           double* z, int64_t zstride, hipStream_t s)
+                           void* ubs, double* z, int64_t zstride, hipStream_t s)
 {
     if (k < 1 || k > kMaxGroupCols || kp != (k + 3) / 4 * 4) return hipErrorInvalidValue;
     const double expo = -(sigma + 1.0);
     const bool f64 = precision == TP_PREC_FP64;
-#define TP_BCT(T, KP) bct_launch<T, KP>(b, bl, nF, leaf, f64, fd, static_cast<const T*>(ub), k, expo, nm, yt, z, zstride, s)
+#define TP_BCT(T, KP) bct_launch<T, KP>(b, bl, nF, leaf, f64, fd, static_cast<const T*>(ub), k, expo, nm, yt, ubs, z, zstride, s)
     if (f64) return kp == 4 ? TP_BCT(double, 4) : kp == 8 ? TP_BCT(double, 8) : TP_BCT(double, 12);
     return kp == 4 ? TP_BCT(float, 4) : kp == 8 ? TP_BCT(float, 8) : TP_BCT(float, 12);
 #undef TP_BCT
+}
+
+// List entries are row << bits | column, bits those of a node number: the sort then has 2 bits / 8
+// passes over a list (four at 65,536 nodes) where row << 32 | column has eight.
+static int bct_bits(int64_t P)
+{
+    int b = 1;
+    while (((int64_t)1 << b) < 2 * P) ++b;
+    return b;
 }
 
 size_t bct_sort_temp_bytes(int64_t n)
@@ -1224,21 +1338,30 @@ hipError_t launch_bct_expand(const double* rec, int64_t P, double chi, const uin
     if (n < 1) return hipSuccess;
     const int64_t per_block = (int64_t)kExpThreads * kExpPer;
     hipLaunchKernelGGL(k_bct_expand, dim3((unsigned)((n + per_block - 1) / per_block)), dim3(kExpThreads), 0, s, cur,
-                       n, reinterpret_cast<const double4*>(rec), P, chi * chi, far, near, next, cnt);
+                       n, reinterpret_cast<const double4*>(rec), P, bct_bits(P), chi * chi, far, near, next, cnt);
+    return hipGetLastError();
+}
+
+hipError_t launch_bct_long(int64_t nleaf, const int32_t* noff, const BctSegs& sg, hipStream_t s)
+{
+    hipError_t e = hipMemsetAsync(sg.count, 0, sizeof(int), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_bct_long, dim3((unsigned)((nleaf + 255) / 256)), dim3(256), 0, s, (int)nleaf, noff, sg);
     return hipGetLastError();
 }
 
 hipError_t launch_bct_sort_csr(const uint64_t* keys, uint64_t* sorted, int64_t n, void* tmp, size_t tmp_bytes,
-                               int64_t rows, int32_t* off, int32_t* col, hipStream_t s)
+                               int64_t P, int64_t rows, int32_t* off, int32_t* col, hipStream_t s)
 {
+    const int bits = bct_bits(P);
     if (n > (int64_t)INT32_MAX) return hipErrorInvalidValue;
     if (n > 0) {
         size_t tb = tmp_bytes;
-        hipError_t e = hipcub::DeviceRadixSort::SortKeys(tmp, tb, keys, sorted, (int)n, 0, 64, s);
+        hipError_t e = hipcub::DeviceRadixSort::SortKeys(tmp, tb, keys, sorted, (int)n, 0, 2 * bits, s);
         if (e != hipSuccess) return e;
     }
     const int64_t m = std::max(rows + 1, n);
-    hipLaunchKernelGGL(k_bct_csr, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, sorted, n, rows, off, col);
+    hipLaunchKernelGGL(k_bct_csr, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, sorted, n, rows, bits, off, col);
     return hipGetLastError();
 }
 

@@ -333,6 +333,15 @@ hipError_t launch_bh_eval(const BhBuffers& b, int64_t nF, int leaf, double theta
 // ([cap][kp], kp = k rounded up to 4, zero padded; FP64 for TP_PREC_FP64 else FP32), node
 // moments nm ([2P][kp] doubles), output z(S) (the row sums without a_S) at z[c * zstride + S],
 // k <= kMaxGroupCols.
+constexpr int kBctSeg = 256;     // list entries of one wave of the exact blocks' kernel
+// Parts of exact lists beyond their first kBctSeg entries.
+struct BctSegs {
+    int max = 0;                         // of them at most (list entries / kBctSeg)
+    int* count = nullptr;                // of them
+    int2* seg = nullptr;                 // [max] (row leaf, which part)
+    int32_t* first = nullptr;            // [leaves] a leaf's first one, -1: none
+    double* part = nullptr;              // [max][8][kp] their sums
+};
 // Block cluster tree of the fractional operator's kernel matrix (device CSR lists): per row
 // node the admissible column nodes, per row leaf the inadmissible column leaves.
 struct BctLists {
@@ -340,12 +349,13 @@ struct BctLists {
     const int32_t* far_col = nullptr;
     const int32_t* near_off = nullptr;   // [P + 1] (leaf index = node - P)
     const int32_t* near_col = nullptr;   // leaf indices
+    BctSegs segs;                        // leaves of at most 8 faces
 };
 // L^sigma's kernel sums by hierarchical multiplication on the lists; nm [2P][kp] node moments,
-// yt [2P][kp + 4] far-field values, output as launch_bh_frac.
+// yt [2P][kp + 4] far-field values, ubs room for nF rows of ub, output as launch_bh_frac.
 hipError_t launch_bct_frac(const BhBuffers& b, const BctLists& bl, int64_t nF, int leaf, int precision,
                            double sigma, const FaceData& fd, const void* ub, int kp, int k, double* nm, double* yt,
-                           double* z, int64_t zstride, hipStream_t s);
+                           void* ubs, double* z, int64_t zstride, hipStream_t s);
 hipError_t launch_bh_frac(const BhBuffers& b, int64_t nF, int leaf, double theta, int precision, double sigma,
                           const FaceData& fd, const void* ub, int kp, int k, double* nm, double* z, int64_t zstride,
                           hipStream_t s);

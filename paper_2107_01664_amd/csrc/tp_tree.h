@@ -28,8 +28,10 @@ size_t bct_sort_temp_bytes(int64_t n);
 // rec: the tree's node records (BhBuffers::rec).
 hipError_t launch_bct_expand(const double* rec, int64_t P, double chi, const uint64_t* cur, int64_t n, uint64_t* far,
                              uint64_t* near, uint64_t* next, unsigned long long* cnt, hipStream_t s);
+// The exact lists' segments (see BctSegs) into sg.count, sg.seg and sg.first.
+hipError_t launch_bct_long(int64_t nleaf, const int32_t* noff, const BctSegs& sg, hipStream_t s);
 hipError_t launch_bct_sort_csr(const uint64_t* keys, uint64_t* sorted, int64_t n, void* tmp, size_t tmp_bytes,
-                               int64_t rows, int32_t* off, int32_t* col, hipStream_t s);
+                               int64_t P, int64_t rows, int32_t* off, int32_t* col, hipStream_t s);
 
 // The walk itself: act(node, took) is called on every lane at every node the wave visits,
 // with took = 1 when the node is admissible for the lane, 2 when it is a leaf the lane sums

@@ -44,3 +44,19 @@ def test_tree_edges(tp, n, leaf, ab, prec):
     tE, tG = (1e-12, 1e-10) if prec == 2 else (1e-5, 1e-5)
     assert abs(E - E0) <= tE * E0
     assert np.linalg.norm(g.cpu().numpy() - g0) <= tG * np.linalg.norm(g0)
+
+
+@pytest.mark.parametrize("prec,tol", [(2, 1e-12), (3, 1e-5)])
+@pytest.mark.parametrize("leaf,k", [(1, 1), (1, 9), (2, 5), (3, 3)])
+def test_long_exact_lists(tp, leaf, k, prec, tol):
+    """Nothing is admissible: every leaf's exact list holds all leaves, 1,280 (three parts), 640 (two)
+    and 427 (one) of them, and the hierarchical product is the direct one."""
+    m = mg.add_noise(mg.icosphere(3), 0.002, 2)
+    u = mg.random_columns(m.nV, k, 3)
+    print(f"[lists] leaf {leaf} columns {k} precision {prec}", flush=True)
+    ref = O.fractional_apply(m.V, m.F, u)
+    p = tp.default_params(precision=prec, chi=1e-9, leaf_size=leaf)
+    with tp.Problem(torch.from_numpy(m.V).cuda(), torch.from_numpy(m.F).cuda(), p) as P:
+        y = P.fractional_apply(torch.from_numpy(u).cuda()).cpu().numpy()
+        assert P.bct_stats() == (0, (-(-m.nF // leaf)) ** 2)
+    assert np.linalg.norm(y - ref) <= tol * np.linalg.norm(ref)
