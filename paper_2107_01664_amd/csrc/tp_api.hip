@@ -583,12 +583,18 @@ tp_status validate_params(const tp_params* in, tp_params& out, double& sigma)
     return TP_OK;
 }
 
-tp_status check_flags(tp_problem* P)
+tp_status fetch_flags(tp_problem* P)
 {
     FetchJob J;
     J.flags = P->flags.p;
     J.hflags = P->hflags.p;
     TP_HIP(launch_fetch(&J, 1, P->stream));
+    return TP_OK;
+}
+
+tp_status check_flags(tp_problem* P, bool fetched = false)
+{
+    if (!fetched) TP_TRY(fetch_flags(P));
     TP_HIP(hipStreamSynchronize(P->stream));
     const int* h = P->hflags.p;
     if (h[0] | h[1] | h[2] | h[3]) TP_HIP(hipMemsetAsync(P->flags.p, 0, sizeof(int) * kNumFlags, P->stream));
@@ -631,12 +637,25 @@ tp_status alloc_faces(tp_problem* P)
     return TP_OK;
 }
 
+FaceGeomJob face_geom_job(const tp_problem* P, const double* V)
+{
+    FaceGeomJob J;
+    J.V = V; J.nV = P->nV; J.F = P->F.p; J.nF = P->nF; J.fd = P->fd; J.flags = P->flags.p;
+    return J;
+}
+
 // Face quantities at vertices Vsrc (defaults to the problem's vertices).
-tp_status geometry(tp_problem* P, const double* Vsrc = nullptr)
+// With set_up the preconditioner's set-up for V is started beside it, and enqueued while the
+// device works on the faces (enqueueing it takes the host longer than the faces take).
+tp_status start_cotan(tp_problem* P);
+tp_status geometry(tp_problem* P, const double* Vsrc = nullptr, bool set_up = false)
 {
     const double* src = Vsrc ? Vsrc : P->V.p;
-    TP_HIP(launch_face_geom(src, P->nV, P->F.p, P->nF, P->fd, P->flags.p, P->stream));
-    TP_TRY(check_flags(P));
+    const FaceGeomJob J = face_geom_job(P, src);
+    TP_HIP(launch_face_geom(&J, 1, P->stream));
+    TP_TRY(fetch_flags(P));
+    if (set_up) TP_TRY(start_cotan(P));
+    TP_TRY(check_flags(P, true));
     P->geom_valid = (Vsrc == nullptr);
     P->fd_V = src;
     ++P->geom_ver;
@@ -1070,13 +1089,56 @@ DotJob dot_job(tp_problem* P, int q, int slot, const double* x, int ldx, const d
 
 // Area and six times the signed volume at Vsrc (the face data must describe Vsrc): their sums as
 // jobs of a launch_dots, from the q-th part of the problem's scratch on.
-tp_status area_volume_jobs(tp_problem* P, const double* Vsrc, int q, std::vector<DotJob>& dots)
+tp_status area_volume_jobs(tp_problem* P, const double* Vsrc, int q, std::vector<DotJob>& dots,
+                           std::vector<FaceVolumeJob>& vols)
 {
-    hipStream_t s = P->stream;
-    TP_TRY(P->vol6.ensure(P->nF, s));
-    TP_HIP(launch_face_volume(Vsrc, P->F.p, P->nF, P->vol6.p, s));
+    TP_TRY(P->vol6.ensure(P->nF, P->stream));
+    FaceVolumeJob J;
+    J.V = Vsrc; J.F = P->F.p; J.nF = P->nF; J.vol6 = P->vol6.p;
+    vols.push_back(J);
     dots.push_back(dot_job(P, q, kSlotArea, &P->dx.p[0].w, 4, nullptr, 0, P->nF, 1));
     dots.push_back(dot_job(P, q + 1, kSlotVol6, P->vol6.p, 1, nullptr, 0, P->nF, 1));
+    return TP_OK;
+}
+
+// x without its per-component means, as a job of launch_project_mean.
+MeanJob mean_job(const tp_problem* P, double* x, const int32_t* comp, const double* inv_count, int ncomp, double* scratch)
+{
+    MeanJob J;
+    J.x = x; J.comp = comp; J.inv_count = inv_count; J.scratch = scratch; J.n = P->nV; J.ncomp = ncomp;
+    J.arrived = reinterpret_cast<unsigned*>(P->dot_red.p + 4);   // (a word of the sums' scratch they leave alone)
+    return J;
+}
+
+tp_status project_batch(const Batch& B, double* const* x, int k)
+{
+    std::vector<MeanJob> jobs;
+    for (size_t m = 0; m < B.size(); ++m) {
+        tp_problem* P = B[m];
+        jobs.push_back(mean_job(P, x[m], P->comp.p, P->npins ? P->inv_count_pin.p : P->inv_count.p, P->ncomp, P->red.p));
+    }
+    TP_HIP(launch_project_mean(jobs.data(), (int)jobs.size(), k, B[0]->stream));
+    for (size_t m = 0; m < B.size(); ++m)
+        if (B[m]->npins) TP_HIP(launch_zero_pinned(x[m], k, k, B[m]->nV, B[m]->pin_mask.p, B[0]->stream));
+    return TP_OK;
+}
+
+// out = a x + sum_m c_m Y[., col_m .. + 2] on rows of three.
+AxpyJob axpy_job(int64_t n, const double* x, int ldx, double a, const double* Y, int ldy, int ncoef, const double* c,
+                 const int* col, double* out)
+{
+    AxpyJob J;
+    J.n = n; J.x = x; J.ldx = ldx; J.a = a; J.Y = Y; J.ldy = ldy; J.out = out; J.ncoef = ncoef;
+    for (int m = 0; m < ncoef; ++m) {
+        J.c[m] = c[m];
+        J.col[m] = col[m];
+    }
+    return J;
+}
+
+tp_status axpy_one(const AxpyJob& J, hipStream_t s)
+{
+    TP_HIP(launch_axpy_block3(&J, 1, s));
     return TP_OK;
 }
 
@@ -1718,6 +1780,13 @@ tp_status pcg_table_slot(tp_problem* O, int n, void** dev, void** host, int* slo
     return TP_OK;
 }
 
+PermJob perm_job(const tp_problem* P, const double* src, double* dst)
+{
+    PermJob J;
+    J.n = P->nV; J.perm = P->pcg.perm; J.src = src; J.dst = dst;
+    return J;
+}
+
 // x[m] = C^+ b[m] for k columns (row stride k) of every problem; b[m] is overwritten with
 // its per-component mean-zero projection.  Iteration counts and final relative residuals
 // go to the pinned mirrors at offset which * kMaxCols (read them after a sync).
@@ -1731,12 +1800,10 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
         tp_problem* P = B[m];
         TP_TRY(ensure_cotan(P));
         TP_TRY(ensure_cg(P, k));
-        TP_HIP(launch_project_mean(b[m], k, k, P->nV, P->comp.p, P->npins ? P->inv_count_pin.p : P->inv_count.p,
-                                   P->ncomp, P->red.p, s));
-        if (P->npins) TP_HIP(launch_zero_pinned(b[m], k, k, P->nV, P->pin_mask.p, s));
         if (P->have_pcg && P->pcg_ml) ml.push_back(m);
         else (P->have_pcg ? pc : plain).push_back(m);
     }
+    TP_TRY(project_batch(B, b, k));
     // solves of many blocks, one problem at a time
     for (size_t m : ml) {
         tp_problem* P = B[m];
@@ -1746,10 +1813,11 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
         w.state = P->ml_state.p; w.state_host = P->ml_state_host.p; w.flags = P->flags.p;
         for (int c0 = 0; c0 < k; c0 += kMaxGroupCols) {
             const int kc = std::min(kMaxGroupCols, k - c0);
-            TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, b[m], P->pcg_bp.p, true, s));
+            const PermJob in = perm_job(P, b[m], P->pcg_bp.p), out = perm_job(P, P->pcg_xp.p, x[m]);
+            TP_HIP(launch_permute_rows(&in, 1, kc, k, c0, true, s));
             TP_HIP(launch_pcg_ml(P->pcg, P->pcg_bp.p, P->pcg_xp.p, kc, P->prm.cg_rtol, P->prm.cg_maxiter, w,
                                  P->cg_iters.p + res0 + c0, P->cg_relres.p + res0 + c0, s));
-            TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, P->pcg_xp.p, x[m], false, s));
+            TP_HIP(launch_permute_rows(&out, 1, kc, k, c0, false, s));
         }
     }
     if (!pc.empty()) {
@@ -1765,17 +1833,18 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
         std::vector<PcgItem> items(pc.size());
         for (int c0 = 0; c0 < k; c0 += kMaxGroupCols) {
             const int kc = std::min(kMaxGroupCols, k - c0);
+            std::vector<PermJob> in, out;
             for (size_t q = 0; q < pc.size(); ++q) {
                 tp_problem* P = B[pc[q]];
-                TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, b[pc[q]], P->pcg_bp.p, true, s));
+                in.push_back(perm_job(P, b[pc[q]], P->pcg_bp.p));
+                out.push_back(perm_job(P, P->pcg_xp.p, x[pc[q]]));
                 PcgItem& it = items[q];
                 it.ps = &P->pcg;
                 it.b = P->pcg_bp.p;
                 it.x = P->pcg_xp.p;
                 // warm start: x[m] still holds this solve's solution of the last step
                 it.warm = warm && P->warm_now ? 1 : 0;
-                if (it.warm)
-                    TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, x[pc[q]], P->pcg_xp.p, true, s));
+                if (it.warm) in.push_back(perm_job(P, x[pc[q]], P->pcg_xp.p));
                 it.w.U = P->pcg_U.p; it.w.G = P->pcg_G.p; it.w.X = P->pcg_X.p;
                 it.w.flags = P->flags.p;
                 it.w.iters = P->cg_iters.p + res0 + c0;
@@ -1783,16 +1852,14 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
                 it.rtol = P->prm.cg_rtol;
                 it.maxiter = P->prm.cg_maxiter;
             }
+            TP_HIP(launch_permute_rows(in.data(), (int)in.size(), kc, k, c0, true, s));
             void *tdev = nullptr, *thost = nullptr;
             int slot = 0;
             TP_TRY(pcg_table_slot(B[0], (int)items.size(), &tdev, &thost, &slot));
             TP_HIP(launch_pcg_batch(items.data(), (int)items.size(), kc, tdev, thost, s));
             TP_HIP(hipEventRecord(B[0]->tab.ev[slot], s));
             B[0]->tab.used[slot] = true;
-            for (size_t q = 0; q < pc.size(); ++q) {
-                tp_problem* P = B[pc[q]];
-                TP_HIP(launch_permute_rows(P->nV, kc, P->pcg.perm, k, c0, P->pcg_xp.p, x[pc[q]], false, s));
-            }
+            TP_HIP(launch_permute_rows(out.data(), (int)out.size(), kc, k, c0, false, s));
         }
     }
     for (size_t m : plain) {
@@ -1803,15 +1870,9 @@ tp_status enqueue_cg(const Batch& B, double* const* b, double* const* x, int k, 
         TP_HIP(launch_cg(P->nV, P->ell_col.p, P->ell_val.p, P->ell_w, b[m], x[m], k, P->prm.cg_rtol,
                          P->prm.cg_maxiter, w, s));
     }
-    for (size_t m = 0; m < B.size(); ++m) {
-        tp_problem* P = B[m];
-        TP_HIP(launch_project_mean(x[m], k, k, P->nV, P->comp.p, P->npins ? P->inv_count_pin.p : P->inv_count.p,
-                                   P->ncomp, P->red.p, s));
-        // the pinned rows are exactly zero (the coarse correction of the preconditioner
-        // leaves rounding-level values there)
-        if (P->npins) TP_HIP(launch_zero_pinned(x[m], k, k, P->nV, P->pin_mask.p, s));
-    }
-    return TP_OK;
+    // (the pinned rows are exactly zero: the coarse correction of the preconditioner leaves
+    // rounding-level values there)
+    return project_batch(B, x, k);
 }
 
 // Largest iteration count and relative residual of solve `which` (after a sync).
@@ -2109,7 +2170,8 @@ tp_status run_sobolev_solve(tp_problem* P, const double* b, int k, double rtol, 
         TP_TRY(P->gm_smw.ensure(n3, s));
         TP_TRY(P->red.ensure(std::max(reduce_scratch_doubles(16), project_scratch_doubles(3, P->ncomp)), s));
         TP_HIP(hipMemcpyAsync(P->gm_sv.p, P->V.p, n3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-        TP_HIP(launch_project_mean(P->gm_sv.p, 3, 3, n, P->comp.p, P->inv_count.p, P->ncomp, P->red.p, s));
+        const MeanJob mj = mean_job(P, P->gm_sv.p, P->comp.p, P->inv_count.p, P->ncomp, P->red.p);
+        TP_HIP(launch_project_mean(&mj, 1, 3, s));
         TP_TRY(run_sobolev(P, P->gm_sv.p, 3, 3, P->gm_sw.p, 3));
         tp_solve_report prep;
         TP_TRY(run_precond(P, P->gm_sw.p, 3, P->gm_smw.p, &prep));
@@ -2131,7 +2193,8 @@ tp_status run_sobolev_solve(tp_problem* P, const double* b, int k, double rtol, 
     const double* pinv = coarse ? P->gm_one.p : P->inv_count.p;
     const int pnc = coarse ? 1 : nc;
     auto project = [&](double* v) -> tp_status {
-        TP_HIP(launch_project_mean(v, k, k, n, plab, pinv, pnc, P->gm_red.p, s));
+        const MeanJob mj = mean_job(P, v, plab, pinv, pnc, P->gm_red.p);
+        TP_HIP(launch_project_mean(&mj, 1, k, s));
         return TP_OK;
     };
     // Z += Q G^+ Q^T V (the coarse term), columnwise
@@ -2418,7 +2481,9 @@ tp_status ensure_initial_measures(tp_problem* P)
     if (P->mean_edge > 0) return TP_OK;
     TP_TRY(ensure_geometry(P));
     std::vector<DotJob> dots;
-    TP_TRY(area_volume_jobs(P, P->V.p, 0, dots));   // the face data describes V
+    std::vector<FaceVolumeJob> vols;
+    TP_TRY(area_volume_jobs(P, P->V.p, 0, dots, vols));   // the face data describes V
+    TP_HIP(launch_face_volume(vols.data(), 1, P->stream));
     TP_TRY(P->edge.ensure(P->nF, P->stream));
     hipLaunchKernelGGL(k_face_edges, dim3((unsigned)((P->nF + 255) / 256)), dim3(256), 0, P->stream,
                        P->V.p, P->F.p, P->nF, P->edge.p);
@@ -2520,7 +2585,9 @@ struct StepState {
 tp_status enqueue_area_volume(tp_problem* P, const double* Vsrc)
 {
     std::vector<DotJob> dots;
-    TP_TRY(area_volume_jobs(P, Vsrc, 0, dots));
+    std::vector<FaceVolumeJob> vols;
+    TP_TRY(area_volume_jobs(P, Vsrc, 0, dots, vols));
+    TP_HIP(launch_face_volume(vols.data(), 1, P->stream));
     TP_HIP(launch_dots(dots.data(), (int)dots.size(), P->stream));
     return TP_OK;
 }
@@ -2582,7 +2649,7 @@ tp_status step_group(std::vector<StepState*>& G)
                 S->pen0 += w * P->hs.p[kSlotObs];
                 TP_HIP(launch_grad_gather(P->V.p, P->F.p, n, P->nF, P->vf_off.p, P->vf_idx.p, P->obs_g.p, P->nF,
                                           P->Vt.p, s));
-                TP_HIP(launch_axpy_block3(n, P->gbuf.p, 3, 1.0, P->Vt.p, 3, 1, &w, &c0, P->gbuf.p, 3, s));
+                TP_TRY(axpy_one(axpy_job(n, P->gbuf.p, 3, 1.0, P->Vt.p, 3, 1, &w, &c0, P->gbuf.p), s));
             }
             if (S->implicit()) {   // the implicit potentials (weights applied in the kernel)
                 const double one = 1.0;
@@ -2590,7 +2657,7 @@ tp_status step_group(std::vector<StepState*>& G)
                 S->pen0 += P->hs.p[kSlotImp];
                 TP_HIP(launch_grad_gather(P->V.p, P->F.p, n, P->nF, P->vf_off.p, P->vf_idx.p, P->imp_g.p, P->nF,
                                           P->Vt.p, s));
-                TP_HIP(launch_axpy_block3(n, P->gbuf.p, 3, 1.0, P->Vt.p, 3, 1, &one, &c0, P->gbuf.p, 3, s));
+                TP_TRY(axpy_one(axpy_job(n, P->gbuf.p, 3, 1.0, P->Vt.p, 3, 1, &one, &c0, P->gbuf.p), s));
             }
             if (!S->penalized()) continue;
             const double area = P->hs.p[kSlotArea], vol = P->hs.p[kSlotVol6] / 6.0;
@@ -2600,12 +2667,12 @@ tp_status step_group(std::vector<StepState*>& G)
                 const double cA = 2.0 * S->o.area_penalty * (area / S->A0 - 1.0) / S->A0;
                 TP_TRY(ensure_cotan(P));
                 TP_HIP(launch_spmm(n, P->lap_off.p, P->lap_col.p, P->lap_val.p, P->V.p, 3, 3, P->Y.p, 3, s));
-                TP_HIP(launch_axpy_block3(n, P->gbuf.p, 3, 1.0, P->Y.p, 3, 1, &cA, &c0, P->gbuf.p, 3, s));
+                TP_TRY(axpy_one(axpy_job(n, P->gbuf.p, 3, 1.0, P->Y.p, 3, 1, &cA, &c0, P->gbuf.p), s));
             }
             if (S->o.volume_penalty > 0.0) {
                 const double cV = 2.0 * S->o.volume_penalty * (vol / S->V0 - 1.0) / S->V0;
                 TP_HIP(launch_volume_gradient(P->V.p, P->F.p, n, P->vf_off.p, P->vf_idx.p, P->Vt.p, 3, 0, s));
-                TP_HIP(launch_axpy_block3(n, P->gbuf.p, 3, 1.0, P->Vt.p, 3, 1, &cV, &c0, P->gbuf.p, 3, s));
+                TP_TRY(axpy_one(axpy_job(n, P->gbuf.p, 3, 1.0, P->Vt.p, 3, 1, &cV, &c0, P->gbuf.p), s));
             }
         }
     }
@@ -2716,12 +2783,18 @@ tp_status step_group(std::vector<StepState*>& G)
         L.push_back(S);
     }
     // 5. direction x = -(y_g - Y S^{-1} J y_g), slope g.x, default step, constraint values
+    std::vector<AxpyJob> axpys;
+    std::vector<FaceGeomJob> geoms;
+    std::vector<FaceVolumeJob> vols;
+    for (StepState* S : L) {
+        tp_problem* P = S->P;
+        const int cols[2] = {3, 6};
+        axpys.push_back(axpy_job(P->nV, P->Y.p, ncol, -1.0, P->Y.p, ncol, S->kc, S->mu, cols, P->dir.p));
+    }
+    TP_HIP(launch_axpy_block3(axpys.data(), (int)axpys.size(), s));
     for (StepState* S : L) {
         tp_problem* P = S->P;
         const int64_t n = P->nV;
-        const double cf[2] = {S->mu[0], S->mu[1]};
-        const int cols[2] = {3, 6};
-        TP_HIP(launch_axpy_block3(n, P->Y.p, ncol, -1.0, P->Y.p, ncol, S->kc, cf, cols, P->dir.p, 3, s));
         if (S->o.barycenter_motion) {
             // barycenter motions (Sec. 7.1.1): add back to the direction, per component, the
             // translation by minus the vertex-area-weighted mean of g (face data describes V)
@@ -2750,9 +2823,10 @@ tp_status step_group(std::vector<StepState*>& G)
         dots.push_back(dot_job(P, 1, kSlotGX, P->gbuf.p, 3, P->dir.p, 3, n, 3));
         dots.push_back(dot_job(P, 2, kSlotMax, P->dir.p, 3, nullptr, 0, n, 1));
         dots.back().kind = kDotMaxRow;
-        TP_TRY(area_volume_jobs(P, P->V.p, 3, dots));    // face data describes V
+        TP_TRY(area_volume_jobs(P, P->V.p, 3, dots, vols));    // face data describes V
     }
     if (!L.empty()) {
+        TP_HIP(launch_face_volume(vols.data(), (int)vols.size(), s));
         TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
         dots.clear();
         TP_TRY(sync_batch(B));
@@ -2784,12 +2858,18 @@ tp_status step_group(std::vector<StepState*>& G)
     std::vector<StepState*> accepted;
     while (!search.empty()) {
         Batch BS;
+        axpys.clear();
+        geoms.clear();
         for (StepState* S : search) {
             tp_problem* P = S->P;
-            const double cf = S->tau;
             const int c0 = 0;
-            TP_HIP(launch_axpy_block3(P->nV, P->V.p, 3, 1.0, P->dir.p, 3, 1, &cf, &c0, P->Vt.p, 3, s));
-            TP_HIP(launch_face_geom(P->Vt.p, P->nV, P->F.p, P->nF, P->fd, P->flags.p, s));
+            axpys.push_back(axpy_job(P->nV, P->V.p, 3, 1.0, P->dir.p, 3, 1, &S->tau, &c0, P->Vt.p));
+            geoms.push_back(face_geom_job(P, P->Vt.p));
+        }
+        TP_HIP(launch_axpy_block3(axpys.data(), (int)axpys.size(), s));
+        TP_HIP(launch_face_geom(geoms.data(), (int)geoms.size(), s));
+        for (StepState* S : search) {
+            tp_problem* P = S->P;
             P->fd_V = P->Vt.p;
             ++P->geom_ver;
             P->geom_valid = false;
@@ -2837,19 +2917,24 @@ tp_status step_group(std::vector<StepState*>& G)
 
     // 7. corrective projection h = -Y S^{-1} Phi(f + tau x) (face data describes f + tau x)
     Batch BA;
+    vols.clear();
     for (StepState* S : accepted) {
         S->R.tau = S->tau;
         S->R.backtracks = S->bt;
-        TP_TRY(area_volume_jobs(S->P, S->P->Vt.p, 0, dots));
+        TP_TRY(area_volume_jobs(S->P, S->P->Vt.p, 0, dots, vols));
         BA.push_back(S->P);
     }
     if (!BA.empty()) {
+        TP_HIP(launch_face_volume(vols.data(), (int)vols.size(), s));
         TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
         dots.clear();
         TP_TRY(sync_batch(BA));
     }
     Batch BF;
     std::vector<StepState*> fin;
+    axpys.clear();
+    geoms.clear();
+    vols.clear();
     for (StepState* S : accepted) {
         tp_problem* P = S->P;
         double phi[2] = {0, 0}, lam[2] = {0, 0};
@@ -2862,18 +2947,23 @@ tp_status step_group(std::vector<StepState*>& G)
         }
         const double cf[2] = {-lam[0], -lam[1]};
         const int cols[2] = {3, 6};
-        TP_HIP(launch_axpy_block3(P->nV, P->Vt.p, 3, 1.0, P->Y.p, ncol, S->kc, cf, cols, P->V.p, 3, s));
+        axpys.push_back(axpy_job(P->nV, P->Vt.p, 3, 1.0, P->Y.p, ncol, S->kc, cf, cols, P->V.p));
+        geoms.push_back(face_geom_job(P, P->V.p));
         if (S->dir_out)
             TP_HIP(hipMemcpyAsync(S->dir_out, P->dir.p, sizeof(double) * 3 * P->nV, hipMemcpyDeviceToDevice, s));
         P->cotan_valid = false;
-        TP_HIP(launch_face_geom(P->V.p, P->nV, P->F.p, P->nF, P->fd, P->flags.p, s));
         P->fd_V = P->V.p;
         ++P->geom_ver;
-        TP_TRY(area_volume_jobs(P, P->V.p, 0, dots));
-        if (S->obstacle()) TP_TRY(enqueue_obstacle(P));
-        if (S->implicit()) TP_TRY(enqueue_implicit(P));
+        TP_TRY(area_volume_jobs(P, P->V.p, 0, dots, vols));
         BF.push_back(P);
         fin.push_back(S);
+    }
+    TP_HIP(launch_axpy_block3(axpys.data(), (int)axpys.size(), s));
+    TP_HIP(launch_face_geom(geoms.data(), (int)geoms.size(), s));
+    TP_HIP(launch_face_volume(vols.data(), (int)vols.size(), s));
+    for (StepState* S : fin) {
+        if (S->obstacle()) TP_TRY(enqueue_obstacle(S->P));
+        if (S->implicit()) TP_TRY(enqueue_implicit(S->P));
     }
     if (!BF.empty()) TP_HIP(launch_dots(dots.data(), (int)dots.size(), s));
     TP_TRY(enqueue_energy(BF, kSlotE));
@@ -3222,8 +3312,7 @@ tp_status tp_problem_set_vertices(tp_problem* P, const double* V)
     // start the set-up for the new ones beside the work that comes first
     const bool solved = P->setup_used;
     P->setup_used = false;
-    if (solved) TP_TRY(start_cotan(P));
-    return geometry(P);
+    return geometry(P, nullptr, solved);
 }
 
 tp_status tp_problem_get_vertices(tp_problem* P, double* V_out)

@@ -82,8 +82,18 @@ struct PairPlan {
 // ------------------------------------------------------------------ kernels (launchers)
 
 // Face geometry from vertices and faces (FP64), written in FP32 hi/lo and FP64 forms.
-hipError_t launch_face_geom(const double* V, int64_t nV, const int32_t* F, int64_t nF,
-                            const FaceData& fd, int* flags, hipStream_t s);
+// Small per-vertex and per-face passes take the problems of a batch together: a job each, up to
+// kMaxVecJobs in one launch (a launch of its own for each of eight problems costs 8 x 5 to 10 us
+// where the pass itself takes 3).
+constexpr int kMaxVecJobs = 16;
+struct FaceGeomJob {
+    const double* V = nullptr;
+    const int32_t* F = nullptr;
+    int64_t nV = 0, nF = 0;
+    FaceData fd;
+    int* flags = nullptr;
+};
+hipError_t launch_face_geom(const FaceGeomJob* jobs, int njobs, hipStream_t s);
 // Face data from caller-given face quantities (X, N row-major nF x 3, a nF).
 hipError_t launch_face_from_quantities(const double* X, const double* N, const double* a,
                                        int64_t nF, const FaceData& fd, int* flags, hipStream_t s);
@@ -221,8 +231,13 @@ hipError_t launch_ut_gather(const int32_t* F, int64_t nV, const int32_t* vf_off,
 hipError_t launch_volume_gradient(const double* V, const int32_t* F, int64_t nV,
                                   const int32_t* vf_off, const int32_t* vf_idx, double* out,
                                   int ldo, int c0, hipStream_t s);
-hipError_t launch_face_volume(const double* V, const int32_t* F, int64_t nF, double* vol6,
-                              hipStream_t s);
+struct FaceVolumeJob {
+    const double* V = nullptr;
+    const int32_t* F = nullptr;
+    int64_t nF = 0;
+    double* vol6 = nullptr;
+};
+hipError_t launch_face_volume(const FaceVolumeJob* jobs, int njobs, hipStream_t s);
 hipError_t launch_spmm(int64_t n, const int32_t* off, const int32_t* col, const double* val,
                        const double* x, int ldx, int k, double* y, int ldy, hipStream_t s);
 
@@ -269,9 +284,16 @@ struct FetchJob {
 };
 hipError_t launch_fetch(const FetchJob* jobs, int njobs, hipStream_t s);
 // Per-component means of k columns, then x -= mean[comp].
-hipError_t launch_project_mean(double* x, int ldx, int k, int64_t n, const int32_t* comp,
-                               const double* inv_count, int ncomp, double* scratch,
-                               hipStream_t s);
+struct MeanJob {
+    double* x = nullptr;              // [n][k]
+    const int32_t* comp = nullptr;
+    const double* inv_count = nullptr;
+    double* scratch = nullptr;        // project_scratch_doubles(k, ncomp)
+    unsigned* arrived = nullptr;      // workgroups done; zero between launches
+    int64_t n = 0;
+    int ncomp = 1;
+};
+hipError_t launch_project_mean(const MeanJob* jobs, int njobs, int k, hipStream_t s);
 size_t project_scratch_doubles(int k, int ncomp);
 // Vertex pins: the solver's copy of the cotan values with the pinned rows and columns
 // replaced by the identity; zeroing of the pinned rows of k columns.
@@ -280,9 +302,16 @@ hipError_t launch_pin_values(int64_t n, const int32_t* off, const int32_t* col, 
 hipError_t launch_zero_pinned(double* x, int ldx, int k, int64_t n, const int8_t* pinned, hipStream_t s);
 
 // y = a*x + b*y style updates on n x 3 blocks: out = x + sum_m coef[m] * Y[:, cols_m].
-hipError_t launch_axpy_block3(int64_t n, const double* x, int ldx, double a,
-                              const double* Y, int ldy, int ncoef, const double* coef_host,
-                              const int* cols_host, double* out, int ldo, hipStream_t s);
+struct AxpyJob {
+    int64_t n = 0;
+    const double* x = nullptr;
+    const double* Y = nullptr;
+    double* out = nullptr;
+    double a = 0.0, c[2] = {0.0, 0.0};
+    int col[2] = {0, 0};
+    int ldx = 3, ldy = 3, ldo = 3, ncoef = 1;
+};
+hipError_t launch_axpy_block3(const AxpyJob* jobs, int njobs, hipStream_t s);
 hipError_t launch_copy_cols(int64_t n, const double* x, int ldx, int k, double* y, int ldy,
                             hipStream_t s);
 

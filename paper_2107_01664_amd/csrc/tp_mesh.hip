@@ -113,20 +113,45 @@ __device__ __forceinline__ void face_geom(const double* __restrict__ V, int64_t 
 
 // One face per thread; fd.cap is a multiple of the tile.  The tile boxes ride along: their own
 // launch took as long as this one (3.3 us each at 5,000 faces, bound by the launch).
-__global__ __launch_bounds__(256) void k_face_geom(const double* __restrict__ V, int64_t nV,
-                                                   const int32_t* __restrict__ F, int64_t nF, FaceData fd,
-                                                   int* __restrict__ flags)
+template <class J>
+struct VecJobs {
+    J j[kMaxVecJobs];
+};
+
+// launch(table, jobs in it, largest value of count(job)) for the jobs, kMaxVecJobs at a time
+template <class J, class Count, class Launch>
+hipError_t for_vec_jobs(const J* jobs, int njobs, Count&& count, Launch&& launch)
 {
+    for (int m0 = 0; m0 < njobs; m0 += kMaxVecJobs) {
+        VecJobs<J> jb;
+        const int n = std::min(kMaxVecJobs, njobs - m0);
+        int64_t most = 1;
+        for (int q = 0; q < n; ++q) {
+            jb.j[q] = jobs[m0 + q];
+            most = std::max<int64_t>(most, count(jb.j[q]));
+        }
+        launch(jb, n, most);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+__global__ __launch_bounds__(256) void k_face_geom(VecJobs<FaceGeomJob> jb)
+{
+    const FaceGeomJob& J = jb.j[blockIdx.y];
+    const FaceData& fd = J.fd;
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < fd.cap) face_geom(V, nV, F, nF, fd, flags, s);
+    if (s < fd.cap) face_geom(J.V, J.nV, J.F, J.nF, fd, J.flags, s);
     if (fd.tbox) write_tile_box(fd, s, s < fd.cap ? fd.fx[s] : make_float4(0.f, 0.f, 0.f, 0.f));
 }
 
-hipError_t launch_face_geom(const double* V, int64_t nV, const int32_t* F, int64_t nF,
-                            const FaceData& fd, int* flags, hipStream_t s)
+hipError_t launch_face_geom(const FaceGeomJob* jobs, int njobs, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_face_geom, dim3(nblocks(fd.cap)), dim3(256), 0, s, V, nV, F, nF, fd, flags);
-    return hipGetLastError();
+    return for_vec_jobs(jobs, njobs, [](const FaceGeomJob& J) { return J.fd.cap; },
+                        [&](const VecJobs<FaceGeomJob>& jb, int n, int64_t cap) {
+                            hipLaunchKernelGGL(k_face_geom, dim3(nblocks(cap), n), dim3(256), 0, s, jb);
+                        });
 }
 
 __device__ __forceinline__ void face_from_quantities(const double* __restrict__ X, const double* __restrict__ N,
@@ -560,23 +585,24 @@ hipError_t launch_volume_gradient(const double* V, const int32_t* F, int64_t nV,
     return hipGetLastError();
 }
 
-__global__ void k_face_volume(const double* __restrict__ V, const int32_t* __restrict__ F,
-                              int64_t nF, double* __restrict__ vol6)
+__global__ void k_face_volume(VecJobs<FaceVolumeJob> jb)
 {
+    const FaceVolumeJob& J = jb.j[blockIdx.y];
     const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nF) return;
-    const double* a = V + 3 * (int64_t)F[3 * f];
-    const double* b = V + 3 * (int64_t)F[3 * f + 1];
-    const double* c = V + 3 * (int64_t)F[3 * f + 2];
-    vol6[f] = a[0] * (b[1] * c[2] - b[2] * c[1]) + a[1] * (b[2] * c[0] - b[0] * c[2]) +
-              a[2] * (b[0] * c[1] - b[1] * c[0]);
+    if (f >= J.nF) return;
+    const double* a = J.V + 3 * (int64_t)J.F[3 * f];
+    const double* b = J.V + 3 * (int64_t)J.F[3 * f + 1];
+    const double* c = J.V + 3 * (int64_t)J.F[3 * f + 2];
+    J.vol6[f] = a[0] * (b[1] * c[2] - b[2] * c[1]) + a[1] * (b[2] * c[0] - b[0] * c[2]) +
+                a[2] * (b[0] * c[1] - b[1] * c[0]);
 }
 
-hipError_t launch_face_volume(const double* V, const int32_t* F, int64_t nF, double* vol6,
-                              hipStream_t s)
+hipError_t launch_face_volume(const FaceVolumeJob* jobs, int njobs, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_face_volume, dim3(nblocks(nF)), dim3(256), 0, s, V, F, nF, vol6);
-    return hipGetLastError();
+    return for_vec_jobs(jobs, njobs, [](const FaceVolumeJob& J) { return J.nF; },
+                        [&](const VecJobs<FaceVolumeJob>& jb, int n, int64_t nF) {
+                            hipLaunchKernelGGL(k_face_volume, dim3(nblocks(nF), n), dim3(256), 0, s, jb);
+                        });
 }
 
 // ------------------------------------------------------------------ sparse times dense
@@ -795,90 +821,90 @@ size_t project_scratch_doubles(int k, int ncomp)
     return (size_t)kRedBlocks * (size_t)ncomp * (size_t)k + (size_t)ncomp * (size_t)k + 64;
 }
 
-__global__ __launch_bounds__(256) void k_comp_partial(const double* __restrict__ x, int ldx, int k,
-                                                      int64_t n, const int32_t* __restrict__ comp,
-                                                      int ncomp, double* __restrict__ partial)
+// Per-component means of k columns: chunk sums as in k_dots (a wave per chunk, the terms added in
+// the order of a workgroup of 256 threads and its tree), the last workgroup of a job forms the
+// means; k_sub_mean takes them off.  Three launches per problem, the middle one a single workgroup,
+// and barriers in every tree took 23 us a problem; two launches for all problems take 12.
+__global__ __launch_bounds__(256) void k_comp_means(VecJobs<MeanJob> jb, int k)
 {
-    __shared__ double sh[256];
-    const int64_t chunk = (n + kRedBlocks - 1) / kRedBlocks;
-    const int64_t b = (int64_t)blockIdx.x * chunk, e = min(n, b + chunk);
-    for (int cp = 0; cp < ncomp; ++cp)
+    const MeanJob& J = jb.j[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = J.ncomp * k;
+    const int64_t q = (int64_t)blockIdx.x * 4 + wave;   // chunk
+    const int64_t chunk = (J.n + kRedBlocks - 1) / kRedBlocks;
+    const int64_t b = q * chunk, e = min(J.n, b + chunk);
+    for (int cp = 0; cp < J.ncomp; ++cp)
         for (int c = 0; c < k; ++c) {
-            double acc = 0.0;
-            for (int64_t i = b + threadIdx.x; i < e; i += 256)
-                if (comp[i] == cp) acc += x[i * ldx + c];
-            const double s = block_sum(acc, sh);
-            if (threadIdx.x == 0) partial[((int64_t)blockIdx.x * ncomp + cp) * k + c] = s;
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int64_t i0 = b + lane; i0 < e; i0 += 256)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t i = i0 + 64 * u;
+                    if (i < e && J.comp[i] == cp) v[u] += J.x[i * k + c];
+                }
+            const double s = chunk_tree(v[0], v[1], v[2], v[3], false);
+            if (lane == 0)
+                __hip_atomic_store(J.scratch + q * nv + cp * k + c, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // the partial sums have arrived
+    __syncthreads();
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        last = __hip_atomic_fetch_add(J.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+        if (last) __hip_atomic_store(J.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last) return;
+    for (int m = wave; m < nv; m += 4) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = __hip_atomic_load(J.scratch + (int64_t)(lane + 64 * u) * nv + m, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+        const double s = chunk_tree(v[0], v[1], v[2], v[3], false);
+        if (lane == 0) J.scratch[(int64_t)kRedBlocks * nv + m] = s * J.inv_count[m / k];
+    }
 }
 
-__global__ __launch_bounds__(256) void k_comp_final(const double* __restrict__ partial, int k,
-                                                    int ncomp, const double* __restrict__ inv_count,
-                                                    double* __restrict__ mean)
+__global__ void k_sub_mean(VecJobs<MeanJob> jb, int k)
 {
-    __shared__ double sh[256];
-    for (int cp = 0; cp < ncomp; ++cp)
-        for (int c = 0; c < k; ++c) {
-            const double s = block_sum(partial[((int64_t)threadIdx.x * ncomp + cp) * k + c], sh);
-            if (threadIdx.x == 0) mean[cp * k + c] = s * inv_count[cp];
-        }
-}
-
-__global__ void k_sub_mean(double* __restrict__ x, int ldx, int k, int64_t n,
-                           const int32_t* __restrict__ comp, const double* __restrict__ mean)
-{
+    const MeanJob& J = jb.j[blockIdx.y];
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * k) return;
+    if (t >= J.n * k) return;
     const int64_t i = t / k;
     const int c = (int)(t - i * k);
-    x[i * ldx + c] -= mean[comp[i] * k + c];
+    J.x[t] -= J.scratch[(int64_t)kRedBlocks * J.ncomp * k + J.comp[i] * k + c];
 }
 
-hipError_t launch_project_mean(double* x, int ldx, int k, int64_t n, const int32_t* comp,
-                               const double* inv_count, int ncomp, double* scratch,
-                               hipStream_t s)
+hipError_t launch_project_mean(const MeanJob* jobs, int njobs, int k, hipStream_t s)
 {
-    double* partial = scratch;
-    double* mean = scratch + (size_t)kRedBlocks * ncomp * k;
-    hipLaunchKernelGGL(k_comp_partial, dim3(kRedBlocks), dim3(256), 0, s, x, ldx, k, n, comp, ncomp, partial);
-    hipLaunchKernelGGL(k_comp_final, dim3(1), dim3(256), 0, s, partial, k, ncomp, inv_count, mean);
-    hipLaunchKernelGGL(k_sub_mean, dim3(nblocks(n * k)), dim3(256), 0, s, x, ldx, k, n, comp, mean);
-    return hipGetLastError();
+    return for_vec_jobs(jobs, njobs, [](const MeanJob& J) { return J.n; },
+                        [&](const VecJobs<MeanJob>& jb, int n, int64_t most) {
+                            hipLaunchKernelGGL(k_comp_means, dim3(kRedBlocks / 4, n), dim3(256), 0, s, jb, k);
+                            hipLaunchKernelGGL(k_sub_mean, dim3(nblocks(most * k), n), dim3(256), 0, s, jb, k);
+                        });
 }
 
 // ------------------------------------------------------------------ small dense updates
 
-struct Coef8 {
-    double c[8];
-    int col[8];
-};
-
-// out[i, 0..2] = a * x[i, 0..2] + sum_m c_m Y[i, col_m + 0..2]
-__global__ void k_axpy_block3(int64_t n, const double* __restrict__ x, int ldx, double a,
-                              const double* __restrict__ Y, int ldy, int ncoef, Coef8 cf,
-                              double* __restrict__ out, int ldo)
+// out[i, 0..2] = a x[i, 0..2] + sum_m c_m Y[i, col_m + 0..2]
+__global__ void k_axpy_block3(VecJobs<AxpyJob> jb)
 {
+    const AxpyJob& J = jb.j[blockIdx.y];
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * 3) return;
+    if (t >= J.n * 3) return;
     const int64_t i = t / 3;
     const int c = (int)(t - i * 3);
-    double v = x ? a * x[i * ldx + c] : 0.0;
-    for (int m = 0; m < ncoef; ++m) v += cf.c[m] * Y[i * ldy + cf.col[m] + c];
-    out[i * ldo + c] = v;
+    double v = J.x ? J.a * J.x[i * J.ldx + c] : 0.0;
+    for (int m = 0; m < J.ncoef; ++m) v += J.c[m] * J.Y[i * J.ldy + J.col[m] + c];
+    J.out[i * J.ldo + c] = v;
 }
 
-hipError_t launch_axpy_block3(int64_t n, const double* x, int ldx, double a,
-                              const double* Y, int ldy, int ncoef, const double* coef_host,
-                              const int* cols_host, double* out, int ldo, hipStream_t s)
+hipError_t launch_axpy_block3(const AxpyJob* jobs, int njobs, hipStream_t s)
 {
-    if (ncoef > 8) return hipErrorInvalidValue;
-    Coef8 cf;
-    for (int m = 0; m < 8; ++m) {
-        cf.c[m] = m < ncoef ? coef_host[m] : 0.0;
-        cf.col[m] = m < ncoef ? cols_host[m] : 0;
-    }
-    hipLaunchKernelGGL(k_axpy_block3, dim3(nblocks(n * 3)), dim3(256), 0, s, n, x, ldx, a, Y, ldy, ncoef, cf, out, ldo);
-    return hipGetLastError();
+    return for_vec_jobs(jobs, njobs, [](const AxpyJob& J) { return J.n; },
+                        [&](const VecJobs<AxpyJob>& jb, int n, int64_t most) {
+                            hipLaunchKernelGGL(k_axpy_block3, dim3(nblocks(most * 3), n), dim3(256), 0, s, jb);
+                        });
 }
 
 __global__ void k_copy_cols(int64_t n, const double* __restrict__ x, int ldx, int k,

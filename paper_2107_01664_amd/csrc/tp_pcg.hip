@@ -498,23 +498,21 @@ __global__ __launch_bounds__(kInvThreads) void k_inverses(int nb, int64_t n, int
     else coarse_inverse(nc, acomp, esum, G);
 }
 
-__global__ void k_fill_zero(double* __restrict__ p, int64_t n)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) p[t] = 0.0;
-}
-
 // forward: dst[i][c] = src[perm[i]][c0 + c] (dst in block order, row stride k);
 // backward: dst[perm[i]][c0 + c] = src[i][c].  ld is the row stride of the vertex-order side.
-__global__ void k_permute_rows(int64_t n, int k, const int32_t* __restrict__ perm, int ld, int c0,
-                               const double* __restrict__ src, double* __restrict__ dst, int forward)
+struct PermJobs {
+    PermJob j[kMaxVecJobs];
+};
+
+__global__ void k_permute_rows(PermJobs jb, int k, int ld, int c0, int forward)
 {
+    const PermJob& J = jb.j[blockIdx.y];
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * k) return;
+    if (t >= J.n * k) return;
     const int64_t i = t / k;
     const int c = (int)(t - i * k);
-    if (forward) dst[i * k + c] = src[(int64_t)perm[i] * ld + c0 + c];
-    else dst[(int64_t)perm[i] * ld + c0 + c] = src[i * k + c];
+    if (forward) J.dst[i * k + c] = J.src[(int64_t)J.perm[i] * ld + c0 + c];
+    else J.dst[(int64_t)J.perm[i] * ld + c0 + c] = J.src[i * k + c];
 }
 
 // Sum of n values p[0], p[stride], ... in a fixed order: four interleaved partial sums, so
@@ -1393,9 +1391,6 @@ hipError_t launch_pcg_setup(const PcgSetup& ps, const double* V, const int32_t* 
     hipLaunchKernelGGL(k_row_coarse, dim3((unsigned)((ps.n + 255) / 256)), dim3(256), 0, s, ps.n, ps.ell_w, ps.pcol,
                        ps.pval, ps.eslot, ps.phi, ps.rw);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int64_t nn = (int64_t)ps.nc * ps.nc;
-    hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, ps.C0inv, nn);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     const size_t asm_smem = sizeof(double) * kAsmGroups * (size_t)ps.na * 16;
     e = hipFuncSetAttribute((const void*)k_coarse_assemble, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(sizeof(double) * kAsmGroups * (kCoarseMax / 4) * 16));
@@ -1411,12 +1406,22 @@ hipError_t launch_pcg_setup(const PcgSetup& ps, const double* V, const int32_t* 
     return hipGetLastError();
 }
 
-hipError_t launch_permute_rows(int64_t n, int k, const int32_t* perm, int ld, int c0, const double* src,
-                               double* dst, bool forward, hipStream_t s)
+hipError_t launch_permute_rows(const PermJob* jobs, int njobs, int k, int ld, int c0, bool forward, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_permute_rows, dim3((unsigned)((n * k + 255) / 256)), dim3(256), 0, s, n, k, perm,
-                       ld, c0, src, dst, forward ? 1 : 0);
-    return hipGetLastError();
+    for (int m0 = 0; m0 < njobs; m0 += kMaxVecJobs) {
+        PermJobs jb;
+        const int n = std::min(kMaxVecJobs, njobs - m0);
+        int64_t most = 1;
+        for (int q = 0; q < n; ++q) {
+            jb.j[q] = jobs[m0 + q];
+            most = std::max(most, jb.j[q].n);
+        }
+        hipLaunchKernelGGL(k_permute_rows, dim3((unsigned)((most * k + 255) / 256), n), dim3(256), 0, s, jb, k, ld, c0,
+                           forward ? 1 : 0);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 namespace {

@@ -87,8 +87,13 @@ int pcg_max_block_aggregates();          // aggregates touching one block, at mo
 // coarse matrix and its inverse.  V: vertices (n x 3, caller order).
 hipError_t launch_pcg_setup(const PcgSetup& ps, const double* V, const int32_t* lap_off, const double* lap_val,
                             hipStream_t s);
-hipError_t launch_permute_rows(int64_t n, int k, const int32_t* perm, int ld, int c0, const double* src,
-                               double* dst, bool forward, hipStream_t s);
+struct PermJob {
+    int64_t n = 0;
+    const int32_t* perm = nullptr;
+    const double* src = nullptr;
+    double* dst = nullptr;
+};
+hipError_t launch_permute_rows(const PermJob* jobs, int njobs, int k, int ld, int c0, bool forward, hipStream_t s);
 // One system of a multi-problem solve: b, x in block order, [n][k].
 struct PcgItem {
     const PcgSetup* ps = nullptr;

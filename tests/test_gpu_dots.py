@@ -54,3 +54,20 @@ def test_many_jobs(tp):
             assert (a.E, a.slope, a.tau, a.E_new) == (r.E, r.slope, r.tau, r.E_new)
             assert torch.equal(Q.vertices(), P.vertices())
         P.close()
+
+
+def test_more_problems_than_a_launch(tp):
+    """Seventeen problems of unequal sizes, some of two components: one more than the vertex and
+    face passes take in a launch.  Each gives the bits of its own step."""
+    meshes = [mg.linked_tori(8 + q, 8, 1.0, 0.25, 1.0) if q % 3 == 0 else mg.add_noise(mg.torus(10 + q, 9, 1.0, 0.3), 1e-3, q)
+              for q in range(17)]
+    probs = [tp.Problem(torch.from_numpy(m.V).cuda(), torch.from_numpy(m.F).cuda()) for m in meshes]
+    sts, reps = tp.batch_step(probs)
+    assert sts == [0] * 17
+    for q, (m, r, P) in enumerate(zip(meshes, reps, probs)):
+        print(f"[batch] problem {q} faces {m.nF}", flush=True)
+        with tp.Problem(torch.from_numpy(m.V).cuda(), torch.from_numpy(m.F).cuda()) as Q:
+            a = Q.step()
+            assert (a.E, a.slope, a.tau, a.E_new) == (r.E, r.slope, r.tau, r.E_new)
+            assert torch.equal(Q.vertices(), P.vertices())
+        P.close()
