@@ -115,7 +115,8 @@ typedef struct {
                             symmetric at any size; symmetric means every unordered pair
                             evaluated once for both rows (the kernel values K(S,T) and
                             K(T,S), |d|^-(2 sigma + 2) and |d|^-2s come from the same d);
-                            E and E + dE stay row by row in precisions 4 and 5            */
+                            E and E + dE stay row by row in precisions 4 and 5.  E + dE in
+                            FP64 likewise: -1 symmetric from 10,240 to about 70,000 faces   */
     int    sym_band;      /* the symmetric kernels take the rows of 256-face blocks in bands,
                             one launch and one FP64 reduction per band, so that their FP32
                             partial buffer (2 * band * k * nF floats, or ceil(nF/256) * k *

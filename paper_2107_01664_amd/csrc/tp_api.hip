@@ -1418,11 +1418,11 @@ constexpr double kSymPartBytes = 512.0 * 1024.0 * 1024.0;
 constexpr int64_t kSymMinFaces = 16384;
 constexpr int kGradOutputs = 7;   // partial sums per face of the E + dE kernels
 
-bool sym_size_ok(const tp_params& prm, int64_t nF, int nacc)
+bool sym_allowed(const tp_params& prm, int64_t nF) { return prm.sym_pairs != 0 && !(prm.theta > 0.0) && nF >= 1; }
+
+bool sym_size_ok(const tp_params& prm, int64_t nF)
 {
-    (void)nacc;
-    if (prm.sym_pairs == 0 || prm.theta > 0.0 || nF < 1) return false;
-    return prm.sym_pairs == 1 || nF >= kSymMinFaces;
+    return sym_allowed(prm, nF) && (prm.sym_pairs == 1 || nF >= kSymMinFaces);
 }
 
 int sym_band_height(const tp_params& prm, int64_t nF, int kc)
@@ -1454,7 +1454,7 @@ tp_status for_each_sym_band(const tp_params& prm, int64_t nF, int kc, Fn&& fn)
 bool sym_frac_eligible(const tp_params& prm, int64_t nF, int kc)
 {
     return prm.precision != TP_PREC_FP64 && !(prm.chi > 0.0) && kc >= 1 && kc <= kMaxGroupCols &&
-           sym_size_ok(prm, nF, kc);
+           sym_size_ok(prm, nF);
 }
 
 // The operator A = B + B0 (direct sums at any theta): the FP32 precisions.
@@ -1468,7 +1468,18 @@ bool sym_sobolev_eligible(const tp_params& prm, int64_t nF)
 bool sym_grad_eligible(const tp_params& prm, int64_t nF)
 {
     const int p = prm.precision;
-    return (p == TP_PREC_FP32_HILO || p == TP_PREC_FP32 || p == TP_PREC_FP32_NEAR64) && sym_size_ok(prm, nF, kGradOutputs);
+    return (p == TP_PREC_FP32_HILO || p == TP_PREC_FP32 || p == TP_PREC_FP32_NEAR64) && sym_size_ok(prm, nF);
+}
+
+// E + dE in FP64 with every unordered pair once: from kSym64MinFaces faces on (10,260 faces: 187 us, row by
+// row 226; 8,320 faces: 169 and 152, too few pairs of blocks to fill the GPU), as long as its
+// slices (56 bytes per face and block of faces) stay within kSym64Bytes (up to 70,000 faces).
+constexpr int64_t kSym64MinFaces = 10240;
+constexpr double kSym64Bytes = 1024.0 * 1024.0 * 1024.0;
+bool sym64_grad_eligible(const tp_params& prm, int64_t nF, int64_t irows)
+{
+    return prm.precision == TP_PREC_FP64 && sym_allowed(prm, nF) &&
+           (prm.sym_pairs == 1 || nF >= kSym64MinFaces) && 56.0 * (double)irows * sym64_slices(nF) <= kSym64Bytes;
 }
 
 // E of every problem (face data must describe the point of evaluation) -> scal[slot] and its host
@@ -1583,9 +1594,18 @@ tp_status enqueue_gradient(const Batch& B, double* const* dE, int slot, bool del
             plans.push_back(pl);
             continue;
         }
+        const bool once = sym64_grad_eligible(P->prm, P->nF, pl.irows);
+        if (once) pl.n_split = sym64_slices(P->nF);
         const int slices = pl.n_split + (near_field(P) ? 1 : 0);
         TP_TRY(P->part.ensure((size_t)slices * 7 * pl.irows, s));
         TP_TRY(P->gface.ensure((size_t)7 * pl.irows, s));
+        if (once) {
+            PairTimer t(kKindGrad, (double)P->nF * (double)(P->nF - 1), 0.0, s);
+            TP_HIP(launch_grad64_sym(P->fd, P->part.p, pl.irows, P->prm.alpha, P->prm.beta, s));
+            t.stop();
+            plans.push_back(pl);
+            continue;
+        }
         jobs.push_back(make_pair_job(P->fd, pl, P->part.p));
         jobs.back().rho2 = (float)P->rho2;
         plans.push_back(pl);
@@ -3145,6 +3165,7 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
     double part = std::max({(double)(pe.n_split + 1) * pe.irows, 7.0 * (pg.n_split + 1) * pg.irows,
                             (double)kf * pf.n_split * pf.irows});
     if (sym_grad_eligible(prm, nF)) part = std::max(part, (double)pe.irows + (double)sym_units(nF));
+    if (sym64_grad_eligible(prm, nF, pg.irows)) part = std::max(part, 7.0 * sym64_slices(nF) * pg.irows);
     const double gface = std::max((double)pe.irows, 7.0 * pg.irows);
     const double esz = prec == TP_PREC_FP64 ? 8 : 4;
     b += 8 * part + 8 * gface + 8.0 * kf * pf.irows + (double)cap * ((kf + 3) / 4 * 4) * esz;

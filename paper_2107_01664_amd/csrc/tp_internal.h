@@ -196,6 +196,10 @@ hipError_t launch_grad_sym(const FaceData& fd, float* part, int K, int a0, int a
 // blocks, sym_units(nF) of them, into upart (their sum, plus the near field's
 // sum_i a_i near[i] when pairs closer than sqrt(rho2) are left to it, is E).
 int64_t sym_units(int64_t nF);
+// The FP64 differential with every unordered pair evaluated once: sym64_slices(nF) slices of
+// [7][irows] in part, to be added by launch_reduce_splits.
+int sym64_slices(int64_t nF);
+hipError_t launch_grad64_sym(const FaceData& fd, double* part, int64_t irows, double alpha, double beta, hipStream_t s);
 hipError_t launch_energy_sym(const FaceData& fd, double* upart, int precision, double alpha, double beta, float rho2,
                              hipStream_t s);
 

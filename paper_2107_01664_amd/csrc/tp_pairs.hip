@@ -1243,6 +1243,172 @@ __global__ __launch_bounds__(kBlock) void k_grad64(PairBatch jb, double alpha, d
     for (int m = 0; m < kGradOut; ++m) dst[m * irows] = out[m];
 }
 
+// ============================================================== symmetric E + dE (FP64)
+//
+// k_grad64 evaluates every pair twice, once for each row, and its issue of FP64 instructions is
+// what bounds it (43 per ordered pair, 93 % of the issue slots).  Here an unordered pair is
+// evaluated once for both rows, 61 instructions, by the scheme of k_grad32_sym: the faces T pass
+// along the wave with their own sums.  A workgroup takes a pair (a, b) of blocks of kSymFaces
+// faces, its two waves half of b each (finer units than a block pair per wave: a CU has 13 of them
+// at 20,000 faces, and the last round is short); wave 0 adds the S-side sums of both.  Row sums
+// go to slice b of row S's block and slice a of row T's, so every face has one FP64 slice per block, in
+// the layout of k_grad64's splits, and the same reduction adds them in order.  Four faces S a lane,
+// because the rotation (36 words a step) must stay below the 240 instructions it serves.
+// E + dE of 20,306 faces: 699 us row by row, 543 us (of which the slices' 91 MB, written and read,
+// 45); of 50,160 faces 3.53 and 2.85 ms.
+struct G64SymArgs {
+    const double4* dx = nullptr;
+    const double4* dn = nullptr;
+    double* part = nullptr;   // [nB][kGradOut][irows]
+    int64_t irows = 0;
+    int nB = 0;
+};
+
+__device__ __forceinline__ double rot64(const WaveRot& rot, double v)
+{
+    return __hiloint2double(rot(__double2hiint(v)), rot(__double2loint(v)));
+}
+
+__device__ __forceinline__ void grad_outputs64(double aF, const double3& N, const double (&c)[kGradAcc], double sign,
+                                               double alpha, double beta, double (&out)[kGradOut])
+{
+    out[0] = sign * (aF * (alpha * (N.x * c[0] + c[1]) - beta * c[4]));
+    out[1] = sign * (aF * (alpha * (N.y * c[0] + c[2]) - beta * c[5]));
+    out[2] = sign * (aF * (alpha * (N.z * c[0] + c[3]) - beta * c[6]));
+    out[3] = aF * alpha * c[7];
+    out[4] = aF * alpha * c[8];
+    out[5] = aF * alpha * c[9];
+    out[6] = c[10];
+}
+
+template <bool DIAG, class Pow>
+__device__ __forceinline__ void g64_unit(const G64SymArgs& A, int a, int b, int half, int lane, const Pow& pw,
+                                         double alpha, double beta, const double3 (&S)[kSymNI],
+                                         const double3 (&N)[kSymNI], const double (&aS)[kSymNI],
+                                         double (&c)[kSymNI][kGradAcc])
+{
+    const WaveRot rot(lane);
+#pragma unroll 1
+    for (int q = 2 * half; q < 2 * half + 2; ++q) {
+        const int64_t T = (int64_t)b * kSymFaces + q * 64 + lane;
+        double4 tx = A.dx[T];
+        const double4 n4 = A.dn[T];
+        double3 tn = make_double3(n4.x, n4.y, n4.z);
+        double ct[kGradAcc];
+#pragma unroll
+        for (int m = 0; m < kGradAcc; ++m) ct[m] = 0.0;
+        int ti = q * 64 + lane;
+#pragma unroll 1
+        for (int step = 0; step < 64; ++step) {
+#pragma unroll
+            for (int r = 0; r < kSymNI; ++r) {
+                const double dx = S[r].x - tx.x, dy = S[r].y - tx.y, dz = S[r].z - tx.z;
+                double r2 = dx * dx + dy * dy + dz * dz;
+                if (DIAG) r2 = r * 64 + lane == ti ? 1.0 : r2;
+                const double inv = rcp_fast(r2);
+                const double qs = N[r].x * dx + N[r].y * dy + N[r].z * dz;
+                const double qt = tn.x * dx + tn.y * dy + tn.z * dz;
+                double K, Kqr, Kp, Kpqr;
+                pw.KG(qs, r2, inv, K, Kqr);
+                pw.KG(qt, r2, inv, Kp, Kpqr);
+                const double KK = K + Kp;
+                const double t = tx.w * inv;
+                const double aq = Kqr * t, ap = Kpqr * t, cc = KK * t;
+                c[r][0] += aq;
+                c[r][1] += ap * tn.x;
+                c[r][2] += ap * tn.y;
+                c[r][3] += ap * tn.z;
+                c[r][4] += cc * dx;
+                c[r][5] += cc * dy;
+                c[r][6] += cc * dz;
+                c[r][7] += aq * dx;
+                c[r][8] += aq * dy;
+                c[r][9] += aq * dz;
+                c[r][10] += KK * tx.w;
+                if (!DIAG) {
+                    // row T: d, N_T.d and N_S.d change sign, so the first seven sums are kept negated
+                    const double ts = aS[r] * inv;
+                    const double bq = Kpqr * ts, bp = Kqr * ts, cs = KK * ts;
+                    ct[0] += bq;
+                    ct[1] += bp * N[r].x;
+                    ct[2] += bp * N[r].y;
+                    ct[3] += bp * N[r].z;
+                    ct[4] += cs * dx;
+                    ct[5] += cs * dy;
+                    ct[6] += cs * dz;
+                    ct[7] += bq * dx;
+                    ct[8] += bq * dy;
+                    ct[9] += bq * dz;
+                    ct[10] += KK * aS[r];
+                }
+            }
+            tx.x = rot64(rot, tx.x);
+            tx.y = rot64(rot, tx.y);
+            tx.z = rot64(rot, tx.z);
+            tx.w = rot64(rot, tx.w);
+            tn.x = rot64(rot, tn.x);
+            tn.y = rot64(rot, tn.y);
+            tn.z = rot64(rot, tn.z);
+            if (!DIAG) {
+#pragma unroll
+                for (int m = 0; m < kGradAcc; ++m) ct[m] = rot64(rot, ct[m]);
+            } else {
+                ti = rot(ti);
+            }
+        }
+        if (!DIAG) {   // 64 rotations later every face T is back in its own lane
+            double out[kGradOut];
+            grad_outputs64(tx.w, tn, ct, -1.0, alpha, beta, out);
+#pragma unroll
+            for (int m = 0; m < kGradOut; ++m) A.part[((int64_t)a * kGradOut + m) * A.irows + T] = out[m];
+        }
+    }
+}
+
+template <class Pow>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k_grad64_sym(G64SymArgs A, double alpha,
+                                                                                         double beta, Pow pw)
+{
+    __shared__ double sh[kGradOut][kSymFaces];
+    const int lane = (int)threadIdx.x & 63, half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int a, b;
+    if (!sym_unit_blocks(blockIdx.x, A.nB, 0, A.nB, a, b)) return;   // the whole workgroup
+    double3 S[kSymNI], N[kSymNI];
+    double aS[kSymNI], c[kSymNI][kGradAcc];
+#pragma unroll
+    for (int r = 0; r < kSymNI; ++r) {
+        const double4 x = A.dx[(int64_t)a * kSymFaces + r * 64 + lane], n = A.dn[(int64_t)a * kSymFaces + r * 64 + lane];
+        S[r] = make_double3(x.x, x.y, x.z);
+        N[r] = make_double3(n.x, n.y, n.z);
+        aS[r] = x.w;
+#pragma unroll
+        for (int m = 0; m < kGradAcc; ++m) c[r][m] = 0.0;
+    }
+    if (a == b) g64_unit<true>(A, a, b, half, lane, pw, alpha, beta, S, N, aS, c);
+    else g64_unit<false>(A, a, b, half, lane, pw, alpha, beta, S, N, aS, c);
+    if (half == 1) {
+#pragma unroll
+        for (int r = 0; r < kSymNI; ++r) {
+            double out[kGradOut];
+            grad_outputs64(aS[r], N[r], c[r], 1.0, alpha, beta, out);
+#pragma unroll
+            for (int m = 0; m < kGradOut; ++m) sh[m][r * 64 + lane] = out[m];
+        }
+    }
+    __syncthreads();
+    if (half == 0) {
+#pragma unroll
+        for (int r = 0; r < kSymNI; ++r) {
+            double out[kGradOut];
+            grad_outputs64(aS[r], N[r], c[r], 1.0, alpha, beta, out);
+#pragma unroll
+            for (int m = 0; m < kGradOut; ++m)
+                A.part[((int64_t)b * kGradOut + m) * A.irows + (int64_t)a * kSymFaces + r * 64 + lane] =
+                    out[m] + sh[m][r * 64 + lane];
+        }
+    }
+}
+
 template <int KC>
 __global__ __launch_bounds__(kBlock) void k_frac64(PairBatch jb, double expo)
 {
@@ -1989,6 +2155,27 @@ hipError_t launch_grad_sym(const FaceData& fd, float* part, int K, int a0, int a
         else if (hilo) hipLaunchKernelGGL((k_grad32_sym<true, false, PowGen>), grid, block, 0, s, A, alpha, beta, pw);
         else hipLaunchKernelGGL((k_grad32_sym<false, false, PowGen>), grid, block, 0, s, A, alpha, beta, pw);
     }
+    return hipGetLastError();
+}
+
+int sym64_slices(int64_t nF) { return (int)sym_blocks(nF); }
+
+hipError_t launch_grad64_sym(const FaceData& fd, double* part, int64_t irows, double alpha, double beta, hipStream_t s)
+{
+    if (fd.nF < 1) return hipSuccess;
+    G64SymArgs A;
+    A.dx = fd.dx;
+    A.dn = fd.dn;
+    A.part = part;
+    A.irows = irows;
+    A.nB = (int)sym_blocks(fd.nF);
+    const int64_t rows = (int64_t)A.nB * kSymFaces;
+    if (rows > fd.cap || rows > irows) return hipErrorInvalidValue;
+    const int64_t units = sym_units(fd.nF);
+    if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)units), block(128);
+    if (is_p6(alpha, beta)) hipLaunchKernelGGL(k_grad64_sym<PowP6>, grid, block, 0, s, A, alpha, beta, PowP6{});
+    else hipLaunchKernelGGL(k_grad64_sym<PowGen>, grid, block, 0, s, A, alpha, beta, make_gen(alpha, beta));
     return hipGetLastError();
 }
 
