@@ -483,8 +483,9 @@ struct tp_problem {
     uint64_t ng_ver = ~0ull;         // geometry version the grid was built for
 
     // pinned host mirrors of device scalars, flags and CG results; multi-problem CG tables
-    HostBuf<double> hs, hrelres;
-    HostBuf<int> hflags, hiters;
+    HostBuf<double> pinned;          // the four mirrors below (an allocation of pinned memory takes 25 us, and as long to free)
+    struct { double* p = nullptr; } hs, hrelres;
+    struct { int* p = nullptr; } hflags, hiters;
     TabRing tab;
 
     // device memory held by the problem
@@ -541,15 +542,17 @@ __global__ void k_permute_faces(const int32_t* __restrict__ Fold, const int32_t*
 }
 
 // Per-face edge-length sums (for the mean edge length of the initial mesh).
-__global__ void k_face_edges(const double* __restrict__ V, const int32_t* __restrict__ F, int64_t nF,
+__global__ void k_face_edges(const double* __restrict__ V, int64_t nV, const int32_t* __restrict__ F, int64_t nF,
                              double* __restrict__ out)
 {
     const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (f >= nF) return;
     double s = 0.0;
     for (int c = 0; c < 3; ++c) {
-        const double* a = V + 3 * (int64_t)F[3 * f + c];
-        const double* b = V + 3 * (int64_t)F[3 * f + (c + 1) % 3];
+        const int32_t i = F[3 * f + c], j = F[3 * f + (c + 1) % 3];
+        if (i < 0 || i >= nV || j < 0 || j >= nV) continue;   // (flagged by the face pass)
+        const double* a = V + 3 * (int64_t)i;
+        const double* b = V + 3 * (int64_t)j;
         const double d0 = a[0] - b[0], d1 = a[1] - b[1], d2 = a[2] - b[2];
         s += sqrt(d0 * d0 + d1 * d1 + d2 * d2);
     }
@@ -630,10 +633,11 @@ tp_status alloc_faces(tp_problem* P)
     P->flags.p = reinterpret_cast<int*>(P->dot_red.p + dot_scratch_doubles());
     TP_HIP(hipMemsetAsync(P->scal.p, 0, sizeof(double) * nsmall, P->stream));
     TP_TRY(P->red.ensure(reduce_scratch_doubles(16), P->stream));
-    TP_TRY(P->hs.ensure(256));
-    TP_TRY(P->hflags.ensure(kNumFlags));
-    TP_TRY(P->hiters.ensure(2 * kMaxCols));
-    TP_TRY(P->hrelres.ensure(2 * kMaxCols));
+    TP_TRY(P->pinned.ensure(kScal + 3 * kMaxCols + kNumFlags));
+    P->hs.p = P->pinned.p;
+    P->hrelres.p = P->hs.p + kScal;
+    P->hiters.p = reinterpret_cast<int*>(P->hrelres.p + 2 * kMaxCols);
+    P->hflags.p = P->hiters.p + 2 * kMaxCols;
     return TP_OK;
 }
 
@@ -1139,16 +1143,6 @@ AxpyJob axpy_job(int64_t n, const double* x, int ldx, double a, const double* Y,
 tp_status axpy_one(const AxpyJob& J, hipStream_t s)
 {
     TP_HIP(launch_axpy_block3(&J, 1, s));
-    return TP_OK;
-}
-
-// Sum of n doubles (device), to the host.
-tp_status device_sum(tp_problem* P, const double* x, int64_t n, double* out)
-{
-    const DotJob J = dot_job(P, 0, kNumSlots, x, 1, nullptr, 0, n, 1);
-    TP_HIP(launch_dots(&J, 1, P->stream));
-    TP_HIP(hipStreamSynchronize(P->stream));
-    *out = P->hs.p[kNumSlots];
     return TP_OK;
 }
 
@@ -2458,37 +2452,43 @@ tp_status create_problem(const double* V, int64_t nV, const int32_t* F, int64_t 
     if (hipMemcpyAsync(P->V.p, V, sizeof(double) * 3 * nV, hipMemcpyDeviceToDevice, stream) != hipSuccess ||
         hipMemcpyAsync(P->F.p, F, sizeof(int32_t) * 3 * nF, hipMemcpyDeviceToDevice, stream) != hipSuccess)
         return bail(fail(TP_E_DEVICE, "copy of V / F failed (are they device pointers?)"));
-    if (launch_check_indices(P->F.p, nF, nV, P->flags.p, stream) != hipSuccess)
-        return bail(fail(TP_E_DEVICE, "index check launch failed"));
-    if ((st = check_flags(P)) != TP_OK) return bail(st);
-    if ((st = geometry(P)) != TP_OK) return bail(st);
-    // store the faces in the Morton order of their barycenters: face tiles become compact
+    // Store the faces in the Morton order of their barycenters: face tiles become compact
     // patches (the near-field tile test and the tree build rely on it); results do not
     // depend on the stored order beyond rounding, and the tree breaks ties by the caller's
-    // face numbers
-    {
-        DevBuf<int32_t> Fold;
-        if ((st = ensure_bh(P)) != TP_OK) return bail(st);
-        if ((st = Fold.ensure(3 * nF, stream)) != TP_OK) return bail(st);
-        if ((st = P->face_orig.ensure(nF, stream)) != TP_OK) return bail(st);
-        if (hipMemcpyAsync(Fold.p, P->F.p, sizeof(int32_t) * 3 * nF, hipMemcpyDeviceToDevice, stream) != hipSuccess ||
-            launch_morton_order(P->bh, P->fd, nF, nullptr, stream) != hipSuccess)
-            return bail(fail(TP_E_DEVICE, "face ordering failed"));
-        hipLaunchKernelGGL(k_permute_faces, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, stream, Fold.p,
-                           P->bh.order, nF, P->F.p, P->face_orig.p);
-        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(stream) != hipSuccess)
-            return bail(fail(TP_E_DEVICE, "face ordering failed"));
-        P->geom_valid = false;
-        if ((st = geometry(P)) != TP_OK) return bail(st);
-    }
-    if (P->prm.precision == TP_PREC_FP32_NEAR64) {
+    // face numbers.  A face with a bad index, without area or not finite is flagged and kept out of
+    // the way by the face pass itself, so everything is enqueued and the flags are looked at
+    // once, at the end (E + dE of 1,280 faces from scratch: 473 us with five waits for the device
+    // and four blocks of pinned memory, 375 with one of each).
+    DevBuf<int32_t> Fold;
+    if ((st = ensure_bh(P)) != TP_OK) return bail(st);
+    if ((st = Fold.ensure(3 * nF, stream)) != TP_OK) return bail(st);
+    if ((st = P->face_orig.ensure(nF, stream)) != TP_OK) return bail(st);
+    const FaceGeomJob G = face_geom_job(P, P->V.p);
+    if (hipMemcpyAsync(Fold.p, P->F.p, sizeof(int32_t) * 3 * nF, hipMemcpyDeviceToDevice, stream) != hipSuccess ||
+        launch_face_geom(&G, 1, stream) != hipSuccess ||
+        launch_morton_order(P->bh, P->fd, nF, nullptr, stream) != hipSuccess)
+        return bail(fail(TP_E_DEVICE, "face ordering failed"));
+    hipLaunchKernelGGL(k_permute_faces, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, stream, Fold.p,
+                       P->bh.order, nF, P->F.p, P->face_orig.p);
+    if (hipGetLastError() != hipSuccess || launch_face_geom(&G, 1, stream) != hipSuccess)
+        return bail(fail(TP_E_DEVICE, "face ordering failed"));
+    P->fd_V = P->V.p;
+    ++P->geom_ver;
+    const bool near = P->prm.precision == TP_PREC_FP32_NEAR64;
+    if (near) {
         if ((st = P->edge.ensure(P->nF, stream)) != TP_OK) return bail(st);
-        hipLaunchKernelGGL(k_face_edges, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, stream, P->V.p, P->F.p,
+        hipLaunchKernelGGL(k_face_edges, dim3((unsigned)((nF + 255) / 256)), dim3(256), 0, stream, P->V.p, nV, P->F.p,
                            nF, P->edge.p);
-        double es = 0;
-        if (hipGetLastError() != hipSuccess) return bail(fail(TP_E_DEVICE, "edge length launch failed"));
-        if ((st = device_sum(P, P->edge.p, nF, &es)) != TP_OK) return bail(st);
-        const double h = es / (3.0 * (double)nF);
+        DotJob J = dot_job(P, 0, kNumSlots, P->edge.p, 1, nullptr, 0, nF, 1);
+        J.flags = P->flags.p;
+        J.hflags = P->hflags.p;
+        if (hipGetLastError() != hipSuccess || launch_dots(&J, 1, stream) != hipSuccess)
+            return bail(fail(TP_E_DEVICE, "edge length launch failed"));
+    }
+    if ((st = check_flags(P, near)) != TP_OK) return bail(st);
+    P->geom_valid = true;
+    if (near) {
+        const double h = P->hs.p[kNumSlots] / (3.0 * (double)nF);
         P->rho2 = 4.0 * h * h;
     }
     *out = P;
@@ -2506,7 +2506,7 @@ tp_status ensure_initial_measures(tp_problem* P)
     TP_HIP(launch_face_volume(vols.data(), 1, P->stream));
     TP_TRY(P->edge.ensure(P->nF, P->stream));
     hipLaunchKernelGGL(k_face_edges, dim3((unsigned)((P->nF + 255) / 256)), dim3(256), 0, P->stream,
-                       P->V.p, P->F.p, P->nF, P->edge.p);
+                       P->V.p, P->nV, P->F.p, P->nF, P->edge.p);
     TP_HIP(hipGetLastError());
     dots.push_back(dot_job(P, 2, kNumSlots, P->edge.p, 1, nullptr, 0, P->nF, 1));
     TP_HIP(launch_dots(dots.data(), (int)dots.size(), P->stream));

@@ -208,7 +208,6 @@ hipError_t launch_reduce_splits(const double* part, int n_split, int nacc, int64
                                 int64_t n, double* out, int64_t out_stride, hipStream_t s);
 
 // Mesh / sparse kernels.
-hipError_t launch_check_indices(const int32_t* F, int64_t nF, int64_t nV, int* flags, hipStream_t s);
 hipError_t launch_vf_count(const int32_t* F, int64_t nF, int64_t nV, int32_t* deg, hipStream_t s);
 hipError_t launch_scan(const int32_t* in, int64_t n, int32_t* out_excl /* n + 1 */, hipStream_t s);
 hipError_t launch_vf_fill(const int32_t* F, int64_t nF, int64_t nV, const int32_t* off,

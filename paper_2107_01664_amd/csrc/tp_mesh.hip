@@ -196,20 +196,6 @@ hipError_t launch_face_from_quantities(const double* X, const double* N, const d
 // row, so every gather over it has a fixed order.  Integer atomics only place entries;
 // the per-row sort makes the result independent of their order.
 
-// Index check: every face corner must name a vertex in [0, nV).
-__global__ void k_check_indices(const int32_t* __restrict__ F, int64_t n3, int64_t nV,
-                                int* __restrict__ flags)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n3 && (F[t] < 0 || F[t] >= nV)) flags[kFlagBadIndex] = 1;
-}
-
-hipError_t launch_check_indices(const int32_t* F, int64_t nF, int64_t nV, int* flags, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_check_indices, dim3(nblocks(3 * nF)), dim3(256), 0, s, F, 3 * nF, nV, flags);
-    return hipGetLastError();
-}
-
 __global__ void k_vf_count(const int32_t* __restrict__ F, int64_t n3, int64_t nV, int32_t* deg)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
