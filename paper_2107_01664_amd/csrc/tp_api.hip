@@ -1387,7 +1387,7 @@ tp_status enqueue_near(const Batch& B, const std::vector<PairPlan>& plans, int n
         if (!near_field(P)) continue;
         const PairPlan& pl = plans[m];
         PairJob J = make_pair_job(P->fd, pl, P->part.p + (size_t)pl.n_split * nacc * pl.irows);
-        J.n_itiles = (int)((P->nF + near_block_faces() - 1) / near_block_faces());
+        J.n_itiles = (int)((P->nF + near_block_faces(grad) - 1) / near_block_faces(grad));
         J.tiles_per_split = J.ntiles_j;
         J.rho2 = (float)P->rho2;
         J.nord = P->ng.ord;

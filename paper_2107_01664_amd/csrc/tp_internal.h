@@ -420,6 +420,6 @@ hipError_t launch_near_grid_build(const NearGridJob* jobs, int njobs, hipStream_
 // the job's partial slice ([7][irows] with grad, else [irows]).  The candidates T of S are
 // the faces of the 27 grid cells around S's cell.
 hipError_t launch_near64(const PairJob* jobs, int njobs, double alpha, double beta, bool grad, hipStream_t s);
-int near_block_faces();           // faces S per near-field workgroup (n_itiles of a near job)
+int near_block_faces(bool grad);           // faces S per near-field workgroup (n_itiles of a near job)
 
 }  // namespace tp

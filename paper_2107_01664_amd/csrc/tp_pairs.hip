@@ -1508,7 +1508,7 @@ __device__ __forceinline__ double near_lane_sum(double v)
 // candidate T the lane forms the FP32 hi+lo squared distance exactly as the FP32 kernels
 // do, and evaluates the pair in FP64 when that distance is below rho2.  Each lane's sums
 // have a fixed order, and so has their combination (near_lane_sum).
-template <bool GEN, bool GRAD>
+template <bool GEN>
 __global__ __launch_bounds__(kNearBlock) void k_near64(PairBatch jb, double alpha, double beta)
 {
     const PairJob J = pick_job(jb);
@@ -1525,7 +1525,6 @@ __global__ __launch_bounds__(kNearBlock) void k_near64(PairBatch jb, double alph
     double c[11];
 #pragma unroll
     for (int m = 0; m < 11; ++m) c[m] = 0.0;
-    double e = 0.0;
     for (int z = max(cz - 1, 0); z <= min(cz + 1, G.g - 1); ++z)
         for (int y = max(cy - 1, 0); y <= min(cy + 1, G.g - 1); ++y)
             for (int x = max(cx - 1, 0); x <= min(cx + 1, G.g - 1); ++x) {
@@ -1544,10 +1543,6 @@ __global__ __launch_bounds__(kNearBlock) void k_near64(PairBatch jb, double alph
                     const double q = Nn.x * dx + Nn.y * dy + Nn.z * dz;
                     double K, Kqr;
                     kg64<GEN>(q, r2, inv, alpha, beta, K, Kqr);
-                    if (!GRAD) {
-                        e += K * Y.w;
-                        continue;
-                    }
                     const double qp = Nt.x * dx + Nt.y * dy + Nt.z * dz;
                     double Kp, Kpqr;
                     kg64<GEN>(qp, r2, inv, alpha, beta, Kp, Kpqr);
@@ -1566,11 +1561,6 @@ __global__ __launch_bounds__(kNearBlock) void k_near64(PairBatch jb, double alph
                     c[10] += KK * Y.w;
                 }
             }
-    if (!GRAD) {
-        e = near_lane_sum(e);
-        if (lane == 0) J.part[S] = e;
-        return;
-    }
 #pragma unroll
     for (int m = 0; m < 11; ++m) c[m] = near_lane_sum(c[m]);
     if (lane != 0) return;
@@ -1585,6 +1575,91 @@ __global__ __launch_bounds__(kNearBlock) void k_near64(PairBatch jb, double alph
     o[6] = c[10];
 #pragma unroll
     for (int m = 0; m < 7; ++m) J.part[m * J.irows + S] = o[m];
+}
+
+// E's rows alone: kNearELanes lanes per face.  What bounds it is latency: cell by cell there are 27
+// loads of a cell's run in series, each with candidates, their numbers and their FP64 data behind
+// it.  The face's lanes read the runs together, then take the candidates in order, one each and U
+// at a time, the loads of a step in flight together.  (The differential keeps eight lanes and its
+// order: its sums feed a solve whose right-hand side is rounded to FP32, where other bits move
+// the step by 1e-9.)  5,084 faces: 33 us with eight lanes, cell by cell, 12 now; 40,000: 46 and 30.
+constexpr int kNearELanes = 32;
+constexpr int kNearEFaces = kNearBlock / kNearELanes;
+template <bool GEN>
+__global__ __launch_bounds__(kNearBlock) void k_near64_energy(PairBatch jb, double alpha, double beta)
+{
+    constexpr int U = GEN ? 1 : 4;            // (the powers of the general exponents are long: one copy)
+    __shared__ int first[kNearEFaces][28];    // candidates before each cell's
+    __shared__ int begin[kNearEFaces][27];
+    const PairJob J = pick_job(jb);
+    const NearGridParams G = *J.ngp;
+    const int lane = (int)threadIdx.x % kNearELanes, face = (int)threadIdx.x / kNearELanes;
+    const int i = ((int)blockIdx.x - J.block0) * kNearEFaces + face;
+    const bool live = i < G.n;                // all lanes of a face alike
+    const int ic = live ? i : 0;
+    const int S = J.nord[ic];
+    const float4 sh = J.nfx[ic], sl = J.nfl[ic];
+    const double4 X = J.dx[S], Nn = J.dn[S];
+    const int x = near_cell_axis(sh.x, G.lo[0], G.inv_cs, G.g) + lane % 3 - 1;
+    const int y = near_cell_axis(sh.y, G.lo[1], G.inv_cs, G.g) + lane / 3 % 3 - 1;
+    const int z = near_cell_axis(sh.z, G.lo[2], G.inv_cs, G.g) + lane / 9 - 1;
+    int2 run = make_int2(0, 0);
+    if (lane < 27 && x >= 0 && y >= 0 && z >= 0 && x < G.g && y < G.g && z < G.g)
+        run = J.ncell[((int64_t)z * G.g + y) * G.g + x];
+    int sum = run.y;                          // inclusive, over the cells up to this lane's
+#pragma unroll
+    for (int o = 1; o < kNearELanes; o <<= 1) {
+        const int v = __shfl_up(sum, o, kNearELanes);
+        if (lane >= o) sum += v;
+    }
+    const int n = __shfl(sum, kNearELanes - 1, kNearELanes);
+    if (lane < 27) {
+        first[face][lane + 1] = sum;
+        begin[face][lane] = run.x;
+    }
+    if (lane == 0) first[face][0] = 0;
+    __syncthreads();
+    if (!live) return;
+    double e = 0.0;
+    int cell = 0;
+    for (int k0 = lane; k0 < n; k0 += U * kNearELanes) {
+        int j[U], T[U];
+        float4 th[U], tl[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * kNearELanes;
+            j[u] = i;                         // (no candidate: the face itself, which is left out)
+            if (k < n) {
+                while (k >= first[face][cell + 1]) ++cell;
+                j[u] = begin[face][cell] + (k - first[face][cell]);
+            }
+            th[u] = J.nfx[j[u]];
+            tl[u] = J.nfl[j[u]];
+            T[u] = J.nord[j[u]];
+        }
+        bool hit[U];
+        double4 Yv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float fdx = (sh.x - th[u].x) + (sl.x - tl[u].x);
+            const float fdy = (sh.y - th[u].y) + (sl.y - tl[u].y);
+            const float fdz = (sh.z - th[u].z) + (sl.z - tl[u].z);
+            hit[u] = dist2_32(fdx, fdy, fdz) < J.rho2 && j[u] != i;
+            Yv[u] = J.dx[hit[u] ? T[u] : S];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!hit[u]) continue;
+            const double dx = X.x - Yv[u].x, dy = X.y - Yv[u].y, dz = X.z - Yv[u].z;
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            double K, Kqr;
+            kg64<GEN>(Nn.x * dx + Nn.y * dy + Nn.z * dz, r2, 1.0 / r2, alpha, beta, K, Kqr);
+            e += K * Yv[u].w;
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < kNearELanes; o <<= 1) e += __shfl_xor(e, o, kNearELanes);
+    if (lane == 0) J.part[S] = e;
 }
 
 // ------------------------------------------------------------------ near-field grid build
@@ -2216,7 +2291,7 @@ hipError_t launch_energy_sym(const FaceData& fd, double* upart, int precision, d
     return hipGetLastError();
 }
 
-int near_block_faces() { return kNearFaces; }
+int near_block_faces(bool grad) { return grad ? kNearFaces : kNearEFaces; }
 
 int near_grid_gmax(int64_t nF)
 {
@@ -2254,11 +2329,11 @@ hipError_t launch_near64(const PairJob* jobs, int njobs, double alpha, double be
     const bool gen = !is_p6(alpha, beta);
     return for_each_batch(jobs, njobs, [&](const PairBatch& jb, dim3 grid) {
         if (grad) {
-            if (gen) hipLaunchKernelGGL((k_near64<true, true>), grid, block, 0, s, jb, alpha, beta);
-            else hipLaunchKernelGGL((k_near64<false, true>), grid, block, 0, s, jb, alpha, beta);
+            if (gen) hipLaunchKernelGGL(k_near64<true>, grid, block, 0, s, jb, alpha, beta);
+            else hipLaunchKernelGGL(k_near64<false>, grid, block, 0, s, jb, alpha, beta);
         } else {
-            if (gen) hipLaunchKernelGGL((k_near64<true, false>), grid, block, 0, s, jb, alpha, beta);
-            else hipLaunchKernelGGL((k_near64<false, false>), grid, block, 0, s, jb, alpha, beta);
+            if (gen) hipLaunchKernelGGL(k_near64_energy<true>, grid, block, 0, s, jb, alpha, beta);
+            else hipLaunchKernelGGL(k_near64_energy<false>, grid, block, 0, s, jb, alpha, beta);
         }
     });
 }
