@@ -1403,8 +1403,8 @@ tp_status enqueue_near(const Batch& B, const std::vector<PairPlan>& plans, int n
 }
 
 // The symmetric all-pairs kernels (launch_grad_sym, launch_frac_sym: each unordered pair
-// evaluated once for both rows) are used for the direct FP32 sums, unless forced by
-// tp_params.sym_pairs = 1, from kSymMinFaces faces on, below which they have too few pairs
+// evaluated once for both rows) are used for the direct FP32 sums of E + dE and the operators,
+// unless forced by tp_params.sym_pairs = 1, from kSymMinFaces faces on, below which they have too few pairs
 // of blocks to fill the GPU.  Their partial buffer is kept within kSymPartBytes by running
 // the rows in bands (one launch and one reduction per band; a single band up to about
 // 68,000 faces for E + dE).
@@ -1465,6 +1465,16 @@ bool sym_grad_eligible(const tp_params& prm, int64_t nF)
     return (p == TP_PREC_FP32_HILO || p == TP_PREC_FP32 || p == TP_PREC_FP32_NEAR64) && sym_size_ok(prm, nF);
 }
 
+// E: the same precisions, at any size (row by row and symmetric: 57 and 46 us at 1,000 faces, 61
+// and 49 at 5,084, 209 and 125 at 16,800, 983 and 474 at 40,000).  Faces given without a mesh keep
+// kSymMinFaces: their two entry points, with and without allocations, give the same digits.
+bool sym_energy_eligible(const tp_params& prm, int64_t nV, int64_t nF)
+{
+    const int p = prm.precision;
+    return (p == TP_PREC_FP32_HILO || p == TP_PREC_FP32 || p == TP_PREC_FP32_NEAR64) &&
+           (nV > 0 ? sym_allowed(prm, nF) : sym_size_ok(prm, nF));
+}
+
 // E + dE in FP64 with every unordered pair once: from kSym64MinFaces faces on (10,260 faces: 187 us, row by
 // row 226; 8,320 faces: 169 and 152, too few pairs of blocks to fill the GPU), as long as its
 // slices (56 bytes per face and block of faces) stay within kSym64Bytes (up to 70,000 faces).
@@ -1494,7 +1504,7 @@ tp_status enqueue_energy(const Batch& B, int slot, bool deliver = false)
     for (size_t m = 0; m < B.size(); ++m) {
         tp_problem* P = B[m];
         PairPlan pl = plan_for(kKindEnergy, prec, 1, P->nF, P->cap);
-        if (sym_grad_eligible(P->prm, P->nF)) {
+        if (sym_energy_eligible(P->prm, P->nV, P->nF)) {
             // symmetric kernel: part = [near field slice (irows)][pair-of-blocks partials]; the
             // near field goes to slice 0
             sym[m] = 1;
@@ -1515,12 +1525,19 @@ tp_status enqueue_energy(const Batch& B, int slot, bool deliver = false)
         TP_HIP(launch_pairs_energy(jobs.data(), (int)jobs.size(), prec, B[0]->prm.alpha, B[0]->prm.beta, s));
         t.stop();
     }
+    std::vector<EnergySymJob> sjobs;
+    double spairs = 0;
     for (size_t m = 0; m < B.size(); ++m) {
         if (!sym[m]) continue;
         tp_problem* P = B[m];
-        PairTimer t(kKindEnergy, (double)P->nF * (double)(P->nF - 1), 0.0, s);
-        TP_HIP(launch_energy_sym(P->fd, P->part.p + plans[m].irows, prec, P->prm.alpha, P->prm.beta, (float)P->rho2,
-                                 s));
+        EnergySymJob J;
+        J.fd = &P->fd; J.upart = P->part.p + plans[m].irows; J.rho2 = (float)P->rho2;
+        sjobs.push_back(J);
+        spairs += (double)P->nF * (double)(P->nF - 1);
+    }
+    if (!sjobs.empty()) {
+        PairTimer t(kKindEnergy, spairs, 0.0, s);
+        TP_HIP(launch_energy_sym(sjobs.data(), (int)sjobs.size(), prec, B[0]->prm.alpha, B[0]->prm.beta, s));
         t.stop();
     }
     TP_TRY(enqueue_near(B, plans, 1, false));
@@ -3164,7 +3181,7 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
     const PairPlan pf = plan_for(kKindFrac, prec, kf, nF, cap);
     double part = std::max({(double)(pe.n_split + 1) * pe.irows, 7.0 * (pg.n_split + 1) * pg.irows,
                             (double)kf * pf.n_split * pf.irows});
-    if (sym_grad_eligible(prm, nF)) part = std::max(part, (double)pe.irows + (double)sym_units(nF));
+    if (sym_energy_eligible(prm, nV, nF)) part = std::max(part, (double)pe.irows + (double)sym_units(nF));
     if (sym64_grad_eligible(prm, nF, pg.irows)) part = std::max(part, 7.0 * sym64_slices(nF) * pg.irows);
     const double gface = std::max((double)pe.irows, 7.0 * pg.irows);
     const double esz = prec == TP_PREC_FP64 ? 8 : 4;

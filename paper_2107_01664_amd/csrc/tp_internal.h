@@ -200,8 +200,12 @@ int64_t sym_units(int64_t nF);
 // [7][irows] in part, to be added by launch_reduce_splits.
 int sym64_slices(int64_t nF);
 hipError_t launch_grad64_sym(const FaceData& fd, double* part, int64_t irows, double alpha, double beta, hipStream_t s);
-hipError_t launch_energy_sym(const FaceData& fd, double* upart, int precision, double alpha, double beta, float rho2,
-                             hipStream_t s);
+struct EnergySymJob {
+    const FaceData* fd = nullptr;
+    double* upart = nullptr;
+    float rho2 = 0.f;
+};
+hipError_t launch_energy_sym(const EnergySymJob* jobs, int njobs, int precision, double alpha, double beta, hipStream_t s);
 
 // Sum the n_split partials of every accumulator in split order: out[acc][i].
 hipError_t launch_reduce_splits(const double* part, int n_split, int nacc, int64_t irows,

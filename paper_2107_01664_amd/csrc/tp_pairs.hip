@@ -1,8 +1,9 @@
 // All-pairs face-face kernels of the tangent-point hot path (gfx950).
 //
-// Two shapes.  The symmetric kernels (k_grad32_sym, k_frac32_sym, k_energy32_sym, from
-// 16,384 faces on) evaluate each unordered pair once for both rows: one wave per pair of
-// 256-face blocks, faces T passed along the wave (see their section below).  The row-by-row
+// Two shapes.  The symmetric kernels (k_grad32_sym and k_frac32_sym from 16,384 faces on,
+// k_energy32_sym at any size, k_grad64_sym from 10,240) evaluate each unordered pair once for
+// both rows: a wave, or the waves of a workgroup, per pair of 256-face blocks, faces T passed
+// along the wave (see their sections below).  The row-by-row
 // kernels (k_*32, k_*64, the FP64 near field) evaluate every ordered pair for its row: a
 // workgroup owns an i-tile of kBlock * NI faces S
 // held in registers (NI per thread) and streams a contiguous range of j-tiles of kTileJ
@@ -926,8 +927,12 @@ __global__ __launch_bounds__(kBlock) void k_grad32_sym(GSymArgs A, double alpha,
 // The energy alone needs no per-face sums: an unordered pair (S, T) adds
 // a_S a_T (K(S,T) + K(T,S)) (a_S a_T K(S,T) on diagonal blocks, where both orders come up),
 // so only the faces S of a lane collect, the faces T pass along the wave with their
-// positions, areas and normals (7 values a step, 10 with the low parts), and each wave writes
-// one FP64 partial for its pair of blocks; the partials are summed in a fixed order.
+// positions, areas and normals (7 values a step, 10 with the low parts).  A workgroup takes a pair
+// of blocks, each of its four waves a quarter of the faces T, and writes one FP64 partial; the
+// partials are summed in a fixed order.  (A pair of blocks per wave takes 75 us however small
+// the mesh, and as long again for a last round that is nearly empty.)  One launch takes all problems
+// of a batch.  E of 5,084 faces 62 us row by row, 102 with a wave per pair of blocks, 49 now; of
+// 16,800 faces 209, 178 and 125, of 40,000 984, 525 and 474.
 
 struct ESymArgs {
     const float4* fx = nullptr;
@@ -939,14 +944,17 @@ struct ESymArgs {
     int nB = 0;
     float rho2 = 0.f;
 };
+struct ESymJobs {
+    ESymArgs j[kMaxVecJobs];
+};
 
 template <bool LO, bool NEAR, bool DIAG, class Pow>
-__device__ __forceinline__ void esym_unit(const ESymArgs& A, int a, int b, int lane, const Pow& pw,
+__device__ __forceinline__ void esym_unit(const ESymArgs& A, int a, int b, int q, int lane, const Pow& pw,
                                           const float3 (&Sh)[kSymNI], const float3 (&Sl)[kSymNI],
                                           const float3 (&Sn)[kSymNI], double (&acc)[kSymNI])
 {
     const WaveRot rot(lane);
-    for (int q = 0; q < kSymFaces / 64; ++q) {
+    {
         const int64_t T = (int64_t)b * kSymFaces + q * 64 + lane;
         float4 th = A.fx[T];
         float3 tl = make_float3(0.f, 0.f, 0.f);
@@ -1008,13 +1016,15 @@ __device__ __forceinline__ void esym_unit(const ESymArgs& A, int a, int b, int l
 }
 
 template <bool HILO, bool NEAR, class Pow>
-__global__ __launch_bounds__(kBlock) void k_energy32_sym(ESymArgs A, Pow pw)
+__global__ __launch_bounds__(kBlock) void k_energy32_sym(ESymJobs jb, Pow pw)
 {
-    const int lane = (int)threadIdx.x & 63;
-    const int64_t unit = (int64_t)blockIdx.x * (kBlock / 64) + ((int)threadIdx.x >> 6);
+    static_assert(kBlock / 64 == kSymFaces / 64, "a wave per 64 faces T");
+    __shared__ double quarter[kBlock / 64];
+    const ESymArgs& A = jb.j[blockIdx.y];
+    const int lane = (int)threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nB = A.nB;
     int a, b;
-    if (!sym_unit_blocks(unit, nB, 0, nB, a, b)) return;   // the whole wave leaves
+    if (!sym_unit_blocks(blockIdx.x, nB, 0, nB, a, b)) return;   // the whole workgroup leaves
     float3 Sh[kSymNI], Sl[kSymNI], Sn[kSymNI];
     float aS[kSymNI];
     double acc[kSymNI];
@@ -1044,13 +1054,13 @@ __global__ __launch_bounds__(kBlock) void k_energy32_sym(ESymArgs A, Pow pw)
         }
     }
     if (a == b)
-        esym_unit<HILO, NEAR, true>(A, a, b, lane, pw, Sh, Sl, Sn, acc);
+        esym_unit<HILO, NEAR, true>(A, a, b, q, lane, pw, Sh, Sl, Sn, acc);
     else if (NEAR && near)
-        esym_unit<HILO, NEAR, false>(A, a, b, lane, pw, Sh, Sl, Sn, acc);
+        esym_unit<HILO, NEAR, false>(A, a, b, q, lane, pw, Sh, Sl, Sn, acc);
     else if (HILO && far)
-        esym_unit<false, false, false>(A, a, b, lane, pw, Sh, Sl, Sn, acc);
+        esym_unit<false, false, false>(A, a, b, q, lane, pw, Sh, Sl, Sn, acc);
     else
-        esym_unit<HILO, false, false>(A, a, b, lane, pw, Sh, Sl, Sn, acc);
+        esym_unit<HILO, false, false>(A, a, b, q, lane, pw, Sh, Sl, Sn, acc);
     // the lane's faces S (padding faces, which can meet each other at distance 0, left out),
     // then the wave's sum by an xor butterfly: every lane adds the same two values in the
     // same order, so all lanes hold the same bits
@@ -1060,7 +1070,9 @@ __global__ __launch_bounds__(kBlock) void k_energy32_sym(ESymArgs A, Pow pw)
         if ((int64_t)a * kSymFaces + r * 64 + lane < A.nF) e += (double)aS[r] * acc[r];
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) e += __shfl_xor(e, m, 64);
-    if (lane == 0) A.upart[unit] = e;
+    if (lane == 0) quarter[q] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) A.upart[blockIdx.x] = (quarter[0] + quarter[1]) + (quarter[2] + quarter[3]);
 }
 
 // The band [a0, a1) of rows, for faces i >= a0 kSymFaces (the others get nothing from it):
@@ -2256,39 +2268,47 @@ hipError_t launch_grad64_sym(const FaceData& fd, double* part, int64_t irows, do
 
 int64_t sym_units(int64_t nF) { return sym_band_units(nF, 0, (int)sym_blocks(nF)); }
 
-hipError_t launch_energy_sym(const FaceData& fd, double* upart, int precision, double alpha, double beta, float rho2,
-                             hipStream_t s)
+hipError_t launch_energy_sym(const EnergySymJob* jobs, int njobs, int precision, double alpha, double beta, hipStream_t s)
 {
-    if (fd.nF < 1) return hipSuccess;
-    if (precision == TP_PREC_FP64 || !fd.tbox) return hipErrorInvalidValue;
-    ESymArgs A;
-    A.fx = fd.fx;
-    A.fl = fd.fl;
-    A.fn = fd.fn;
-    A.tbox = fd.tbox;
-    A.upart = upart;
-    A.nF = fd.nF;
-    A.nB = (int)sym_blocks(fd.nF);
-    A.rho2 = rho2;
-    if ((int64_t)A.nB * kSymFaces > fd.cap) return hipErrorInvalidValue;
-    const int64_t units = sym_units(fd.nF);
-    const int64_t blocks = (units + kBlock / 64 - 1) / (kBlock / 64);
-    if (blocks > (int64_t)INT32_MAX) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(kBlock);
+    if (precision == TP_PREC_FP64) return hipErrorInvalidValue;
     const bool hilo = precision == TP_PREC_FP32_HILO || precision == TP_PREC_FP32_NEAR64;
     const bool near = precision == TP_PREC_FP32_NEAR64;
-    if (is_p6(alpha, beta)) {
-        const PowP6 pw;
-        if (near) hipLaunchKernelGGL((k_energy32_sym<true, true, PowP6>), grid, block, 0, s, A, pw);
-        else if (hilo) hipLaunchKernelGGL((k_energy32_sym<true, false, PowP6>), grid, block, 0, s, A, pw);
-        else hipLaunchKernelGGL((k_energy32_sym<false, false, PowP6>), grid, block, 0, s, A, pw);
-    } else {
-        const PowGen pw = make_gen(alpha, beta);
-        if (near) hipLaunchKernelGGL((k_energy32_sym<true, true, PowGen>), grid, block, 0, s, A, pw);
-        else if (hilo) hipLaunchKernelGGL((k_energy32_sym<true, false, PowGen>), grid, block, 0, s, A, pw);
-        else hipLaunchKernelGGL((k_energy32_sym<false, false, PowGen>), grid, block, 0, s, A, pw);
+    for (int m0 = 0; m0 < njobs; m0 += kMaxVecJobs) {
+        ESymJobs jb;
+        const int n = std::min(kMaxVecJobs, njobs - m0);
+        int64_t units = 1;
+        for (int m = 0; m < n; ++m) {
+            const FaceData& fd = *jobs[m0 + m].fd;
+            ESymArgs& A = jb.j[m];
+            if (!fd.tbox) return hipErrorInvalidValue;
+            A.fx = fd.fx;
+            A.fl = fd.fl;
+            A.fn = fd.fn;
+            A.tbox = fd.tbox;
+            A.upart = jobs[m0 + m].upart;
+            A.nF = fd.nF;
+            A.nB = (int)sym_blocks(fd.nF);
+            A.rho2 = jobs[m0 + m].rho2;
+            if ((int64_t)A.nB * kSymFaces > fd.cap) return hipErrorInvalidValue;
+            units = std::max(units, sym_units(fd.nF));
+        }
+        if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)units, n), block(kBlock);
+        if (is_p6(alpha, beta)) {
+            const PowP6 pw;
+            if (near) hipLaunchKernelGGL((k_energy32_sym<true, true, PowP6>), grid, block, 0, s, jb, pw);
+            else if (hilo) hipLaunchKernelGGL((k_energy32_sym<true, false, PowP6>), grid, block, 0, s, jb, pw);
+            else hipLaunchKernelGGL((k_energy32_sym<false, false, PowP6>), grid, block, 0, s, jb, pw);
+        } else {
+            const PowGen pw = make_gen(alpha, beta);
+            if (near) hipLaunchKernelGGL((k_energy32_sym<true, true, PowGen>), grid, block, 0, s, jb, pw);
+            else if (hilo) hipLaunchKernelGGL((k_energy32_sym<true, false, PowGen>), grid, block, 0, s, jb, pw);
+            else hipLaunchKernelGGL((k_energy32_sym<false, false, PowGen>), grid, block, 0, s, jb, pw);
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 int near_block_faces(bool grad) { return grad ? kNearFaces : kNearEFaces; }
