@@ -42,8 +42,8 @@ PEAK_HBM_GBS = 8000.0
 GRAD_TRAFFIC = {
     "sources": ["paper_2107_01664_amd/csrc/tp_pairs.hip", "paper_2107_01664_amd/csrc/tp_tiles.h",
                 "paper_2107_01664_amd/csrc/tp_internal.h", "paper_2107_01664_amd/csrc/tp_sym.h"],
-    "sha256": "5c05e40fbf4863bb757f34705e256546ea9ba153b9480c4d6d93b914f5e60f9b",
-    "fetch_bytes": int(58749.90625 * 1024) * 2,
+    "sha256": "06ce114739726300f3ae34dd87bda5875ad234a36fbb90ee43e955fb015ca84d",
+    "fetch_bytes": int(58673.69293 * 1024) * 2,
     "write_bytes": 172543 * 1024,
 }
 
