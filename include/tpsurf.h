@@ -94,7 +94,7 @@ typedef struct {
     double cg_rtol;      /* CG stops when ||b - C x|| <= cg_rtol ||b||, default 1e-10   */
     int    cg_maxiter;   /* default 20000                                               */
     int    cg_precond;   /* 1: two-level additive Schwarz preconditioner (default, used
-                            when the mesh has at most 256 blocks of 128 vertices);
+                            up to 16,384 blocks of 128 vertices and 40 components);
                             0: unpreconditioned CG                                        */
     double theta;        /* 0 (default): E and dE by the direct all-pairs sums; > 0: the
                             Barnes-Hut approximation of Sec. 4 with opening parameter
