@@ -827,6 +827,7 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
     std::vector<int32_t> lcol, halo_off(1, 0), hrow;
     int max_halo = 0;
     if (!P->pcg_ml) {
+        const int room = pcg_max_halo(nb);
         lcol.resize((size_t)w * n);
         std::vector<int32_t> lst, slot(n, -1);   // slot: of a row in the current block's list
         for (int b = 0; b < nb; ++b) {
@@ -841,7 +842,7 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
                     }
                 }
             std::sort(lst.begin(), lst.end());
-            const int nh = std::min((int)lst.size(), kPcgMaxHalo);
+            const int nh = std::min((int)lst.size(), room);
             for (int q = 0; q < (int)lst.size(); ++q) slot[lst[q]] = q < nh ? BS + q : ~lst[q];
             for (int e = 0; e < w; ++e)
                 for (int32_t i = i0; i < i1; ++i) {

@@ -35,6 +35,7 @@ const char* get_error();
         hipError_t e_ = (call);                                                        \
         if (e_ != hipSuccess) {                                                        \
             ::tp::set_error(std::string(#call) + ": " + hipGetErrorString(e_));        \
+            (void)hipGetLastError(); /* reported here: the next call starts clean */   \
             return TP_E_DEVICE;                                                        \
         }                                                                              \
     } while (0)

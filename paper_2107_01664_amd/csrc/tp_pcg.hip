@@ -785,6 +785,24 @@ struct PcgShared {
                                              // then [rows, halo][K] block solves or x
 };
 
+// LDS of a workgroup of a problem of nb blocks whose blocks keep up to halo rows of others on chip.
+constexpr size_t kLdsBytes = 160 * 1024;
+template <int K>
+constexpr size_t pcg_lds(int nb, int halo)
+{
+    return sizeof(PcgShared<K>) + sizeof(double) * K * (3 * (size_t)nb + kBS + halo);
+}
+// The halo that fits for every number of columns: 256 rows up to 244 blocks, 220 at 256 blocks (nine
+// columns).  Compact blocks of 128 vertices have about 60, blocks of a thin tube or around a pole
+// of high degree more than any bound; rows beyond it are read from memory one by one.
+template <int... K>
+constexpr int pcg_halo_room(int nb, std::integer_sequence<int, K...>)
+{
+    return std::min({kPcgMaxHalo, (int)((kLdsBytes - pcg_lds<K + 1>(nb, 0)) / (sizeof(double) * (K + 1)))...});
+}
+int pcg_max_halo(int nb) { return pcg_halo_room(nb, std::make_integer_sequence<int, kMaxGroupCols>{}); }
+static_assert(pcg_lds<kMaxGroupCols>(kMaxNbPcg, 200) <= kLdsBytes, "room for the halo of compact blocks");
+
 // One launch solves the systems of ntab independent problems: problem m owns workgroups
 // [tab[m].block0, tab[m + 1].block0) and exchanges values only among them, so its iterates
 // are those of a launch of its own.
@@ -1488,12 +1506,10 @@ hipError_t launch_pcg_batch(const PcgItem* items, int n, int k, void* tab_dev, v
     const PcgKernel kern = pcg_kernel(k);
     const void* fn = kern.fn;
     if (!fn) return hipErrorInvalidValue;
-    int nb_max = 0;
-    for (int m = 0; m < n; ++m) nb_max = std::max(nb_max, items[m].ps->nb);
-    int halo_max = 0;
-    for (int m = 0; m < n; ++m) halo_max = std::max(halo_max, items[m].ps->max_halo);
-    const int vs = kBS + halo_max;
-    const size_t smem = kern.smem + sizeof(double) * ((size_t)nb_max * 3 + (size_t)vs) * (size_t)k;
+    // (each problem's own blocks and halo: the largest of each, taken apart, may not fit together)
+    size_t rows = 0;
+    for (int m = 0; m < n; ++m) rows = std::max(rows, 3 * (size_t)items[m].ps->nb + kBS + items[m].ps->max_halo);
+    const size_t smem = kern.smem + sizeof(double) * rows * (size_t)k;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     int per_cu = 0;

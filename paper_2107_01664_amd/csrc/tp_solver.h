@@ -83,6 +83,7 @@ int pcg_block_size();
 int pcg_max_blocks();                    // blocks of one problem, at most
 int pcg_max_coarse();                    // coarse functions of one problem, at most
 int pcg_max_block_aggregates();          // aggregates touching one block, at most
+int pcg_max_halo(int nb);                // halo rows of a block that fit on chip with nb blocks
 // Per-geometry set-up: permuted matrix values, block inverses, coarse functions, the
 // coarse matrix and its inverse.  V: vertices (n x 3, caller order).
 hipError_t launch_pcg_setup(const PcgSetup& ps, const double* V, const int32_t* lap_off, const double* lap_val,
