@@ -828,6 +828,10 @@ static_assert(pcg_lds<kMaxGroupCols>(kMaxNbPcg, 200) <= kLdsBytes, "room for the
 // (6.9, plus 5 waiting for blocks that touch eight or more aggregates), their sums 2.3 (2.7),
 // scalars 1.2 (1.4).  With 9 columns the 8-byte loads past the L2 (80 KB per workgroup and
 // iteration) and the LDS reads of the rows and coarse values are the larger part.
+// A row's entries beyond the first kCache come from memory again in each pass, four at a time: on a
+// torus of 40,000 faces with random diagonals (degrees 4 to 8) nine columns take 2.40 ms, on the grid
+// 2.36; two vertices of degree 40 among 16,002 make an iteration 1.5 times as long, of degree 200
+// among 20,002 five times.
 template <int K>
 __global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__ tab, int ntab)
 {
@@ -879,9 +883,12 @@ __global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__
             if (S.nbl[e] == own) own_slot = e;
     }
 
-    // the matrix row: columns as slots of the rows in LDS
+    // the matrix row: columns as slots of the rows in LDS, the first ones in registers.  The longest
+    // row sets ell_w; a row's own entries are counted here (its padding names the row itself,
+    // which is an entry once), so one vertex of high degree costs only the waves it is in.
     int32_t cj[kCache];
     double cv[kCache];
+    int len = 0;
     bool edge = false;    // the row has a neighbour in another block, whose workgroup reads it
                           // (the pattern is symmetric)
 #pragma unroll
@@ -890,13 +897,18 @@ __global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__
         cj[e] = in ? global(A.lcol)[(int64_t)e * n + i] : row;
         cv[e] = in ? global(A.pval)[(int64_t)e * n + i] : 0.0;
     }
-    bool direct = false;  // some entry is not in LDS: beyond kCache, or its row not among the halo
-    if (act)
+    bool direct = false;  // the row of one of the first entries is not among the halo
+    if (act) {
+        int self = -1;
         for (int e = 0; e < A.ell_w; ++e) {
             const int32_t j = global(A.lcol)[(int64_t)e * n + i];
             edge = edge || j < 0 || j >= kBS;
-            direct = direct || j < 0 || e >= kCache;
+            direct = direct || (j < 0 && e < kCache);
+            if (j != row) len = e + 1;
+            else if (self < 0) self = e;
         }
+        len = max(len, self + 1);
+    }
     // halo: rows of other blocks, [nh][K] values per exchange
     const int nh = global(A.hoff)[B + 1] - global(A.hoff)[B], nhk = nh * K;
     for (int e = t; e < nh; e += T) S.hrow[e] = global(A.hrow)[global(A.hoff)[B] + e];
@@ -940,9 +952,8 @@ __global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__
     auto halo = [&](const double* U, int e) {
         return peek(U + (unsigned)(S.hrow[e / K] * K + e % K));
     };
-    // the value of column c in the row of entry e, wherever it is
-    auto entry = [&](const double* U, int c, int e) {
-        const int32_t j = global(rare()->lcol)[(int64_t)e * n + i];
+    // the value of column c in row j (a slot of the rows in LDS, or ~row), wherever it is
+    auto value = [&](const double* U, int32_t j, int c) {
         if (j >= 0) return rows[j * K + c];
         unsigned spins = 0;
         unsigned long long w;
@@ -1199,6 +1210,26 @@ __global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__
         double m[KG], an[KG];
 #pragma unroll
         for (int ii = 0; ii < KG; ++ii) m[ii] = an[ii] = 0.0;
+        // entries ea .. eb from memory, the loads of kSpan of them in flight together
+        auto span = [&](int ea, int eb) {
+            constexpr int kSpan = 4;
+            for (int e0 = ea; e0 < eb; e0 += kSpan) {
+                int32_t j[kSpan];
+                double a[kSpan];
+#pragma unroll
+                for (int u = 0; u < kSpan; ++u) {
+                    const int64_t at = (int64_t)min(e0 + u, eb - 1) * n + i;
+                    j[u] = global(rare()->lcol)[at];
+                    a[u] = global(rare()->pval)[at];
+                }
+#pragma unroll
+                for (int u = 0; u < kSpan; ++u)
+                    if (e0 + u < eb)
+#pragma unroll
+                        for (int ii = 0; ii < KG; ++ii)
+                            if (q + ii * Q < K) an[ii] = __builtin_fma(a[u], value(U, j[u], q + ii * Q), an[ii]);
+            }
+        };
         if (!direct) {
 #pragma unroll
             for (int e = 0; e < kCache; ++e)
@@ -1206,10 +1237,7 @@ __global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__
                 for (int ii = 0; ii < KG; ++ii)
                     if (q + ii * Q < K) an[ii] = __builtin_fma(cv[e], rows[cj[e] * K + q + ii * Q], an[ii]);
         } else {
-            for (int e = 0; e < min(kCache, rare()->ell_w); ++e)
-#pragma unroll
-                for (int ii = 0; ii < KG; ++ii)
-                    if (q + ii * Q < K) an[ii] = __builtin_fma(global(rare()->pval)[(int64_t)e * n + i], entry(U, q + ii * Q, e), an[ii]);
+            span(0, min(kCache, len));
         }
         if (step) {
 #pragma unroll
@@ -1242,11 +1270,7 @@ __global__ __launch_bounds__(kPcgThreads) void k_pcg(const PcgArgs* __restrict__
                 }
             }
         }
-        if (direct)   // (their coarse part is in rw)
-            for (int e = kCache; e < rare()->ell_w; ++e)
-#pragma unroll
-                for (int ii = 0; ii < KG; ++ii)
-                    if (q + ii * Q < K) an[ii] = __builtin_fma(global(rare()->pval)[(int64_t)e * n + i], entry(U, q + ii * Q, e), an[ii]);
+        span(kCache, len);   // (their coarse part is in rw)
 #pragma unroll
         for (int ii = 0; ii < KG; ++ii) {
             const int c = q + ii * Q;
