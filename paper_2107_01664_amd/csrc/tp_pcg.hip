@@ -1619,6 +1619,7 @@ struct WideArgs {
 typedef float wide_float4 __attribute__((ext_vector_type(4)));
 constexpr int kWideCols = 3;          // columns at most: what the registers of a workgroup hold
 constexpr int kWideThreads = 512;     // per workgroup: 256 registers each, 64 NBK / 2 of them for the inverses
+constexpr double kFresh = 1e-4;       // fall of |r| after which the coarse values are formed anew
 constexpr int kWideSum = 8;           // doubles of a record of the all-to-all exchange (seven used)
 constexpr int kWideCache = 8;         // entries of a matrix row kept in LDS
 constexpr int kWideEntries = kMaxBarrierW + kCoarseMax / 4;   // records: one per workgroup and one more per aggregate
@@ -1660,6 +1661,7 @@ struct WideShared {
     double cval[NBK][4][K];                           // coarse values of the own aggregates
     double crow[NBK][kCoarseMax / 4][16];             // their rows of C0^{-1}, by aggregate
     int live[K];                                      // column not yet converged
+    int stale[K];                                     // its coarse values are to be formed anew
     int bad;                                          // a wait gave up
     int wcount[D::NW], e0, ne;                        // records: this workgroup's first, all
     int la[NBK];                                      // own aggregate of each own block
@@ -1689,7 +1691,11 @@ __global__ void k_wide_empty(WideArgs A, int k)
 // of its own aggregates while it adds the dot products, and the coarse values of the new residual
 // follow by the recurrence of the residual itself (c -= alpha C0^{-1} Phi^T s), restarted from the
 // true residual with it; then u = M^{-1} r is known before the first exchange, which passes
-// boundary values to neighbouring blocks only.  A workgroup's blocks in one aggregate are one
+// boundary values to neighbouring blocks only.  The recurrence's rounding stays as large as it was
+// where c was, while r shrinks: by itself it held three columns of 100,002 vertices at a relative
+// residual of 2e-12, whatever the tolerance.  So c is formed from r anew, by one more all-to-all
+// exchange, whenever |r| has fallen to kFresh of what it was (two of 187 iterations' exchanges at
+// 1e-10).  A workgroup's blocks in one aggregate are one
 // record of the all-to-all exchange, so what it polls does not grow with NBK.
 // Three columns of 100,002 vertices (782 blocks, 185 iterations): 7.8 ms in five launches per
 // iteration (42 us), 2.8 ms here (15 us); one column 6.9 and 1.5 ms.  1,024 threads with two columns
@@ -1986,6 +1992,7 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
         return s;
     };
     double my_bb = 0.0, my_rr = 0.0, my_gam = 0.0, my_alpha = 0.0, my_c = 0.0, my_cs = 0.0;
+    double my_ref = 0.0;   // |r|^2 where my_c was last formed from r
     bool my_done = false;
     int my_its = 0;
     double r[KG];
@@ -1999,10 +2006,12 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
     int total_it = 0, cycle = 0;
     bool first = true;
     // Passes: kZero forms the residual of x = 0 (which gives |b|^2 and so fixes the tolerance),
-    // kStep is an iteration, kVerify forms the true residual
-    // once the iteration's own has converged, and starts another cycle from it when it has
-    // not.  One copy of the product and of the exchange serves them all.
-    enum { kZero, kStep, kVerify };
+    // kStep is an iteration, kCoarse forms the coarse values from the iteration's residual, kVerify
+    // forms the true residual once the iteration's own has converged, and starts another cycle
+    // from it when it has not.  One copy of the product and of the exchange serves them all.
+    // (kCoarse has no neighbour exchange: the rows that its exchange empties are empty already,
+    // and its owner fills them again only after the next one.)
+    enum { kZero, kStep, kCoarse, kVerify };
     int pass = kZero;
     __syncthreads();
     for (;;) {
@@ -2055,23 +2064,25 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
 #pragma unroll
             for (int ii = 0; ii < KG; ++ii) u[ii] = q + ii * Q < K ? S.x[q + ii * Q][row] : 0.0;
         }
-        product(u, w);
+        if (pass != kCoarse) product(u, w);
         if (pass != kStep)
 #pragma unroll
             for (int ii = 0; ii < KG; ++ii) {
                 const int c = q + ii * Q;
-                r[ii] = act && c < K ? A.b[(int64_t)i * A.ld + c] - w[ii] : 0.0;
-                if (c < K) S.p[c][row] = S.s[c][row] = 0.0;
+                if (pass != kCoarse) {
+                    r[ii] = act && c < K ? A.b[(int64_t)i * A.ld + c] - w[ii] : 0.0;
+                    if (c < K) S.p[c][row] = S.s[c][row] = 0.0;
+                }
                 u[ii] = 0.0;
                 w[ii] = r[ii];
             }
-        // sums of r u, w u, r r and the shares of w (of the true residual: u = 0, w = r)
+        // sums of r u, w u, r r and the shares of w (of a residual: u = 0, w = r)
         if (!exchange(r, u, w)) return;
         if (pass != kStep) {
             if (scalar) {
-                my_rr = total(2);
+                my_rr = my_ref = total(2);
                 my_c = total(3 + (sc_a & 3));
-                my_cs = 0.0;
+                if (pass != kCoarse) my_cs = 0.0;
                 S.cval[sc_a >> 2][sc_a & 3][sc_c] = my_c;
                 if (pass == kZero) {
                     my_bb = my_rr;
@@ -2088,8 +2099,8 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
                 if (all || total_it >= A.maxiter || cycle == kMaxRestarts) break;
                 ++cycle;
             }
+            if (pass != kCoarse) first = true;
             pass = kStep;
-            first = true;
             continue;
         }
         const bool can = total_it < A.maxiter;
@@ -2118,12 +2129,16 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
                 S.coef[0][sc_c] = al;
                 S.coef[1][sc_c] = be;
                 S.live[sc_c] = live ? 1 : 0;
+                S.stale[sc_c] = live && my_rr < kFresh * kFresh * my_ref ? 1 : 0;
             }
         }
         __syncthreads();
-        bool conv = true;
+        bool conv = true, stale = false;
 #pragma unroll
-        for (int c = 0; c < K; ++c) conv = conv && S.live[c] == 0;
+        for (int c = 0; c < K; ++c) {
+            conv = conv && S.live[c] == 0;
+            stale = stale || S.stale[c] != 0;
+        }
 #pragma unroll
         for (int ii = 0; ii < KG; ++ii) {
             const int c = q + ii * Q;
@@ -2142,6 +2157,7 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
         } else {
             ++total_it;
             first = false;
+            if (stale) pass = kCoarse;
         }
     }
     if (act)
