@@ -209,6 +209,7 @@ __global__ __launch_bounds__(kSubLeaves) void k_bh_subtrees(int64_t nF, int leaf
     __shared__ double sh[10][kSubLeaves];
     const int t = threadIdx.x;
     const int64_t l = (int64_t)blockIdx.x * kSubLeaves + t;
+    if (l == 0) b.nxa[0] = double4{0.0, 0.0, 0.0, 0.0};   // (no node: what k_bct_far reads past a list's end)
     if (l < P) {
         NodeSums n = {{0.0, 0.0, 0.0, 0.0, INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY}};
         for (int64_t p = l * leaf; p < (l + 1) * leaf && p < nF; ++p) {
@@ -658,6 +659,9 @@ __global__ __launch_bounds__(kSubLeaves) void k_bh_moments(int64_t nF, int leaf,
     const int t = threadIdx.x;
     const int64_t l = (int64_t)blockIdx.x * kSubLeaves + t;
     double acc[KP];
+    if (l == 0)
+#pragma unroll
+        for (int c = 0; c < KP; ++c) nm[c] = 0.0;   // (no node, see k_bct_far)
     if (l < P) {
 #pragma unroll
         for (int c = 0; c < KP; ++c) acc[c] = 0.0;
@@ -829,7 +833,11 @@ __global__ __launch_bounds__(256) void k_bct_far(int64_t M, const int32_t* __res
         double4 Y[U];
         double m[U][KP];
 #pragma unroll
-        for (int q = 0; q < U; ++q) J[q] = col[min(e + 64 * q, e1 - 1)];
+        for (int q = 0; q < U; ++q) {
+            const int32_t j = col[min(e + 64 * q, e1 - 1)];
+            J[q] = e + 64 * q < e1 ? j : 0;   // (past the end node 0, whose moments and area are zero:
+                                              // a weight of 0 alone does not keep out a moment of inf)
+        }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             Y[q] = nxa[J[q]];
