@@ -1660,8 +1660,8 @@ struct WideShared {
     double coef[2][K];                                // alpha, beta of every column
     double cval[NBK][4][K];                           // coarse values of the own aggregates
     double crow[NBK][kCoarseMax / 4][16];             // their rows of C0^{-1}, by aggregate
-    int live[K];                                      // column not yet converged
-    int stale[K];                                     // its coarse values are to be formed anew
+    int live[K];                                      // column not yet converged; 2: with its coarse values
+                                                      // to be formed anew
     int bad;                                          // a wait gave up
     int wcount[D::NW], e0, ne;                        // records: this workgroup's first, all
     int la[NBK];                                      // own aggregate of each own block
@@ -2128,8 +2128,7 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
             if (sc_a == 0) {
                 S.coef[0][sc_c] = al;
                 S.coef[1][sc_c] = be;
-                S.live[sc_c] = live ? 1 : 0;
-                S.stale[sc_c] = live && my_rr < kFresh * kFresh * my_ref ? 1 : 0;
+                S.live[sc_c] = live ? my_rr < kFresh * kFresh * my_ref ? 2 : 1 : 0;
             }
         }
         __syncthreads();
@@ -2137,7 +2136,7 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
 #pragma unroll
         for (int c = 0; c < K; ++c) {
             conv = conv && S.live[c] == 0;
-            stale = stale || S.stale[c] != 0;
+            stale = stale || S.live[c] == 2;
         }
 #pragma unroll
         for (int ii = 0; ii < KG; ++ii) {
