@@ -1347,6 +1347,7 @@ size_t near_grid_bytes(int64_t nF)
 tp_status ensure_near_grids(const Batch& B)
 {
     std::vector<NearGridJob> jobs;
+    Batch built;
     for (tp_problem* P : B) {
         if (!near_field(P) || P->ng_ver == P->geom_ver) continue;
         hipStream_t s = P->stream;
@@ -1370,10 +1371,12 @@ tp_status ensure_near_grids(const Batch& B)
         g.ntiles = (int)(P->fd.cap / kTileJ);
         g.nF = (int)P->nF;
         g.rho2 = (float)P->rho2;
-        P->ng_ver = P->geom_ver;
         jobs.push_back(g);
+        built.push_back(P);
     }
     if (!jobs.empty()) TP_HIP(launch_near_grid_build(jobs.data(), (int)jobs.size(), B[0]->stream));
+    // (only now: an allocation for a later problem of the batch may have failed before the launch)
+    for (tp_problem* P : built) P->ng_ver = P->geom_ver;
     return TP_OK;
 }
 
