@@ -407,7 +407,7 @@ struct tp_problem {
     bool have_pcg = false;
     PcgSetup pcg;
     DevBuf<int32_t> pcg_perm, pcg_pcol, pcg_bstart, pcg_whole, pcg_blk, pcg_astart, pcg_aob, pcg_acomp,
-        pcg_abl_off, pcg_abl, pcg_lcol, pcg_hoff, pcg_hrow;
+        pcg_abl_off, pcg_abl, pcg_lcol, pcg_hoff, pcg_hrow, pcg_toff, pcg_tslot;
     DevBuf<int8_t> pcg_rslot, pcg_eslot;
     DevBuf<float> pcg_Binv;
     DevBuf<double> pcg_pval, pcg_phi, pcg_rw, pcg_esum, pcg_C0inv, pcg_U, pcg_G, pcg_X, pcg_bp, pcg_xp;
@@ -498,7 +498,7 @@ struct tp_problem {
              ell_val.bytes();
         b += pcg_perm.bytes() + pcg_pcol.bytes() + pcg_bstart.bytes() + pcg_whole.bytes() + pcg_blk.bytes() +
              pcg_astart.bytes() + pcg_aob.bytes() + pcg_acomp.bytes() + pcg_abl_off.bytes() + pcg_abl.bytes() +
-             pcg_lcol.bytes() + pcg_hoff.bytes() + pcg_hrow.bytes() +
+             pcg_lcol.bytes() + pcg_hoff.bytes() + pcg_hrow.bytes() + pcg_toff.bytes() + pcg_tslot.bytes() +
              pcg_rslot.bytes() + pcg_eslot.bytes() + pcg_phi.bytes() + pcg_rw.bytes() + pcg_esum.bytes() +
              pcg_Binv.bytes() + pcg_pval.bytes() + pcg_C0inv.bytes() + pcg_U.bytes() +
              pcg_G.bytes() + pcg_X.bytes() + pcg_bp.bytes() + pcg_xp.bytes();
@@ -824,7 +824,8 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
     }
     // per block the rows of other blocks its rows have entries in, and the columns as slots of
     // the block's rows and of that list (rows beyond the list's capacity are read one by one)
-    std::vector<int32_t> lcol, halo_off(1, 0), hrow;
+    // (with more blocks: how many entries the rows have beyond those kept on chip)
+    std::vector<int32_t> lcol, halo_off(1, 0), hrow, toff;
     int max_halo = 0;
     if (!P->pcg_ml) {
         const int room = pcg_max_halo(nb);
@@ -855,6 +856,12 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
             max_halo = std::max(max_halo, nh);
         }
     }
+    if (P->pcg_ml && w > kPcgWideCache) {
+        toff.assign(n + 1, 0);
+        for (int64_t i = 0; i < n; ++i)
+            toff[i + 1] = toff[i] + std::max(0, hoff[perm[i] + 1] - hoff[perm[i]] - kPcgWideCache);
+        TP_TRY(P->pcg_tslot.ensure(toff[n], s));
+    }
     auto up = [&](auto& buf, const auto& host) -> tp_status {
         TP_TRY(buf.ensure(std::max<size_t>(host.size(), 1), s));
         TP_HIP(hipMemcpyAsync(buf.p, host.data(), sizeof(host[0]) * host.size(), hipMemcpyHostToDevice, s));
@@ -875,6 +882,7 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
     TP_TRY(up(P->pcg_lcol, lcol));
     TP_TRY(up(P->pcg_hoff, halo_off));
     TP_TRY(up(P->pcg_hrow, hrow));
+    TP_TRY(up(P->pcg_toff, toff));
     const int nc = 4 * na;
     TP_TRY(P->pcg_pval.ensure((size_t)w * n, s));
     TP_TRY(P->pcg_phi.ensure((size_t)4 * n, s));
@@ -890,6 +898,7 @@ tp_status build_pcg(tp_problem* P, const std::vector<int32_t>& label, int ncomp,
     ps.astart = P->pcg_astart.p; ps.agg_of_block = P->pcg_aob.p; ps.acomp = P->pcg_acomp.p;
     ps.abl_off = P->pcg_abl_off.p; ps.abl = P->pcg_abl.p; ps.rslot = P->pcg_rslot.p; ps.eslot = P->pcg_eslot.p;
     ps.lcol = P->pcg_lcol.p; ps.hoff = P->pcg_hoff.p; ps.hrow = P->pcg_hrow.p; ps.max_halo = max_halo;
+    ps.toff = P->pcg_toff.p; ps.tslot = P->pcg_tslot.p;
     ps.phi = P->pcg_phi.p; ps.rw = P->pcg_rw.p; ps.esum = P->pcg_esum.p;
     ps.Binv = P->pcg_Binv.p; ps.C0inv = P->pcg_C0inv.p;
     P->have_pcg = true;
@@ -3167,7 +3176,8 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
                      8 * 3 * nb * pcg_sum_stride(kMaxGroupCols);
             } else {
                 // multi-launch work: six [n][k] vectors, permuted b and x, block shares, coarse
-                // right-hand side, per-workgroup partial sums, state
+                // right-hand side, per-workgroup partial sums, state, rows' entries not kept on chip
+                b += 4.0 * (n + 1) + 4.0 * n * std::max(0.0, w - kPcgWideCache);
                 b += 8.0 * n * kMaxGroupCols * 8 + 8 * nb * 4 * kMaxGroupCols + 8 * ncmax * kMaxGroupCols +
                      8.0 * (double)pcg_ml_part_doubles(nV) + (double)pcg_ml_state_bytes();
             }

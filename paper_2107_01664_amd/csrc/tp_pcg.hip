@@ -1597,6 +1597,8 @@ struct WideArgs {
     int nb, nc, ell_w;
     const int32_t* pcol;      // [ell_w][n] (padding entries: the row itself, value 0)
     const double* pval;       // [ell_w][n]
+    const int32_t* toff;      // [n + 1] the rows' entries beyond the first kWideCache (when some row has any)
+    int32_t* tslot;           // [toff[n]] their columns as slots
     const int32_t* bstart;    // [nb + 1]
     const int32_t* blk;       // [n] block of each row
     const int32_t* agg_of_block;
@@ -1621,7 +1623,8 @@ constexpr int kWideCols = 3;          // columns at most: what the registers of 
 constexpr int kWideThreads = 512;     // per workgroup: 256 registers each, 64 NBK / 2 of them for the inverses
 constexpr double kFresh = 1e-4;       // fall of |r| after which the coarse values are formed anew
 constexpr int kWideSum = 8;           // doubles of a record of the all-to-all exchange (seven used)
-constexpr int kWideCache = 8;         // entries of a matrix row kept in LDS
+constexpr int kWideCache = kPcgWideCache;   // entries of a matrix row kept in LDS
+constexpr int kWideTail = 32;         // entries beyond them that a thread takes by itself
 constexpr int kWideEntries = kMaxBarrierW + kCoarseMax / 4;   // records: one per workgroup and one more per aggregate
 
 template <int K, int NBK>
@@ -1701,7 +1704,13 @@ __global__ void k_wide_empty(WideArgs A, int k)
 // iteration (42 us), 2.8 ms here (15 us); one column 6.9 and 1.5 ms.  1,024 threads with two columns
 // each spill (133 registers).  A record read by one lane in seven loads instead of by eight lanes
 // in one: 3.5 ms, because each load of a lane is a request of its own to the coherence point.
-template <int K, int NBK>
+//
+// A row's entries beyond the first kWideCache (TAIL: some row has any) come from memory in each
+// product, four at a time in a thread, a row of more than kWideTail of them by the wave.  Nine
+// columns on a globe of 36,102 vertices with two poles of degree 190: 36.8 us an iteration; 993
+// when every row walked as many entries as the longest has and formed their slots again, 158 in five
+// launches; 32.8 on a torus grid of as many vertices.
+template <int K, int NBK, bool TAIL>
 __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
 {
     using D = WideDims<K, NBK>;
@@ -1741,26 +1750,31 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
     bool edge = false;    // the row is read by another workgroup (the pattern is symmetric)
     if (t == 0) S.nx = 0;
     __syncthreads();
+    auto place = [&](int32_t sl) -> int32_t {               // R + the value's place in ext, when there is room
+        if (sl >= 0) return sl;
+        const int at = atomicAdd(&S.nx, 1);
+        if (at >= D::XE) return sl;
+        S.xrow[at] = ~sl;
+        return R + at;
+    };
 #pragma unroll
     for (int e = 0; e < kWideCache; ++e) {
         const bool in = act && e < A.ell_w;
-        int32_t sl = in ? slot_of(A.pcol[(int64_t)e * n + i]) : row;
+        const int32_t sl = in ? slot_of(A.pcol[(int64_t)e * n + i]) : row;
         const double v = in ? A.pval[(int64_t)e * n + i] : 0.0;
         edge = edge || sl < 0;
         if (q == 0) {
-            if (sl < 0) {                                   // R + the value's place in ext, when there is room
-                const int at = atomicAdd(&S.nx, 1);
-                if (at < D::XE) {
-                    S.xrow[at] = ~sl;
-                    sl = R + at;
-                }
-            }
-            S.cj[e][row] = sl;
+            S.cj[e][row] = place(sl);
             S.cv[e][row] = v;
         }
     }
-    if (act)
-        for (int e = kWideCache; e < A.ell_w; ++e) edge = edge || slot_of(A.pcol[(int64_t)e * n + i]) < 0;
+    // the row's own entries beyond them (the longest row sets ell_w): slots formed here, once
+    const int t0 = TAIL && act ? A.toff[i] : 0, tn = TAIL && act ? A.toff[i + 1] - t0 : 0;
+    for (int e = 0; e < tn; ++e) {
+        const int32_t sl = slot_of(A.pcol[(int64_t)(kWideCache + e) * n + i]);
+        edge = edge || sl < 0;
+        if (q == 0) A.tslot[t0 + e] = place(sl);
+    }
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         const double v = act ? A.phi[i * 4 + a] : 0.0;
@@ -1837,6 +1851,9 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
             }
             return as_value(v);
         };
+        auto value = [&](int32_t j, int c) -> double {
+            return j < 0 ? wait_for(~j, c) : *(j < R ? &S.u[c][j] : &S.ext[c][j - R]);
+        };
         const int nx = min(S.nx, D::XE) * K;
         constexpr int PX = 4;             // values per thread with their loads in flight together
         for (int f0 = t; f0 < nx && !fail; f0 += PX * D::T) {
@@ -1871,17 +1888,49 @@ __global__ __launch_bounds__((WideDims<K, NBK>::T)) void k_pcg_wide(WideArgs A)
             if (c < K) {
 #pragma unroll
                 for (int e = 0; e < kWideCache; ++e) {
-                    const int32_t j = S.cj[e][row];
-                    const double v = j < 0 ? wait_for(~j, c) : *(j < R ? &S.u[c][j] : &S.ext[c][j - R]);
-                    acc += S.cv[e][row] * v;
+                    acc += S.cv[e][row] * value(S.cj[e][row], c);
                 }
-                if (act)
-                    for (int e = kWideCache; e < A.ell_w && !fail; ++e) {   // rows of more than kWideCache entries
-                        const int32_t j = slot_of(A.pcol[(int64_t)e * n + i]);
-                        acc += A.pval[(int64_t)e * n + i] * (j >= 0 ? S.u[c][j] : wait_for(~j, c));
-                    }
             }
             w[ii] = acc;
+        }
+        if (TAIL && tn > 0 && tn <= kWideTail) {
+            constexpr int UT = 4;             // entries with their loads in flight together
+            for (int e0 = 0; e0 < tn; e0 += UT) {
+                int32_t j[UT];
+                double a[UT];
+#pragma unroll
+                for (int m = 0; m < UT; ++m) {
+                    const int e = min(e0 + m, tn - 1);
+                    j[m] = A.tslot[t0 + e];
+                    a[m] = A.pval[(int64_t)(kWideCache + e) * n + i];
+                }
+#pragma unroll
+                for (int m = 0; m < UT; ++m)
+                    if (e0 + m < tn)
+#pragma unroll
+                        for (int ii = 0; ii < KG; ++ii)
+                            if (q + ii * Q < K) w[ii] += a[m] * value(j[m], q + ii * Q);
+            }
+        }
+        for (unsigned long long ml = TAIL ? __ballot(tn > kWideTail) : 0; ml; ml &= ml - 1) {   // the wave together
+            const int l = __builtin_ctzll(ml);
+            const int lt0 = __builtin_amdgcn_readlane(t0, l), ltn = __builtin_amdgcn_readlane(tn, l);
+            const int li = __builtin_amdgcn_readlane(i, l);
+            double sum[KG];
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) sum[ii] = 0.0;
+            for (int e = lane; e < ltn; e += 64) {
+                const int32_t j = A.tslot[lt0 + e];
+                const double a = A.pval[(int64_t)(kWideCache + e) * n + li];
+#pragma unroll
+                for (int ii = 0; ii < KG; ++ii)
+                    if (q + ii * Q < K) sum[ii] += a * value(j, q + ii * Q);
+            }
+#pragma unroll
+            for (int ii = 0; ii < KG; ++ii) {
+                const double all = wave_sum(sum[ii]);
+                if (lane == l) w[ii] += all;
+            }
         }
         if (fail) S.bad = 1;
     };
@@ -2187,21 +2236,22 @@ hipError_t launch_pcg_wide(const PcgSetup& ps, const double* b, double* x, int k
         const void* fn;
         size_t smem;
     };
-    static const Kernel kernels[2][kWideCols] = {
-        {{(const void*)k_pcg_wide<1, 2>, sizeof(WideShared<1, 2>)},
-         {(const void*)k_pcg_wide<2, 2>, sizeof(WideShared<2, 2>)},
-         {(const void*)k_pcg_wide<3, 2>, sizeof(WideShared<3, 2>)}},
-        {{(const void*)k_pcg_wide<1, 4>, sizeof(WideShared<1, 4>)},
-         {(const void*)k_pcg_wide<2, 4>, sizeof(WideShared<2, 4>)},
-         {(const void*)k_pcg_wide<3, 4>, sizeof(WideShared<3, 4>)}}};
+#define TP_WIDE(K, NBK, TAIL) {(const void*)k_pcg_wide<K, NBK, TAIL>, sizeof(WideShared<K, NBK>)}
+    static const Kernel kernels[2][2][kWideCols] = {
+        {{TP_WIDE(1, 2, false), TP_WIDE(2, 2, false), TP_WIDE(3, 2, false)},
+         {TP_WIDE(1, 4, false), TP_WIDE(2, 4, false), TP_WIDE(3, 4, false)}},
+        {{TP_WIDE(1, 2, true), TP_WIDE(2, 2, true), TP_WIDE(3, 2, true)},
+         {TP_WIDE(1, 4, true), TP_WIDE(2, 4, true), TP_WIDE(3, 4, true)}}};
+#undef TP_WIDE
     WideArgs A;
     A.n = ps.n; A.nb = ps.nb; A.nc = ps.nc; A.ell_w = ps.ell_w; A.pcol = ps.pcol; A.pval = ps.pval;
+    A.toff = ps.toff; A.tslot = ps.tslot;
     A.bstart = ps.bstart; A.blk = ps.blk; A.agg_of_block = ps.agg_of_block; A.phi = ps.phi; A.Binv = ps.Binv;
     A.C0inv = ps.C0inv; A.ld = k; A.U0 = w.m; A.U1 = w.an; A.X = w.v; A.flags = w.flags; A.rtol = rtol;
     A.maxiter = maxiter;
     for (int c0 = 0; c0 < k; c0 += kWideCols) {
         const int kc = std::min(kWideCols, k - c0);
-        const Kernel& kern = kernels[nbk == 2 ? 0 : 1][kc - 1];
+        const Kernel& kern = kernels[ps.ell_w > kWideCache ? 1 : 0][nbk == 2 ? 0 : 1][kc - 1];
         hipError_t e = hipFuncSetAttribute(kern.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kern.smem);
         if (e != hipSuccess) return e;
         int per_cu = 0;

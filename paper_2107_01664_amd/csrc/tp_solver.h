@@ -35,6 +35,7 @@ hipError_t launch_cg(int64_t n, const int32_t* ecol, const double* eval, int ell
 constexpr int kPcgRowSlots = 8;          // aggregates one row's entries reach, at most
 constexpr int kPcgRegSlots = 4;          // of them, kept on chip by the solver
 constexpr int kPcgMaxHalo = 256;         // rows of other blocks a block keeps on chip, at most
+constexpr int kPcgWideCache = 8;         // entries of a matrix row that the solve of 257 to 1,024 blocks keeps there
 struct PcgSetup {
     int64_t n = 0;
     int nb = 0;
@@ -49,6 +50,8 @@ struct PcgSetup {
     const int32_t* hoff = nullptr;        // [nb + 1] halo of each block: columns in other blocks
     const int32_t* hrow = nullptr;        //          (sorted; the first kPcgMaxHalo of them)
     int max_halo = 0;
+    const int32_t* toff = nullptr;        // more than pcg_max_blocks() blocks: [n + 1] entries of the rows
+    int32_t* tslot = nullptr;             // beyond kPcgWideCache, and [toff[n]] room for their slots
     const int32_t* bstart = nullptr;      // [nb + 1]
     const int32_t* whole = nullptr;       // [nb] block is a whole component
     const int32_t* blk = nullptr;         // [n] block of each (permuted) row
