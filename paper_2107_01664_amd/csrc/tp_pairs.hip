@@ -1023,8 +1023,9 @@ __global__ __launch_bounds__(kBlock) void k_energy32_sym(ESymJobs jb, Pow pw)
     const ESymArgs& A = jb.j[blockIdx.y];
     const int lane = (int)threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nB = A.nB;
+    const int64_t unit = (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
     int a, b;
-    if (!sym_unit_blocks(blockIdx.x, nB, 0, nB, a, b)) return;   // the whole workgroup leaves
+    if (!sym_unit_blocks(unit, nB, 0, nB, a, b)) return;   // the whole workgroup leaves
     float3 Sh[kSymNI], Sl[kSymNI], Sn[kSymNI];
     float aS[kSymNI];
     double acc[kSymNI];
@@ -1072,7 +1073,7 @@ __global__ __launch_bounds__(kBlock) void k_energy32_sym(ESymJobs jb, Pow pw)
     for (int m = 32; m >= 1; m >>= 1) e += __shfl_xor(e, m, 64);
     if (lane == 0) quarter[q] = e;
     __syncthreads();
-    if (threadIdx.x == 0) A.upart[blockIdx.x] = (quarter[0] + quarter[1]) + (quarter[2] + quarter[3]);
+    if (threadIdx.x == 0) A.upart[unit] = (quarter[0] + quarter[1]) + (quarter[2] + quarter[3]);
 }
 
 // The band [a0, a1) of rows, for faces i >= a0 kSymFaces (the others get nothing from it):
@@ -2268,6 +2269,7 @@ hipError_t launch_grad64_sym(const FaceData& fd, double* part, int64_t irows, do
 
 int64_t sym_units(int64_t nF) { return sym_band_units(nF, 0, (int)sym_blocks(nF)); }
 
+constexpr int64_t kSymGridX = 1 << 20;   // pairs of blocks in x, the rest in z
 hipError_t launch_energy_sym(const EnergySymJob* jobs, int njobs, int precision, double alpha, double beta, hipStream_t s)
 {
     if (precision == TP_PREC_FP64) return hipErrorInvalidValue;
@@ -2292,8 +2294,10 @@ hipError_t launch_energy_sym(const EnergySymJob* jobs, int njobs, int precision,
             if ((int64_t)A.nB * kSymFaces > fd.cap) return hipErrorInvalidValue;
             units = std::max(units, sym_units(fd.nF));
         }
-        if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
-        const dim3 grid((unsigned)units, n), block(kBlock);
+        // a launch holds less than 2^32 threads a dimension (2^24 pairs of blocks: 1.48 million faces)
+        const int64_t nx = std::min<int64_t>(units, kSymGridX), nz = (units + nx - 1) / nx;
+        if (nz > 65535) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)nx, n, (unsigned)nz), block(kBlock);
         if (is_p6(alpha, beta)) {
             const PowP6 pw;
             if (near) hipLaunchKernelGGL((k_energy32_sym<true, true, PowP6>), grid, block, 0, s, jb, pw);
