@@ -116,7 +116,10 @@ typedef struct {
                             evaluated once for both rows (the kernel values K(S,T) and
                             K(T,S), |d|^-(2 sigma + 2) and |d|^-2s come from the same d);
                             E and E + dE stay row by row in precisions 4 and 5.  E + dE in
-                            FP64 likewise: -1 symmetric from 10,240 to about 70,000 faces   */
+                            FP64 likewise: -1 symmetric from 10,240 to about 70,000 faces,
+                            with 56 bytes of device memory per face and 256 faces (93 MB at
+                            20,306 faces, up to 1 GiB) that the problem keeps; row by row
+                            for good once the allocator has refused them                    */
     int    sym_band;      /* the symmetric kernels take the rows of 256-face blocks in bands,
                             one launch and one FP64 reduction per band, so that their FP32
                             partial buffer (2 * band * k * nF floats, or ceil(nF/256) * k *

@@ -427,6 +427,7 @@ struct tp_problem {
 
     // work
     DevBuf<double> part, gface, zbuf, scal, red, vol6, edge;
+    bool sym64_refused = false;                  // the slices of the symmetric FP64 E + dE could not be had
     struct { double* p = nullptr; } dot_red;     // chunk sums and counters of launch_dots, in scal's buffer
     // GMRES on A = B + B0: Krylov blocks V, Z, work vectors, small device arrays
     DevBuf<double> gm_V, gm_Z, gm_w, gm_b, gm_r, gm_x, gm_small, gm_red, gm_Q, gm_Qn, gm_AQ, gm_one, gm_dinv,
@@ -1618,8 +1619,18 @@ tp_status enqueue_gradient(const Batch& B, double* const* dE, int slot, bool del
             plans.push_back(pl);
             continue;
         }
-        const bool once = sym64_grad_eligible(P->prm, P->nF, pl.irows);
-        if (once) pl.n_split = sym64_slices(P->nF);
+        bool once = !P->sym64_refused && sym64_grad_eligible(P->prm, P->nF, pl.irows);
+        if (once) {
+            const tp_status st = P->part.ensure((size_t)sym64_slices(P->nF) * 7 * pl.irows, s);
+            if (st != TP_OK && st != TP_E_OUT_OF_MEMORY) return st;
+            once = st == TP_OK;
+            if (once) {
+                pl.n_split = sym64_slices(P->nF);
+            } else {   // row by row takes a few slices only
+                P->sym64_refused = true;
+                set_error("");
+            }
+        }
         const int slices = pl.n_split + (near_field(P) ? 1 : 0);
         TP_TRY(P->part.ensure((size_t)slices * 7 * pl.irows, s));
         TP_TRY(P->gface.ensure((size_t)7 * pl.irows, s));
