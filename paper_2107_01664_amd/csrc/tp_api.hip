@@ -1182,14 +1182,11 @@ tp_status flag_status(tp_problem* P)
 
 // ------------------------------------------------------------------ Barnes-Hut
 
-tp_status ensure_bh(tp_problem* P)
+// What the Morton order needs of the tree's buffers.
+tp_status ensure_order(tp_problem* P)
 {
     hipStream_t s = P->stream;
     const int64_t nF = P->nF;
-    const int64_t M = (int64_t)bh_node_count(nF, P->prm.leaf_size, nullptr);
-    TP_TRY(P->bh_flo.ensure(3 * nF, s));
-    TP_TRY(P->bh_fhi.ensure(3 * nF, s));
-    TP_TRY(P->bh_fr2.ensure(nF, s));
     TP_TRY(P->bh_box.ensure(kBhBoxDoubles, s));
     TP_TRY(P->bh_kin.ensure(nF, s));
     TP_TRY(P->bh_kout.ensure(nF, s));
@@ -1197,6 +1194,22 @@ tp_status ensure_bh(tp_problem* P)
     TP_TRY(P->bh_tmp.ensure(tb, s));
     TP_TRY(P->bh_order.ensure(nF, s));
     TP_TRY(P->bh_pos.ensure(nF, s));
+    BhBuffers& b = P->bh;
+    b.box = P->bh_box.p; b.keys_in = P->bh_kin.p; b.keys_out = P->bh_kout.p; b.sort_tmp = P->bh_tmp.p;
+    b.sort_bytes = tb; b.order = P->bh_order.p; b.pos = P->bh_pos.p;
+    return TP_OK;
+}
+
+// The rest, for problems that use the tree.
+tp_status ensure_bh(tp_problem* P)
+{
+    TP_TRY(ensure_order(P));
+    hipStream_t s = P->stream;
+    const int64_t nF = P->nF;
+    const int64_t M = (int64_t)bh_node_count(nF, P->prm.leaf_size, nullptr);
+    TP_TRY(P->bh_flo.ensure(3 * nF, s));
+    TP_TRY(P->bh_fhi.ensure(3 * nF, s));
+    TP_TRY(P->bh_fr2.ensure(nF, s));
     TP_TRY(P->bh_na.ensure(M, s));
     TP_TRY(P->bh_nsx.ensure(3 * M, s));
     TP_TRY(P->bh_nX.ensure(3 * M, s));
@@ -1211,9 +1224,8 @@ tp_status ensure_bh(tp_problem* P)
     TP_TRY(P->bh_counts.ensure((size_t)kBhCounts + 4 * (M + nF), s));
     TP_TRY(P->bh_nm.ensure((size_t)M * ((kMaxGroupCols + 3) / 4 * 4), s));
     BhBuffers& b = P->bh;
-    b.flo = P->bh_flo.p; b.fhi = P->bh_fhi.p; b.fr2 = P->bh_fr2.p; b.box = P->bh_box.p;
-    b.keys_in = P->bh_kin.p; b.keys_out = P->bh_kout.p; b.sort_tmp = P->bh_tmp.p; b.sort_bytes = tb;
-    b.order = P->bh_order.p; b.pos = P->bh_pos.p; b.na = P->bh_na.p; b.nsx = P->bh_nsx.p; b.nX = P->bh_nX.p;
+    b.flo = P->bh_flo.p; b.fhi = P->bh_fhi.p; b.fr2 = P->bh_fr2.p;
+    b.na = P->bh_na.p; b.nsx = P->bh_nsx.p; b.nX = P->bh_nX.p;
     b.nlo = P->bh_nlo.p; b.nhi = P->bh_nhi.p; b.nr2 = P->bh_nr2.p; b.gS = P->bh_gS.p; b.eS = P->bh_eS.p;
     b.rec = P->bh_rec.p; b.nxa = P->bh_nxa.p; b.srt = P->bh_srt.p; b.counts = P->bh_counts.p;
     b.accN = reinterpret_cast<double*>(P->bh_counts.p + kBhCounts);
@@ -2501,7 +2513,7 @@ tp_status create_problem(const double* V, int64_t nV, const int32_t* F, int64_t 
     // once, at the end (E + dE of 1,280 faces from scratch: 473 us with five waits for the device
     // and four blocks of pinned memory, 375 with one of each).
     DevBuf<int32_t> Fold;
-    if ((st = ensure_bh(P)) != TP_OK) return bail(st);
+    if ((st = P->prm.theta > 0.0 || P->prm.chi > 0.0 ? ensure_bh(P) : ensure_order(P)) != TP_OK) return bail(st);
     if ((st = Fold.ensure(3 * nF, stream)) != TP_OK) return bail(st);
     if ((st = P->face_orig.ensure(nF, stream)) != TP_OK) return bail(st);
     const FaceGeomJob G = face_geom_job(P, P->V.p);
@@ -3217,11 +3229,12 @@ uint64_t estimate_bytes(int64_t nV, int64_t nF, int max_degree, int ncomp, const
     b += symb;
     // step work arrays, per-face volumes and edge lengths, CG tables
     b += 8 * n * ncol * 4 + 8 * n * 3 * 3 + 16 * f + 4096;
-    // Barnes-Hut tree, keys, sort scratch and per-face sums (allocated at creation, where
-    // the Morton order of the faces is computed with them)
-    {
+    // Morton order: keys, sort scratch, order and the caller's numbers
+    b += f * 28.0 + (double)bh_sort_temp_bytes(nF) + 8 * kBhBoxDoubles;
+    // tree of the faces and per-face sums, where a parameter asks for it
+    if (prm.theta > 0.0 || prm.chi > 0.0) {
         const double M = (double)bh_node_count(nF, prm.leaf_size, nullptr);
-        b += f * (208.0 + 56.0) + M * (240.0 + 8.0 * kMaxGroupCols) + (double)bh_sort_temp_bytes(nF) + 8 * kBhBoxDoubles + 64;
+        b += f * (208.0 + 28.0) + M * (240.0 + 8.0 * kMaxGroupCols) + 64;
         // block cluster tree lists and far-field values (chi > 0; about 64 blocks per node)
         if (prm.chi > 0.0) b += M * (8.0 * (2 * kMaxGroupCols + 1) + 4.0 * 64 + 8.0) + f * ((kf + 3) / 4 * 4) * esz;
     }
