@@ -407,7 +407,7 @@ struct NearGridJob {
     int nF = 0;
     int gmax = 1;                 // cells per axis at most
     float rho2 = 0.f;             // squared near radius
-    int32_t* key = nullptr;       // [nF] cell of each face
+    int32_t* key = nullptr;       // [nF] cell of each face, and the length of a part that it begins
     int32_t* rank = nullptr;      // [nF] its place among the faces of its cell, as counted
     int32_t* tmp = nullptr;       // [nF] faces by cell, each cell's as counted
     int32_t* ord = nullptr;       // [nF] faces by cell, each cell's in face order

@@ -1745,20 +1745,46 @@ __global__ __launch_bounds__(256) void k_near_grid_clear(NearGridBatch jb)
     }
 }
 
-// key = the face's cell, rank = how many faces of the cell came before; cell.y counts them.
+// key = the face's cell, rank = how many faces of the cell came before; cell.y counts them.  A wave's
+// faces in the same cell are added together, for up to kNearShared cells of a wave (32,000 faces in
+// one cell, one addition each, took 340 us): they are a part of the cell's run in face order, whose
+// length its first face has above the cell's kNearCellBits bits of key.
+constexpr int kNearShared = 3;
+constexpr int kNearCellBits = 22;             // 128^3 cells at most
+__device__ __forceinline__ int near_key_cell(int key) { return key & ((1 << kNearCellBits) - 1); }
+__device__ __forceinline__ int near_key_part(int key) { return key >> kNearCellBits; }
 __global__ void k_near_grid_count(NearGridBatch jb)
 {
     const NearGridJob& J = jb.j[blockIdx.y];
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= J.nF) return;
+    const bool live = s < J.nF;
     const NearGridParams G = *J.prm;
-    const float4 p = J.fx[s];
+    const float4 p = J.fx[live ? s : 0];
     const int cx = near_cell_axis(p.x, G.lo[0], G.inv_cs, G.g);
     const int cy = near_cell_axis(p.y, G.lo[1], G.inv_cs, G.g);
     const int cz = near_cell_axis(p.z, G.lo[2], G.inv_cs, G.g);
     const int k = (int)(((int64_t)cz * G.g + cy) * G.g + cx);
-    J.key[s] = k;
-    J.rank[s] = atomicAdd(&J.cell[k].y, 1);
+    const int lane = threadIdx.x & 63;
+    unsigned long long left = __ballot(live);
+    int add = live ? 1 : 0, from = lane, before = 0;   // who adds for this lane, and its place among them
+#pragma unroll
+    for (int q = 0; q < kNearShared; ++q) {
+        if (!left) break;
+        const int l = __builtin_ctzll(left);
+        const unsigned long long same = __ballot(k == __builtin_amdgcn_readlane(k, l)) & left;
+        if ((same >> lane) & 1) {
+            from = l;
+            before = __builtin_popcountll(same & ((1ull << lane) - 1));
+            add = lane == l ? __builtin_popcountll(same) : 0;
+        }
+        left &= ~same;
+    }
+    int base = 0;
+    if (add) base = atomicAdd(&J.cell[k].y, add);
+    base = __shfl(base, from);
+    if (!live) return;
+    J.key[s] = k | add << kNearCellBits;
+    J.rank[s] = base + before;
 }
 
 // The first face of a cell takes the cell's run: cell.x its begin (one atomic addition per wave).
@@ -1767,7 +1793,7 @@ __global__ void k_near_grid_place(NearGridBatch jb)
     const NearGridJob& J = jb.j[blockIdx.y];
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     const bool first = s < J.nF && J.rank[s] == 0;
-    const int k = first ? J.key[s] : 0;
+    const int k = first ? near_key_cell(J.key[s]) : 0;
     const int c = first ? J.cell[k].y : 0;
     const int lane = threadIdx.x & 63;
     int incl = c;
@@ -1786,19 +1812,59 @@ __global__ void k_near_grid_drop(NearGridBatch jb)
 {
     const NearGridJob& J = jb.j[blockIdx.y];
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < J.nF) J.tmp[J.cell[J.key[s]].x + J.rank[s]] = s;
+    if (s < J.nF) J.tmp[J.cell[near_key_cell(J.key[s])].x + J.rank[s]] = s;
 }
 
-// Each run in face order, with the face records.
+// Each run in face order, with the face records.  A run is a few faces long, or, where the faces are
+// much smaller than the near radius (a surface that has shrunk since its first mesh, a fine part
+// of a graded one), most of the mesh.  A lane takes the faces of a short run by itself, four loads in
+// flight.  A longer one the wave reads together and compares by its parts: those of other waves lie
+// before or after a face as a whole.
+constexpr int kNearLong = 32;
 __global__ void k_near_grid_order(NearGridBatch jb)
 {
     const NearGridJob& J = jb.j[blockIdx.y];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= J.nF) return;
-    const int s = J.tmp[i];
-    const int2 run = J.cell[J.key[s]];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x & 63;
+    const bool live = i < J.nF;
+    const int s = live ? J.tmp[i] : 0;
+    const int2 run = live ? J.cell[near_key_cell(J.key[s])] : make_int2(0, 0);
     int pos = run.x;
-    for (int j = run.x; j < run.x + run.y; ++j) pos += J.tmp[j] < s ? 1 : 0;
+    const int end = run.x + run.y;
+    if (run.y <= kNearLong)
+        for (int j = run.x; j < end; j += 4) {
+            int v[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) v[m] = J.tmp[min(j + m, end - 1)];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) pos += j + m < end && v[m] < s ? 1 : 0;
+        }
+    unsigned long long left = __ballot(run.y > kNearLong);
+    while (left) {                            // the lanes of one run at a time
+        const int l = __builtin_ctzll(left);
+        const int b = __builtin_amdgcn_readlane(run.x, l), e = __builtin_amdgcn_readlane(end, l);
+        const bool mine = run.x == b && run.y > kNearLong;
+        int less = 0;
+        constexpr int U = 4;                  // 64 faces each, with their loads in flight together
+        for (int j = b; j < e; j += 64 * U) {
+            int v[U], part[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = J.tmp[min(j + 64 * u + lane, e - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) part[u] = j + 64 * u + lane < e ? near_key_part(J.key[v[u]]) : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                for (unsigned long long m = __ballot(part[u] > 0); m; m &= m - 1) {
+                    const int h = __builtin_ctzll(m);
+                    const int t = __builtin_amdgcn_readlane(v[u], h), n = __builtin_amdgcn_readlane(part[u], h);
+                    // (a wave has one part of more than one face in a cell: the face's own then)
+                    const int before = n > 1 && t >> 6 == s >> 6 ? i - (j + 64 * u + h) : n;
+                    less += t < s ? before : 0;
+                }
+        }
+        if (mine) pos += less;
+        left &= ~__ballot(mine);
+    }
+    if (!live) return;
     J.ord[pos] = s;
     J.sfx[pos] = J.fx[s];
     J.sfl[pos] = J.fl[s];
