@@ -111,7 +111,8 @@ typedef struct {
                             see tp_problem_bct_stats                                     */
     int    sym_pairs;     /* direct FP32 sums of E, E + dE, the fractional apply and the
                             operator A = B + B0: -1 (default) symmetric from 16,384 faces
-                            on (E at any size), 0 row by row (every ordered pair evaluated for its row), 1
+                            on (E of a mesh at any size, of given face quantities from 16,384),
+                            0 row by row (every ordered pair evaluated for its row), 1
                             symmetric at any size; symmetric means every unordered pair
                             evaluated once for both rows (the kernel values K(S,T) and
                             K(T,S), |d|^-(2 sigma + 2) and |d|^-2s come from the same d);
