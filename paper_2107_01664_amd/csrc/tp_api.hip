@@ -1430,8 +1430,12 @@ tp_status enqueue_near(const Batch& B, const std::vector<PairPlan>& plans, int n
 
 // The symmetric all-pairs kernels (launch_grad_sym, launch_frac_sym: each unordered pair
 // evaluated once for both rows) are used for the direct FP32 sums of E + dE and the operators,
-// unless forced by tp_params.sym_pairs = 1, from kSymMinFaces faces on, below which they have too few pairs
-// of blocks to fill the GPU.  Their partial buffer is kept within kSymPartBytes by running
+// unless forced by tp_params.sym_pairs = 1, from kSymMinFaces faces on.  A wave takes a pair of blocks, and
+// one takes 140 to 220 us however small the mesh, so below some size they lose to the row by row
+// kernels: E + dE of 5,084 faces 138 us row by row and 232, of 8,320 199 and 239, of 10,260 253 and
+// 244, of 14,040 345 and 291, of 16,560 392 and 377 (L^sigma u, three columns: 64 and 110, 98 and
+// 111, 118 and 114, 155 and 141, 213 and 167; A u 100 and 210, 176 and 218, 232 and 221, 346 and 282,
+// 411 and 406).  Their partial buffer is kept within kSymPartBytes by running
 // the rows in bands (one launch and one reduction per band; a single band up to about
 // 68,000 faces for E + dE).
 constexpr double kSymPartBytes = 512.0 * 1024.0 * 1024.0;
@@ -1503,7 +1507,9 @@ bool sym_energy_eligible(const tp_params& prm, int64_t nV, int64_t nF)
 
 // E + dE in FP64 with every unordered pair once: from kSym64MinFaces faces on (10,260 faces: 187 us, row by
 // row 226; 8,320 faces: 169 and 152, too few pairs of blocks to fill the GPU), as long as its
-// slices (56 bytes per face and block of faces) stay within kSym64Bytes (up to 70,000 faces).
+// slices (56 bytes per face and block of faces) stay within kSym64Bytes (up to 70,000 faces) and
+// can be had.  The problems of a batch run one launch each: steps of eight problems of 10,360 faces
+// 18.0 ms, row by row in shared launches 17.9, of four of 20,306 24.7 and 24.7.
 constexpr int64_t kSym64MinFaces = 10240;
 constexpr double kSym64Bytes = 1024.0 * 1024.0 * 1024.0;
 bool sym64_grad_eligible(const tp_params& prm, int64_t nF, int64_t irows)

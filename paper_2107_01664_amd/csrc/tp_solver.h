@@ -48,7 +48,7 @@ struct PcgSetup {
     const int32_t* lcol = nullptr;        // [ell_w][n] the columns as the persistent solver keeps them:
                                           // row within the block, block size + halo slot, or ~column
     const int32_t* hoff = nullptr;        // [nb + 1] halo of each block: columns in other blocks
-    const int32_t* hrow = nullptr;        //          (sorted; the first kPcgMaxHalo of them)
+    const int32_t* hrow = nullptr;        //          (sorted; the first pcg_max_halo(nb) of them)
     int max_halo = 0;
     const int32_t* toff = nullptr;        // more than pcg_max_blocks() blocks: [n + 1] entries of the rows
     int32_t* tslot = nullptr;             // beyond kPcgWideCache, and [toff[n]] room for their slots
