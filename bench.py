@@ -42,8 +42,8 @@ PEAK_HBM_GBS = 8000.0
 GRAD_TRAFFIC = {
     "sources": ["paper_2107_01664_amd/csrc/tp_pairs.hip", "paper_2107_01664_amd/csrc/tp_tiles.h",
                 "paper_2107_01664_amd/csrc/tp_internal.h", "paper_2107_01664_amd/csrc/tp_sym.h"],
-    "sha256": "06ce114739726300f3ae34dd87bda5875ad234a36fbb90ee43e955fb015ca84d",
-    "fetch_bytes": int(58673.69293 * 1024) * 2,
+    "sha256": "7dfc0ff3ac86f96afa39383873c08b1c8dde5c485ec69165b54b842b1398d119",
+    "fetch_bytes": int(58742.984375 * 1024) * 2,
     "write_bytes": 172543 * 1024,
 }
 
